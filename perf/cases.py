@@ -113,7 +113,8 @@ def _chunk(case):
     return ([case["chunk_start"]], [n[0]]) if case["chunk_start"] else None
 
 
-def prepare(case, seed):
+def _inputs(case, seed):
+    """Q, K and V of the whole sequences, bf16, and cu_seqlens."""
     lens, B, d, hq, hkv = _lens(case), case["B"], case["d"], case["hq"], case["hkv"]
     dev = torch.device("cuda:0")
     g = torch.Generator(device=dev).manual_seed(int(seed))
@@ -141,8 +142,12 @@ def prepare(case, seed):
             gain[picked] = wl.V_OUTLIER_GAIN
             v[lo:hi, h] *= gain.repeat_interleave(B)[:n, None]
     del mean, qg
-    q, k, v = q.to(torch.bfloat16), k.to(torch.bfloat16), v.to(torch.bfloat16)
+    return q.to(torch.bfloat16), k.to(torch.bfloat16), v.to(torch.bfloat16), cu
 
+
+def prepare(case, seed):
+    q, k, v, cu = _inputs(case, seed)
+    lens, B, dev = _lens(case), case["B"], q.device
     k_start = [case["k_start"] * -(-n // B) for n in lens]
     args = (cu, B, k_start, case["mu"], case["k_min"], case["n_sink"], case["n_local"])
     kw = dict(want_lse=case["lse"], ad_stride=case["ad_stride"], group_share=case["group_share"] or None)
@@ -165,6 +170,101 @@ def run(state):
     if pf.lse is not None:
         out["lse"] = pf.lse
     return out
+
+
+# Above this many operations of stage 3 the 64-bit result takes too long.
+EXACT_FLOPS = 2.5e13
+
+
+def exact(case, seed):
+    """The three stages in 64 bits: block means and value magnitudes, the metric, the lists with ties to the
+    lower block, and the softmax over the listed keys."""
+    if work(case)["flops"] > EXACT_FLOPS:
+        return None
+    lens, B, d, hq, hkv, S = _lens(case), case["B"], case["d"], case["hq"], case["hkv"], case["ad_stride"]
+    q, k, v, cu = _inputs(case, seed)
+    G, start, dev = hq // hkv, case["chunk_start"], q.device
+    spans = [(start if start else 0, n) for n in lens]
+    rows = [-(-n // B) - lo // B for lo, n in spans]
+    tokens = sum(n - lo for lo, n in spans)
+    budgets = []
+    for (lo, n), ks in zip(spans, [case["k_start"] * -(-x // B) for x in lens]):
+        nb = -(-n // B)
+        step = ks * (1.0 - case["mu"]) / nb
+        of_seq = []
+        for i in range(lo // B, nb):
+            head = min(case["n_sink"], i + 1)
+            forced = head + i + 1 - max(head, i + 1 - case["n_local"])
+            of_seq.append(min(i + 1, max(math.floor(ks - step * (i + 1) + 1e-9), case["k_min"], forced)))
+        budgets.append(of_seq)
+    kmax = max(max(b) for b in budgets)
+    lists = hkv if case["group_share"] else hq
+    out = torch.empty(tokens, hq, d, dtype=torch.float64, device=dev)
+    lse = torch.empty(hq, tokens, dtype=torch.float64, device=dev)
+    counts = torch.empty(lists, sum(rows), dtype=torch.int32, device=dev)
+    indices = torch.full((lists, sum(rows), kmax), -1, dtype=torch.int32, device=dev)
+
+    def blocks(x, lo, n):                              # [blocks, B, d] of one head, 64 bits, zeros after the end
+        nb = -(-n // B)
+        y = torch.zeros(nb * B, d, dtype=torch.float64, device=dev)
+        y[:n] = x[lo:lo + n]
+        return y.view(nb, B, d)
+
+    def means(y, n):                                   # [blocks, S, d]: one mean per residue class
+        nb = y.shape[0]
+        members = (torch.arange(nb * B, device=dev).view(nb, B // S, S) < n).sum(dim=1)
+        return y.view(nb, B // S, S, d).sum(dim=1) / members.clamp(min=1)[:, :, None]
+
+    r0 = t0 = 0
+    for s, n in enumerate(lens):
+        lo, R, nb = spans[s][0], rows[s], -(-n // B)
+        first, nq = lo // B, n - lo
+        if R == 0:
+            continue
+        i = torch.arange(first, nb, device=dev)[:, None]
+        j = torch.arange(nb, device=dev)[None, :]
+        budget = torch.tensor(budgets[s], device=dev)
+        forced = (j < case["n_sink"]) | (j > i - case["n_local"])
+        for g in range(hkv):
+            kb, vb = blocks(k[:, g], cu[s], n), blocks(v[:, g], cu[s], n)
+            mag = vb.norm(dim=-1).amax(dim=-1).log().clamp(min=0.0)
+            k_bar = means(kb, n).flip(1).reshape(nb, S * d)
+            qb = [blocks(q[:, g * G + x], cu[s] + lo, nq) for x in range(G)]
+            metric = [means(y, nq).reshape(R, S * d) @ k_bar.T / S + 0.2 * mag for y in qb]
+            if case["group_share"]:
+                metric = torch.stack(metric)
+                metric = [metric.amax(dim=0) if case["group_share"] == "max" else metric.mean(dim=0)]
+            for x in range(G):
+                h = g if case["group_share"] else g * G + x
+                if x < len(metric):                    # the list: forced blocks first, then by the metric
+                    m = metric[x].masked_fill(forced, math.inf).masked_fill(j > i, -math.inf)
+                    order = m.sort(dim=1, descending=True, stable=True).indices
+                    kept = torch.zeros(R, nb, dtype=torch.bool, device=dev)
+                    kept.scatter_(1, order, torch.arange(nb, device=dev)[None, :] < budget[:, None])
+                    picked = torch.where(kept, j, nb).sort(dim=1).values[:, :kmax]
+                    counts[h, r0:r0 + R] = budget
+                    indices[h, r0:r0 + R, :picked.shape[1]] = picked.masked_fill(picked == nb, -1)
+                at = max(1, int(1.5e9 // (B * B * picked.shape[1] + 2 * B * d * picked.shape[1])))
+                for a in range(0, R, at):
+                    of = picked[a:a + at]
+                    of = of[:, :int((of < nb).sum(dim=1).max())]
+                    there = of.clamp(max=nb - 1)
+                    keys = (there[:, :, None] * B + torch.arange(B, device=dev)).flatten(1)
+                    keys = torch.where((of < nb).repeat_interleave(B, dim=1), keys, nb * B)
+                    queries = (torch.arange(first + a, first + a + of.shape[0], device=dev)[:, None] * B
+                               + torch.arange(B, device=dev))
+                    z = torch.bmm(qb[x][a:a + at], kb[there].flatten(1, 2).transpose(1, 2).contiguous())
+                    z = (z * d ** -0.5).masked_fill_(keys[:, None, :] > queries[:, :, None], -math.inf)
+                    total = torch.logsumexp(z, dim=2, keepdim=True)
+                    o = torch.bmm((z - total).exp_(), vb[there].flatten(1, 2))
+                    lo_t, hi_t = a * B, min((a + of.shape[0]) * B, nq)
+                    out[t0 + lo_t:t0 + hi_t, g * G + x] = o.view(-1, d)[:hi_t - lo_t]
+                    lse[g * G + x, t0 + lo_t:t0 + hi_t] = total.view(-1)[:hi_t - lo_t]
+        r0, t0 = r0 + R, t0 + nq
+    result = {"out": out, "counts": counts, "indices": indices}
+    if case["lse"]:
+        result["lse"] = lse
+    return result
 
 
 def work(case):

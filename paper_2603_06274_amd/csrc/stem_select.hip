@@ -150,21 +150,28 @@ int launch_select(const Problem& p, int heads, const float* scores, const int32_
 //
 // One workgroup owns (head h, band of ROWS consecutive rows of one sequence).  Phase 1 fills
 // sc[row][key block] for the key blocks the band can see; phase 2: every wave runs select_row on
-// its rows with the scores read from LDS.  ROWS = 16 serves up to 1024 key blocks per row, ROWS = 4
-// up to 4096 (64 KiB of fp32 scores either way).
+// its rows with the scores read from LDS.
 //
-// Phase 1, ROWS = 16: the fp32 matrix instruction v_mfma_f32_16x16x4_f32 on tiles of 16 key blocks
+// Phase 1: the fp32 matrix instruction v_mfma_f32_16x16x4_f32 on tiles of 16 key blocks
 // x the band's 16 rows, operands loaded straight from the pooled workspace into registers (it is
 // L2-resident and every value is used once per tile, so LDS staging would only add traffic).  The
 // order in which the products walk the depth is free as long as both operands agree: lane
 // (r = lane % 16, c = lane / 16) holds, of its key block or row r, the floats 16u + 4c .. + 3 of
 // every 64-byte group u, so a 16-byte load serves four product steps and the four lanes of a row
-// read 64 contiguous bytes.  The workgroup has 8 waves; wave w owns the tiles w, w + 8, ...; their
-// accumulators (at most 8 tiles x 4 registers) stay in registers across the whole depth, which is
-// walked 64 floats at a time; the next tile's keys are in flight during the products of the
-// current one.  With 128 registers per lane two such workgroups (16 waves) share a CU.
-// Phase 1, ROWS = 4: v_mfma_f32_4x4x1_16B_f32 on 256-key chunks staged through LDS 8 floats of the
-// contraction at a time; every wave takes 64 keys against the band's four rows.
+// read 64 contiguous bytes.  Wave w owns the tiles w, w + WAVES, ...; their accumulators stay in
+// registers across the whole depth, which is walked 64 floats at a time; the next tile's keys are
+// in flight during the products of the current one.
+//
+// Three shapes, by the key blocks a row can have; the band's scores decide what shares a CU:
+//   <= 1024: 16 rows, 64 KiB, 8 waves; two workgroups per CU, one selects while the other multiplies
+//   <= 2048: 16 rows, 128 KiB, 16 waves, one workgroup per CU.  Every key operand still serves 16 rows.
+//            8 rows in 64 KiB, two workgroups per CU, leave half of each product empty and fetch every
+//            key block twice as often: 0.60 against 0.41 ms at 1563 rows and key blocks, 32 / 8 heads,
+//            d = 128 (0.27 ms without phase 2, 0.20 ms without the products)
+//   <= 4096: 8 rows, 128 KiB, 8 waves: half-empty products, which still take 0.71 instead of 1.00 ms
+//            (pooling included) at 3126 rows and key blocks, 8 / 1 heads, against the 4-row bands on
+//            v_mfma_f32_4x4x1_16B_f32, staged 8 floats of the depth at a time, that served all rows
+//            above 1024 key blocks before (0.99 ms in the case of 1563)
 // ------------------------------------------------------------------------------------------------
 struct BandTable {
     int32_t band_start[STEM_MAX_BATCH + 1];            // prefix sums of ceil(rows of the call / ROWS)
@@ -172,15 +179,12 @@ struct BandTable {
 
 constexpr int kScorePad = 4;                           // floats between rows of sc: 16-byte writes of 16 rows spread over all banks
 
-template <int ROWS>
-__global__ __launch_bounds__(ROWS == 16 ? 512 : 256, 2) void score_select_kernel(
+template <int ROWS, int NBcap, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, NBcap <= 2048 ? 4 : 2) void score_select_kernel(
     const float* __restrict__ q_bar, const float* __restrict__ k_bar, const float* __restrict__ m_v,
     const int32_t* __restrict__ budget, int32_t* __restrict__ counts, int32_t* __restrict__ indices,
     float* __restrict__ debug_scores, SeqTable seq, BandTable bands, int R, int Rk, int NBmax, int G,
     int S, int d_log2, float beta, float route_scale, int n_sink, int n_local, int kmax) {
-    constexpr int NBcap = ROWS == 16 ? 1024 : 4096;    // key blocks per row held in LDS
-    constexpr int WAVES = ROWS == 16 ? 8 : 4;
-    constexpr int RPW = ROWS / WAVES;                  // rows per wave in phase 2
     constexpr int ITEMS = NBcap / 64;
     __shared__ __attribute__((aligned(16))) float sc[ROWS][NBcap + kScorePad];
 
@@ -205,161 +209,83 @@ __global__ __launch_bounds__(ROWS == 16 ? 512 : 256, 2) void score_select_kernel
     const float* b_src = k_bar + ((int64_t)g * Rk + krow0) * depth;
     const float* mag_src = m_v + (int64_t)g * Rk + krow0;
     float* dbg = debug_scores != nullptr ? debug_scores + ((int64_t)h * R + row0 + ic0) * NBmax : nullptr;
-    int done;                                          // key blocks per row that phase 1 gives a value
 
-    if constexpr (ROWS == 16) {
-        typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
-        constexpr int TPW = NBcap / 16 / WAVES;        // tiles per wave
-        const int r = lane & 15, c = lane >> 4;
-        const int n_tiles = (n_keys + 15) >> 4;
-        done = n_tiles * 16;
-        f32x4_t acc[TPW];
+    typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
+    constexpr int TPW = NBcap / 16 / WAVES;            // tiles per wave
+    const int r = lane & 15, c = lane >> 4;
+    const int n_tiles = (n_keys + 15) >> 4;
+    const int done = n_tiles * 16;                     // key blocks per row that get a value here
+    f32x4_t acc[TPW];
 #pragma unroll
-        for (int t = 0; t < TPW; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < TPW; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-        // The contraction runs over S * d / 64 segments of 64 floats, each inside one residue class
-        // a of the query block; its partner among the keys is the same columns of class S-1-a.
-        const int segs_per_class = d >> 6;
-        for (int seg = 0; seg < S * segs_per_class; ++seg) {
-            const int a = seg / segs_per_class, col0 = (seg - a * segs_per_class) * 64 + 4 * c;
-            float4 qv[4];
-            const float* q_row = a_src + (int64_t)r * depth + a * d + col0;
+    // The contraction runs over S * d / 64 segments of 64 floats, each inside one residue class
+    // a of the query block; its partner among the keys is the same columns of class S-1-a.
+    const int segs_per_class = d >> 6;
+    for (int seg = 0; seg < S * segs_per_class; ++seg) {
+        const int a = seg / segs_per_class, col0 = (seg - a * segs_per_class) * 64 + 4 * c;
+        float4 qv[4];
+        const float* q_row = a_src + (int64_t)r * depth + a * d + col0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            qv[u] = (r < band_rows) ? *reinterpret_cast<const float4*>(q_row + 16 * u) : make_float4(0.f, 0.f, 0.f, 0.f);
+        const float* k_cls = b_src + (S - 1 - a) * d + col0;
+        float4 kv[4], kn[4];
+        auto load_keys = [&](float4* dst, int tile) {
+            const int j = tile * 16 + r;
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                qv[u] = (r < band_rows) ? *reinterpret_cast<const float4*>(q_row + 16 * u) : make_float4(0.f, 0.f, 0.f, 0.f);
-            const float* k_cls = b_src + (S - 1 - a) * d + col0;
-            float4 kv[4], kn[4];
-            auto load_keys = [&](float4* dst, int tile) {
-                const int j = tile * 16 + r;
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    dst[u] = (j < n_keys) ? *reinterpret_cast<const float4*>(k_cls + (int64_t)j * depth + 16 * u)
-                                          : make_float4(0.f, 0.f, 0.f, 0.f);
-            };
-            if (w < n_tiles) load_keys(kv, w);
-#pragma unroll
-            for (int t = 0; t < TPW; ++t) {
-                const int tile = WAVES * t + w;
-                if (tile >= n_tiles) break;            // wave-uniform
-                if (tile + WAVES < n_tiles) load_keys(kn, tile + WAVES);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[u].x, qv[u].x, acc[t], 0, 0, 0);
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[u].y, qv[u].y, acc[t], 0, 0, 0);
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[u].z, qv[u].z, acc[t], 0, 0, 0);
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[u].w, qv[u].w, acc[t], 0, 0, 0);
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) kv[u] = kn[u];
-            }
-        }
-        // accumulator x of a lane: band row r, key block 16 tile + 4c + x
+                dst[u] = (j < n_keys) ? *reinterpret_cast<const float4*>(k_cls + (int64_t)j * depth + 16 * u)
+                                      : make_float4(0.f, 0.f, 0.f, 0.f);
+        };
+        if (w < n_tiles) load_keys(kv, w);
 #pragma unroll
         for (int t = 0; t < TPW; ++t) {
             const int tile = WAVES * t + w;
-            if (tile >= n_tiles) break;
-            const int j0 = tile * 16 + 4 * c;
-            float val[4];
+            if (tile >= n_tiles) break;                // wave-uniform
+            if (tile + WAVES < n_tiles) load_keys(kn, tile + WAVES);
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const int j = j0 + x;
-                val[x] = neg_inf;
-                if (r < band_rows && j <= first + ic0 + r)   // implies j < n_keys
-                    val[x] = fmaf(route_scale / (float)S, acc[t][x], beta * fmaxf(0.f, mag_src[j]));
+            for (int u = 0; u < 4; ++u) {
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[u].x, qv[u].x, acc[t], 0, 0, 0);
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[u].y, qv[u].y, acc[t], 0, 0, 0);
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[u].z, qv[u].z, acc[t], 0, 0, 0);
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[u].w, qv[u].w, acc[t], 0, 0, 0);
             }
-            if (r >= band_rows) continue;
-            *reinterpret_cast<float4*>(&sc[r][j0]) = make_float4(val[0], val[1], val[2], val[3]);
-            if (dbg != nullptr) {
 #pragma unroll
-                for (int x = 0; x < 4; ++x)
-                    if (j0 + x < NBmax) dbg[(int64_t)r * NBmax + j0 + x] = val[x];
-            }
+            for (int u = 0; u < 4; ++u) kv[u] = kn[u];
         }
-    } else {
-        // 4-row bands: v_mfma_f32_4x4x1_16B_f32, sixteen independent 4 x 4 outer products per
-        // instruction: block l / 4 of the wave pairs the band's row l % 4 (A operand) with key
-        // block 4 (l / 4) + l % 4 = l of the wave's 64 (B operand), and lane l ends up with the four
-        // rows' scores of its key block.  Keys are staged through LDS 256 at a time (64 per wave),
-        // 8 floats of the contraction per step, row-major with 48-byte rows, so a lane's 16-byte
-        // reads of its own key row are conflict-free; the next step's global loads are in flight
-        // during the products.  The staging is kept this small so that, next to the 64 KiB of
-        // scores, two workgroups fit a CU: the selection phase of one then runs beside the score
-        // phase of the other.
-        typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
-        constexpr int kKeys = 64 * WAVES, kSlice = 8, kPad = kSlice + 4;
-        __shared__ __attribute__((aligned(16))) float ks[kKeys][kPad];   // [key][contraction]
-        __shared__ __attribute__((aligned(16))) float qs[ROWS][kPad];    // [row][contraction]
-        const int slices = depth / kSlice;             // per key chunk
-        const int chunks = (n_keys + kKeys - 1) / kKeys;
-        const int steps = chunks * slices;
-        done = chunks * kKeys;
-        constexpr int kPerThread = kKeys * (kSlice / 4) / (64 * WAVES);   // float4 per thread and step
-        float4 bv[kPerThread], av;
-        auto fetch = [&](int step) {
-            const int j0 = (step / slices) * kKeys, kc = (step % slices) * kSlice;
-            // a slice lies inside one residue class a of the query block; its partner is class S-1-a
-            const int kb = (S - 1 - (kc >> d_log2)) * d + (kc & (d - 1));
+    }
+    // accumulator x of a lane: band row r, key block 16 tile + 4c + x
 #pragma unroll
-            for (int u = 0; u < kPerThread; ++u) {
-                const int idx = tid + 64 * WAVES * u;
-                const int row = idx / (kSlice / 4), c4 = (idx % (kSlice / 4)) * 4;
-                bv[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (j0 + row < n_keys) bv[u] = *reinterpret_cast<const float4*>(b_src + (int64_t)(j0 + row) * depth + kb + c4);
-            }
-            av = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (tid < ROWS * (kSlice / 4) && tid / (kSlice / 4) < band_rows)
-                av = *reinterpret_cast<const float4*>(a_src + (int64_t)(tid / (kSlice / 4)) * depth + kc + (tid % (kSlice / 4)) * 4);
-        };
-        f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-        if (steps > 0) fetch(0);
-        for (int step = 0; step < steps; ++step) {
+    for (int t = 0; t < TPW; ++t) {
+        const int tile = WAVES * t + w;
+        if (tile >= n_tiles) break;
+        const int j0 = tile * 16 + 4 * c;
+        float val[4];
 #pragma unroll
-            for (int u = 0; u < kPerThread; ++u) {
-                const int idx = tid + 64 * WAVES * u;
-                *reinterpret_cast<float4*>(&ks[idx / (kSlice / 4)][(idx % (kSlice / 4)) * 4]) = bv[u];
-            }
-            if (tid < ROWS * (kSlice / 4))
-                *reinterpret_cast<float4*>(&qs[tid / (kSlice / 4)][(tid % (kSlice / 4)) * 4]) = av;
-            __syncthreads();
-            if (step + 1 < steps) fetch(step + 1);
+        for (int x = 0; x < 4; ++x) {
+            const int j = j0 + x;
+            val[x] = neg_inf;
+            if (r < band_rows && j <= first + ic0 + r)   // implies j < n_keys
+                val[x] = fmaf(route_scale / (float)S, acc[t][x], beta * fmaxf(0.f, mag_src[j]));
+        }
+        if (r >= band_rows) continue;
+        *reinterpret_cast<float4*>(&sc[r][j0]) = make_float4(val[0], val[1], val[2], val[3]);
+        if (dbg != nullptr) {
 #pragma unroll
-            for (int u = 0; u < kSlice / 4; ++u) {
-                const float4 kf = *reinterpret_cast<const float4*>(&ks[w * 64 + lane][4 * u]);
-                const float4 qf = *reinterpret_cast<const float4*>(&qs[lane & 3][4 * u]);
-                acc = __builtin_amdgcn_mfma_f32_4x4x1f32(qf.x, kf.x, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_4x4x1f32(qf.y, kf.y, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_4x4x1f32(qf.z, kf.z, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_4x4x1f32(qf.w, kf.w, acc, 0, 0, 0);
-            }
-            __syncthreads();
-            if (step % slices == slices - 1) {         // the chunk's contraction is complete
-                const int j = (step / slices) * kKeys + w * 64 + lane;
-                const float mag = (j < n_keys) ? beta * fmaxf(0.f, mag_src[j]) : 0.f;
-#pragma unroll
-                for (int row = 0; row < ROWS; ++row) {
-                    const float val = (j <= first + ic0 + row) ? fmaf(route_scale / (float)S, acc[row], mag) : neg_inf;
-                    if (row >= band_rows || j >= NBcap) continue;
-                    sc[row][j] = val;
-                    if (dbg != nullptr && j < NBmax) dbg[(int64_t)row * NBmax + j] = val;
-                }
-                acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            }
+            for (int x = 0; x < 4; ++x)
+                if (j0 + x < NBmax) dbg[(int64_t)r * NBmax + j0 + x] = val[x];
         }
     }
     // the rest of a debug row is -inf, as in the unfused score tensor
     if (dbg != nullptr) {
-        for (int x = 0; x < RPW; ++x) {
-            const int row = w * RPW + x;
-            if (row >= band_rows) continue;
+        for (int row = w; row < band_rows; row += WAVES)
             for (int j = done + lane; j < NBmax; j += 64) dbg[(int64_t)row * NBmax + j] = neg_inf;
-        }
     }
     __syncthreads();
 
     // ---- phase 2: selection from LDS, one row at a time per wave ----
-    for (int x = 0; x < RPW; ++x) {
-        const int row = w * RPW + x;
-        if (row >= band_rows) break;                   // wave-uniform
+    for (int row = w; row < band_rows; row += WAVES) { // wave-uniform
         const int r = row0 + ic0 + row;
         const float* scr = sc[row];
         select_row<ITEMS>([&](int j) { return scr[j]; }, first + ic0 + row, budget[r], n_sink, n_local, kmax,
@@ -372,7 +298,7 @@ int launch_score_select(const Problem& p, int ad_stride, const float* q_bar, con
                         int32_t n_sink, int32_t n_local, int32_t* counts, int32_t* indices,
                         int32_t kmax, float* debug_scores, hipStream_t stream) {
     if (p.NBmax > 4096) return STEM_ERR_UNSUPPORTED;
-    const int rows_per_band = p.NBmax <= 1024 ? 16 : 4;
+    const int rows_per_band = p.NBmax <= 2048 ? 16 : 8;   // see the kernel
     BandTable bands;
     int total = 0;
     for (int s = 0; s <= STEM_MAX_BATCH; ++s) {
@@ -381,15 +307,15 @@ int launch_score_select(const Problem& p, int ad_stride, const float* q_bar, con
     }
     if (total == 0) return STEM_OK;
     if (p.Hq > 65535) return STEM_ERR_UNSUPPORTED;
-    dim3 grid(total, p.Hq), block(rows_per_band == 16 ? 512 : 256);
-    if (rows_per_band == 16)
-        hipLaunchKernelGGL(score_select_kernel<16>, grid, block, 0, stream, q_bar, k_bar, m_v, budget, counts,
-                           indices, debug_scores, p.seq, bands, p.R, p.Rk, p.NBmax, p.G, ad_stride,
-                           __builtin_ctz(p.d), beta, route_scale, n_sink, n_local, kmax);
-    else
-        hipLaunchKernelGGL(score_select_kernel<4>, grid, block, 0, stream, q_bar, k_bar, m_v, budget, counts,
-                           indices, debug_scores, p.seq, bands, p.R, p.Rk, p.NBmax, p.G, ad_stride,
-                           __builtin_ctz(p.d), beta, route_scale, n_sink, n_local, kmax);
+    dim3 grid(total, p.Hq);
+#define STEM_SCORE_SELECT_LAUNCH(ROWS, NB, WAVES)                                                              \
+    hipLaunchKernelGGL((score_select_kernel<ROWS, NB, WAVES>), grid, dim3(64 * WAVES), 0, stream, q_bar, k_bar, \
+                       m_v, budget, counts, indices, debug_scores, p.seq, bands, p.R, p.Rk, p.NBmax, p.G,      \
+                       ad_stride, __builtin_ctz(p.d), beta, route_scale, n_sink, n_local, kmax)
+    if (p.NBmax <= 1024) STEM_SCORE_SELECT_LAUNCH(16, 1024, 8);
+    else if (p.NBmax <= 2048) STEM_SCORE_SELECT_LAUNCH(16, 2048, 16);
+    else STEM_SCORE_SELECT_LAUNCH(8, 4096, 8);
+#undef STEM_SCORE_SELECT_LAUNCH
     return check_launch();
 }
 

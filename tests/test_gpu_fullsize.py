@@ -135,7 +135,7 @@ def test_packed_varlen_128k():
 
 
 def test_fused_estimate_select_128k_and_most_blocks():
-    """The fused stage 1-2 at the headline size (16-row bands) and at 4096 key blocks (4-row bands):
+    """The fused stage 1-2 at the headline size (16-row bands) and at 4096 key blocks (8-row bands):
     lists against the oracle, and the whole chained output against the unfused path's."""
     big = wl.small("max_blocks_b64", seed=51, num_q_heads=2, num_kv_heads=1, seq_lens=(4096 * 64 - 17,),
                    block_size=64, k_start=(40,), n_sink=2, n_local=2, outliers=(32,))

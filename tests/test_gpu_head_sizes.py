@@ -37,7 +37,7 @@ def test_head_size_whole_path(d, name):
 
 @pytest.mark.parametrize("d,ad_stride", [(64, 1), (256, 2)])
 def test_head_size_fused_above_1024_blocks(d, ad_stride):
-    """The fused stage 1-2 with more than 1024 key blocks per row (its 4-row bands) at the other head
+    """The fused stage 1-2 with more than 1024 key blocks per row (128 KiB bands) at the other head
     sizes: dumped scores and lists against the oracle."""
     import torch
     import parity_util as pu
@@ -55,3 +55,46 @@ def test_head_size_fused_above_1024_blocks(d, ad_stride):
     _, counts, indices = pu.oracle_select(w, scores)
     same = pu.check_lists(w, pf.counts.cpu().numpy(), pf.indices.cpu().numpy(), counts, indices, scores, print)
     assert same.mean() > 0.99
+
+
+@pytest.mark.parametrize("blocks,chunk_blocks", [(1024, 0), (1025, 0), (2048, 40), (2049, 41), (4096, 23)])
+def test_fused_band_shapes_at_their_edges(blocks, chunk_blocks):
+    """The three band shapes of the fused stage 1-2 at the first and last number of key blocks each
+    serves, next to a short sequence (bands of one row): the dumped scores against the unfused score
+    kernel's, the lists against the unfused selection on the dumped scores, which must be identical."""
+    import torch
+    import parity_util as pu
+    w = wl.small("bands_%d" % blocks, seed=66, num_q_heads=2, num_kv_heads=1, seq_lens=(blocks * 64 - 3, 70),
+                 block_size=64, k_start=(30, 2), n_sink=2, n_local=2, outliers=(8, 1), head_dim=64)
+    data = wl.generate(w)
+    dev = torch.device("cuda:0")
+    q, k, v = (data[x].to(dev) for x in "qkv")
+    ws = chunk = None
+    args = (w.cu_seqlens, w.block_size, w.k_start_blocks, w.mu, w.k_min, w.n_sink, w.n_local)
+    if chunk_blocks:                                   # the last rows only, as in chunked prefill
+        n = blocks * 64 - 3
+        start = (blocks - chunk_blocks) * 64
+        earlier = pu.StemPrefill(torch.cat([q[:start], q[n:n + 64]]), k, v, *args, chunk=([0, 0], [start, 64]))
+        q = torch.cat([q[start:n], q[n + 64:]])
+        chunk = ([start, 64], [n, 70])
+        pf = pu.StemPrefill(q, k, v, *args, chunk=chunk, fill_scores=True)
+        ws = torch.empty(max(earlier.workspace.numel(), pf.workspace.numel()), dtype=torch.uint8, device=dev)
+        earlier.workspace = pf.workspace = ws
+        earlier.pool()
+    else:
+        pf = pu.StemPrefill(q, k, v, *args, fill_scores=True)
+    assert pf.nbmax == blocks
+    dump = torch.full_like(pf.scores, float("nan"))
+    pf.estimate_select(dump)
+    counts, indices = pf.counts.clone(), pf.indices.clone()
+    pf.estimate()
+    torch.cuda.synchronize()
+    assert torch.equal(torch.isinf(dump), torch.isinf(pf.scores))
+    seen = ~torch.isinf(dump)
+    # both sum 64 products in fp32, in another order: 64 roundings of 2^-24 of the largest partial sum
+    bound = 64 * 2.0 ** -24 * float(pf.scores[seen].abs().max()) * 2
+    assert float((dump[seen] - pf.scores[seen]).abs().max()) <= bound
+    pf.scores.copy_(dump)
+    pf.select()
+    torch.cuda.synchronize()
+    assert torch.equal(counts, pf.counts) and torch.equal(indices, pf.indices)

@@ -172,12 +172,37 @@ int launch_select(const Problem& p, int heads, const float* scores, const int32_
 //            (pooling included) at 3126 rows and key blocks, 8 / 1 heads, against the 4-row bands on
 //            v_mfma_f32_4x4x1_16B_f32, staged 8 floats of the depth at a time, that served all rows
 //            above 1024 key blocks before (0.99 ms in the case of 1563)
+// The 4-row bands added the products of a score in ascending depth.  Scores that are compared with
+// each other keep that order: above 1024 key blocks both operands are transposed within the groups
+// of four lanes of a row (transpose_quads), so that step s of a 64-byte group takes its floats
+// 4s .. 4s + 3 and the sums are the same bits as before (0.43 instead of 0.41 ms).
 // ------------------------------------------------------------------------------------------------
 struct BandTable {
     int32_t band_start[STEM_MAX_BATCH + 1];            // prefix sums of ceil(rows of the call / ROWS)
 };
 
 constexpr int kScorePad = 4;                           // floats between rows of sc: 16-byte writes of 16 rows spread over all banks
+
+// Four floats per lane, lane group c = lane / 16 holding positions 4c .. 4c + 3 of sixteen: afterwards
+// register s of group c holds position 4s + c, what step s of v_mfma_f32_16x16x4_f32 takes from group c
+// if the sixteen are to be added in ascending order.
+__device__ __forceinline__ float4 transpose_quads(float4 x) {
+    auto swap32 = [](float& a, float& b) {             // upper half of a <-> lower half of b
+        const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        a = __uint_as_float(y[0]);
+        b = __uint_as_float(y[1]);
+    };
+    auto swap16 = [](float& a, float& b) {             // odd rows of 16 lanes of a <-> even rows of b
+        const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        a = __uint_as_float(y[0]);
+        b = __uint_as_float(y[1]);
+    };
+    swap32(x.x, x.z);
+    swap32(x.y, x.w);
+    swap16(x.x, x.y);
+    swap16(x.z, x.w);
+    return x;
+}
 
 template <int ROWS, int NBcap, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, NBcap <= 2048 ? 4 : 2) void score_select_kernel(
@@ -229,6 +254,10 @@ __global__ __launch_bounds__(64 * WAVES, NBcap <= 2048 ? 4 : 2) void score_selec
 #pragma unroll
         for (int u = 0; u < 4; ++u)
             qv[u] = (r < band_rows) ? *reinterpret_cast<const float4*>(q_row + 16 * u) : make_float4(0.f, 0.f, 0.f, 0.f);
+        if constexpr (NBcap > 1024) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) qv[u] = transpose_quads(qv[u]);
+        }
         const float* k_cls = b_src + (S - 1 - a) * d + col0;
         float4 kv[4], kn[4];
         auto load_keys = [&](float4* dst, int tile) {
@@ -244,6 +273,10 @@ __global__ __launch_bounds__(64 * WAVES, NBcap <= 2048 ? 4 : 2) void score_selec
             const int tile = WAVES * t + w;
             if (tile >= n_tiles) break;                // wave-uniform
             if (tile + WAVES < n_tiles) load_keys(kn, tile + WAVES);
+            if constexpr (NBcap > 1024) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) kv[u] = transpose_quads(kv[u]);
+            }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[u].x, qv[u].x, acc[t], 0, 0, 0);

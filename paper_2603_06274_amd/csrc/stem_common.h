@@ -68,12 +68,20 @@ inline int check_launch() {
 }
 
 #if defined(__HIPCC__)
-// Sequence of a global query-block row: the last s with row_start[s] <= r.  Wave-uniform.
-__device__ __forceinline__ int seq_of_row(const SeqTable& t, int r) {
-    int s = 0;
-    for (int x = 1; x < t.batch; ++x) s = (r >= t.row_start[x]) ? x : s;
-    return s;
+// Place of x in the n + 1 ascending prefix sums `start` (start[0] = 0, n <= 64): the last s < n with
+// start[s] <= x.  One load per lane and a ballot: a scalar loop over the sums waits for one load after
+// the other, which every workgroup of a packed batch paid before its first load of data
+// (18 prompts of 389 to 3185 tokens, 32 / 8 heads: all stages 2 % faster).  Called by whole waves with one x per wave.
+__device__ __forceinline__ int place_in(const int32_t* start, int n, int x) {
+    static_assert(STEM_MAX_BATCH <= 64, "one lane per sequence");
+    if (n == 1) return 0;
+    const int lane = threadIdx.x & 63;
+    const bool below = lane < n && start[lane] <= x;
+    return (int)__popcll(__builtin_amdgcn_ballot_w64(below)) - 1;
 }
+
+// Sequence of a global query-block row.  Wave-uniform.
+__device__ __forceinline__ int seq_of_row(const SeqTable& t, int r) { return place_in(t.row_start, t.batch, r); }
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }

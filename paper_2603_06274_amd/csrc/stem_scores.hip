@@ -65,8 +65,7 @@ __global__ __launch_bounds__(kScoreThreads) void block_scores_kernel(
     auto decode = [&](int f) {
         const int h = f / tiles_per_head;
         int x = f - h * tiles_per_head;
-        int s = 0;
-        for (int y = 1; y < seq.batch; ++y) s = (x >= tiles.causal_start[y]) ? y : s;
+        const int s = place_in(tiles.causal_start, seq.batch, x);
         x -= tiles.causal_start[s];
         const int row0 = seq.row_start[s];
         const int first = seq.first_block[s];          // block index of the sequence's first row in the call

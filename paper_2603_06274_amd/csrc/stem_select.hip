@@ -215,8 +215,7 @@ __global__ __launch_bounds__(64 * WAVES, NBcap <= 2048 ? 4 : 2) void score_selec
 
     // bands are handed out last first: within a sequence the later bands see more keys and take longer
     const int band = bands.band_start[seq.batch] - 1 - (int)blockIdx.x;
-    int s = 0;
-    for (int x = 1; x < seq.batch; ++x) s = (band >= bands.band_start[x]) ? x : s;
+    const int s = place_in(bands.band_start, seq.batch, band);
     const int row0 = seq.row_start[s];
     const int n_rows = seq.row_start[s + 1] - row0;    // rows of this sequence in the call
     const int first = seq.first_block[s];
@@ -250,10 +249,12 @@ __global__ __launch_bounds__(64 * WAVES, NBcap <= 2048 ? 4 : 2) void score_selec
     for (int seg = 0; seg < S * segs_per_class; ++seg) {
         const int a = seg / segs_per_class, col0 = (seg - a * segs_per_class) * 64 + 4 * c;
         float4 qv[4];
-        const float* q_row = a_src + (int64_t)r * depth + a * d + col0;
+        // rows and key blocks past the end repeat the last one (no branch around a load): what they give
+        // is not stored, or replaced by -inf
+        const float* q_row = a_src + (int64_t)min(r, band_rows - 1) * depth + a * d + col0;
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            qv[u] = (r < band_rows) ? *reinterpret_cast<const float4*>(q_row + 16 * u) : make_float4(0.f, 0.f, 0.f, 0.f);
+            qv[u] = *reinterpret_cast<const float4*>(q_row + 16 * u);
         if constexpr (NBcap > 1024) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) qv[u] = transpose_quads(qv[u]);
@@ -261,11 +262,10 @@ __global__ __launch_bounds__(64 * WAVES, NBcap <= 2048 ? 4 : 2) void score_selec
         const float* k_cls = b_src + (S - 1 - a) * d + col0;
         float4 kv[4], kn[4];
         auto load_keys = [&](float4* dst, int tile) {
-            const int j = tile * 16 + r;
+            const int j = min(tile * 16 + r, n_keys - 1);
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                dst[u] = (j < n_keys) ? *reinterpret_cast<const float4*>(k_cls + (int64_t)j * depth + 16 * u)
-                                      : make_float4(0.f, 0.f, 0.f, 0.f);
+                dst[u] = *reinterpret_cast<const float4*>(k_cls + (int64_t)j * depth + 16 * u);
         };
         if (w < n_tiles) load_keys(kv, w);
 #pragma unroll

@@ -19,6 +19,9 @@
 // share a CU, so one workgroup's matrix work fills the other's waits (at head size 256 the two
 // 64 KiB buffers and about 490 registers leave room for one).
 //
+// Calls with too few (head, query block) pairs to fill the chip give each several such groups of waves in
+// one workgroup, which share its list and are added up at the end (SPLIT of them, launch_sparse_attn).
+//
 // Inside a wave the instruction stream is kept dense around the matrix instructions: LDS operands
 // are read six matrix instructions ahead into a ring of registers, the softmax of a block is
 // spread pair by pair over the wave's own matrix instructions (the eight pairs of a 32-key tile
@@ -251,6 +254,16 @@ static_assert(SoftmaxSchedule<4, 8>::valid() && SoftmaxSchedule<2, 8>::valid(), 
 static_assert(SoftmaxSchedule<4, 16>::valid() && SoftmaxSchedule<2, 16>::valid(), "softmax schedule, d = 256");
 static_assert(SoftmaxSchedule<4, 4>::valid() && SoftmaxSchedule<2, 4>::valid(), "softmax schedule, d = 64");
 
+// The order in which the query-block rows are handed out: the sequences by the length of their longest
+// list's bound (the block index of the last row), longest first, and a sequence's rows from the last
+// to the first, so that what starts last is short.  Packed as they come, a batch of short prompts can
+// leave its longest row for the end: 12 prompts of 1 to 2047 tokens, 32 / 8 heads, all blocks kept,
+// 155.8 -> 149.6 us for all stages; nothing changes where there is one sequence.
+struct RowWalk {
+    int32_t start[STEM_MAX_BATCH + 1];                 // prefix sums of the rows of the sequences in this order
+    int32_t seq[STEM_MAX_BATCH];
+};
+
 // The body takes the two LDS buffers as __restrict__ parameters: once inlined, every access carries
 // alias-scope information, which lets the compiler's wait-count insertion tell a read of one buffer
 // from an in-flight global->LDS load into the other (otherwise it waits for all of them).
@@ -258,7 +271,7 @@ template <int B, int D, int SPLIT>
 __device__ __forceinline__ void sparse_attn_body(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ counts, const int32_t* __restrict__ indices,
-    uint16_t* __restrict__ out, float* __restrict__ lse, const SeqTable& seq, int Hq, int R, int G,
+    uint16_t* __restrict__ out, float* __restrict__ lse, const SeqTable& seq, const RowWalk& walk, int Hq, int R, int G,
     int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh,
     float scale, int items_per_xcd, int xcds_per_kv_head, int items_per_round, unsigned char* __restrict__ k_all,
     unsigned char* __restrict__ v_all, float2* __restrict__ part_ml) {
@@ -282,23 +295,24 @@ __device__ __forceinline__ void sparse_attn_body(
     // rows first), the G heads of a group side by side; otherwise every XCD takes a contiguous
     // range of the (KV head, row descending, head in group) order ----
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    int g, r, h;
+    int g, h, pos;                                     // pos: place of the row in the walk
     if (xcds_per_kv_head > 0) {
-        const int rank = (slot / G) * xcds_per_kv_head + xcd % xcds_per_kv_head;
-        if (slot >= items_per_xcd || rank >= R) return;
+        pos = (slot / G) * xcds_per_kv_head + xcd % xcds_per_kv_head;
+        if (slot >= items_per_xcd || pos >= R) return;
         g = xcd / xcds_per_kv_head;
-        r = R - 1 - rank;
         h = g * G + slot % G;
     } else {
         const int64_t item = (int64_t)xcd * items_per_xcd + slot;
         if (slot >= items_per_xcd || item >= (int64_t)Hq * R) return;
         g = (int)(item / ((int64_t)R * G));
         const int rem = (int)(item - (int64_t)g * R * G);
-        r = R - 1 - rem / G;
+        pos = rem / G;
         h = g * G + rem % G;
     }
 
-    const int s = seq_of_row(seq, r);
+    const int turn = place_in(walk.start, seq.batch, pos);
+    const int s = walk.seq[turn];
+    const int r = seq.row_start[s + 1] - 1 - (pos - walk.start[turn]);
     const int ic = r - seq.row_start[s];               // row inside the call's chunk of the sequence
     const int i = seq.first_block[s] + ic;             // block index in the sequence
     const int seq_lo = seq.tok_start[s], seq_hi = seq.kv_end[s];   // key token rows the call may read
@@ -372,7 +386,8 @@ __device__ __forceinline__ void sparse_attn_body(
     // the reads hit, 52 GB of misses; with every list replaced by the same blocks 7.62 instead of
     // 8.79 ms), and a round that begins where the last one ended shares with its stragglers: 8.61 ->
     // 8.34 ms.  With 128-token blocks, 87 % hits, there is next to nothing to gain (1 % between real
-    // lists and identical ones) and the direction makes no difference.
+    // lists and identical ones) and the direction makes no difference; nor is there any while a head's keys
+    // and values are within twice the L2 (the host's items_per_round is out of reach then).
     const bool backwards = SPLIT == 1 && B == 64 && ((slot / items_per_round) & 1);
     // Group `part` of a split workgroup takes the entries part, part + SPLIT, ...  All groups pass the
     // same barriers, so they all run the longest share's number of blocks; where a share is one
@@ -673,6 +688,7 @@ __device__ __forceinline__ void sparse_attn_body(
 
     // ---- split list: the other groups hand over their reference, row sum and O (fp32, through the K and
     // V buffers, which hold exactly that many accumulators), group 0 adds them up in group order ----
+    static_assert(SPLIT == 1 || !kManualHazards, "the other groups' registers are read by plain vector code");
     if constexpr (SPLIT > 1) {
         constexpr int kQuads = DT * 4;                 // float4 per lane; half of them fit the K buffer
         auto slot_of = [&](int g2, int y) {
@@ -749,13 +765,13 @@ template <int B, int D, int SPLIT>
 __global__ __launch_bounds__(B * 2 * SPLIT, D == 256 ? 1 : 2) void sparse_attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ counts, const int32_t* __restrict__ indices,
-    uint16_t* __restrict__ out, float* __restrict__ lse, SeqTable seq, int Hq, int R, int G, int T,
+    uint16_t* __restrict__ out, float* __restrict__ lse, SeqTable seq, RowWalk walk, int Hq, int R, int G, int T,
     int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh, float scale,
     int items_per_xcd, int xcds_per_kv_head, int items_per_round) {
     __shared__ __attribute__((aligned(1024))) unsigned char k_lds[SPLIT * B * D * 2];
     __shared__ __attribute__((aligned(1024))) unsigned char v_lds[SPLIT * B * D * 2];
     __shared__ float2 part_ml[SPLIT > 1 ? (SPLIT - 1) * B * 2 : 1];
-    sparse_attn_body<B, D, SPLIT>(q, k, v, counts, indices, out, lse, seq, Hq, R, G, T, kmax, shared_lists, q_st, q_sh,
+    sparse_attn_body<B, D, SPLIT>(q, k, v, counts, indices, out, lse, seq, walk, Hq, R, G, T, kmax, shared_lists, q_st, q_sh,
                            kv_st, kv_sh, scale, items_per_xcd, xcds_per_kv_head, items_per_round, k_lds, v_lds, part_ml);
 }
 
@@ -772,9 +788,26 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
                                 : (items + 7) / 8;
     if (per_xcd * 8 > 0x7fffffff) return STEM_ERR_UNSUPPORTED;
     dim3 grid((unsigned)(per_xcd * 8));
+    RowWalk walk;
+    auto last_block = [&](int s) { return p.seq.first_block[s] + p.seq.row_start[s + 1] - p.seq.row_start[s]; };
+    for (int x = 0; x < p.batch; ++x) {                // insertion sort of at most 64; of equal ones the later first
+        int y = x;
+        for (; y > 0 && last_block(walk.seq[y - 1]) <= last_block(x); --y) walk.seq[y] = walk.seq[y - 1];
+        walk.seq[y] = x;
+    }
+    walk.start[0] = 0;
+    for (int x = 0; x < p.batch; ++x)
+        walk.start[x + 1] = walk.start[x] + p.seq.row_start[walk.seq[x] + 1] - p.seq.row_start[walk.seq[x]];
     // workgroups of an XCD that run at a time: 32 CUs, each as many as its waves' registers allow (three
     // waves per SIMD at B = 64, d = 64, one at d = 256, else two).  Only the walking direction hangs on it.
-    const int per_round = 32 * (p.d == 256 ? 1 : p.d == 64 && p.B == 64 ? 3 : 2) * (p.B == 64 ? 2 : 1);
+    int64_t longest = 0;
+    for (int x = 0; x < p.batch; ++x) {
+        const int64_t keys = p.seq.kv_end[x] - p.seq.tok_start[x];
+        longest = keys > longest ? keys : longest;
+    }
+    constexpr int64_t kTwiceL2 = 8 << 20;
+    const int per_round = longest * p.d * 4 <= kTwiceL2 ? 0x7fffffff
+                          : 32 * (p.d == 256 ? 1 : p.d == 64 && p.B == 64 ? 3 : 2) * (p.B == 64 ? 2 : 1);
     int device = 0, cus = 0;
     if (hipGetDevice(&device) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0)
@@ -785,7 +818,7 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     // lists are long enough to pay for the hand-over, about one block's time.  Measured, one / split:
     // 126 rows of 25 blocks of 64 27.0 / 18.9 us, 64 rows of 11 14.9 / 12.9 us; 235 rows of 23 blocks of
     // 128 51.5 / 46.5 us, but 252 rows of 12 29.0 / 29.7 us, hence 16 entries there.
-    const int fit = p.B == 64 ? (p.d == 256 ? 2 : 4) : (p.d == 256 ? 1 : 2);   // groups a CU has room for
+    const int fit = p.d == 256 ? 1 : p.B == 64 ? 4 : 2;   // groups a CU has room for; none shared at d = 256
     int split = 1;
     while (split < fit && items * (split * 2) <= (int64_t)cus * fit && kmax >= (p.B == 64 ? 8 : 16)) split *= 2;
     const uint16_t* qq = static_cast<const uint16_t*>(q);
@@ -794,7 +827,7 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     uint16_t* oo = static_cast<uint16_t*>(out);
 #define STEM_ATTN_LAUNCH(BB, DD, SS)                                                                         \
     hipLaunchKernelGGL((sparse_attn_kernel<BB, DD, SS>), grid, dim3(BB * 2 * SS), 0, stream, qq, kk, vv, counts, \
-                       indices, oo, lse, p.seq, p.Hq, p.R, p.G, p.T, kmax, lists_per_kv_head, p.q_st, p.q_sh, \
+                       indices, oo, lse, p.seq, walk, p.Hq, p.R, p.G, p.T, kmax, lists_per_kv_head, p.q_st, p.q_sh, \
                        p.kv_st, p.kv_sh, softmax_scale, (int)per_xcd, xcds_per_kv_head, per_round)
 #define STEM_ATTN_LAUNCH_2(BB, DD)                      \
     do {                                                \
@@ -811,7 +844,7 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     else if (p.B == 128 && p.d == 64) STEM_ATTN_LAUNCH_2(128, 64);
     else if (p.B == 64 && p.d == 64) STEM_ATTN_LAUNCH_4(64, 64);
     else if (p.B == 128 && p.d == 256) STEM_ATTN_LAUNCH(128, 256, 1);
-    else if (p.B == 64 && p.d == 256) STEM_ATTN_LAUNCH_2(64, 256);
+    else if (p.B == 64 && p.d == 256) STEM_ATTN_LAUNCH(64, 256, 1);
     else return STEM_ERR_UNSUPPORTED;
 #undef STEM_ATTN_LAUNCH_4
 #undef STEM_ATTN_LAUNCH_2

@@ -1,0 +1,22 @@
+"""Packed batches in orders that the hand-out of query-block rows has to untangle (longest sequence first,
+rows of a sequence from the last to the first), with empty, equal and one-token sequences, for head counts that
+take either mapping of heads to XCDs; every row of every sequence against the oracle."""
+import pytest
+
+from paper_2603_06274_amd import workloads as wl
+
+from test_gpu_parity import run_both
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,heads,lens", [
+    (128, (4, 2), (64, 700, 0, 700, 1300, 1)),                 # ascending with a tie, an empty and a short end
+    (64, (3, 3), (0, 900, 130, 0, 64, 65)),                    # an empty head, descending; 3 KV heads
+    (64, (8, 1), tuple(37 * ((7 * x) % 64) for x in range(64))),   # the most sequences a call takes, one empty
+])
+def test_sequence_orders(B, heads, lens):
+    w = wl.small("orders_%d_%d" % (B, len(lens)), seed=68, num_q_heads=heads[0], num_kv_heads=heads[1], seq_lens=lens,
+                 block_size=B, k_start=tuple(min(4, max(1, -(-n // B))) for n in lens), n_sink=1, n_local=1,
+                 outliers=tuple(1 if n else 0 for n in lens))
+    run_both(w)

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
     # items = Hq x 25 rows (B = 64) or 13 rows (B = 128) on 256 CUs
     (64, 128, 4, 2), (64, 128, 16, 2), (64, 128, 44, 2),       # 100: four groups, 400: two, 1100: one
     (64, 64, 10, 1), (64, 64, 20, 1), (64, 64, 43, 1),         # 250: four, 500: two, 1075: one
-    (64, 256, 10, 2), (64, 256, 12, 1),                        # 250: two, 300: one
+    (64, 256, 10, 2), (128, 256, 10, 1),                       # one, whatever the size of the call
     (128, 128, 18, 3), (128, 128, 22, 2),                      # 234: two, 286: one
     (128, 64, 4, 1), (128, 64, 24, 2),                         # 52: two, 312: one
 ])

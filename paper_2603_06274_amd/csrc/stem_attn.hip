@@ -261,7 +261,7 @@ static_assert(SoftmaxSchedule<4, 4>::valid() && SoftmaxSchedule<2, 4>::valid(), 
 // 155.8 -> 149.6 us for all stages; nothing changes where there is one sequence.
 struct RowWalk {
     int32_t start[STEM_MAX_BATCH + 1];                 // prefix sums of the rows of the sequences in this order
-    int32_t seq[STEM_MAX_BATCH];
+    uint8_t seq[STEM_MAX_BATCH];
 };
 
 // The body takes the two LDS buffers as __restrict__ parameters: once inlined, every access carries
@@ -793,7 +793,7 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     for (int x = 0; x < p.batch; ++x) {                // insertion sort of at most 64; of equal ones the later first
         int y = x;
         for (; y > 0 && last_block(walk.seq[y - 1]) <= last_block(x); --y) walk.seq[y] = walk.seq[y - 1];
-        walk.seq[y] = x;
+        walk.seq[y] = (uint8_t)x;
     }
     walk.start[0] = 0;
     for (int x = 0; x < p.batch; ++x)
@@ -808,10 +808,8 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     constexpr int64_t kTwiceL2 = 8 << 20;
     const int per_round = longest * p.d * 4 <= kTwiceL2 ? 0x7fffffff
                           : 32 * (p.d == 256 ? 1 : p.d == 64 && p.B == 64 ? 3 : 2) * (p.B == 64 ? 2 : 1);
-    int device = 0, cus = 0;
-    if (hipGetDevice(&device) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0)
-        return STEM_ERR_HIP;
+    const int cus = compute_units();
+    if (cus <= 0) return STEM_ERR_HIP;
     // How many groups of waves share a row's list, where the rows alone leave the chip idle: as long as
     // the groups of all rows fit the chip at once (a group at B = 64 is two waves and leaves half of a CU's
     // SIMDs idle, one at B = 128 is a wave per SIMD and gains only what a second wave adds), and the

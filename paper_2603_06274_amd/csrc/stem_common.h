@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "stem.h"
 
 namespace stem {
@@ -62,6 +64,19 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
                        const int32_t* counts, const int32_t* indices, int32_t kmax,
                        bool lists_per_kv_head, float softmax_scale, void* out, float* lse,
                        hipStream_t stream);
+
+// Compute units of the current device, 0 on failure.  A constant of the device, kept after the first call
+// (several threads may store the same value): the query costs a call that has 30 us in all about 1 %.
+inline int compute_units() {
+    constexpr int kDevices = 64;
+    static std::atomic<int> known[kDevices];           // zero at start
+    int device = 0, cus = 0;
+    if (hipGetDevice(&device) != hipSuccess || device < 0) return 0;
+    if (device < kDevices && (cus = known[device].load(std::memory_order_relaxed)) > 0) return cus;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0) return 0;
+    if (device < kDevices) known[device].store(cus, std::memory_order_relaxed);
+    return cus;
+}
 
 inline int check_launch() {
     return hipGetLastError() == hipSuccess ? STEM_OK : STEM_ERR_HIP;

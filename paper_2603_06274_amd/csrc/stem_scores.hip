@@ -252,10 +252,8 @@ int launch_block_scores(const Problem& p, int ad_stride, const float* q_bar, con
     }
     if (row_tiles == 0) return STEM_OK;
     if (p.Hq > 65535 || (int64_t)causal * p.Hq > 0x7fffffff) return STEM_ERR_UNSUPPORTED;
-    int device = 0, cus = 0;
-    if (hipGetDevice(&device) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0)
-        return STEM_ERR_HIP;
+    const int cus = compute_units();
+    if (cus <= 0) return STEM_ERR_HIP;
     const int total = causal * p.Hq;
     const int workgroups = total < cus * kScoreWorkgroupsPerCU ? total : cus * kScoreWorkgroupsPerCU;
     hipLaunchKernelGGL(block_scores_kernel, dim3(workgroups), dim3(kScoreThreads), 0, stream, q_bar, k_bar, m_v,

@@ -19,9 +19,6 @@
 // share a CU, so one workgroup's matrix work fills the other's waits (at head size 256 the two
 // 64 KiB buffers and about 490 registers leave room for one).
 //
-// Calls with too few (head, query block) pairs to fill the chip give each several such groups of waves in
-// one workgroup, which share its list and are added up at the end (SPLIT of them, launch_sparse_attn).
-//
 // Inside a wave the instruction stream is kept dense around the matrix instructions: LDS operands
 // are read six matrix instructions ahead into a ring of registers, the softmax of a block is
 // spread pair by pair over the wave's own matrix instructions (the eight pairs of a 32-key tile
@@ -267,18 +264,18 @@ struct RowWalk {
 // The body takes the two LDS buffers as __restrict__ parameters: once inlined, every access carries
 // alias-scope information, which lets the compiler's wait-count insertion tell a read of one buffer
 // from an in-flight global->LDS load into the other (otherwise it waits for all of them).
-template <int B, int D, int SPLIT>
+template <int B, int D>
 __device__ __forceinline__ void sparse_attn_body(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ counts, const int32_t* __restrict__ indices,
     uint16_t* __restrict__ out, float* __restrict__ lse, const SeqTable& seq, const RowWalk& walk, int Hq, int R, int G,
     int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh,
-    float scale, int items_per_xcd, int xcds_per_kv_head, int items_per_round, unsigned char* __restrict__ k_all,
-    unsigned char* __restrict__ v_all, float2* __restrict__ part_ml) {
+    float scale, int items_per_xcd, int xcds_per_kv_head, int items_per_round, unsigned char* __restrict__ k_lds,
+    unsigned char* __restrict__ v_lds) {
     constexpr int KT = B / 32;                         // 32-key tiles per block
     constexpr int KS = D / 16;                         // 16-wide steps of S^T along d; also requests per wave, tensor and block
     constexpr int DT = D / 32;                         // 32-row tiles of O^T along d
-    constexpr int NW = B / 32;                         // waves of a group: one 32-query tile each
+    constexpr int NW = B / 32;                         // waves
     constexpr int kRowBytes = D * 2;                   // one K or V row in LDS
     constexpr int kSliceRows = 1024 / kRowBytes;       // rows one wave-wide 1 KiB request covers
     // head size 256 needs more than 256 registers per lane: matrix instructions by hand (see above)
@@ -329,11 +326,7 @@ __device__ __forceinline__ void sparse_attn_body(
     const int q_hi = seq.q_tok_start[s + 1];
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int part = SPLIT > 1 ? wave / NW : 0;        // which share of the list
-    const int w = SPLIT > 1 ? wave % NW : wave;
-    unsigned char* k_lds = k_all + part * (B * kRowBytes);
-    unsigned char* v_lds = v_all + part * (B * kRowBytes);
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, hi = lane >> 5;
     const int qrow = w * 32 + col;                     // query row inside the block
     const int tok_q = tok_q0 + qrow;
@@ -374,8 +367,8 @@ __device__ __forceinline__ void sparse_attn_body(
         for (int x = 0; x < kKVariants; ++x) rq.lane_off[x] = k_off[x] + off;
         return rq;
     };
-    auto v_request = [&](int j, bool real) {
-        const uint32_t off = real ? j * block_bytes : 0x80000000u;
+    auto v_request = [&](int j) {
+        const uint32_t off = j * block_bytes;
         return BlockRequest<1>{v_rsrc, {v_off + off}};
     };
     unsigned char* k_slice0 = k_lds + w * 1024;        // this wave's first request slice
@@ -397,20 +390,15 @@ __device__ __forceinline__ void sparse_attn_body(
     // 8.34 ms.  With 128-token blocks, 87 % hits, there is next to nothing to gain (1 % between real
     // lists and identical ones) and the direction makes no difference; nor is there any while a head's keys
     // and values are within twice the L2 (the host's items_per_round is out of reach then).
-    const bool backwards = SPLIT == 1 && B == 64 && ((slot / items_per_round) & 1);
-    // Group `part` of a split workgroup takes the entries part, part + SPLIT, ...  All groups pass the
-    // same barriers, so they all run the longest share's number of blocks; where a share is one
-    // entry short, the block is absent (-1): nothing is fetched and everything is masked.
-    const int blocks = SPLIT > 1 ? (cnt + SPLIT - 1) / SPLIT : cnt;
+    const bool backwards = B == 64 && ((slot / items_per_round) & 1);
     auto list_chunk = [&](int first) {
-        const int e = SPLIT > 1 ? (first + lane) * SPLIT + part : first + lane;
-        return e < cnt ? list[backwards ? cnt - 1 - e : e] : SPLIT > 1 ? -1 : 0;
+        const int e = first + lane;
+        return e < cnt ? list[backwards ? cnt - 1 - e : e] : 0;
     };
-    auto fetched = [&](int j) { return SPLIT == 1 || j >= 0; };
     int list_reg = list_chunk(0);
     int j_cur = __builtin_amdgcn_readlane(list_reg, 0);
     if (cnt > 0) {
-        const auto rq = k_request(clamped(j_cur), fetched(j_cur));
+        const auto rq = k_request(clamped(j_cur), true);
 #pragma unroll
         for (int u = 0; u < KS; ++u) rq.issue(u, k_slice0, slice_step, slice_lds_step);
     }
@@ -610,7 +598,7 @@ __device__ __forceinline__ void sparse_attn_body(
     auto one_block = [&](int it, auto first_tag) {
         constexpr bool kFirst = decltype(first_tag)::value;
         const int j = clamped(j_cur);
-        const bool has_next = it + 1 < blocks;
+        const bool has_next = it + 1 < cnt;
         if (((it + 1) & 63) == 0) list_reg = list_chunk(it + 1);
         // on the diagonal block keys above the query are masked; an unusable entry is masked entirely
         const bool masked = (j == i) || !usable(j_cur);
@@ -623,7 +611,7 @@ __device__ __forceinline__ void sparse_attn_body(
         uint4 ka[kSlots];
 #pragma unroll
         for (int n = 0; n < kAhead; ++n) ka[n] = load_k(n);
-        const auto v_rq = v_request(j, fetched(j_cur));
+        const auto v_rq = v_request(j);
         const int j_nxt = __builtin_amdgcn_readlane(list_reg, (it + 1) & 63);   // 0 past the end
         clear_sum();
         STEM_SCHED_FENCE();
@@ -659,7 +647,7 @@ __device__ __forceinline__ void sparse_attn_body(
         uint4 va[kSlots];
 #pragma unroll
         for (int n = 0; n < kAhead; ++n) va[n] = load_v(n);
-        const auto k_rq = k_request(clamped(j_nxt), has_next && fetched(j_nxt));
+        const auto k_rq = k_request(clamped(j_nxt), has_next);
         STEM_SCHED_FENCE();
         auto pv_range = [&](int n_lo, int n_hi) {      // even bounds
 #pragma unroll
@@ -690,50 +678,10 @@ __device__ __forceinline__ void sparse_attn_body(
         pv_range(kCheckSlot[1] - NS, NS);
         j_cur = j_nxt;
     };
-    if (blocks > 0) one_block(0, std::true_type{});
-    for (int it = 1; it < blocks; ++it) one_block(it, std::false_type{});
+    if (cnt > 0) one_block(0, std::true_type{});
+    for (int it = 1; it < cnt; ++it) one_block(it, std::false_type{});
     STEM_WAIT_VMCNT(0);                                // no request may outlive the workgroup's LDS
     if constexpr (kManualHazards) wait_states_acc<16>(o_acc);   // the last O^T instructions have written
-
-    // ---- split list: the other groups hand over their reference, row sum and O (fp32, through the K and
-    // V buffers, which hold exactly that many accumulators), group 0 adds them up in group order ----
-    static_assert(SPLIT == 1 || !kManualHazards, "the other groups' registers are read by plain vector code");
-    if constexpr (SPLIT > 1) {
-        constexpr int kQuads = DT * 4;                 // float4 per lane; half of them fit the K buffer
-        auto slot_of = [&](int g2, int y) {
-            unsigned char* base = y < kQuads / 2 ? k_all : v_all;
-            return reinterpret_cast<float4*>(base + g2 * (B * kRowBytes)) + (w * (kQuads / 2) + y % (kQuads / 2)) * 64 + lane;
-        };
-        STEM_BARRIER();                                // nothing reads or fills a buffer any more
-        if (part > 0) {
-            part_ml[((part - 1) * NW + w) * 64 + lane] = make_float2(m_ref, l_run);
-#pragma unroll
-            for (int y = 0; y < kQuads; ++y) {
-                const int dt = y / 4, x = (y % 4) * 4;
-                *slot_of(part, y) = make_float4(o_acc[dt][x], o_acc[dt][x + 1], o_acc[dt][x + 2], o_acc[dt][x + 3]);
-            }
-        }
-        __syncthreads();
-        if (part > 0) return;                          // no barrier follows
-#pragma unroll 1
-        for (int g2 = 1; g2 < SPLIT; ++g2) {
-            const float2 ml = part_ml[((g2 - 1) * NW + w) * 64 + lane];
-            const float m_new = fmaxf(m_ref, ml.x);
-            const float c0 = m_ref == neg_inf ? 0.f : __builtin_amdgcn_exp2f((m_ref - m_new) * sl2);
-            const float c1 = ml.x == neg_inf ? 0.f : __builtin_amdgcn_exp2f((ml.x - m_new) * sl2);
-            m_ref = m_new;
-            l_run = l_run * c0 + ml.y * c1;
-#pragma unroll
-            for (int y = 0; y < kQuads; ++y) {
-                const int dt = y / 4, x = (y % 4) * 4;
-                const float4 o2 = *slot_of(g2, y);
-                o_acc[dt][x] = o_acc[dt][x] * c0 + o2.x * c1;
-                o_acc[dt][x + 1] = o_acc[dt][x + 1] * c0 + o2.y * c1;
-                o_acc[dt][x + 2] = o_acc[dt][x + 2] * c0 + o2.z * c1;
-                o_acc[dt][x + 3] = o_acc[dt][x + 3] * c0 + o2.w * c1;
-            }
-        }
-    }
 
     // ---- normalise and store: accumulator x of d tile dt is column dt*32 + 8*(x/4) + 4*hi + x%4 ----
     float l_tot;
@@ -770,18 +718,17 @@ __device__ __forceinline__ void sparse_attn_body(
     }
 }
 
-template <int B, int D, int SPLIT>
-__global__ __launch_bounds__(B * 2 * SPLIT, D == 256 ? 1 : 2) void sparse_attn_kernel(
+template <int B, int D>
+__global__ __launch_bounds__(B * 2, D == 256 ? 1 : 2) void sparse_attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ counts, const int32_t* __restrict__ indices,
     uint16_t* __restrict__ out, float* __restrict__ lse, SeqTable seq, RowWalk walk, int Hq, int R, int G, int T,
     int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh, float scale,
     int items_per_xcd, int xcds_per_kv_head, int items_per_round) {
-    __shared__ __attribute__((aligned(1024))) unsigned char k_lds[SPLIT * B * D * 2];
-    __shared__ __attribute__((aligned(1024))) unsigned char v_lds[SPLIT * B * D * 2];
-    __shared__ float2 part_ml[SPLIT > 1 ? (SPLIT - 1) * B * 2 : 1];
-    sparse_attn_body<B, D, SPLIT>(q, k, v, counts, indices, out, lse, seq, walk, Hq, R, G, T, kmax, shared_lists, q_st, q_sh,
-                           kv_st, kv_sh, scale, items_per_xcd, xcds_per_kv_head, items_per_round, k_lds, v_lds, part_ml);
+    __shared__ __attribute__((aligned(1024))) unsigned char k_lds[B * D * 2];
+    __shared__ __attribute__((aligned(1024))) unsigned char v_lds[B * D * 2];
+    sparse_attn_body<B, D>(q, k, v, counts, indices, out, lse, seq, walk, Hq, R, G, T, kmax, shared_lists, q_st, q_sh,
+                           kv_st, kv_sh, scale, items_per_xcd, xcds_per_kv_head, items_per_round, k_lds, v_lds);
 }
 
 int launch_sparse_attn(const Problem& p, const void* q, const void* k, const void* v,
@@ -796,7 +743,7 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
                                 ? (int64_t)((p.R + xcds_per_kv_head - 1) / xcds_per_kv_head) * p.G
                                 : (items + 7) / 8;
     if (per_xcd * 8 > 0x7fffffff) return STEM_ERR_UNSUPPORTED;
-    dim3 grid((unsigned)(per_xcd * 8));
+    dim3 grid((unsigned)(per_xcd * 8)), block(p.B * 2);
     RowWalk walk;
     auto last_block = [&](int s) { return p.seq.first_block[s] + p.seq.row_start[s + 1] - p.seq.row_start[s]; };
     for (int x = 0; x < p.batch; ++x) {                // insertion sort of at most 64; of equal ones the later first
@@ -817,44 +764,21 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     constexpr int64_t kTwiceL2 = 8 << 20;
     const int per_round = longest * p.d * 4 <= kTwiceL2 ? 0x7fffffff
                           : 32 * (p.d == 256 ? 1 : p.d == 64 && p.B == 64 ? 3 : 2) * (p.B == 64 ? 2 : 1);
-    const int cus = compute_units();
-    if (cus <= 0) return STEM_ERR_HIP;
-    // How many groups of waves share a row's list, where the rows alone leave the chip idle: as long as
-    // the groups of all rows fit the chip at once (a group at B = 64 is two waves and leaves half of a CU's
-    // SIMDs idle, one at B = 128 is a wave per SIMD and gains only what a second wave adds), and the
-    // lists are long enough to pay for the hand-over, about one block's time.  Measured, one / split:
-    // 126 rows of 25 blocks of 64 27.0 / 18.9 us, 64 rows of 11 14.9 / 12.9 us; 235 rows of 23 blocks of
-    // 128 51.5 / 46.5 us, but 252 rows of 12 29.0 / 29.7 us, hence 16 entries there.
-    const int fit = p.d == 256 ? 1 : p.B == 64 ? 4 : 2;   // groups a CU has room for; none shared at d = 256
-    int split = 1;
-    while (split < fit && items * (split * 2) <= (int64_t)cus * fit && kmax >= (p.B == 64 ? 8 : 16)) split *= 2;
     const uint16_t* qq = static_cast<const uint16_t*>(q);
     const uint16_t* kk = static_cast<const uint16_t*>(k);
     const uint16_t* vv = static_cast<const uint16_t*>(v);
     uint16_t* oo = static_cast<uint16_t*>(out);
-#define STEM_ATTN_LAUNCH(BB, DD, SS)                                                                         \
-    hipLaunchKernelGGL((sparse_attn_kernel<BB, DD, SS>), grid, dim3(BB * 2 * SS), 0, stream, qq, kk, vv, counts, \
-                       indices, oo, lse, p.seq, walk, p.Hq, p.R, p.G, p.T, kmax, lists_per_kv_head, p.q_st, p.q_sh, \
+#define STEM_ATTN_LAUNCH(BB, DD)                                                                          \
+    hipLaunchKernelGGL((sparse_attn_kernel<BB, DD>), grid, block, 0, stream, qq, kk, vv, counts, indices, \
+                       oo, lse, p.seq, walk, p.Hq, p.R, p.G, p.T, kmax, lists_per_kv_head, p.q_st, p.q_sh, \
                        p.kv_st, p.kv_sh, softmax_scale, (int)per_xcd, xcds_per_kv_head, per_round)
-#define STEM_ATTN_LAUNCH_2(BB, DD)                      \
-    do {                                                \
-        if (split == 2) STEM_ATTN_LAUNCH(BB, DD, 2);    \
-        else STEM_ATTN_LAUNCH(BB, DD, 1);               \
-    } while (0)
-#define STEM_ATTN_LAUNCH_4(BB, DD)                      \
-    do {                                                \
-        if (split == 4) STEM_ATTN_LAUNCH(BB, DD, 4);    \
-        else STEM_ATTN_LAUNCH_2(BB, DD);                \
-    } while (0)
-    if (p.B == 128 && p.d == 128) STEM_ATTN_LAUNCH_2(128, 128);
-    else if (p.B == 64 && p.d == 128) STEM_ATTN_LAUNCH_4(64, 128);
-    else if (p.B == 128 && p.d == 64) STEM_ATTN_LAUNCH_2(128, 64);
-    else if (p.B == 64 && p.d == 64) STEM_ATTN_LAUNCH_4(64, 64);
-    else if (p.B == 128 && p.d == 256) STEM_ATTN_LAUNCH(128, 256, 1);
-    else if (p.B == 64 && p.d == 256) STEM_ATTN_LAUNCH(64, 256, 1);
+    if (p.B == 128 && p.d == 128) STEM_ATTN_LAUNCH(128, 128);
+    else if (p.B == 64 && p.d == 128) STEM_ATTN_LAUNCH(64, 128);
+    else if (p.B == 128 && p.d == 64) STEM_ATTN_LAUNCH(128, 64);
+    else if (p.B == 64 && p.d == 64) STEM_ATTN_LAUNCH(64, 64);
+    else if (p.B == 128 && p.d == 256) STEM_ATTN_LAUNCH(128, 256);
+    else if (p.B == 64 && p.d == 256) STEM_ATTN_LAUNCH(64, 256);
     else return STEM_ERR_UNSUPPORTED;
-#undef STEM_ATTN_LAUNCH_4
-#undef STEM_ATTN_LAUNCH_2
 #undef STEM_ATTN_LAUNCH
     return check_launch();
 }

@@ -1,0 +1,100 @@
+"""Stage 3 sums a row in one order, whatever else its call holds: rows asked for in a chunk, without the
+sequences they were packed with, or by fewer heads come out as the same bits of output and lse."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import stem_oracle as so
+from paper_2603_06274_amd import binding as sb
+
+pytestmark = pytest.mark.gpu
+
+
+class Call:
+    """Inputs and lists of a packed call on the device, and parts of it as calls of their own."""
+
+    def __init__(self, B, d, Hq, Hkv, lens, longest_list, shared=False, wide=0):
+        self.B, self.d, self.Hq, self.Hkv, self.G = B, d, Hq, Hkv, Hq // Hkv
+        self.cu = [0] + np.cumsum(lens).tolist()
+        T = self.cu[-1]
+        dev = torch.device("cuda:0")
+        g = torch.Generator().manual_seed(9)
+        ramp = 1.0 + 3.0 * torch.arange(T).float() / T                 # the softmax reference moves
+        q = 2.0 * torch.randn(T, Hq, d, generator=g)
+        k = torch.randn(T, Hkv, d, generator=g) * ramp[:, None, None]
+        self.q = q.to(torch.bfloat16).to(dev)
+        self.kv = []
+        for x in (k, torch.randn(T, Hkv, d, generator=g)):
+            rows = torch.empty(T, Hkv, d + wide, dtype=torch.bfloat16, device=dev)
+            rows[:, :, :d] = x.to(torch.bfloat16).to(dev)
+            self.kv.append(rows[:, :, :d])
+        r = np.random.default_rng(5)
+        self.table = so.sequence_table(self.cu, B)
+        R, lists = so.total_rows(self.cu, B)[0], Hkv if shared else Hq
+        self.shared = shared
+        counts = np.zeros((lists, R), np.int32)
+        indices = np.full((lists, R, longest_list), -1, np.int32)
+        for (_, _, nb, row0) in self.table:
+            for i in range(nb):
+                for h in range(lists):
+                    n = min(i + 1, int(r.integers(1, longest_list + 1)))
+                    pick = np.sort(np.append(r.permutation(i)[:n - 1], i))
+                    counts[h, row0 + i] = n
+                    indices[h, row0 + i, :n] = pick
+        self.counts, self.indices = torch.from_numpy(counts).to(dev), torch.from_numpy(indices).to(dev)
+
+    def attend(self, seqs, chunk=None, kv_heads=None):
+        """out and lse of the sequences `seqs` (chunk: block range of each, (lo, hi)), of the first kv_heads
+        KV heads, as one call; and the token rows of the whole call that they are."""
+        kv_heads = kv_heads or self.Hkv
+        heads = kv_heads * self.G
+        B, cu, starts, ends = self.B, [0], [], []
+        tokens, keys, rows = [], [], []
+        for x, s in enumerate(seqs):
+            lo, hi, nb, row0 = self.table[s]
+            a, b = chunk[x] if chunk else (0, nb)
+            starts.append(a * B)
+            ends.append(min(b * B, hi - lo))
+            cu.append(cu[-1] + hi - lo)
+            keys.append(torch.arange(lo, hi))
+            tokens.append(torch.arange(lo + starts[-1], lo + ends[-1]))
+            rows.append(torch.arange(row0 + a, row0 + b))
+        tokens, keys, rows = torch.cat(tokens), torch.cat(keys), torch.cat(rows)
+        q = self.q[tokens][:, :heads].contiguous()
+        if len(seqs) == len(self.table):
+            k, v = (x[:, :kv_heads] for x in self.kv)
+        else:
+            k, v = (x[keys][:, :kv_heads].contiguous() for x in self.kv)
+        lists = kv_heads if self.shared else heads
+        counts, indices = (x[:lists, rows].contiguous() for x in (self.counts, self.indices))
+        shape = sb.Shape.from_tensors(q, k, B, cu, (starts, ends) if chunk else None)
+        out = torch.full_like(q, float("nan"))
+        lse = torch.full((heads, q.shape[0]), float("nan"), dtype=torch.float32, device=q.device)
+        sb.stem_sparse_attn(shape, q, k, v, counts, indices, indices.shape[2], self.d ** -0.5, out, lse,
+                            lists_per_kv_head=self.shared)
+        torch.cuda.synchronize()
+        assert not torch.isnan(out).any().item() and not torch.isnan(lse).any().item()
+        return out, lse, tokens
+
+    def check_part(self, whole, seqs, chunk=None, kv_heads=None):
+        out, lse, tokens = self.attend(seqs, chunk, kv_heads)
+        print("part: sequences", seqs, "blocks", chunk, "kv heads", kv_heads or self.Hkv, flush=True)
+        assert torch.equal(out, whole[0][tokens][:, :out.shape[1]])
+        assert torch.equal(lse, whole[1][:lse.shape[0], tokens])
+
+
+@pytest.mark.parametrize("B,d,shared,wide", [
+    (64, 128, False, 0), (64, 64, True, 0), (64, 256, False, 0),
+    (128, 128, True, 0), (128, 64, False, 0), (128, 256, False, 0), (128, 128, False, 24),
+])
+def test_parts_of_a_call_by_themselves(B, d, shared, wide):
+    """A call with more (head, row) pairs than the chip takes at a time, and parts of it that
+    leave most of the chip idle, down to one row of one group of heads."""
+    blocks = 110 if B == 64 else 80
+    c = Call(B, d, 16, 4, (blocks * B - 5, 20 * B, 3 * B + 1), 70, shared, wide)
+    whole = c.attend([0, 1, 2])
+    c.check_part(whole, [1])
+    c.check_part(whole, [0, 1, 2], [(blocks - 12, blocks), (9, 9), (2, 4)])
+    c.check_part(whole, [0], [(blocks - 30, blocks - 26)])
+    c.check_part(whole, [0], [(blocks - 1, blocks)], 1)
+    c.check_part(whole, [1, 0], None, 1)

@@ -1,7 +1,5 @@
-"""Attention over lists that several groups of waves share: which launches split is a rule on the number
-of (head, row) items, the block and head size and the list length; every group count of every
-instantiation is met here, each with one-entry lists (groups without a block), unusable entries and logits
-that make the softmax reference move inside every group."""
+"""Attention in launches around the number of workgroups that the chip takes at a time, every instantiation:
+one-entry lists, unusable entries, an empty list and logits that make the softmax reference move in every block."""
 import numpy as np
 import pytest
 
@@ -9,14 +7,14 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("B,d,Hq,Hkv", [
-    # items = Hq x 25 rows (B = 64) or 13 rows (B = 128) on 256 CUs
-    (64, 128, 4, 2), (64, 128, 16, 2), (64, 128, 44, 2),       # 100: four groups, 400: two, 1100: one
-    (64, 64, 10, 1), (64, 64, 20, 1), (64, 64, 43, 1),         # 250: four, 500: two, 1075: one
-    (64, 256, 10, 2), (128, 256, 10, 1),                       # one, whatever the size of the call
-    (128, 128, 18, 3), (128, 128, 22, 2),                      # 234: two, 286: one
-    (128, 64, 4, 1), (128, 64, 24, 2),                         # 52: two, 312: one
+    # Hq x 25 rows (B = 64) or 13 rows (B = 128)
+    (64, 128, 4, 2), (64, 128, 16, 2), (64, 128, 44, 2),
+    (64, 64, 10, 1), (64, 64, 20, 1), (64, 64, 43, 1),
+    (64, 256, 10, 2), (128, 256, 10, 1),
+    (128, 128, 18, 3), (128, 128, 22, 2),
+    (128, 64, 4, 1), (128, 64, 24, 2),
 ])
-def test_split_lists(B, d, Hq, Hkv):
+def test_small_launches(B, d, Hq, Hkv):
     import torch
     import parity_util as pu
     from oracle import stem_oracle as so

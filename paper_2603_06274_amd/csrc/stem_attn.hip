@@ -270,7 +270,7 @@ __device__ __forceinline__ void sparse_attn_body(
     const int32_t* __restrict__ counts, const int32_t* __restrict__ indices,
     uint16_t* __restrict__ out, float* __restrict__ lse, const SeqTable& seq, const RowWalk& walk, int Hq, int R, int G,
     int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh,
-    float scale, int items_per_xcd, int xcds_per_kv_head, int items_per_round, unsigned char* __restrict__ k_lds,
+    float scale, int items_per_xcd, int xcds_per_kv_head, unsigned char* __restrict__ k_lds,
     unsigned char* __restrict__ v_lds) {
     constexpr int KT = B / 32;                         // 32-key tiles per block
     constexpr int KS = D / 16;                         // 16-wide steps of S^T along d; also requests per wave, tensor and block
@@ -381,20 +381,7 @@ __device__ __forceinline__ void sparse_attn_body(
     // The list lives in a vector register, 64 entries at a time (lane e holds entry e of the
     // chunk), and entries are taken out with v_readlane: no scalar load sits in the loop, so the
     // in-order LDS operand reads are the only users of their counter there.
-    // With 64-token blocks every second round of workgroups (items_per_round of an XCD run at a time)
-    // walks its lists backwards.  An XCD's L2 holds about one K and V block per workgroup in flight, so
-    // a block is found there only while the workgroups walk the sequence in step; they start in step
-    // and drift apart (measured at 100003 tokens, 32 / 8 heads, d = 128, 80 blocks listed per row: 60 % of
-    // the reads hit, 52 GB of misses; with every list replaced by the same blocks 7.62 instead of
-    // 8.79 ms), and a round that begins where the last one ended shares with its stragglers: 8.61 ->
-    // 8.34 ms.  With 128-token blocks, 87 % hits, there is next to nothing to gain (1 % between real
-    // lists and identical ones) and the direction makes no difference; nor is there any while a head's keys
-    // and values are within twice the L2 (the host's items_per_round is out of reach then).
-    const bool backwards = B == 64 && ((slot / items_per_round) & 1);
-    auto list_chunk = [&](int first) {
-        const int e = first + lane;
-        return e < cnt ? list[backwards ? cnt - 1 - e : e] : 0;
-    };
+    auto list_chunk = [&](int first) { return first + lane < cnt ? list[first + lane] : 0; };
     int list_reg = list_chunk(0);
     int j_cur = __builtin_amdgcn_readlane(list_reg, 0);
     if (cnt > 0) {
@@ -724,11 +711,11 @@ __global__ __launch_bounds__(B * 2, D == 256 ? 1 : 2) void sparse_attn_kernel(
     const int32_t* __restrict__ counts, const int32_t* __restrict__ indices,
     uint16_t* __restrict__ out, float* __restrict__ lse, SeqTable seq, RowWalk walk, int Hq, int R, int G, int T,
     int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh, float scale,
-    int items_per_xcd, int xcds_per_kv_head, int items_per_round) {
+    int items_per_xcd, int xcds_per_kv_head) {
     __shared__ __attribute__((aligned(1024))) unsigned char k_lds[B * D * 2];
     __shared__ __attribute__((aligned(1024))) unsigned char v_lds[B * D * 2];
     sparse_attn_body<B, D>(q, k, v, counts, indices, out, lse, seq, walk, Hq, R, G, T, kmax, shared_lists, q_st, q_sh,
-                           kv_st, kv_sh, scale, items_per_xcd, xcds_per_kv_head, items_per_round, k_lds, v_lds);
+                           kv_st, kv_sh, scale, items_per_xcd, xcds_per_kv_head, k_lds, v_lds);
 }
 
 int launch_sparse_attn(const Problem& p, const void* q, const void* k, const void* v,
@@ -754,16 +741,6 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     walk.start[0] = 0;
     for (int x = 0; x < p.batch; ++x)
         walk.start[x + 1] = walk.start[x] + p.seq.row_start[walk.seq[x] + 1] - p.seq.row_start[walk.seq[x]];
-    // workgroups of an XCD that run at a time: 32 CUs, each as many as its waves' registers allow (three
-    // waves per SIMD at B = 64, d = 64, one at d = 256, else two).  Only the walking direction hangs on it.
-    int64_t longest = 0;
-    for (int x = 0; x < p.batch; ++x) {
-        const int64_t keys = p.seq.kv_end[x] - p.seq.tok_start[x];
-        longest = keys > longest ? keys : longest;
-    }
-    constexpr int64_t kTwiceL2 = 8 << 20;
-    const int per_round = longest * p.d * 4 <= kTwiceL2 ? 0x7fffffff
-                          : 32 * (p.d == 256 ? 1 : p.d == 64 && p.B == 64 ? 3 : 2) * (p.B == 64 ? 2 : 1);
     const uint16_t* qq = static_cast<const uint16_t*>(q);
     const uint16_t* kk = static_cast<const uint16_t*>(k);
     const uint16_t* vv = static_cast<const uint16_t*>(v);
@@ -771,7 +748,7 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
 #define STEM_ATTN_LAUNCH(BB, DD)                                                                          \
     hipLaunchKernelGGL((sparse_attn_kernel<BB, DD>), grid, block, 0, stream, qq, kk, vv, counts, indices, \
                        oo, lse, p.seq, walk, p.Hq, p.R, p.G, p.T, kmax, lists_per_kv_head, p.q_st, p.q_sh, \
-                       p.kv_st, p.kv_sh, softmax_scale, (int)per_xcd, xcds_per_kv_head, per_round)
+                       p.kv_st, p.kv_sh, softmax_scale, (int)per_xcd, xcds_per_kv_head)
     if (p.B == 128 && p.d == 128) STEM_ATTN_LAUNCH(128, 128);
     else if (p.B == 64 && p.d == 128) STEM_ATTN_LAUNCH(64, 128);
     else if (p.B == 128 && p.d == 64) STEM_ATTN_LAUNCH(128, 64);

@@ -101,9 +101,9 @@ def test_fused_band_shapes_at_their_edges(blocks, chunk_blocks):
 
 
 @pytest.mark.parametrize("d", [64, 128, 256])
-def test_rounds_that_walk_their_lists_backwards(d):
+def test_several_rounds_of_long_lists(d):
     """B = 64, enough rows for several rounds of workgroups on each XCD and lists of more than the 64
-    entries a wave holds at a time: the rounds that walk their lists from the end, against the oracle."""
+    entries a wave holds at a time, against the oracle."""
     w = wl.small("rounds_d%d" % d, seed=67, num_q_heads=8, num_kv_heads=1, seq_lens=(600 * 64 - 5,),
                  block_size=64, k_start=(90,), n_sink=2, n_local=2, outliers=(20,), head_dim=d)
     run_both(w, rows=range(3, 600, 17), heads=[0, 5])

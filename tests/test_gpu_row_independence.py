@@ -98,3 +98,14 @@ def test_parts_of_a_call_by_themselves(B, d, shared, wide):
     c.check_part(whole, [0], [(blocks - 30, blocks - 26)])
     c.check_part(whole, [0], [(blocks - 1, blocks)], 1)
     c.check_part(whole, [1, 0], None, 1)
+
+
+@pytest.mark.parametrize("d,blocks", [(128, 300), (64, 600), (256, 200)])
+def test_rows_of_a_call_of_several_rounds(d, blocks):
+    """B = 64 and more keys than an XCD's L2 holds: the rows that run late in a call of several rounds of
+    workgroups, against a call of their own (in which they run first), and packed with another sequence."""
+    c = Call(64, d, 8, 1, (blocks * 64 - 7, 11 * 64), 100)
+    whole = c.attend([0, 1])
+    c.check_part(whole, [0])
+    c.check_part(whole, [0], [(blocks // 3, blocks // 3 + 40)])
+    c.check_part(whole, [0, 1], [(blocks // 2, blocks // 2 + 60), (11, 11)])

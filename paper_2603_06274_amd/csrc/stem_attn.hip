@@ -251,15 +251,16 @@ static_assert(SoftmaxSchedule<4, 8>::valid() && SoftmaxSchedule<2, 8>::valid(), 
 static_assert(SoftmaxSchedule<4, 16>::valid() && SoftmaxSchedule<2, 16>::valid(), "softmax schedule, d = 256");
 static_assert(SoftmaxSchedule<4, 4>::valid() && SoftmaxSchedule<2, 4>::valid(), "softmax schedule, d = 64");
 
-// The order in which the query-block rows are handed out: the sequences by the length of their longest
-// list's bound (the block index of the last row), longest first, and a sequence's rows from the last
-// to the first, so that what starts last is short.  Packed as they come, a batch of short prompts can
-// leave its longest row for the end: 12 prompts of 1 to 2047 tokens, 32 / 8 heads, all blocks kept,
-// 155.8 -> 149.6 us for all stages; nothing changes where there is one sequence.
+// The order in which the query-block rows of a packed batch are handed out (launch_sparse_attn says when): the
+// sequences by the length of their longest list's bound (the block index of the last row), longest first, and a
+// sequence's rows from the last to the first, so that what starts last is short.  Packed as they come, a batch
+// of short prompts can leave its longest row for the end.
 struct RowWalk {
-    int32_t start[STEM_MAX_BATCH + 1];                 // prefix sums of the rows of the sequences in this order
+    int32_t start[STEM_MAX_BATCH];                     // prefix sums of the rows of the sequences in this order, then R
     uint8_t seq[STEM_MAX_BATCH];
 };
+// one sequence; several, rows from the last of the call to the first; several, in the walk's order
+enum RowOrder : int { kOneSequence, kAsPacked, kWalk };
 
 // The body takes the two LDS buffers as __restrict__ parameters: once inlined, every access carries
 // alias-scope information, which lets the compiler's wait-count insertion tell a read of one buffer
@@ -269,7 +270,7 @@ __device__ __forceinline__ void sparse_attn_body(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ counts, const int32_t* __restrict__ indices,
     uint16_t* __restrict__ out, float* __restrict__ lse, const SeqTable& seq, const RowWalk& walk, int Hq, int R, int G,
-    int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh,
+    int order, int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh,
     float scale, int items_per_xcd, int xcds_per_kv_head, unsigned char* __restrict__ k_lds,
     unsigned char* __restrict__ v_lds) {
     constexpr int KT = B / 32;                         // 32-key tiles per block
@@ -307,18 +308,19 @@ __device__ __forceinline__ void sparse_attn_body(
         h = g * G + rem % G;
     }
 
-    // the sequence and its place in the walk, both from one load per lane (place_in): a chain of scalar
-    // loads here is time before the first load of data, 1 % of a call of 30 us (30.31 against 30.06)
-    int s = 0, walked = 0;
-    if (seq.batch > 1) {
+    // The row comes first: its count and list entries are what everything else waits for.  `order` travels
+    // beside R, so that a call of one sequence waits for no load here.  In the walk's order the sequence and its
+    // place are found as in place_in, by a load per lane of either.
+    int r = R - 1 - pos, s = 0;
+    if (D != 256 && order == kWalk) {
         const int x = threadIdx.x & 63;
-        const int start_x = x < seq.batch ? walk.start[x] : 0x7fffffff;
-        const int seq_x = x < seq.batch ? walk.seq[x] : 0;
+        const int start_x = walk.start[x], seq_x = walk.seq[x];
         const int turn = (int)__popcll(__builtin_amdgcn_ballot_w64(start_x <= pos)) - 1;
         s = __builtin_amdgcn_readlane(seq_x, turn);
-        walked = __builtin_amdgcn_readlane(start_x, turn);
+        r = seq.row_start[s + 1] - 1 - (pos - __builtin_amdgcn_readlane(start_x, turn));
+    } else if (order == kAsPacked) {
+        s = seq_of_row(seq, r);
     }
-    const int r = seq.row_start[s + 1] - 1 - (pos - walked);
     const int ic = r - seq.row_start[s];               // row inside the call's chunk of the sequence
     const int i = seq.first_block[s] + ic;             // block index in the sequence
     const int seq_lo = seq.tok_start[s], seq_hi = seq.kv_end[s];   // key token rows the call may read
@@ -709,12 +711,12 @@ template <int B, int D>
 __global__ __launch_bounds__(B * 2, D == 256 ? 1 : 2) void sparse_attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ counts, const int32_t* __restrict__ indices,
-    uint16_t* __restrict__ out, float* __restrict__ lse, SeqTable seq, RowWalk walk, int Hq, int R, int G, int T,
-    int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh, float scale,
+    uint16_t* __restrict__ out, float* __restrict__ lse, SeqTable seq, RowWalk walk, int Hq, int R, int G,
+    int order, int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh, float scale,
     int items_per_xcd, int xcds_per_kv_head) {
     __shared__ __attribute__((aligned(1024))) unsigned char k_lds[B * D * 2];
     __shared__ __attribute__((aligned(1024))) unsigned char v_lds[B * D * 2];
-    sparse_attn_body<B, D>(q, k, v, counts, indices, out, lse, seq, walk, Hq, R, G, T, kmax, shared_lists, q_st, q_sh,
+    sparse_attn_body<B, D>(q, k, v, counts, indices, out, lse, seq, walk, Hq, R, G, order, T, kmax, shared_lists, q_st, q_sh,
                            kv_st, kv_sh, scale, items_per_xcd, xcds_per_kv_head, k_lds, v_lds);
 }
 
@@ -731,23 +733,38 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
                                 : (items + 7) / 8;
     if (per_xcd * 8 > 0x7fffffff) return STEM_ERR_UNSUPPORTED;
     dim3 grid((unsigned)(per_xcd * 8)), block(p.B * 2);
-    RowWalk walk;
+    // The walk's order is for batches of eight sequences and more that come in another order, at d = 64 and 128,
+    // where more rows wait than run at a time (two workgroups per CU at B = 128, four at B = 64) and a quarter
+    // as many again.  Attention alone over all blocks, rows from the last to the first / in the walk's order:
+    // 12 prompts to 2047 tokens, 32 / 8 heads 118 / 110 us, 40 to 900, 4 / 4 heads 36.3 / 29.3 us, and between
+    // 0.6 % slower and 25 % faster in 41 such batches.  With fewer sequences it is chance (2 to 6, 56 batches: from
+    // 4 % slower to 14 % faster), as with fewer rows (8 sequences, 1.17 times what runs: 4 % slower); batches in
+    // ascending order start with the longest as they are and pay only the lookup (up to 5 %); at d = 256, one
+    // workgroup per CU, it is 6 % slower to 15 % faster, most of it by chance.
+    RowWalk walk = {};
+    int order = p.batch > 1 ? kAsPacked : kOneSequence;
     auto last_block = [&](int s) { return p.seq.first_block[s] + p.seq.row_start[s + 1] - p.seq.row_start[s]; };
-    for (int x = 0; x < p.batch; ++x) {                // insertion sort of at most 64; of equal ones the later first
-        int y = x;
-        for (; y > 0 && last_block(walk.seq[y - 1]) <= last_block(x); --y) walk.seq[y] = walk.seq[y - 1];
-        walk.seq[y] = (uint8_t)x;
+    bool ascending = true;
+    for (int x = 1; x < p.batch; ++x) ascending = ascending && last_block(x - 1) <= last_block(x);
+    if (p.batch >= 8 && !ascending && p.d != 256 && items * 4 > (int64_t)compute_units() * (256 / p.B) * 5) {
+        order = kWalk;
+        for (int x = 0; x < p.batch; ++x) {            // insertion sort of at most 64
+            int y = x;
+            for (; y > 0 && last_block(walk.seq[y - 1]) < last_block(x); --y) walk.seq[y] = walk.seq[y - 1];
+            walk.seq[y] = (uint8_t)x;
+        }
+        for (int x = 0, rows = 0; x < STEM_MAX_BATCH; ++x) {
+            walk.start[x] = rows;
+            if (x < p.batch) rows += p.seq.row_start[walk.seq[x] + 1] - p.seq.row_start[walk.seq[x]];
+        }
     }
-    walk.start[0] = 0;
-    for (int x = 0; x < p.batch; ++x)
-        walk.start[x + 1] = walk.start[x] + p.seq.row_start[walk.seq[x] + 1] - p.seq.row_start[walk.seq[x]];
     const uint16_t* qq = static_cast<const uint16_t*>(q);
     const uint16_t* kk = static_cast<const uint16_t*>(k);
     const uint16_t* vv = static_cast<const uint16_t*>(v);
     uint16_t* oo = static_cast<uint16_t*>(out);
 #define STEM_ATTN_LAUNCH(BB, DD)                                                                          \
     hipLaunchKernelGGL((sparse_attn_kernel<BB, DD>), grid, block, 0, stream, qq, kk, vv, counts, indices, \
-                       oo, lse, p.seq, walk, p.Hq, p.R, p.G, p.T, kmax, lists_per_kv_head, p.q_st, p.q_sh, \
+                       oo, lse, p.seq, walk, p.Hq, p.R, p.G, order, p.T, kmax, lists_per_kv_head, p.q_st, p.q_sh, \
                        p.kv_st, p.kv_sh, softmax_scale, (int)per_xcd, xcds_per_kv_head)
     if (p.B == 128 && p.d == 128) STEM_ATTN_LAUNCH(128, 128);
     else if (p.B == 64 && p.d == 128) STEM_ATTN_LAUNCH(64, 128);

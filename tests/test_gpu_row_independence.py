@@ -61,7 +61,7 @@ class Call:
             rows.append(torch.arange(row0 + a, row0 + b))
         tokens, keys, rows = torch.cat(tokens), torch.cat(keys), torch.cat(rows)
         q = self.q[tokens][:, :heads].contiguous()
-        if len(seqs) == len(self.table):
+        if seqs == list(range(len(self.table))):
             k, v = (x[:, :kv_heads] for x in self.kv)
         else:
             k, v = (x[keys][:, :kv_heads].contiguous() for x in self.kv)
@@ -109,3 +109,17 @@ def test_rows_of_a_call_of_several_rounds(d, blocks):
     c.check_part(whole, [0])
     c.check_part(whole, [0], [(blocks // 3, blocks // 3 + 40)])
     c.check_part(whole, [0, 1], [(blocks // 2, blocks // 2 + 60), (11, 11)])
+
+
+@pytest.mark.parametrize("B,d,heads,lens", [
+    (128, 128, (16, 4), (1500, 70, 900, 1300, 0, 400, 1500, 129, 2000, 64)),
+    (64, 64, (24, 3), (1500, 70, 900, 1300, 0, 400, 1500, 65, 2000, 64)),
+])
+def test_rows_of_a_batch_in_another_order(B, d, heads, lens):
+    """A batch whose rows are handed out longest sequence first: sequences by themselves, in another order
+    (ascending, as they come) and with chunks."""
+    c = Call(B, d, *heads, lens, 20)
+    whole = c.attend(list(range(len(lens))))
+    c.check_part(whole, [2])
+    c.check_part(whole, sorted(range(len(lens)), key=lambda s: lens[s]))
+    c.check_part(whole, [8, 1, 0], [(9, 12), (0, 1), (2, 5)])

@@ -1,6 +1,6 @@
 """Packed batches in orders that the hand-out of query-block rows has to untangle (longest sequence first,
-rows of a sequence from the last to the first), with empty, equal and one-token sequences, for head counts that
-take either mapping of heads to XCDs; every row of every sequence against the oracle."""
+rows of a sequence from the last to the first) or leaves as they come, with empty, equal and one-token sequences,
+for head counts that take either mapping of heads to XCDs; every row of every sequence against the oracle."""
 import pytest
 
 from paper_2603_06274_amd import workloads as wl
@@ -14,6 +14,9 @@ pytestmark = pytest.mark.gpu
     (128, (4, 2), (64, 700, 0, 700, 1300, 1)),                 # ascending with a tie, an empty and a short end
     (64, (3, 3), (0, 900, 130, 0, 64, 65)),                    # an empty head, descending; 3 KV heads
     (64, (8, 1), tuple(37 * ((7 * x) % 64) for x in range(64))),   # the most sequences a call takes, one empty
+    (128, (24, 3), (700, 64, 0, 1300, 129, 700, 1, 640, 0)),   # 24 x 32 rows: the longest first
+    (128, (24, 3), (64, 129, 700, 1300, 640, 300, 1)),         # seven sequences: as they come
+    (128, (24, 3), (1, 64, 64, 300, 300, 640, 700, 1300)),     # ascending: as they come
 ])
 def test_sequence_orders(B, heads, lens):
     w = wl.small("orders_%d_%d" % (B, len(lens)), seed=68, num_q_heads=heads[0], num_kv_heads=heads[1], seq_lens=lens,

@@ -83,16 +83,18 @@ inline int check_launch() {
 }
 
 #if defined(__HIPCC__)
-// Place of x in the n + 1 ascending prefix sums `start` (start[0] = 0, n <= 64): the last s < n with
-// start[s] <= x.  One load per lane and a ballot: a scalar loop over the sums waits for one load after
-// the other, which every workgroup of a packed batch paid before its first load of data
-// (18 prompts of 389 to 3185 tokens, 32 / 8 heads: all stages 2 % faster).  Called by whole waves with one x per wave.
+// Place of x in the n ascending prefix sums `start` (start[0] = 0, n <= 64, entries n .. 63 beyond every x): the last
+// s < n with start[s] <= x.  Three sums and fewer are looked at one after the other.  For more, every lane
+// loads one and a ballot counts: a scalar loop waits for one load after the other, which every workgroup of a
+// packed batch paid before its first load of data (64 prompts of 100 tokens, 8 / 1 heads, all stages
+// 44.6 -> 31.4 us; equal at four prompts, and at two the one scalar load is 0.1 us a kernel shorter than a load
+// per lane).  Called by whole waves with one x per wave.
 __device__ __forceinline__ int place_in(const int32_t* start, int n, int x) {
     static_assert(STEM_MAX_BATCH <= 64, "one lane per sequence");
-    if (n == 1) return 0;
-    const int lane = threadIdx.x & 63;
-    const bool below = lane < n && start[lane] <= x;
-    return (int)__popcll(__builtin_amdgcn_ballot_w64(below)) - 1;
+    if (n > 3) return (int)__popcll(__builtin_amdgcn_ballot_w64(start[threadIdx.x & 63] <= x)) - 1;
+    int s = 0;
+    for (int y = 1; y < n; ++y) s = x >= start[y] ? y : s;
+    return s;
 }
 
 // Sequence of a global query-block row.  Wave-uniform.

@@ -46,16 +46,13 @@ __global__ __launch_bounds__(2 * D * HW) void pool_kernel(
     const int n_valid = min(B, seq.kv_end[s] - kv_tok0);
     const int key_row = seq.key_row_start[s] + i;      // row of k_bar and m_v
 
-    const uint16_t* src;
-    int64_t st;
-    int kind, head, tok0;                              // 0: Q, 1: K, 2: V
-    if (slot < Hq) {
-        kind = 0; head = slot; src = q + (int64_t)head * q_sh; st = q_st; tok0 = q_tok0;
-    } else if (slot < Hq + Hkv) {
-        kind = 1; head = slot - Hq; src = k + (int64_t)head * kv_sh; st = kv_st; tok0 = kv_tok0;
-    } else {
-        kind = 2; head = slot - Hq - Hkv; src = v + (int64_t)head * kv_sh; st = kv_st; tok0 = kv_tok0;
-    }
+    // (selections, not branches: a pointer is then loaded with the first arguments instead of in its branch)
+    const bool is_q = slot < Hq, is_k = slot < Hq + Hkv;
+    const int kind = is_q ? 0 : is_k ? 1 : 2;          // 0: Q, 1: K, 2: V
+    int head = slot - (is_q ? 0 : is_k ? Hq : Hq + Hkv);
+    const int tok0 = is_q ? q_tok0 : kv_tok0;
+    const int64_t st = is_q ? q_st : kv_st;
+    const uint16_t* src = (is_q ? q : is_k ? k : v) + (int64_t)head * (is_q ? q_sh : kv_sh);
 
     const int tid = threadIdx.x;
     const int c = tid % kChunks;                       // 16-byte chunk of the row

@@ -13,6 +13,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("B,heads,lens", [
     (128, (4, 2), (64, 700, 0, 700, 1300, 1)),                 # ascending with a tie, an empty and a short end
     (64, (3, 3), (0, 900, 130, 0, 64, 65)),                    # an empty head, descending; 3 KV heads
+    (64, (4, 2), (300, 0, 500)),                               # the most sequences looked at one after the other
+    (64, (4, 2), (0, 300, 500, 64)),                           # the fewest counted by a ballot
     (64, (8, 1), tuple(37 * ((7 * x) % 64) for x in range(64))),   # the most sequences a call takes, one empty
     (128, (24, 3), (700, 64, 0, 1300, 129, 700, 1, 640, 0)),   # 24 x 32 rows: the longest first
     (128, (24, 3), (64, 129, 700, 1300, 640, 300, 1)),         # seven sequences: as they come

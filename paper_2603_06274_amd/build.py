@@ -18,6 +18,9 @@ LIB = os.path.join(PKG, "libstem_hip.so")
 
 SOURCES = ["stem_api.cpp", "stem_pool.hip", "stem_scores.hip", "stem_select.hip", "stem_attn.hip", "stem_static.hip"]
 
+# instantiations of sparse_attn_kernel: block sizes 64 and 128 times head sizes 64, 128 and 256
+ATTENTION_KERNELS = 6
+
 # -packed-fp32-ops: keep the compiler from forming v_pk_*_f32 out of plain float code.
 COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-I" + os.path.join(ROOT, "include"),
           "-I" + CSRC, "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -56,8 +59,8 @@ def check_wait_states(extra=()) -> None:
     with open(asm_path) as f:
         asm = f.read()
     names = wait_states.kernels(asm, "sparse_attn_kernel")
-    if len(names) < 6:
-        raise RuntimeError("expected the six attention kernels in %s, found %d" % (asm_path, len(names)))
+    if len(names) != ATTENTION_KERNELS:
+        raise RuntimeError("expected %d attention kernels in %s, found %d" % (ATTENTION_KERNELS, asm_path, len(names)))
     for name in names:
         broken = wait_states.check_kernel(asm, name)
         if broken:

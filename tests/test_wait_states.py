@@ -86,3 +86,15 @@ def test_attention_kernel_assembly_passes():
     for k in hand_placed:                          # the check did look at hand-placed instructions
         body = asm[asm.index(k + ":"):]
         assert "v_mfma_f32_32x32x16_bf16 v[" in body[:body.index(".Lfunc_end")]
+
+
+@pytest.mark.parametrize("found", [build.ATTENTION_KERNELS - 1, build.ATTENTION_KERNELS + 1])
+def test_an_instantiation_that_is_not_expected_fails_the_build(found, tmp_path, monkeypatch):
+    """One that is missing in the assembly was not checked, one too many is not known to be."""
+    (tmp_path / "stem_attn.s").write_text("")
+    monkeypatch.setattr(build, "OBJ", str(tmp_path))
+    monkeypatch.setattr(build, "hipcc", lambda: "true")
+    monkeypatch.setattr(wait_states, "kernels", lambda asm, name: ["_Z%d" % x for x in range(found)])
+    monkeypatch.setattr(wait_states, "check_kernel", lambda asm, name: [])
+    with pytest.raises(RuntimeError, match="found %d" % found):
+        build.check_wait_states()

@@ -34,8 +34,9 @@
  *     (rows at or after chunk_end[s] are not read).  R counts the chunks' query blocks, NBmax the
  *     most key blocks a row of the call can see, and rows keep their block index i inside the
  *     sequence for the schedule, the causal limit and the windows, so the chunks of a prompt give
- *     the rows of the one-piece call.  chunk_start must be a multiple of B, chunk_end a multiple
- *     of B or the sequence's length; an empty chunk (start == end) contributes nothing.
+ *     the rows of the one-piece call, bit for bit (stem_estimate_select: see there).  chunk_start
+ *     must be a multiple of B, chunk_end a multiple of B or the sequence's length; an empty chunk
+ *     (start == end) contributes nothing.
  *   - Q, K and V are expected to hold finite values.  An inf or NaN in them is not detected: it
  *     spreads as IEEE arithmetic spreads it (a non-finite key or value makes the output rows that
  *     attend to it non-finite, a non-finite pooled score is ranked by its bit pattern), and
@@ -224,9 +225,11 @@ int stem_select(const stem_shape* shape, const float* scores, const int32_t* bud
  * Stages 1 and 2 in one call that never writes the score tensor: stem_pool, then one kernel that
  * computes the metric of a band of rows into on-chip memory and selects from there.  Same results
  * as stem_estimate followed by stem_select with lists_per_kv_head = 0, up to the rounding order of
- * the fp32 score sums (near-ties may resolve differently).  debug_scores, if not NULL, is a device
- * fp32 [Hq, R, NBmax] buffer that receives the scores the selection saw (for checking; it defeats
- * the purpose otherwise).  Arguments as for the two calls it replaces.
+ * the fp32 score sums (near-ties may resolve differently).  That order is one up to NBmax = 1024 and
+ * another above, so a chunk that ends within the first 1024 blocks of a longer prompt agrees with the
+ * one-piece call only up to the same.  debug_scores, if not NULL, is a device fp32 [Hq, R, NBmax]
+ * buffer that receives the scores the selection saw (for checking; it defeats the purpose otherwise).
+ * Arguments as for the two calls it replaces.
  */
 int stem_estimate_select(const stem_shape* shape, const void* q, const void* k, const void* v,
                          float beta, float route_scale, int32_t ad_stride, const int32_t* budget,

@@ -168,14 +168,18 @@ int launch_select(const Problem& p, int heads, const float* scores, const int32_
 //            8 rows in 64 KiB, two workgroups per CU, leave half of each product empty and fetch every
 //            key block twice as often: 0.60 against 0.41 ms at 1563 rows and key blocks, 32 / 8 heads,
 //            d = 128 (0.27 ms without phase 2, 0.20 ms without the products)
-//   <= 4096: 8 rows, 128 KiB, 8 waves: half-empty products, which still take 0.71 instead of 1.00 ms
-//            (pooling included) at 3126 rows and key blocks, 8 / 1 heads, against the 4-row bands on
-//            v_mfma_f32_4x4x1_16B_f32, staged 8 floats of the depth at a time, that served all rows
-//            above 1024 key blocks before (0.99 ms in the case of 1563)
-// The 4-row bands added the products of a score in ascending depth.  Scores that are compared with
-// each other keep that order: above 1024 key blocks both operands are transposed within the groups
-// of four lanes of a row (transpose_quads), so that step s of a 64-byte group takes its floats
-// 4s .. 4s + 3 and the sums are the same bits as before (0.43 instead of 0.41 ms).
+//   <= 4096: 8 rows, 128 KiB, 8 waves: half-empty products.  The selection over 64 scores per lane does not
+//            fit the registers: 14 vector ones go to scratch (60 bytes per lane) and 354 scalar ones into
+//            vector lanes (select_kernel<64>, the same selection by itself: none and 310)
+// The last two serve what 4-row bands on v_mfma_f32_4x4x1_16B_f32 served before, staged through LDS 8
+// floats of the depth at a time.  Both sides with pooling, B = 64, d = 128, before / now: 1025 key blocks, 32 / 8
+// heads 0.59 / 0.35 ms; 2048 1.87 / 0.93; 2049 1.87 / 1.42; 4096 6.46 / 4.63; the last 56 rows of 4096 0.198 /
+// 0.137; 1 / 1 head 1100 0.062 / 0.051, 3000 0.147 / 0.114; d = 64, 8 / 1 heads, 3000 0.58 / 0.48.
+//
+// Up to 1024 key blocks a score's products are added in the order of the loads.  Above, both operands are
+// transposed within the groups of four lanes of a row (transpose_quads), so that step s of a 64-byte group takes
+// its floats 4s .. 4s + 3 and the sum runs in ascending depth, as the 4-row bands summed: no score and no
+// near-tie of a caller's lists changed with the kernel.  It costs 5 % (0.41 -> 0.43 ms in the case of 1563).
 // ------------------------------------------------------------------------------------------------
 struct BandTable {
     int32_t band_start[STEM_MAX_BATCH + 1];            // prefix sums of ceil(rows of the call / ROWS)

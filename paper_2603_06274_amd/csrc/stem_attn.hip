@@ -735,12 +735,12 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     dim3 grid((unsigned)(per_xcd * 8)), block(p.B * 2);
     // The walk's order is for batches of eight sequences and more that come in another order, at d = 64 and 128,
     // where more rows wait than run at a time (two workgroups per CU at B = 128, four at B = 64) and a quarter
-    // as many again.  Attention alone over all blocks, rows from the last to the first / in the walk's order:
-    // 12 prompts to 2047 tokens, 32 / 8 heads 118 / 110 us, 40 to 900, 4 / 4 heads 36.3 / 29.3 us, and between
-    // 0.6 % slower and 25 % faster in 41 such batches.  With fewer sequences it is chance (2 to 6, 56 batches: from
-    // 4 % slower to 14 % faster), as with fewer rows (8 sequences, 1.17 times what runs: 4 % slower); batches in
-    // ascending order start with the longest as they are and pay only the lookup (up to 5 %); at d = 256, one
-    // workgroup per CU, it is 6 % slower to 15 % faster, most of it by chance.
+    // as many again.  Attention alone, rows from the last to the first / in the walk's order: 12 prompts to 2047
+    // tokens, 32 / 8 heads 118 / 110 us; 40 prompts to 900, 4 / 4 heads 36 / 29 us; 84 such batches, all blocks or
+    // 30 % of them, from 0.6 % slower to 27 % faster, 5 % in the middle.  Beyond the lines it is chance: two
+    // to six sequences (53 batches) 5 % slower to 15 % faster and nothing in the middle, fewer rows (24) 4 % slower
+    // to 16 % faster, d = 256, one workgroup per CU (23), 5 % slower to 17 % faster and nothing in the middle.
+    // Batches in ascending order start with the longest as they are and would pay the lookup, up to 5 %.
     RowWalk walk = {};
     int order = p.batch > 1 ? kAsPacked : kOneSequence;
     auto last_block = [&](int s) { return p.seq.first_block[s] + p.seq.row_start[s + 1] - p.seq.row_start[s]; };

@@ -733,21 +733,31 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
                                 : (items + 7) / 8;
     if (per_xcd * 8 > 0x7fffffff) return STEM_ERR_UNSUPPORTED;
     dim3 grid((unsigned)(per_xcd * 8)), block(p.B * 2);
-    // The walk's order is for batches of eight sequences and more that come in another order, at d = 64 and 128,
-    // where more rows wait than run at a time (two workgroups per CU at B = 128, four at B = 64) and a quarter
-    // as many again.  Attention alone, rows from the last to the first / in the walk's order: 12 prompts to 2047
-    // tokens, 32 / 8 heads 118 / 110 us; 40 prompts to 900, 4 / 4 heads 36 / 29 us; 84 such batches, all blocks or
-    // 30 % of them, from 0.6 % slower to 27 % faster, 5 % in the middle.  Beyond the lines it is chance: two
-    // to six sequences (53 batches) 5 % slower to 15 % faster and nothing in the middle, fewer rows (24) 4 % slower
-    // to 16 % faster, d = 256, one workgroup per CU (23), 5 % slower to 17 % faster and nothing in the middle.
+    // The walk's order is for batches of ten sequences and more, at d = 64 and 128, where rows wait for a place (1.5
+    // to 8 times what runs at a time: two workgroups per CU at B = 128, four at B = 64), lists grow with the row
+    // (kmax is more than half of the longest sequence's blocks, and these are three or more) and the sequences
+    // come in another order.  Attention alone, rows from the last to the first / in the walk's order: 12 prompts
+    // to 2047 tokens, 32 / 8 heads, all blocks 118 / 110 us; 161 such batches from 2 % slower to 26 % faster, 4 % in the
+    // middle.  Beyond the lines chance prevails: fewer rows (1.25 to 1.5 times, 18 batches) 9 % slower to 12 %
+    // faster; eight or nine sequences (23) 2 % slower to 15 % faster, in another sample (13) 11 % slower; two to
+    // six (53) 5 % slower to 15 % faster and nothing in the middle; lists cut shorter (184) 6 % slower to 24 % faster,
+    // 2 % in the middle; two blocks at most (49) 5 % slower to 11 % faster, more rows (45) 2 % slower to 5 % faster and
+    // d = 256, one workgroup per CU (23), 5 % slower to 17 % faster, nothing in the middle of any.
     // Batches in ascending order start with the longest as they are and would pay the lookup, up to 5 %.
     RowWalk walk = {};
     int order = p.batch > 1 ? kAsPacked : kOneSequence;
     auto last_block = [&](int s) { return p.seq.first_block[s] + p.seq.row_start[s + 1] - p.seq.row_start[s]; };
-    bool ascending = true;
-    for (int x = 1; x < p.batch; ++x) ascending = ascending && last_block(x - 1) <= last_block(x);
-    if (p.batch >= 8 && !ascending && p.d != 256 && items * 4 > (int64_t)compute_units() * (256 / p.B) * 5) {
-        order = kWalk;
+    const int64_t at_a_time = p.batch >= 10 && p.d != 256 ? (int64_t)compute_units() * (256 / p.B) : 0;
+    if (items * 2 > at_a_time * 3 && items <= at_a_time * 8) {
+        bool ascending = true;
+        int longest = last_block(0);
+        for (int x = 1; x < p.batch; ++x) {
+            ascending = ascending && last_block(x - 1) <= last_block(x);
+            longest = last_block(x) > longest ? last_block(x) : longest;
+        }
+        if (!ascending && longest > 2 && kmax > longest / 2) order = kWalk;
+    }
+    if (order == kWalk) {
         for (int x = 0; x < p.batch; ++x) {            // insertion sort of at most 64
             int y = x;
             for (; y > 0 && last_block(walk.seq[y - 1]) < last_block(x); --y) walk.seq[y] = walk.seq[y - 1];

@@ -33,6 +33,12 @@
 // accumulators that the first block's products can start, only tiles on or above the wave's diagonal are masked,
 // maxima are taken three at a time, and Q and the list are asked for before the count is known.  Attention before /
 // now: 5 % density (lists of 13), 64K 1435 / 1420 us; 128K (42) 9984 / 9956; 12 prompts to 2047 tokens 110.1 / 109.1.
+// Every list of the selection ends with the diagonal block, where a wave's queries see only the key tiles up to
+// their own: that block has a body of its own that leaves the others out of both products (3/8 of its work
+// at B = 128, 1/4 at 64).  The wave with all tiles still takes the block's time, but its neighbours on the SIMD
+// gain: before / now, 5 % density, 64K 1421 / 1390 us; 32K at 15 % (lists of 20) 1208 / 1184; 128K 9956 / 9822;
+// 12 prompts to 2047 tokens 104.9 / 100.2; d = 64, 64K 1500 / 1480; dense 64K (256 blocks) within 0.3 %.  Not
+// at d = 256, one wave per SIMD: nobody is there to use the time.
 //
 // The kernel is a template over the block size B (64, 128) and the head size D (64, 128, 256).
 //
@@ -70,6 +76,15 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
     float r;
     asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
     return r;
+}
+
+// Lanes (query lane % 32 of the tile, half lane / 32) whose query lies before the key of accumulator x of the
+// tile on the diagonal, key 16 (x / 8) + 8 (lane / 32) + x % 8
+constexpr uint64_t lanes_before_key(int x) {
+    uint64_t lanes = 0;
+    for (int l = 0; l < 64; ++l)
+        if (16 * (x / 8) + 8 * (l / 32) + x % 8 > l % 32) lanes |= 1ull << l;
+    return lanes;
 }
 
 __device__ __forceinline__ int swap_bits_2_3(int x) {
@@ -583,6 +598,7 @@ __device__ __forceinline__ void sparse_attn_body(
     constexpr int kStepsPerRequestV = (NS / 2) / KS;   // V's KS requests go under the first half of S^T,
     constexpr int kStepsPerRequestK = NS / KS;         // the next K's under all of O^T
     const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const f32x16_t none16 = zero16 + neg_inf;
 
     // One listed block.  The first block of a row is a version of its own (first_tag = true): no
     // query has a reference yet, so the probabilities of the first window cannot be formed under
@@ -671,14 +687,87 @@ __device__ __forceinline__ void sparse_attn_body(
         pv_range(kCheckSlot[1] - NS, NS);
         j_cur = j_nxt;
     };
+    // The diagonal block at the end of a list: wave w's queries see its key tiles 0 .. w, and no block follows.
+    // One window for all its pairs, formed before O^T starts (a tile's under the next tile's products, the last
+    // tile's by themselves); the operand ring starts anew with every tile, so that nothing is carried past a tile
+    // that may not be there.
+    auto diagonal_block = [&]() {
+        STEM_WAIT_VMCNT(0);
+        STEM_BARRIER();                                // K(i) is in LDS; V buffer is free
+        const auto v_rq = v_request(i);
+        clear_sum();
+        constexpr int kRing = KS < kAhead ? KS : kAhead;   // the ring starts anew with every tile
+#pragma unroll
+        for (int t = 0; t < KT; ++t) {
+            if (t > 0 && t > w) {                      // wave-uniform
+                // nothing of an earlier block lives on in this tile's registers (no instruction)
+                asm volatile("" : "=v"(s_acc[t]));
+#pragma unroll
+                for (int x = 0; x < 8; ++x) asm volatile("" : "=v"(p_pk[t][x]));
+                continue;
+            }
+            uint4 ka[kSlots];
+#pragma unroll
+            for (int n = 0; n < kRing; ++n) ka[n] = load_k(t * KS + n);
+            STEM_SCHED_FENCE();
+#pragma unroll
+            for (int n = t * KS; n < t * KS + KS; ++n) {
+                const int x = n % KS;
+                if (x + kAhead < KS) ka[(x + kAhead) % kSlots] = load_k(n + kAhead);
+                if ((x & 1) == 0) wait_lgkmcnt((x + kAhead + 1 < KS ? kAhead + 1 : KS - x) - 2);
+                if (t == 0) v_rq.issue(n, v_slice0, slice_step, slice_lds_step);   // every wave has this tile
+                s_acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ka[x % kSlots]), q_reg[x],
+                                                                  x == 0 ? zero16 : s_acc[t], 0, 0, 0);
+                if (t > 0) softmax_slot(n);            // pairs of tile t - 1
+                STEM_SCHED_FENCE();
+            }
+            if (t == w) {
+#pragma unroll
+                for (int x = 0; x < 16; ++x)
+                    s_acc[t][x] = __builtin_amdgcn_inverse_ballot_w64(lanes_before_key(x)) ? neg_inf : s_acc[t][x];
+#pragma unroll
+                for (int q = 8 * t; q < 8 * t + 8; ++q) softmax_pair(q);
+            }
+        }
+
+        STEM_WAIT_VMCNT(0);
+        STEM_BARRIER();                                // V(i) is in LDS
+        uint4 va[kSlots];
+#pragma unroll
+        for (int n = 0; n < kAhead; ++n) va[n] = load_v(n);
+        STEM_SCHED_FENCE();
+        if (needs_fix(window_sum())) {                 // one window, the tiles that the wave has
+#pragma unroll
+            for (int t = 1; t < KT; ++t)
+                if (t > w) s_acc[t] = none16;
+            fix_window(0, 8 * KT);
+        }
+        l_run += window_sum();
+#pragma unroll
+        for (int t = 0; t < KT; ++t) {
+            if (t > 0 && t > w) continue;
+#pragma unroll
+            for (int n = t * KS; n < t * KS + KS; ++n) {
+                if (n + kAhead < NS) va[(n + kAhead) % kSlots] = load_v(n + kAhead);
+                if ((n & 1) == 0) wait_lgkmcnt(2 * ((n + kAhead + 1 < NS ? kAhead + 1 : NS - n) - 2));
+                const int u = (n / DT) & 1, dt = n % DT;
+                const uint4 pb = make_uint4(p_pk[t][u * 4], p_pk[t][u * 4 + 1], p_pk[t][u * 4 + 2], p_pk[t][u * 4 + 3]);
+                o_acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(va[n % kSlots]), as_bf16x8(pb),
+                                                                   o_acc[dt], 0, 0, 0);
+                STEM_SCHED_FENCE();
+            }
+        }
+    };
     int it = 0;
-    if (cnt > 0) {
+    if (cnt > 1 || (cnt == 1 && (kManualHazards || j_cur != i))) {
         one_block(it++, std::true_type{});
     } else {
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) o_acc[dt] = zero16;
     }
-    for (; it < cnt; ++it) one_block(it, std::false_type{});
+    for (; it < cnt && (kManualHazards || it + 1 < cnt || j_cur != i); ++it) one_block(it, std::false_type{});
+    if constexpr (!kManualHazards)
+        if (it < cnt) diagonal_block();
     STEM_WAIT_VMCNT(0);                                // no request may outlive the workgroup's LDS
     if constexpr (kManualHazards) wait_states_acc<16>(o_acc);   // the last O^T instructions have written
 

@@ -260,6 +260,23 @@ int stem_sparse_attn(const stem_shape* shape, const void* q, const void* k, cons
                      int32_t lists_per_kv_head, float softmax_scale, void* out, float* lse,
                      void* hip_stream);
 
+/*
+ * stem_sparse_attn with scratch for handing out the last rows of a long call as the chip's dies get to them,
+ * instead of an equal share to each (they are not equally fast: 1 to 3 % of calls of a millisecond and more).
+ * The same bits as without.
+ *   - stem_attn_queue_bytes: STEM_ATTN_QUEUE_BYTES if a call of this shape and kmax makes use of it on the
+ *     current device, else 0.
+ *   - queue: device memory, 16-byte aligned, of queue_bytes >= STEM_ATTN_QUEUE_BYTES (else STEM_ERR_WORKSPACE), or NULL.
+ *     Its contents do not matter before or after; until the call's work has finished it belongs to this
+ *     call alone, so calls that may overlap in time each need their own.
+ */
+#define STEM_ATTN_QUEUE_BYTES 1024
+int stem_attn_queue_bytes(const stem_shape* shape, int32_t kmax, size_t* host_bytes);
+int stem_sparse_attn_queued(const stem_shape* shape, const void* q, const void* k, const void* v,
+                            const int32_t* counts, const int32_t* indices, int32_t kmax,
+                            int32_t lists_per_kv_head, float softmax_scale, void* out, float* lse,
+                            void* queue, size_t queue_bytes, void* hip_stream);
+
 #ifdef __cplusplus
 }
 #endif

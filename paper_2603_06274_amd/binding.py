@@ -73,6 +73,8 @@ def lib() -> ctypes.CDLL:
             "stem_estimate_select": [shp, vp, vp, vp, f32, f32, i32, vp, i32, i32, vp, vp, i32, vp, vp, sz, vp],
             "stem_select": [shp, vp, vp, i32, i32, i32, vp, vp, i32, vp],
             "stem_sparse_attn": [shp, vp, vp, vp, vp, vp, i32, i32, f32, vp, vp, vp],
+            "stem_attn_queue_bytes": [shp, i32, ctypes.POINTER(sz)],
+            "stem_sparse_attn_queued": [shp, vp, vp, vp, vp, vp, i32, i32, f32, vp, vp, vp, sz, vp],
         }
         for name, args in sigs.items():
             fn = getattr(L, name)
@@ -85,7 +87,8 @@ def lib() -> ctypes.CDLL:
 EXPORTED = ["stem_version", "stem_strerror", "stem_rows", "stem_workspace_bytes",
             "stem_workspace_layout", "stem_budget_schedule", "stem_pool", "stem_block_scores",
             "stem_group_scores", "stem_estimate_select",
-            "stem_estimate", "stem_estimate_static", "stem_select", "stem_sparse_attn"]
+            "stem_estimate", "stem_estimate_static", "stem_select", "stem_sparse_attn",
+            "stem_attn_queue_bytes", "stem_sparse_attn_queued"]
 
 
 def _check(status: int, where: str) -> None:
@@ -239,3 +242,19 @@ def stem_sparse_attn(shape: Shape, q, k, v, counts: torch.Tensor, indices: torch
     _check(lib().stem_sparse_attn(shape.ref(), _ptr(q), _ptr(k), _ptr(v), _ptr(counts), _ptr(indices),
                                   int(kmax), int(bool(lists_per_kv_head)), float(softmax_scale), _ptr(out),
                                   _ptr(lse), _stream()), "stem_sparse_attn")
+
+
+def stem_attn_queue_bytes(shape: Shape, kmax: int) -> int:
+    n = ctypes.c_size_t()
+    _check(lib().stem_attn_queue_bytes(shape.ref(), int(kmax), ctypes.byref(n)), "stem_attn_queue_bytes")
+    return n.value
+
+
+def stem_sparse_attn_queued(shape: Shape, q, k, v, counts: torch.Tensor, indices: torch.Tensor, kmax: int,
+                            softmax_scale: float, out: torch.Tensor, lse: Optional[torch.Tensor],
+                            queue: Optional[torch.Tensor], lists_per_kv_head: bool = False) -> None:
+    _check(lib().stem_sparse_attn_queued(shape.ref(), _ptr(q), _ptr(k), _ptr(v), _ptr(counts), _ptr(indices),
+                                         int(kmax), int(bool(lists_per_kv_head)), float(softmax_scale), _ptr(out),
+                                         _ptr(lse), _ptr(queue),
+                                         queue.numel() * queue.element_size() if queue is not None else 0, _stream()),
+           "stem_sparse_attn_queued")

@@ -302,10 +302,27 @@ int stem_select(const stem_shape* shape, const float* scores, const int32_t* bud
                          indices, kmax, static_cast<hipStream_t>(hip_stream));
 }
 
+int stem_attn_queue_bytes(const stem_shape* shape, int32_t kmax, size_t* host_bytes) {
+    Problem p;
+    int st = make_problem(shape, &p);
+    if (st != STEM_OK) return st;
+    if (!host_bytes || kmax < 1) return STEM_ERR_INVALID_ARG;
+    *host_bytes = p.R > 0 && attention_claims_rows(p, kmax) ? STEM_ATTN_QUEUE_BYTES : 0;
+    return STEM_OK;
+}
+
 int stem_sparse_attn(const stem_shape* shape, const void* q, const void* k, const void* v,
                      const int32_t* counts, const int32_t* indices, int32_t kmax,
                      int32_t lists_per_kv_head, float softmax_scale, void* out, float* lse,
                      void* hip_stream) {
+    return stem_sparse_attn_queued(shape, q, k, v, counts, indices, kmax, lists_per_kv_head, softmax_scale, out, lse,
+                                   nullptr, 0, hip_stream);
+}
+
+int stem_sparse_attn_queued(const stem_shape* shape, const void* q, const void* k, const void* v,
+                            const int32_t* counts, const int32_t* indices, int32_t kmax,
+                            int32_t lists_per_kv_head, float softmax_scale, void* out, float* lse,
+                            void* queue, size_t queue_bytes, void* hip_stream) {
     Problem p;
     int st = make_problem(shape, &p);
     if (st != STEM_OK) return st;
@@ -319,9 +336,11 @@ int stem_sparse_attn(const stem_shape* shape, const void* q, const void* k, cons
         const int64_t rows = p.seq.tok_start[s + 1] - p.seq.tok_start[s];
         if (rows > 0 && (rows - 1) * p.kv_st * 2 + p.d * 2 > 0x7fffffffll) return STEM_ERR_UNSUPPORTED;
     }
+    if (queue && !aligned16(queue)) return STEM_ERR_INVALID_ARG;
+    if (queue && queue_bytes < STEM_ATTN_QUEUE_BYTES) return STEM_ERR_WORKSPACE;
     if (p.R == 0) return STEM_OK;
     return launch_sparse_attn(p, q, k, v, counts, indices, kmax, lists_per_kv_head != 0, softmax_scale,
-                              out, lse, static_cast<hipStream_t>(hip_stream));
+                              out, lse, static_cast<int32_t*>(queue), static_cast<hipStream_t>(hip_stream));
 }
 
 }  // extern "C"

@@ -289,6 +289,46 @@ struct RowWalk {
 // one sequence; several, rows from the last of the call to the first; several, in the walk's order
 enum RowOrder : int { kOneSequence, kAsPacked, kWalk };
 
+// Workgroup id -> XCD is id % 8 and cannot be changed once launched, and the XCDs of a chip are not equally fast
+// under this kernel: given an eighth of the rows each, the last one ends 3 to 4.5 % after the mean (128K: 9.09 to 9.69 ms).
+// So in long launches the last eighth of every XCD's rows is not handed out by workgroup id: the
+// workgroups from slot `claim_from` on claim theirs when they start, from their own XCD's queue as long as it has
+// rows, then from the one with most left.  There are a quarter more such workgroups than rows, so that a fast XCD can
+// take more than its share; who finds nothing returns.  A claim is one atomic addition (taken[x * kQueueStride]: rows of
+// XCD x claimed so far) with a look at the other counters in flight beside it.  Which workgroup takes a row has no
+// influence on the row's result.
+constexpr int kQueueStride = 32;                       // a 128-byte line each
+static_assert(8 * kQueueStride * sizeof(int32_t) == STEM_ATTN_QUEUE_BYTES, "one line per XCD");
+
+// The claim of one wave.  rows_of(x): how many rows XCD x has beyond claim_from (<= 0: none).  Sets xcd and slot;
+// false if all queues are empty.  Every turn of the loop that does not end it finds one more queue used up, for good.
+template <typename Rows>
+__device__ __forceinline__ bool claim_row(int32_t* taken, int claim_from, Rows rows_of, int& xcd, int& slot) {
+    const int lane = threadIdx.x & 63, x = lane & 7;
+    const int rows = rows_of(x);
+    for (int from = xcd;;) {
+        int got = 0;
+        if (lane == 0) got = __hip_atomic_fetch_add(taken + from * kQueueStride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int left = rows - __hip_atomic_load(taken + x * kQueueStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int n = __builtin_amdgcn_readfirstlane(got);
+        if (n < __builtin_amdgcn_readlane(rows, from)) {
+            xcd = from;
+            slot = claim_from + n;
+            return true;
+        }
+        int most = 0, next = -1;
+        for (int y = 0; y < 8; ++y) {
+            const int l = __builtin_amdgcn_readlane(left, y);
+            if (y != from && l > most) { most = l; next = y; }
+        }
+        if (next < 0) return false;
+        from = next;
+    }
+}
+
+// All queues at the start of a launch.  (A kernel and not a memset, which a captured graph would not replay reliably.)
+__global__ void clear_row_queues_kernel(int32_t* taken) { taken[threadIdx.x * kQueueStride] = 0; }
+
 // The body takes the two LDS buffers as __restrict__ parameters: once inlined, every access carries
 // alias-scope information, which lets the compiler's wait-count insertion tell a read of one buffer
 // from an in-flight global->LDS load into the other (otherwise it waits for all of them).
@@ -297,8 +337,8 @@ __device__ __forceinline__ void sparse_attn_body(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ counts, const int32_t* __restrict__ indices,
     uint16_t* __restrict__ out, float* __restrict__ lse, const SeqTable& seq, const RowWalk& walk, int Hq, int R, int G,
-    int order, int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh,
-    float scale, int items_per_xcd, int xcds_per_kv_head, unsigned char* __restrict__ k_lds,
+    int order, int claim_from, int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh,
+    float scale, int items_per_xcd, int xcds_per_kv_head, int32_t* __restrict__ taken, unsigned char* __restrict__ k_lds,
     unsigned char* __restrict__ v_lds) {
     constexpr int KT = B / 32;                         // 32-key tiles per block
     constexpr int KS = D / 16;                         // 16-wide steps of S^T along d; also requests per wave, tensor and block
@@ -319,7 +359,27 @@ __device__ __forceinline__ void sparse_attn_body(
     // (Hkv divides 8) XCD x serves KV head x / m and every m-th row of it, rows descending (long
     // rows first), the G heads of a group side by side; otherwise every XCD takes a contiguous
     // range of the (KV head, row descending, head in group) order ----
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    if (__builtin_expect(slot >= claim_from, 0)) {     // (travels beside `order`)
+        int* const claimed = reinterpret_cast<int*>(k_lds);   // not in use yet
+        if (threadIdx.x < 64) {
+            const bool found = claim_row(taken, claim_from, [&](int x) {
+                const int all = xcds_per_kv_head > 0
+                                    ? (R - x % xcds_per_kv_head + xcds_per_kv_head - 1) / xcds_per_kv_head * G
+                                    : (int)min((int64_t)items_per_xcd, (int64_t)Hq * R - (int64_t)x * items_per_xcd);
+                return all - claim_from;
+            }, xcd, slot);
+            if (threadIdx.x == 0) {
+                claimed[0] = found ? xcd : -1;
+                claimed[1] = slot;
+            }
+        }
+        __syncthreads();
+        xcd = __builtin_amdgcn_readfirstlane(claimed[0]);
+        slot = __builtin_amdgcn_readfirstlane(claimed[1]);
+        __syncthreads();
+        if (xcd < 0) return;
+    }
     int g, h, pos;                                     // pos: place of the row in the walk
     if (xcds_per_kv_head > 0) {
         pos = (slot / G) * xcds_per_kv_head + xcd % xcds_per_kv_head;
@@ -811,27 +871,62 @@ __global__ __launch_bounds__(B * 2, D == 256 ? 1 : 2) void sparse_attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ counts, const int32_t* __restrict__ indices,
     uint16_t* __restrict__ out, float* __restrict__ lse, SeqTable seq, RowWalk walk, int Hq, int R, int G,
-    int order, int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh, float scale,
-    int items_per_xcd, int xcds_per_kv_head) {
+    int order, int claim_from, int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh,
+    float scale, int items_per_xcd, int xcds_per_kv_head, int32_t* __restrict__ taken) {
     __shared__ __attribute__((aligned(1024))) unsigned char k_lds[B * D * 2];
     __shared__ __attribute__((aligned(1024))) unsigned char v_lds[B * D * 2];
-    sparse_attn_body<B, D>(q, k, v, counts, indices, out, lse, seq, walk, Hq, R, G, order, T, kmax, shared_lists, q_st, q_sh,
-                           kv_st, kv_sh, scale, items_per_xcd, xcds_per_kv_head, k_lds, v_lds);
+    sparse_attn_body<B, D>(q, k, v, counts, indices, out, lse, seq, walk, Hq, R, G, order, claim_from, T, kmax, shared_lists,
+                           q_st, q_sh, kv_st, kv_sh, scale, items_per_xcd, xcds_per_kv_head, taken, k_lds, v_lds);
+}
+
+// XCDs that share one KV head's rows (the kernel says how); 0: contiguous ranges of all rows instead
+static int xcds_of_kv_head(const Problem& p) { return p.Hkv <= 8 && 8 % p.Hkv == 0 ? 8 / p.Hkv : 0; }
+
+// workgroups of one XCD if every row is handed out by workgroup id
+static int64_t slots_per_xcd(const Problem& p) {
+    const int m = xcds_of_kv_head(p);
+    return m > 0 ? (int64_t)((p.R + m - 1) / m) * p.G : ((int64_t)p.Hq * p.R + 7) / 8;
+}
+
+// Claiming (claim_row) costs 1 us for clearing the counters and 1 to 2 us for each row claimed, and gains what the
+// XCDs differ by at the end.  Attention alone, by workgroup id / claimed: gqa 32 / 8, 128K at 8 % 9671 / 9447 us, 32K at
+// 15 % 1160 / 1148; 28 / 4, 64K dense 25.4 / 25.0 ms; d = 256, 32K 2432 / 2378; B = 64, 100K 8699 / 8448; but 16K 317 / 317, 24K
+// 694 / 692, 12 prompts to 2047 tokens 108 / 110, B = 64, 16K 376 / 380.  So: 1e12 operations and more (about
+// 0.9 ms), lists bounded by kmax, and eight rounds of what runs at a time, below which an eighth is less than a
+// round.  An eighth or a quarter of the rows are as good; a sixteenth is too few (dense: 25.3 ms).
+bool attention_claims_rows(const Problem& p, int32_t kmax) {
+    const int64_t at_a_time = (int64_t)compute_units() * (p.d == 256 ? 128 / p.B : 256 / p.B);
+    if (at_a_time <= 0 || (int64_t)p.Hq * p.R < 8 * at_a_time) return false;
+    double blocks = 0.0;                               // of one head: rows first .. last - 1 list at most min(i + 1, kmax)
+    for (int s = 0; s < p.batch; ++s) {
+        const double first = p.seq.first_block[s], last = first + p.seq.row_start[s + 1] - p.seq.row_start[s];
+        auto up_to = [&](double n) {
+            const double k = kmax < n ? kmax : n;
+            return k * (k + 1.0) / 2.0 + (n - k) * k;
+        };
+        blocks += up_to(last) - up_to(first);
+    }
+    return blocks * p.Hq * 4.0 * p.d * p.B * p.B >= 1e12;
 }
 
 int launch_sparse_attn(const Problem& p, const void* q, const void* k, const void* v,
                        const int32_t* counts, const int32_t* indices, int32_t kmax,
                        bool lists_per_kv_head, float softmax_scale, void* out, float* lse,
-                       hipStream_t stream) {
+                       int32_t* queue, hipStream_t stream) {
     // (the host entry point has checked that one sequence of one KV head spans less than 2 GiB: the
     // block requests use a 32-bit byte offset, with offsets from 2^31 on reserved for "fetch nothing")
     const int64_t items = (int64_t)p.Hq * p.R;
-    const int xcds_per_kv_head = (p.Hkv <= 8 && 8 % p.Hkv == 0) ? 8 / p.Hkv : 0;
-    const int64_t per_xcd = xcds_per_kv_head > 0
-                                ? (int64_t)((p.R + xcds_per_kv_head - 1) / xcds_per_kv_head) * p.G
-                                : (items + 7) / 8;
-    if (per_xcd * 8 > 0x7fffffff) return STEM_ERR_UNSUPPORTED;
-    dim3 grid((unsigned)(per_xcd * 8)), block(p.B * 2);
+    const int xcds_per_kv_head = xcds_of_kv_head(p);
+    const int64_t per_xcd = slots_per_xcd(p);
+    int claim_from = 0x7fffffff;
+    int64_t slots = per_xcd;
+    if (queue != nullptr && attention_claims_rows(p, kmax)) {
+        const int64_t claimed = per_xcd / 8;
+        claim_from = (int)(per_xcd - claimed);
+        slots = per_xcd + (claimed + 3) / 4;
+    }
+    if (slots * 8 > 0x7fffffff) return STEM_ERR_UNSUPPORTED;
+    dim3 grid((unsigned)(slots * 8)), block(p.B * 2);
     // The walk's order is for batches of ten sequences and more, at d = 64 and 128, where rows wait for a place (1.5
     // to 8 times what runs at a time: two workgroups per CU at B = 128, four at B = 64), lists grow with the row
     // (kmax is more than half of the longest sequence's blocks, and these are three or more) and the sequences
@@ -871,10 +966,11 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     const uint16_t* kk = static_cast<const uint16_t*>(k);
     const uint16_t* vv = static_cast<const uint16_t*>(v);
     uint16_t* oo = static_cast<uint16_t*>(out);
+    if (slots > per_xcd) hipLaunchKernelGGL(clear_row_queues_kernel, dim3(1), dim3(8), 0, stream, queue);
 #define STEM_ATTN_LAUNCH(BB, DD)                                                                          \
     hipLaunchKernelGGL((sparse_attn_kernel<BB, DD>), grid, block, 0, stream, qq, kk, vv, counts, indices, \
-                       oo, lse, p.seq, walk, p.Hq, p.R, p.G, order, p.T, kmax, lists_per_kv_head, p.q_st, p.q_sh, \
-                       p.kv_st, p.kv_sh, softmax_scale, (int)per_xcd, xcds_per_kv_head)
+                       oo, lse, p.seq, walk, p.Hq, p.R, p.G, order, claim_from, p.T, kmax, lists_per_kv_head, p.q_st, p.q_sh, \
+                       p.kv_st, p.kv_sh, softmax_scale, (int)per_xcd, xcds_per_kv_head, queue)
     if (p.B == 128 && p.d == 128) STEM_ATTN_LAUNCH(128, 128);
     else if (p.B == 64 && p.d == 128) STEM_ATTN_LAUNCH(64, 128);
     else if (p.B == 128 && p.d == 64) STEM_ATTN_LAUNCH(128, 64);

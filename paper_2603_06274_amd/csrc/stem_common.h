@@ -63,7 +63,9 @@ int launch_score_select(const Problem& p, int ad_stride, const float* q_bar, con
 int launch_sparse_attn(const Problem& p, const void* q, const void* k, const void* v,
                        const int32_t* counts, const int32_t* indices, int32_t kmax,
                        bool lists_per_kv_head, float softmax_scale, void* out, float* lse,
-                       hipStream_t stream);
+                       int32_t* queue, hipStream_t stream);
+// whether launch_sparse_attn makes use of a queue (STEM_ATTN_QUEUE_BYTES of scratch), if it gets one
+bool attention_claims_rows(const Problem& p, int32_t kmax);
 
 // Compute units of the current device, 0 on failure.  A constant of the device, kept after the first call
 // (several threads may store the same value): the query costs a call that has 30 us in all about 1 %.

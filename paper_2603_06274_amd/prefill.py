@@ -44,6 +44,7 @@ class StemPrefill:
         budget_host, kmax = sb.stem_budget_schedule(self.shape, k_start_blocks, mu, k_min, n_sink, n_local)
         self.budget_host = budget_host
         self.kmax = max(kmax, 1)
+        self.queue_bytes = sb.stem_attn_queue_bytes(self.shape, self.kmax)
         dev = q.device
         Hq, T = q.shape[1], q.shape[0]
         self.budget = budget_host.to(dev)
@@ -81,8 +82,15 @@ class StemPrefill:
                        lists_per_kv_head=bool(self.group_share))
 
     def attend(self) -> None:
-        sb.stem_sparse_attn(self.shape, self.q, self.k, self.v, self.counts, self.indices, self.kmax,
-                            self.softmax_scale, self.out, self.lse, lists_per_kv_head=bool(self.group_share))
+        if not self.queue_bytes:
+            sb.stem_sparse_attn(self.shape, self.q, self.k, self.v, self.counts, self.indices, self.kmax,
+                                self.softmax_scale, self.out, self.lse, lists_per_kv_head=bool(self.group_share))
+            return
+        # a long call (about 1 ms and more); scratch of its own each time, so that calls on several streams do not meet in it
+        queue = torch.empty(self.queue_bytes, dtype=torch.uint8, device=self.q.device)
+        sb.stem_sparse_attn_queued(self.shape, self.q, self.k, self.v, self.counts, self.indices, self.kmax,
+                                   self.softmax_scale, self.out, self.lse, queue,
+                                   lists_per_kv_head=bool(self.group_share))
 
     def estimate_select(self, debug_scores: Optional[torch.Tensor] = None) -> None:
         """Stages 1-2 without the score tensor (per-head lists only)."""

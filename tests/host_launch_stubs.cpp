@@ -22,9 +22,10 @@ int launch_score_select(const Problem&, int, const float*, const float*, const f
     return STEM_OK;
 }
 int launch_sparse_attn(const Problem&, const void*, const void*, const void*, const int32_t*, const int32_t*, int32_t,
-                       bool, float, void*, float*, hipStream_t) {
+                       bool, float, void*, float*, int32_t*, hipStream_t) {
     return STEM_OK;
 }
+bool attention_claims_rows(const Problem&, int32_t) { return false; }
 
 }  // namespace stem
 

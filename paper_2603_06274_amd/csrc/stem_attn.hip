@@ -895,8 +895,6 @@ static int64_t slots_per_xcd(const Problem& p) {
 // 0.9 ms), lists bounded by kmax, and eight rounds of what runs at a time, below which an eighth is less than a
 // round.  An eighth or a quarter of the rows are as good; a sixteenth is too few (dense: 25.3 ms).
 bool attention_claims_rows(const Problem& p, int32_t kmax) {
-    const int64_t at_a_time = (int64_t)compute_units() * (p.d == 256 ? 128 / p.B : 256 / p.B);
-    if (at_a_time <= 0 || (int64_t)p.Hq * p.R < 8 * at_a_time) return false;
     double blocks = 0.0;                               // of one head: rows first .. last - 1 list at most min(i + 1, kmax)
     for (int s = 0; s < p.batch; ++s) {
         const double first = p.seq.first_block[s], last = first + p.seq.row_start[s + 1] - p.seq.row_start[s];
@@ -906,7 +904,9 @@ bool attention_claims_rows(const Problem& p, int32_t kmax) {
         };
         blocks += up_to(last) - up_to(first);
     }
-    return blocks * p.Hq * 4.0 * p.d * p.B * p.B >= 1e12;
+    if (blocks * p.Hq * 4.0 * p.d * p.B * p.B < 1e12) return false;
+    const int64_t at_a_time = (int64_t)compute_units() * (p.d == 256 ? 128 / p.B : 256 / p.B);
+    return at_a_time > 0 && (int64_t)p.Hq * p.R >= 8 * at_a_time;
 }
 
 int launch_sparse_attn(const Problem& p, const void* q, const void* k, const void* v,

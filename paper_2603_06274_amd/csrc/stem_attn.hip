@@ -14,7 +14,7 @@
 //
 // K and V blocks go from global memory straight into LDS (buffer_load ... lds, no staging
 // registers), one buffer each, refilled in split phases behind two barriers per block: the V block
-// is requested during the first half of S^T and must have landed when S^T ends; the next K block
+// is requested while S^T starts and must have landed when S^T ends; the next K block
 // is requested during O^T and must have landed when the next iteration starts.  Two workgroups
 // share a CU, so one workgroup's matrix work fills the other's waits (at head size 256 the two
 // 64 KiB buffers and about 490 registers leave room for one).
@@ -655,8 +655,16 @@ __device__ __forceinline__ void sparse_attn_body(
             if (t * 32 + 16 * (x >> 3) + (x & 7) > limit) s_acc[t][x] = neg_inf;
     };
 
-    constexpr int kStepsPerRequestV = (NS / 2) / KS;   // V's KS requests go under the first half of S^T,
-    constexpr int kStepsPerRequestK = NS / KS;         // the next K's under all of O^T
+    // The matrix instruction of S^T under which request u of V is issued, and of O^T for the next K.  At B = 64 a
+    // product lasts only 16 of them (32 at d = 256), about the latency of a block that comes from beyond the L2, so
+    // requests go out at the start, two at a time; at B = 128 they are spread, which leaves the LDS reads alone,
+    // to the middle of S^T and two thirds of O^T.  Attention alone, spread over the first half of S^T and all of O^T as
+    // at first / now: B = 64, 100K tokens at 6 % 8321 / 7876 us, d = 64, 64K at 5 % 1384 / 1348, d = 256, 64K 5198 / 4745
+    // (two V at a time 4768, and 30.7 against 29.1 us for one head of 4096), one head of 4096 13.8 / 13.5; B = 128, one third
+    // earlier for K 1.000 to 0.996, everything at the start up to 1 % slower, d = 256 7 %.
+    auto v_slot = [](int u) { return B == 128 ? 2 * u : D == 256 ? u : u / 2; };
+    auto k_slot = [](int u) { return B == 128 ? 3 * u + 1 : u / 2; };
+    static_assert(2 * (KS - 1) < NS && 3 * (KS - 1) + 1 < 4 * KS, "every request has a slot");
     const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     const f32x16_t none16 = zero16 + neg_inf;
 
@@ -676,7 +684,7 @@ __device__ __forceinline__ void sparse_attn_body(
         STEM_WAIT_VMCNT(0);
         STEM_BARRIER();                                // K(j) is in LDS; V buffer is free
 
-        // ---- S^T = K Q^T, with the V requests in between during the first half ----
+        // ---- S^T = K Q^T, with the V requests in between ----
         uint4 ka[kSlots];
 #pragma unroll
         for (int n = 0; n < kAhead; ++n) ka[n] = load_k(n);
@@ -693,8 +701,9 @@ __device__ __forceinline__ void sparse_attn_body(
                     if (n + kAhead + 1 < NS) ka[(n + kAhead + 1) % kSlots] = load_k(n + kAhead + 1);
                     wait_lgkmcnt((n + kAhead + 2 < NS ? kAhead + 2 : NS - n) - 2);
                 }
-                if (n < NS / 2 && n % kStepsPerRequestV == 0)
-                    v_rq.issue(n / kStepsPerRequestV, v_slice0, slice_step, slice_lds_step);
+#pragma unroll
+                for (int u = 0; u < KS; ++u)
+                    if (v_slot(u) == n) v_rq.issue(u, v_slice0, slice_step, slice_lds_step);
                 if constexpr (kManualHazards) {
                     if ((n % KS) == 0) mfma_scores_first(s_acc[t], ka[n % kSlots], q_acc[n % KS]);
                     else mfma_scores(s_acc[t], ka[n % kSlots], q_acc[n % KS]);
@@ -711,8 +720,8 @@ __device__ __forceinline__ void sparse_attn_body(
         STEM_WAIT_VMCNT(0);
         STEM_BARRIER();                                // every wave is done with K(j); V(j) is in LDS
 
-        // ---- O^T += V^T P^T.  The next block's K requests are spread over the whole product;
-        //      after the last block they are empty (a zero-sized resource: nothing is fetched) ----
+        // ---- O^T += V^T P^T, with the next block's K requests in between; after the last block they
+        //      are empty (an offset beyond the resource: nothing is fetched) ----
         uint4 va[kSlots];
 #pragma unroll
         for (int n = 0; n < kAhead; ++n) va[n] = load_v(n);
@@ -727,7 +736,9 @@ __device__ __forceinline__ void sparse_attn_body(
                 } else {
                     if (n + kAhead < NS) va[(n + kAhead) % kSlots] = load_v(n + kAhead);
                 }
-                if (n % kStepsPerRequestK == 1) k_rq.issue(n / kStepsPerRequestK, k_slice0, slice_step, slice_lds_step);
+#pragma unroll
+                for (int u = 0; u < KS; ++u)
+                    if (k_slot(u) == n) k_rq.issue(u, k_slice0, slice_step, slice_lds_step);
                 const int g2 = n / DT, t = g2 >> 1, u = g2 & 1, dt = n % DT;
                 const uint4 pb = make_uint4(p_pk[t][u * 4], p_pk[t][u * 4 + 1], p_pk[t][u * 4 + 2], p_pk[t][u * 4 + 3]);
                 if constexpr (kManualHazards) {

@@ -115,7 +115,12 @@ __device__ __forceinline__ void wait_lgkmcnt(int n) {   // n is a constant after
 }
 
 // Nothing is scheduled across this point: keeps the next group of LDS operand reads ahead of the
-// matrix instructions that consume the current group.
+// matrix instructions that consume the current group, operand reads in the order of their use, and a matrix
+// instruction ahead of the softmax pair that goes under it (the compiler put the first pair of a tile, which waits
+// for the tile's last product, before the next tile's first product, and read a block's first operands in an order
+// of its own, with one wait for all of them).  Attention alone, without / with the last two: 128K 9410 / 9329 us,
+// 64K dense 25208 / 24964, 5 % 1351 / 1338, 32K 1141 / 1133, d = 64 64K 1443 / 1430, B = 64 100K 7979 / 7894, one head of 4096
+// 13.55 / 13.13; d = 256 as before.
 #define STEM_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 
 // Matrix instructions with the register file chosen by hand (head size 256).  A wave that may use
@@ -500,6 +505,10 @@ __device__ __forceinline__ void sparse_attn_body(
         for (int u = 0; u < KS; ++u) rq.issue(u, k_slice0, slice_step, slice_lds_step);
     }
 
+    // The output pointers are taken now: a scalar load still in flight would make every wait for LDS operands in the
+    // blocks one for all of them (the two kinds return in any order on one counter).
+    asm volatile("" : : "s"(out), "s"(lse));
+
     f32x16_t o_acc[DT];                                // the first block's products start it
     const float neg_inf = -__builtin_huge_valf();
     float m_ref = neg_inf;                             // softmax reference (raw score units)
@@ -687,7 +696,10 @@ __device__ __forceinline__ void sparse_attn_body(
         // ---- S^T = K Q^T, with the V requests in between ----
         uint4 ka[kSlots];
 #pragma unroll
-        for (int n = 0; n < kAhead; ++n) ka[n] = load_k(n);
+        for (int n = 0; n < kAhead; ++n) {
+            ka[n] = load_k(n);
+            if (n & 1) STEM_SCHED_FENCE();             // in the order of their use
+        }
         const auto v_rq = v_request(j);
         const int j_nxt = __builtin_amdgcn_readlane(list_reg, (it + 1) & 63);   // 0 past the end
         clear_sum();
@@ -711,7 +723,10 @@ __device__ __forceinline__ void sparse_attn_body(
                     s_acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ka[n % kSlots]), q_reg[n % KS],
                                                                       (n % KS) == 0 ? zero16 : s_acc[t], 0, 0, 0);
                 }
-                if constexpr (!kFirst) softmax_slot(n);
+                if constexpr (!kFirst) {
+                    if (n >= KS) STEM_SCHED_FENCE();   // the matrix instruction first
+                    softmax_slot(n);
+                }
                 STEM_SCHED_FENCE();
             }
             if (t >= mask_from) mask_tile(t, mask_limit);
@@ -724,7 +739,10 @@ __device__ __forceinline__ void sparse_attn_body(
         //      are empty (an offset beyond the resource: nothing is fetched) ----
         uint4 va[kSlots];
 #pragma unroll
-        for (int n = 0; n < kAhead; ++n) va[n] = load_v(n);
+        for (int n = 0; n < kAhead; ++n) {
+            va[n] = load_v(n);
+            if (n & 1) STEM_SCHED_FENCE();
+        }
         const auto k_rq = k_request(clamped(j_nxt), has_next);
         STEM_SCHED_FENCE();
         auto pv_range = [&](int n_lo, int n_hi) {      // even bounds
@@ -747,6 +765,7 @@ __device__ __forceinline__ void sparse_attn_body(
                 } else
                     o_acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(va[n % kSlots]), as_bf16x8(pb),
                                                                        kFirst && n < DT ? zero16 : o_acc[dt], 0, 0, 0);
+                STEM_SCHED_FENCE();
                 softmax_slot(NS + n);
                 STEM_SCHED_FENCE();
             }
@@ -779,7 +798,10 @@ __device__ __forceinline__ void sparse_attn_body(
             }
             uint4 ka[kSlots];
 #pragma unroll
-            for (int n = 0; n < kRing; ++n) ka[n] = load_k(t * KS + n);
+            for (int n = 0; n < kRing; ++n) {
+                ka[n] = load_k(t * KS + n);
+                if (n & 1) STEM_SCHED_FENCE();
+            }
             STEM_SCHED_FENCE();
 #pragma unroll
             for (int n = t * KS; n < t * KS + KS; ++n) {
@@ -789,7 +811,10 @@ __device__ __forceinline__ void sparse_attn_body(
                 if (t == 0) v_rq.issue(n, v_slice0, slice_step, slice_lds_step);   // every wave has this tile
                 s_acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ka[x % kSlots]), q_reg[x],
                                                                   x == 0 ? zero16 : s_acc[t], 0, 0, 0);
-                if (t > 0) softmax_slot(n);            // pairs of tile t - 1
+                if (t > 0) {                           // pairs of tile t - 1
+                    STEM_SCHED_FENCE();
+                    softmax_slot(n);
+                }
                 STEM_SCHED_FENCE();
             }
             if (t == w) {
@@ -805,7 +830,10 @@ __device__ __forceinline__ void sparse_attn_body(
         STEM_BARRIER();                                // V(i) is in LDS
         uint4 va[kSlots];
 #pragma unroll
-        for (int n = 0; n < kAhead; ++n) va[n] = load_v(n);
+        for (int n = 0; n < kAhead; ++n) {
+            va[n] = load_v(n);
+            if (n & 1) STEM_SCHED_FENCE();
+        }
         STEM_SCHED_FENCE();
         if (needs_fix(window_sum())) {                 // one window, the tiles that the wave has
 #pragma unroll

@@ -27,7 +27,7 @@
 // on the first block and moved only when a window of probabilities overflows (slow path).
 // The vector unit's issue slots are what the kernel runs short of (every vector instruction taken
 // out of the loop shows in the run time), so whatever can go elsewhere does: the row sums of the
-// probabilities are taken by the matrix pipe (a 4x4x4 product with a matrix of ones), the
+// probabilities are taken by the matrix pipe (a small product with a 0/1 matrix), the
 // per-request address arithmetic by the scalar unit (the scalar offset operand of the loads).
 // A row's own work beside its blocks counts the same way where lists are short: no zeros are written to
 // accumulators that the first block's products can start, only tiles on or above the wave's diagonal are masked,
@@ -512,7 +512,7 @@ __device__ __forceinline__ void sparse_attn_body(
     f32x16_t o_acc[DT];                                // the first block's products start it
     const float neg_inf = -__builtin_huge_valf();
     float m_ref = neg_inf;                             // softmax reference (raw score units)
-    float l_run = 0.f;                                 // this lane's share of the softmax sum
+    float l_run = 0.f;                                 // softmax sum of the query (of this lane's keys, unless kStepSums)
     const float sl2 = scale * 1.4426950408889634f;
 
     // per-lane LDS offsets that do not change between blocks.  Both swizzles are XORs of address
@@ -554,16 +554,27 @@ __device__ __forceinline__ void sparse_attn_body(
     auto pairs_by = [](int slot) { return Sched::kTable.v[slot + 1]; };
     constexpr int kCheckSlot[2] = {Sched::check_slot(0), Sched::check_slot(1)};
 
+    // 0/1 operand of the row-sum product (softmax_pair): row m takes the lane groups g of 16 with g % 2 = (m / 4) % 2
+    constexpr bool kStepSums = B == 128 && D != 256;
+    const uint32_t own_pair = ((lane >> 2) ^ (lane >> 4)) & 1 ? 0u : 0x3f803f80u;
+    const uint4 own_query = make_uint4(own_pair, own_pair, own_pair, own_pair);
+
     f32x16_t s_acc[KT];
     uint32_t p_pk[KT][8];                              // bf16 pairs: [tile][16-key step * 4 + pair]
     f32x4_t l_win = {0.f, 0.f, 0.f, 0.f};              // row sum of the current window (four equal copies)
     float off = 0.f;                                   // reference in exp2 units; changes on the slow path only
 
     // softmax of pair q (tile q/8, accumulators 2*(q%8) and +1): exp2 domain, reference m_ref,
-    // packed to bf16.  The row sum is taken from the rounded values, two pairs at a time, by the
-    // matrix pipe: in v_mfma_f32_4x4x4_16B_bf16 lane l supplies column l % 4 of block l / 4 of B (four
-    // values along the contraction) and receives that column of the 4 x 4 result, so with A = ones
-    // every lane gets the sum of its own four values, in each of its four result registers.
+    // packed to bf16.  The row sum is taken from the rounded values by the matrix pipe: in
+    // v_mfma_f32_4x4x4_16B_bf16 lane l supplies column l % 4 of block l / 4 of B (four values along the contraction, two
+    // pairs) and receives that column of the 4 x 4 result, so with A = ones every lane gets the sum of its own four
+    // values, in each of its four result registers.
+    // At B = 128, d = 64 and 128, a 16-key step at a time: the B operand that the step's O^T product takes (lane l: query
+    // l % 32, keys 8 (l / 32) .. + 7) is, to v_mfma_f32_16x16x32_bf16, column l % 16 and lane group l / 16 of the
+    // contraction, so groups 0 and 2 hold query c, 1 and 3 query c + 16, and a 0/1 operand that picks a group's parity by
+    // the result's row gives every lane the sum over all sixteen keys of its own query.  Eight of these take the
+    // matrix pipe the time of the sixteen others, with half the issue slots: 128K 9221 / 9176 us, 64K dense
+    // 25133 / 25025, 5 % 1326 / 1318, d = 64 64K 1425 / 1416; at B = 64 no difference, and 0.05 us more per call.
     auto softmax_pair = [&](int q) {
         const int t = q >> 3, x = (q & 7) * 2;
         // hand-placed form: a matrix result may be read 12 issue slots after its instruction; the
@@ -580,7 +591,13 @@ __device__ __forceinline__ void sparse_attn_body(
         // each pair next to "its" matrix instruction.
         asm volatile("" : "+v"(pk));
         p_pk[t][q & 7] = pk;
-        if (q & 1) {                                   // windows hold an even number of pairs
+        if constexpr (kStepSums) {
+            if ((q & 3) == 3) {                        // windows hold whole 16-key steps
+                const int u = q & 4;
+                const uint4 step = make_uint4(p_pk[t][u], p_pk[t][u + 1], p_pk[t][u + 2], p_pk[t][u + 3]);
+                l_win = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(own_query), as_bf16x8(step), l_win, 0, 0, 0);
+            }
+        } else if (q & 1) {
             const uint2 four = make_uint2(p_pk[t][(q & 7) - 1], pk);
             const uint2 ones = make_uint2(0x3f803f80u, 0x3f803f80u);
             if constexpr (kManualHazards)
@@ -603,19 +620,20 @@ __device__ __forceinline__ void sparse_attn_body(
     // which keeps its masked scores at exp2(-inf) = 0
     auto reference_offset = [&]() { return m_ref == neg_inf ? 0.f : m_ref * sl2; };
     // Largest score of the query in pairs [q_lo, q_hi) (both of its lanes get it)
-    auto window_max = [&](int q_lo, int q_hi) {
+    auto lane_max = [&](int q_lo, int q_hi) {          // of this lane's keys
         float mx4[4] = {neg_inf, neg_inf, neg_inf, neg_inf};
 #pragma unroll
         for (int q = q_lo; q < q_hi; ++q)
             mx4[q & 3] = max3(mx4[q & 3], s_acc[q >> 3][(q & 7) * 2], s_acc[q >> 3][(q & 7) * 2 + 1]);
-        const float mx = max3(max3(mx4[0], mx4[1], mx4[2]), mx4[3], mx4[3]);
+        return max3(max3(mx4[0], mx4[1], mx4[2]), mx4[3], mx4[3]);
+    };
+    auto both_lanes_max = [&](float mx) {
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
         return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
     };
-    // Slow path for the window of pairs [q_lo, q_hi): take their true maximum, move the reference
-    // up to it (rescaling O and l), and recompute the window's probabilities.
-    auto fix_window = [&](int q_lo, int q_hi) {
-        const float mx = window_max(q_lo, q_hi);
+    auto window_max = [&](int q_lo, int q_hi) { return both_lanes_max(lane_max(q_lo, q_hi)); };
+    // Moves the reference up to mx (rescaling O and l) if that is higher, and starts the window's sum anew.
+    auto raise_reference = [&](float mx) {
         if (mx > m_ref) {
             const float corr = (m_ref == neg_inf) ? 0.f : __builtin_amdgcn_exp2f((m_ref - mx) * sl2);
             m_ref = mx;
@@ -629,6 +647,11 @@ __device__ __forceinline__ void sparse_attn_body(
         }
         off = reference_offset();
         clear_sum();
+    };
+    // Slow path for the window of pairs [q_lo, q_hi): take their true maximum, move the reference
+    // up to it, and recompute the window's probabilities.
+    auto fix_window = [&](int q_lo, int q_hi) {
+        raise_reference(window_max(q_lo, q_hi));
 #pragma unroll
         for (int q = q_lo; q < q_hi; ++q) softmax_pair(q);
     };
@@ -675,7 +698,6 @@ __device__ __forceinline__ void sparse_attn_body(
     auto k_slot = [](int u) { return B == 128 ? 3 * u + 1 : u / 2; };
     static_assert(2 * (KS - 1) < NS && 3 * (KS - 1) + 1 < 4 * KS, "every request has a slot");
     const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    const f32x16_t none16 = zero16 + neg_inf;
 
     // One listed block.  The first block of a row is a version of its own (first_tag = true): no
     // query has a reference yet, so the probabilities of the first window cannot be formed under
@@ -786,7 +808,10 @@ __device__ __forceinline__ void sparse_attn_body(
         STEM_BARRIER();                                // K(i) is in LDS; V buffer is free
         const auto v_rq = v_request(i);
         clear_sum();
-        constexpr int kRing = KS < kAhead ? KS : kAhead;   // the ring starts anew with every tile
+        // (B = 128, d = 128 has no register left: operands of S^T four ahead, those of O^T after the check, or it spills)
+        constexpr bool kTight = B == 128 && D == 128;
+        constexpr int kAheadD = kTight ? 4 : kAhead;
+        constexpr int kRing = KS < kAheadD ? KS : kAheadD;
 #pragma unroll
         for (int t = 0; t < KT; ++t) {
             if (t > 0 && t > w) {                      // wave-uniform
@@ -806,8 +831,8 @@ __device__ __forceinline__ void sparse_attn_body(
 #pragma unroll
             for (int n = t * KS; n < t * KS + KS; ++n) {
                 const int x = n % KS;
-                if (x + kAhead < KS) ka[(x + kAhead) % kSlots] = load_k(n + kAhead);
-                if ((x & 1) == 0) wait_lgkmcnt((x + kAhead + 1 < KS ? kAhead + 1 : KS - x) - 2);
+                if (x + kAheadD < KS) ka[(x + kAheadD) % kSlots] = load_k(n + kAheadD);
+                if ((x & 1) == 0) wait_lgkmcnt((x + kAheadD + 1 < KS ? kAheadD + 1 : KS - x) - 2);
                 if (t == 0) v_rq.issue(n, v_slice0, slice_step, slice_lds_step);   // every wave has this tile
                 s_acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ka[x % kSlots]), q_reg[x],
                                                                   x == 0 ? zero16 : s_acc[t], 0, 0, 0);
@@ -828,20 +853,34 @@ __device__ __forceinline__ void sparse_attn_body(
 
         STEM_WAIT_VMCNT(0);
         STEM_BARRIER();                                // V(i) is in LDS
+        constexpr int kPre = kTight ? 0 : kAhead;
         uint4 va[kSlots];
 #pragma unroll
-        for (int n = 0; n < kAhead; ++n) {
+        for (int n = 0; n < kPre; ++n) {
             va[n] = load_v(n);
             if (n & 1) STEM_SCHED_FENCE();
         }
         STEM_SCHED_FENCE();
-        if (needs_fix(window_sum())) {                 // one window, the tiles that the wave has
+        if (needs_fix(window_sum())) {                 // fix_window of the tiles that the wave has, as one window
+            float mx = lane_max(0, 8);
 #pragma unroll
             for (int t = 1; t < KT; ++t)
-                if (t > w) s_acc[t] = none16;
-            fix_window(0, 8 * KT);
+                if (t <= w) mx = fmaxf(mx, lane_max(8 * t, 8 * t + 8));
+            raise_reference(both_lanes_max(mx));
+#pragma unroll
+            for (int t = 0; t < KT; ++t) {
+                if (t > 0 && t > w) continue;
+#pragma unroll
+                for (int q = 8 * t; q < 8 * t + 8; ++q) softmax_pair(q);
+            }
         }
         l_run += window_sum();
+        STEM_SCHED_FENCE();
+#pragma unroll
+        for (int n = kPre; n < kAhead; ++n) {
+            va[n] = load_v(n);
+            if (n & 1) STEM_SCHED_FENCE();
+        }
 #pragma unroll
         for (int t = 0; t < KT; ++t) {
             if (t > 0 && t > w) continue;
@@ -871,8 +910,8 @@ __device__ __forceinline__ void sparse_attn_body(
     if constexpr (kManualHazards) wait_states_acc<16>(o_acc);   // the last O^T instructions have written
 
     // ---- normalise and store: accumulator x of d tile dt is column dt*32 + 8*(x/4) + 4*hi + x%4 ----
-    float l_tot;
-    {
+    float l_tot = l_run;
+    if constexpr (!kStepSums) {                        // each lane has summed its own half of the keys
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
         l_tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
     }

@@ -14,6 +14,7 @@ Rules checked (wait states = instructions issued in between, `s_nop N` counting 
     different-but-overlapping C operand 10 later; the identical C operand (accumulation) may
     follow at once (two matrix results that overlap need nothing: the matrix pipe completes in
     order, and the compiler's own code for the builtin form places them back to back);
+  * for a 16x16x32 one (4 passes) the distances are 8 and 6 (the compiler's own code for the builtin form keeps 8);
   * for a 4x4x4 matrix instruction (2 passes) the distances are 5 and 4, and the next
     accumulation into the identical registers needs 2;
   * a matrix instruction may read a register 2 wait states after a vector instruction wrote it.
@@ -104,7 +105,7 @@ def check_kernel(asm: str, symbol: str) -> List[str]:
                         found.add("matrix read after vector write, line %d `%s` after line %d `%s`: %d wait states, 2 needed"
                                   % (i, line, written[r][1], written[r][2], state - written[r][0] - 1))
                         break
-                need, need_c = (5, 4) if "4x4x4" in op else (12, 10)
+                need, need_c = (5, 4) if "4x4x4" in op else (8, 6) if "16x16x32" in op else (12, 10)
                 pending[:] = [p for p in pending if state - p[3] - 1 < p[1] and p[0] != dst]
                 pending.append((dst, need, need_c, state, i, line))
                 state += 1

@@ -54,6 +54,17 @@ def test_row_sum_instruction():
     assert not broken(ROW_SUM + FILLER * 2 + ROW_SUM)
 
 
+def test_four_pass_instruction():
+    row_sum = "\tv_mfma_f32_16x16x32_bf16 v[40:43], v[36:39], v[44:47], v[40:43]\n"
+    read = "\tv_add_f32_e32 v1, v2, v40\n"
+    assert broken(row_sum + FILLER * 7 + read)
+    assert not broken(row_sum + FILLER * 8 + read)
+    assert not broken(row_sum + row_sum)
+    shifted = "\tv_mfma_f32_16x16x32_bf16 v[42:45], v[36:39], v[48:51], v[42:45]\n"
+    assert broken(row_sum + FILLER * 5 + shifted)
+    assert not broken(row_sum + FILLER * 6 + shifted)
+
+
 def test_matrix_read_after_vector_write():
     write = "\tv_accvgpr_write_b32 a2, v9\n"
     assert broken(write + FILLER + S_TILE)

@@ -20,7 +20,7 @@
 // 64 KiB buffers and about 490 registers leave room for one).
 //
 // Inside a wave the instruction stream is kept dense around the matrix instructions: LDS operands
-// are read six matrix instructions ahead into a ring of registers, the softmax of a block is
+// are read four (B = 64: two) matrix instructions ahead into a ring of registers, the softmax of a block is
 // spread pair by pair over the wave's own matrix instructions (the eight pairs of a 32-key tile
 // under the matrix instructions that follow the tile), and the softmax runs without a running
 // maximum: a per-query reference is set
@@ -544,7 +544,10 @@ __device__ __forceinline__ void sparse_attn_body(
     // their use: the loaded LDS latency is several matrix instructions long.  They are consumed
     // two at a time behind one wait (every instruction, waits included, takes an issue slot of
     // the wave).  An O^T operand is two reads, and at most 15 reads can be counted in flight.
-    constexpr int kSlots = 8, kAhead = 6;
+    // Reading further ahead costs more than it hides, with two waves on a SIMD: six ahead / four (two at B = 64), attention
+    // alone: 128K 9393 / 9340 us, 64K dense 25252 / 25135, 5 % 1356 / 1345, 32K 1142 / 1137, d = 64 64K 1437 / 1430, one
+    // head of 4096 16.6 / 16.5; B = 64 100K six / four / two 8015 / 7922 / 7855; two at B = 128 up to 3 % slower in small calls.
+    constexpr int kAhead = B == 64 && D != 256 ? 2 : 4, kSlots = kAhead + 2;
 
     // The softmax of a block is 8*KT accumulator pairs per lane.  Vector and matrix instructions
     // of the SAME wave overlap well, those of two waves sharing a SIMD do not, so the pairs are
@@ -808,10 +811,9 @@ __device__ __forceinline__ void sparse_attn_body(
         STEM_BARRIER();                                // K(i) is in LDS; V buffer is free
         const auto v_rq = v_request(i);
         clear_sum();
-        // (B = 128, d = 128 has no register left: operands of S^T four ahead, those of O^T after the check, or it spills)
+        // (B = 128, d = 128 has no register left: the operands of O^T are read after the check, or it spills)
         constexpr bool kTight = B == 128 && D == 128;
-        constexpr int kAheadD = kTight ? 4 : kAhead;
-        constexpr int kRing = KS < kAheadD ? KS : kAheadD;
+        static_assert(kAhead <= KS, "a tile fills the ring");
 #pragma unroll
         for (int t = 0; t < KT; ++t) {
             if (t > 0 && t > w) {                      // wave-uniform
@@ -823,7 +825,7 @@ __device__ __forceinline__ void sparse_attn_body(
             }
             uint4 ka[kSlots];
 #pragma unroll
-            for (int n = 0; n < kRing; ++n) {
+            for (int n = 0; n < kAhead; ++n) {
                 ka[n] = load_k(t * KS + n);
                 if (n & 1) STEM_SCHED_FENCE();
             }
@@ -831,8 +833,8 @@ __device__ __forceinline__ void sparse_attn_body(
 #pragma unroll
             for (int n = t * KS; n < t * KS + KS; ++n) {
                 const int x = n % KS;
-                if (x + kAheadD < KS) ka[(x + kAheadD) % kSlots] = load_k(n + kAheadD);
-                if ((x & 1) == 0) wait_lgkmcnt((x + kAheadD + 1 < KS ? kAheadD + 1 : KS - x) - 2);
+                if (x + kAhead < KS) ka[(x + kAhead) % kSlots] = load_k(n + kAhead);
+                if ((x & 1) == 0) wait_lgkmcnt((x + kAhead + 1 < KS ? kAhead + 1 : KS - x) - 2);
                 if (t == 0) v_rq.issue(n, v_slice0, slice_step, slice_lds_step);   // every wave has this tile
                 s_acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ka[x % kSlots]), q_reg[x],
                                                                   x == 0 ? zero16 : s_acc[t], 0, 0, 0);

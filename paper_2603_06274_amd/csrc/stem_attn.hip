@@ -259,7 +259,7 @@ struct SoftmaxSchedule {
         for (int c = 0; c < kChecks; ++c) {
             const int slot = check_slot(c);
             if (slot < NS || slot % DT) return false;
-            if (pairs_by(slot - 1) % 2) return false;        // the row sums are taken two pairs at a time
+            if (pairs_by(slot - 1) % 4) return false;        // the row sums are taken up to four pairs at a time
             if (lo > 4 * ((slot - NS) / DT)) return false;   // pairs below the window are consumed (4 per step)
             for (int q = lo; q < pairs_by(slot - 1); ++q)
                 if (use_slot(q) < slot) return false;        // pairs of the window are not consumed yet
@@ -973,7 +973,7 @@ static int64_t slots_per_xcd(const Problem& p) {
 // 15 % 1160 / 1148; 28 / 4, 64K dense 25.4 / 25.0 ms; d = 256, 32K 2432 / 2378; B = 64, 100K 8699 / 8448; but 16K 317 / 317, 24K
 // 694 / 692, 12 prompts to 2047 tokens 108 / 110, B = 64, 16K 376 / 380.  So: 1e12 operations and more (about
 // 0.9 ms), lists bounded by kmax, and eight rounds of what runs at a time, below which an eighth is less than a
-// round.  An eighth or a quarter of the rows are as good; a sixteenth is too few (dense: 25.3 ms).
+// round.
 bool attention_claims_rows(const Problem& p, int32_t kmax) {
     double blocks = 0.0;                               // of one head: rows first .. last - 1 list at most min(i + 1, kmax)
     for (int s = 0; s < p.batch; ++s) {
@@ -1001,7 +1001,10 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     int claim_from = 0x7fffffff;
     int64_t slots = per_xcd;
     if (queue != nullptr && attention_claims_rows(p, kmax)) {
-        const int64_t claimed = per_xcd / 8;
+        // (rows go out from the last to the first: where lists grow with the row the last ones handed out are short, and a
+        // quarter of the rows is about an eighth of the blocks.  64K dense by workgroup id / an eighth / a quarter
+        // 25411 / 25013 / 24858 us; 5 % density 1388 / 1376 / 1378, packed 4675 / 4613 / 4629)
+        const int64_t claimed = per_xcd / (kmax > p.NBmax / 2 ? 4 : 8);
         claim_from = (int)(per_xcd - claimed);
         slots = per_xcd + (claimed + 3) / 4;
     }

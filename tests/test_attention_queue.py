@@ -37,15 +37,16 @@ CASES = [
     dict(hq=32, hkv=16, d=256, B=128, lens=(18000,)),
     dict(hq=32, hkv=8, d=128, B=64, lens=(24000,), share="max"),
     dict(hq=32, hkv=8, d=128, B=128, lens=(65536,), chunk=24576),
+    dict(hq=28, hkv=4, d=128, B=128, lens=(24000, 12001), keep=1.0),   # lists that grow with the row: a quarter is claimed
 ]
 
 
-def make(hq, hkv, d, B, lens, share=None, chunk=0, seed=3):
+def make(hq, hkv, d, B, lens, share=None, chunk=0, keep=0.3, seed=3):
     dev = torch.device("cuda:0")
     g = torch.Generator(device=dev).manual_seed(seed)
     cu = [0] + np.cumsum(lens).tolist()
     q, k, v = (torch.randn(cu[-1], h, d, generator=g, device=dev).to(torch.bfloat16) for h in (hq, hkv, hkv))
-    pf = StemPrefill(q[chunk:].contiguous(), k, v, cu, B, [0.3 * -(-n // B) for n in lens], n_sink=2, n_local=2, want_lse=True,
+    pf = StemPrefill(q[chunk:].contiguous(), k, v, cu, B, [keep * -(-n // B) for n in lens], n_sink=2, n_local=2, want_lse=True,
                      group_share=share, chunk=([chunk], [lens[0]]) if chunk else None)
     if chunk:                                          # the earlier keys are not pooled: lists that the budget alone makes
         pf.workspace.zero_()

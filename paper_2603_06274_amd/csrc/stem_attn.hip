@@ -296,7 +296,7 @@ enum RowOrder : int { kOneSequence, kAsPacked, kWalk };
 
 // Workgroup id -> XCD is id % 8 and cannot be changed once launched, and the XCDs of a chip are not equally fast
 // under this kernel: given an eighth of the rows each, the last one ends 3 to 4.5 % after the mean (128K: 9.09 to 9.69 ms).
-// So in long launches the last eighth of every XCD's rows is not handed out by workgroup id: the
+// So in long launches the last eighth or quarter of every XCD's rows is not handed out by workgroup id: the
 // workgroups from slot `claim_from` on claim theirs when they start, from their own XCD's queue as long as it has
 // rows, then from the one with most left.  There are a quarter more such workgroups than rows, so that a fast XCD can
 // take more than its share; who finds nothing returns.  A claim is one atomic addition (taken[x * kQueueStride]: rows of

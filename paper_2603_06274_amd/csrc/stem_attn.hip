@@ -259,7 +259,7 @@ struct SoftmaxSchedule {
         for (int c = 0; c < kChecks; ++c) {
             const int slot = check_slot(c);
             if (slot < NS || slot % DT) return false;
-            if (pairs_by(slot - 1) % 4) return false;        // the row sums are taken up to four pairs at a time
+            if (pairs_by(slot - 1) % 8) return false;        // the row sums are taken up to four pairs at a time, once more by tiles
             if (lo > 4 * ((slot - NS) / DT)) return false;   // pairs below the window are consumed (4 per step)
             for (int q = lo; q < pairs_by(slot - 1); ++q)
                 if (use_slot(q) < slot) return false;        // pairs of the window are not consumed yet
@@ -557,7 +557,7 @@ __device__ __forceinline__ void sparse_attn_body(
     auto pairs_by = [](int slot) { return Sched::kTable.v[slot + 1]; };
     constexpr int kCheckSlot[2] = {Sched::check_slot(0), Sched::check_slot(1)};
 
-    // 0/1 operand of the row-sum product (softmax_pair): row m takes the lane groups g of 16 with g % 2 = (m / 4) % 2
+    // 0/1 operand of the row-sum product (softmax_pair; keep_sums_apart for what is not finite): row m takes the lane groups g of 16 with g % 2 = (m / 4) % 2
     constexpr bool kStepSums = B == 128 && D != 256;
     const uint32_t own_pair = ((lane >> 2) ^ (lane >> 4)) & 1 ? 0u : 0x3f803f80u;
     const uint4 own_query = make_uint4(own_pair, own_pair, own_pair, own_pair);
@@ -619,6 +619,37 @@ __device__ __forceinline__ void sparse_attn_body(
         return l_win[0];
     };
     auto clear_sum = [&]() { l_win = f32x4_t{0.f, 0.f, 0.f, 0.f}; };
+    // The row sums of a window whose probabilities were formed with a reference that suits them, where a sum is
+    // not finite all the same (a score was NaN or inf): the 0/1 operand leaves the other query of a column out of the
+    // product only as long as that one's probabilities are finite (0 x inf and 0 x NaN are NaN), so here the two go into
+    // a product each, with zeros for the other's, which is what the common product makes of finite ones: the same bits
+    // for a finite query.  there(t): whether the wave has tile t (diagonal block).
+    auto sums_finite = [&]() { return __builtin_amdgcn_ballot_w64(!(window_sum() < -neg_inf)) == 0; };
+    auto keep_sums_apart = [&](int q_lo, int q_hi, auto there) {
+        if constexpr (kStepSums) {
+            if (sums_finite()) return;
+            float own = 0.f;
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const bool mine = ((lane >> 4) & 1) == half;
+                clear_sum();
+#pragma unroll
+                for (int t = q_lo / 8; t < q_hi / 8; ++t) {
+                    if (!there(t)) continue;
+#pragma unroll
+                    for (int u = 0; u < 8; u += 4) {
+                        const uint4 step = make_uint4(mine ? p_pk[t][u] : 0u, mine ? p_pk[t][u + 1] : 0u,
+                                                      mine ? p_pk[t][u + 2] : 0u, mine ? p_pk[t][u + 3] : 0u);
+                        l_win = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(own_query), as_bf16x8(step), l_win,
+                                                                       0, 0, 0);
+                    }
+                }
+                if (mine) own = l_win[0];
+            }
+            l_win[0] = own;
+        }
+    };
+    auto whole_block = [](int) { return true; };
     // exp2-domain offset of the reference; a query that has seen nothing yet (m_ref = -inf) uses 0,
     // which keeps its masked scores at exp2(-inf) = 0
     auto reference_offset = [&]() { return m_ref == neg_inf ? 0.f : m_ref * sl2; };
@@ -657,6 +688,7 @@ __device__ __forceinline__ void sparse_attn_body(
         raise_reference(window_max(q_lo, q_hi));
 #pragma unroll
         for (int q = q_lo; q < q_hi; ++q) softmax_pair(q);
+        keep_sums_apart(q_lo, q_hi, whole_block);
     };
     // The first window of a row, pairs [0, q_hi): O and l are still zero, so there is nothing to
     // rescale; a query that sees none of the window's keys keeps m_ref = -inf (offset 0, zero
@@ -667,6 +699,7 @@ __device__ __forceinline__ void sparse_attn_body(
         clear_sum();
 #pragma unroll
         for (int q = 0; q < q_hi; ++q) softmax_pair(q);
+        keep_sums_apart(0, q_hi, whole_block);
         l_run += window_sum();
         clear_sum();
     };
@@ -875,6 +908,7 @@ __device__ __forceinline__ void sparse_attn_body(
 #pragma unroll
                 for (int q = 8 * t; q < 8 * t + 8; ++q) softmax_pair(q);
             }
+            keep_sums_apart(0, 8 * KT, [&](int t) { return t == 0 || t <= w; });
         }
         l_run += window_sum();
         STEM_SCHED_FENCE();

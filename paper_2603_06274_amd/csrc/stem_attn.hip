@@ -424,7 +424,6 @@ __device__ __forceinline__ void sparse_attn_body(
     const int col = lane & 31, hi = lane >> 5;
     const int qrow = w * 32 + col;                     // query row inside the block
     const int tok_q = tok_q0 + qrow;
-    const bool q_valid = tok_q < q_hi;
 
     const int lh = shared_lists ? g : h;               // whose list: the KV head's or the query head's
     const int64_t list_row = (int64_t)lh * R + r;
@@ -666,9 +665,16 @@ __device__ __forceinline__ void sparse_attn_body(
         return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
     };
     auto window_max = [&](int q_lo, int q_hi) { return both_lanes_max(lane_max(q_lo, q_hi)); };
-    // Moves the reference up to mx (rescaling O and l) if that is higher, and starts the window's sum anew.
-    auto raise_reference = [&](float mx) {
-        if (mx > m_ref) {
+    // Moves the references of the wave's queries up to mx (rescaling O and l) where that is higher, and starts the
+    // window's sum anew.  Where sums are not finite only if a query gains by it: one that has no reference, or
+    // probabilities far beyond its own (a sum over 2^16 of 128 keys at most holds one over 2^9), and a finite score to go
+    // to.  A query that is NaN or inf for good comes here with every window and leaves the others as they are.
+    auto raise_reference = [&](float mx, bool finite) {
+        if (!finite) {
+            const bool gains = mx < -neg_inf && mx > m_ref && (m_ref == neg_inf || mx * sl2 - off > 8.9f);
+            finite = __builtin_amdgcn_ballot_w64(gains) != 0;
+        }
+        if (finite && mx > m_ref) {
             const float corr = (m_ref == neg_inf) ? 0.f : __builtin_amdgcn_exp2f((m_ref - mx) * sl2);
             m_ref = mx;
             l_run *= corr;
@@ -680,15 +686,17 @@ __device__ __forceinline__ void sparse_attn_body(
             if constexpr (kManualHazards) wait_states_acc<4>(o_acc);    // before the next one reads them
         }
         off = reference_offset();
+        asm volatile("" : "+v"(off));                  // not folded into the exponentials: the bits of the common path
         clear_sum();
     };
     // Slow path for the window of pairs [q_lo, q_hi): take their true maximum, move the reference
     // up to it, and recompute the window's probabilities.
     auto fix_window = [&](int q_lo, int q_hi) {
-        raise_reference(window_max(q_lo, q_hi));
+        const bool finite = sums_finite();
+        raise_reference(window_max(q_lo, q_hi), finite);
 #pragma unroll
         for (int q = q_lo; q < q_hi; ++q) softmax_pair(q);
-        keep_sums_apart(q_lo, q_hi, whole_block);
+        if (!finite) keep_sums_apart(q_lo, q_hi, whole_block);
     };
     // The first window of a row, pairs [0, q_hi): O and l are still zero, so there is nothing to
     // rescale; a query that sees none of the window's keys keeps m_ref = -inf (offset 0, zero
@@ -901,14 +909,15 @@ __device__ __forceinline__ void sparse_attn_body(
 #pragma unroll
             for (int t = 1; t < KT; ++t)
                 if (t <= w) mx = fmaxf(mx, lane_max(8 * t, 8 * t + 8));
-            raise_reference(both_lanes_max(mx));
+            const bool finite = sums_finite();
+            raise_reference(both_lanes_max(mx), finite);
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
                 if (t > 0 && t > w) continue;
 #pragma unroll
                 for (int q = 8 * t; q < 8 * t + 8; ++q) softmax_pair(q);
             }
-            keep_sums_apart(0, 8 * KT, [&](int t) { return t == 0 || t <= w; });
+            if (!finite) keep_sums_apart(0, 8 * KT, [&](int t) { return t == 0 || t <= w; });
         }
         l_run += window_sum();
         STEM_SCHED_FENCE();
@@ -969,14 +978,18 @@ __device__ __forceinline__ void sparse_attn_body(
             const auto s1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
             packed[dt][m] = make_uint4(s0[0], s1[0], s0[1], s1[1]);
         }
-    if (q_valid) {
-        uint16_t* dst = out + (int64_t)tok_q * q_st + (int64_t)h * q_sh + hi * 8;
+    // (the lane's query from the lane's number once more: no register holds it through the blocks, of which B = 128, d = 128
+    // has none left)
+    const int lane_end = kManualHazards ? lane : __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    const int tok_end = tok_q0 + w * 32 + (lane_end & 31), hi_end = lane_end >> 5;
+    if (tok_end < q_hi) {
+        uint16_t* dst = out + (int64_t)tok_end * q_st + (int64_t)h * q_sh + hi_end * 8;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
             for (int m = 0; m < 2; ++m) *reinterpret_cast<uint4*>(dst + dt * 32 + m * 16) = packed[dt][m];
-        if (lse != nullptr && hi == 0)
-            lse[(int64_t)h * T + tok_q] = l_tot > 0.f ? m_ref * scale + __logf(l_tot) : neg_inf;
+        if (lse != nullptr && hi_end == 0)
+            lse[(int64_t)h * T + tok_end] = l_tot > 0.f ? m_ref * scale + __logf(l_tot) : neg_inf;
     }
 }
 

@@ -847,7 +847,7 @@ __device__ __forceinline__ void sparse_attn_body(
     // One window for all its pairs, formed before O^T starts (a tile's under the next tile's products, the last
     // tile's by themselves); the operand ring starts anew with every tile, so that nothing is carried past a tile
     // that may not be there.
-    auto diagonal_block = [&]() {
+    auto diagonal_block = [&](bool alone) {
         STEM_WAIT_VMCNT(0);
         STEM_BARRIER();                                // K(i) is in LDS; V buffer is free
         const auto v_rq = v_request(i);
@@ -907,10 +907,17 @@ __device__ __forceinline__ void sparse_attn_body(
         if (needs_fix(window_sum())) {                 // fix_window of the tiles that the wave has, as one window
             float mx = lane_max(0, 8);
 #pragma unroll
-            for (int t = 1; t < KT; ++t)
+            for (int t = 1; t < KT - 1; ++t)
                 if (t <= w) mx = fmaxf(mx, lane_max(8 * t, 8 * t + 8));
+            mx = both_lanes_max(mx);
+            // (a row of this block alone takes its reference, like any row from its first window, from the tiles before
+            // the last, unless the last one's probabilities overflow it)
+            if (w == KT - 1) {
+                const float all = fmaxf(mx, window_max(8 * KT - 8, 8 * KT));
+                if (!alone || (all - mx) * sl2 > 16.f) mx = all;
+            }
             const bool finite = sums_finite();
-            raise_reference(both_lanes_max(mx), finite);
+            raise_reference(mx, finite);
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
                 if (t > 0 && t > w) continue;
@@ -950,7 +957,7 @@ __device__ __forceinline__ void sparse_attn_body(
     }
     for (; it < cnt && (kManualHazards || it + 1 < cnt || j_cur != i); ++it) one_block(it, std::false_type{});
     if constexpr (!kManualHazards)
-        if (it < cnt) diagonal_block();
+        if (it < cnt) diagonal_block(it == 0);
     STEM_WAIT_VMCNT(0);                                // no request may outlive the workgroup's LDS
     if constexpr (kManualHazards) wait_states_acc<16>(o_acc);   // the last O^T instructions have written
 

@@ -96,9 +96,15 @@ def _check(status: int, where: str) -> None:
         raise StemError(status, where)
 
 
+# A private name of torch, which may not be there: then the handle comes from a Stream object.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    """The handle of torch.cuda.current_stream(), without making a Stream object (0.4 us instead of 2.8 per call)."""
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    """The handle of torch.cuda.current_stream(), without making a Stream object if torch can (0.4 us instead of 2.8 per call)."""
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:

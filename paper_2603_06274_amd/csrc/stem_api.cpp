@@ -103,6 +103,49 @@ WorkspaceLayout workspace_layout(const Problem& p, int ad_stride) {
     return w;
 }
 
+// Claiming (claim_row) costs 1 us for clearing the counters and 1 to 2 us for each row claimed, and gains what the
+// XCDs differ by at the end.  Attention alone, by workgroup id / claimed: gqa 32 / 8, 128K at 8 % 9671 / 9447 us, 32K at
+// 15 % 1160 / 1148; 28 / 4, 64K dense 25.4 / 25.0 ms; d = 256, 32K 2432 / 2378; B = 64, 100K 8699 / 8448; but 16K 317 / 317, 24K
+// 694 / 692, 12 prompts to 2047 tokens 108 / 110, B = 64, 16K 376 / 380.  So: 1e12 operations and more (about
+// 0.9 ms), lists bounded by kmax, and eight rounds of what runs at a time, below which an eighth is less than a
+// round.
+bool attention_claims_rows(const Problem& p, int32_t kmax, int (*units)()) {
+    double blocks = 0.0;                               // of one head: rows first .. last - 1 list at most min(i + 1, kmax)
+    for (int s = 0; s < p.batch; ++s) {
+        const double first = p.seq.first_block[s], last = first + p.seq.row_start[s + 1] - p.seq.row_start[s];
+        auto up_to = [&](double n) {
+            const double k = kmax < n ? kmax : n;
+            return k * (k + 1.0) / 2.0 + (n - k) * k;
+        };
+        blocks += up_to(last) - up_to(first);
+    }
+    if (blocks * p.Hq * 4.0 * p.d * p.B * p.B < 1e12) return false;
+    const int64_t at_a_time = (int64_t)units() * (p.d == 256 ? 128 / p.B : 256 / p.B);
+    return at_a_time > 0 && (int64_t)p.Hq * p.R >= 8 * at_a_time;
+}
+
+AttentionGrid attention_grid(const Problem& p, int32_t kmax, bool queue, int (*units)()) {
+    AttentionGrid ag;
+    const int m = p.Hkv <= 8 && 8 % p.Hkv == 0 ? 8 / p.Hkv : 0;
+    const int64_t per_xcd = m > 0 ? (int64_t)((p.R + m - 1) / m) * p.G : ((int64_t)p.Hq * p.R + 7) / 8;
+    ag.xcds_per_kv_head = m;
+    ag.items_per_xcd = (int32_t)per_xcd;
+    ag.claim_from = 0x7fffffff;
+    ag.slots = per_xcd;
+    if (queue && attention_claims_rows(p, kmax, units)) {
+        // (rows go out from the last to the first: where lists grow with the row the last ones handed out are short, and a
+        // quarter of the rows is about an eighth of the blocks.  64K dense by workgroup id / an eighth / a quarter
+        // 25411 / 25013 / 24858 us; 5 % density 1388 / 1376 / 1378, packed 4675 / 4613 / 4629)
+        const int64_t claimed = per_xcd / (kmax > p.NBmax / 2 ? 4 : 8);
+        const int64_t slots = per_xcd + (claimed + 3) / 4;
+        if (slots * 8 <= kMaxWorkgroups) {             // (not for the claiming's sake may a call be refused)
+            ag.claim_from = (int32_t)(per_xcd - claimed);
+            ag.slots = slots;
+        }
+    }
+    return ag;
+}
+
 }  // namespace stem
 
 using namespace stem;

@@ -369,10 +369,7 @@ __device__ __forceinline__ void sparse_attn_body(
         int* const claimed = reinterpret_cast<int*>(k_lds);   // not in use yet
         if (threadIdx.x < 64) {
             const bool found = claim_row(taken, claim_from, [&](int x) {
-                const int all = xcds_per_kv_head > 0
-                                    ? (R - x % xcds_per_kv_head + xcds_per_kv_head - 1) / xcds_per_kv_head * G
-                                    : (int)min((int64_t)items_per_xcd, (int64_t)Hq * R - (int64_t)x * items_per_xcd);
-                return all - claim_from;
+                return rows_of_xcd(x, Hq, R, G, items_per_xcd, xcds_per_kv_head) - claim_from;
             }, xcd, slot);
             if (threadIdx.x == 0) {
                 claimed[0] = found ? xcd : -1;
@@ -1013,36 +1010,6 @@ __global__ __launch_bounds__(B * 2, D == 256 ? 1 : 2) void sparse_attn_kernel(
                            q_st, q_sh, kv_st, kv_sh, scale, items_per_xcd, xcds_per_kv_head, taken, k_lds, v_lds);
 }
 
-// XCDs that share one KV head's rows (the kernel says how); 0: contiguous ranges of all rows instead
-static int xcds_of_kv_head(const Problem& p) { return p.Hkv <= 8 && 8 % p.Hkv == 0 ? 8 / p.Hkv : 0; }
-
-// workgroups of one XCD if every row is handed out by workgroup id
-static int64_t slots_per_xcd(const Problem& p) {
-    const int m = xcds_of_kv_head(p);
-    return m > 0 ? (int64_t)((p.R + m - 1) / m) * p.G : ((int64_t)p.Hq * p.R + 7) / 8;
-}
-
-// Claiming (claim_row) costs 1 us for clearing the counters and 1 to 2 us for each row claimed, and gains what the
-// XCDs differ by at the end.  Attention alone, by workgroup id / claimed: gqa 32 / 8, 128K at 8 % 9671 / 9447 us, 32K at
-// 15 % 1160 / 1148; 28 / 4, 64K dense 25.4 / 25.0 ms; d = 256, 32K 2432 / 2378; B = 64, 100K 8699 / 8448; but 16K 317 / 317, 24K
-// 694 / 692, 12 prompts to 2047 tokens 108 / 110, B = 64, 16K 376 / 380.  So: 1e12 operations and more (about
-// 0.9 ms), lists bounded by kmax, and eight rounds of what runs at a time, below which an eighth is less than a
-// round.
-bool attention_claims_rows(const Problem& p, int32_t kmax) {
-    double blocks = 0.0;                               // of one head: rows first .. last - 1 list at most min(i + 1, kmax)
-    for (int s = 0; s < p.batch; ++s) {
-        const double first = p.seq.first_block[s], last = first + p.seq.row_start[s + 1] - p.seq.row_start[s];
-        auto up_to = [&](double n) {
-            const double k = kmax < n ? kmax : n;
-            return k * (k + 1.0) / 2.0 + (n - k) * k;
-        };
-        blocks += up_to(last) - up_to(first);
-    }
-    if (blocks * p.Hq * 4.0 * p.d * p.B * p.B < 1e12) return false;
-    const int64_t at_a_time = (int64_t)compute_units() * (p.d == 256 ? 128 / p.B : 256 / p.B);
-    return at_a_time > 0 && (int64_t)p.Hq * p.R >= 8 * at_a_time;
-}
-
 int launch_sparse_attn(const Problem& p, const void* q, const void* k, const void* v,
                        const int32_t* counts, const int32_t* indices, int32_t kmax,
                        bool lists_per_kv_head, float softmax_scale, void* out, float* lse,
@@ -1050,20 +1017,9 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     // (the host entry point has checked that one sequence of one KV head spans less than 2 GiB: the
     // block requests use a 32-bit byte offset, with offsets from 2^31 on reserved for "fetch nothing")
     const int64_t items = (int64_t)p.Hq * p.R;
-    const int xcds_per_kv_head = xcds_of_kv_head(p);
-    const int64_t per_xcd = slots_per_xcd(p);
-    int claim_from = 0x7fffffff;
-    int64_t slots = per_xcd;
-    if (queue != nullptr && attention_claims_rows(p, kmax)) {
-        // (rows go out from the last to the first: where lists grow with the row the last ones handed out are short, and a
-        // quarter of the rows is about an eighth of the blocks.  64K dense by workgroup id / an eighth / a quarter
-        // 25411 / 25013 / 24858 us; 5 % density 1388 / 1376 / 1378, packed 4675 / 4613 / 4629)
-        const int64_t claimed = per_xcd / (kmax > p.NBmax / 2 ? 4 : 8);
-        claim_from = (int)(per_xcd - claimed);
-        slots = per_xcd + (claimed + 3) / 4;
-    }
-    if (slots * 8 > 0x7fffffff) return STEM_ERR_UNSUPPORTED;
-    dim3 grid((unsigned)(slots * 8)), block(p.B * 2);
+    const AttentionGrid ag = attention_grid(p, kmax, queue != nullptr);
+    if (ag.slots * 8 > kMaxWorkgroups) return STEM_ERR_UNSUPPORTED;
+    dim3 grid((unsigned)(ag.slots * 8)), block(p.B * 2);
     // The walk's order is for batches of ten sequences and more, at d = 64 and 128, where rows wait for a place (1.5
     // to 8 times what runs at a time: two workgroups per CU at B = 128, four at B = 64), lists grow with the row
     // (kmax is more than half of the longest sequence's blocks, and these are three or more) and the sequences
@@ -1103,11 +1059,11 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     const uint16_t* kk = static_cast<const uint16_t*>(k);
     const uint16_t* vv = static_cast<const uint16_t*>(v);
     uint16_t* oo = static_cast<uint16_t*>(out);
-    if (slots > per_xcd) hipLaunchKernelGGL(clear_row_queues_kernel, dim3(1), dim3(8), 0, stream, queue);
+    if (ag.slots > ag.items_per_xcd) hipLaunchKernelGGL(clear_row_queues_kernel, dim3(1), dim3(8), 0, stream, queue);
 #define STEM_ATTN_LAUNCH(BB, DD)                                                                          \
     hipLaunchKernelGGL((sparse_attn_kernel<BB, DD>), grid, block, 0, stream, qq, kk, vv, counts, indices, \
-                       oo, lse, p.seq, walk, p.Hq, p.R, p.G, order, claim_from, p.T, kmax, lists_per_kv_head, p.q_st, p.q_sh, \
-                       p.kv_st, p.kv_sh, softmax_scale, (int)per_xcd, xcds_per_kv_head, queue)
+                       oo, lse, p.seq, walk, p.Hq, p.R, p.G, order, ag.claim_from, p.T, kmax, lists_per_kv_head, p.q_st, p.q_sh, \
+                       p.kv_st, p.kv_sh, softmax_scale, ag.items_per_xcd, ag.xcds_per_kv_head, queue)
     if (p.B == 128 && p.d == 128) STEM_ATTN_LAUNCH(128, 128);
     else if (p.B == 64 && p.d == 128) STEM_ATTN_LAUNCH(64, 128);
     else if (p.B == 128 && p.d == 64) STEM_ATTN_LAUNCH(128, 64);

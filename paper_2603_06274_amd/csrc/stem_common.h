@@ -64,9 +64,6 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
                        const int32_t* counts, const int32_t* indices, int32_t kmax,
                        bool lists_per_kv_head, float softmax_scale, void* out, float* lse,
                        int32_t* queue, hipStream_t stream);
-// whether launch_sparse_attn makes use of a queue (STEM_ATTN_QUEUE_BYTES of scratch), if it gets one
-bool attention_claims_rows(const Problem& p, int32_t kmax);
-
 // Compute units of the current device, 0 on failure.  A constant of the device, kept after the first call
 // (several threads may store the same value): the query costs a call that has 30 us in all about 1 %.
 inline int compute_units() {
@@ -78,6 +75,25 @@ inline int compute_units() {
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0) return 0;
     if (device < kDevices) known[device].store(cus, std::memory_order_relaxed);
     return cus;
+}
+
+// How launch_sparse_attn hands its rows (head, query block) out to the workgroups: XCD x has slots 0 .. slots - 1, of which
+// those before claim_from are rows by their number and the others claim one.
+struct AttentionGrid {
+    int32_t xcds_per_kv_head;   // XCDs that share one KV head's rows; 0: contiguous ranges of all rows instead
+    int32_t items_per_xcd;      // most rows of one XCD
+    int32_t claim_from;         // 0x7fffffff: no row is claimed
+    int64_t slots;              // per XCD
+};
+constexpr int64_t kMaxWorkgroups = 0x7fffffff;         // of a launch
+// units: where the number of compute units comes from (asked for long calls only)
+bool attention_claims_rows(const Problem& p, int32_t kmax, int (*units)() = compute_units);
+AttentionGrid attention_grid(const Problem& p, int32_t kmax, bool queue, int (*units)() = compute_units);
+// rows of XCD x (0 and less: none)
+__host__ __device__ inline int rows_of_xcd(int x, int Hq, int R, int G, int items_per_xcd, int xcds_per_kv_head) {
+    if (xcds_per_kv_head > 0) return (R - x % xcds_per_kv_head + xcds_per_kv_head - 1) / xcds_per_kv_head * G;
+    const int64_t left = (int64_t)Hq * R - (int64_t)x * items_per_xcd;
+    return left < items_per_xcd ? (int)left : items_per_xcd;
 }
 
 inline int check_launch() {

@@ -1,7 +1,7 @@
 """The library's host code (argument checks, shape bookkeeping, the Eq. 3 schedule: everything in
 csrc/stem_api.cpp) built for the CPU only with AddressSanitizer and UndefinedBehaviorSanitizer, the
-kernel launchers replaced by no-op stand-ins (tests/host_launch_stubs.cpp), and the host ABI tests run
-against that build in a child process.  Any out-of-bounds access, overflow or misaligned access in
+kernel launchers replaced by no-op stand-ins (tests/host_launch_stubs.cpp), and the host ABI tests and those of stage 3's
+grid run against that build in a child process.  Any out-of-bounds access, overflow or misaligned access in
 the host code aborts the child."""
 import os
 import shutil
@@ -36,7 +36,8 @@ def test_host_abi_under_address_and_ub_sanitizers(tmp_path):
     env = dict(os.environ, LD_PRELOAD=":".join(preload), STEM_HIP_LIBRARY=lib,
                ASAN_OPTIONS="detect_leaks=0:abort_on_error=1", UBSAN_OPTIONS="halt_on_error=1:print_stacktrace=1",
                PYTHONDONTWRITEBYTECODE="1")
-    run = subprocess.run([sys.executable, "-m", "pytest", os.path.join(ROOT, "tests", "test_host_abi.py"), "-x", "-q",
+    run = subprocess.run([sys.executable, "-m", "pytest", os.path.join(ROOT, "tests", "test_host_abi.py"),
+                          os.path.join(ROOT, "tests", "test_attention_grid.py"), "-x", "-q",
                           "-p", "no:cacheprovider"], cwd=ROOT, env=env, capture_output=True, text=True)
     assert run.returncode == 0, (run.stdout[-3000:], run.stderr[-3000:])
     assert "passed" in run.stdout and "Sanitizer" not in run.stderr and "runtime error" not in run.stderr

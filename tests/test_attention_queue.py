@@ -55,6 +55,28 @@ def make(hq, hkv, d, B, lens, share=None, chunk=0, keep=0.3, seed=3):
     return pf
 
 
+def check_queue(pf, queue):
+    """What a call left in its scratch, a count of claims for each XCD every 128 bytes: each of them went through all the rows
+    that its XCD had to claim, and every workgroup that claims has claimed at least once and no queue more than once
+    beyond its end."""
+    R, Hq, Hkv = pf.rows, pf.q.shape[1], pf.k.shape[1]
+    share = 4 if pf.kmax > pf.nbmax // 2 else 8
+    if 8 % Hkv == 0:                                   # m XCDs take turns at a KV head's rows
+        m = 8 // Hkv
+        rows = [len(range(x % m, R, m)) * (Hq // Hkv) for x in range(8)]
+    else:                                              # contiguous ranges of all rows
+        items = -(-Hq * R // 8)
+        rows = [min(items, Hq * R - x * items) for x in range(8)]
+    claimed = max(rows) // share
+    to_claim = [max(0, r - (max(rows) - claimed)) for r in rows]
+    claimers = 8 * (claimed + -(-claimed // 4))
+    taken = queue.view(torch.int32)[::32].tolist()
+    assert sum(to_claim) > 0 and len(taken) == 8
+    assert all(n >= rows for n, rows in zip(taken, to_claim)), (taken, to_claim)
+    assert all(n <= rows + claimers for n, rows in zip(taken, to_claim)), (taken, to_claim)
+    assert claimers <= sum(taken) <= sum(to_claim) + 8 * claimers
+
+
 def plain(pf):
     pf.out.fill_(float("nan"))
     sb.stem_sparse_attn(pf.shape, pf.q, pf.k, pf.v, pf.counts, pf.indices, pf.kmax, pf.softmax_scale, pf.out, pf.lse,
@@ -79,6 +101,7 @@ def test_claimed_rows_give_the_same_bits(case):
                                    pf.lse, queue, lists_per_kv_head=bool(pf.group_share))
         torch.cuda.synchronize()
         assert torch.equal(pf.out.view(torch.int16), out.view(torch.int16)) and torch.equal(pf.lse, lse)
+        check_queue(pf, queue)
 
 
 @pytest.mark.gpu

@@ -20,6 +20,7 @@ def say(*a):
 PLACES = {
     "last": lambda before, i: before + [i],
     "first": lambda before, i: [i] + before,
+    "twice": lambda before, i: before[:1] + [i] + before[1:] + [i],
     "middle": lambda before, i: before[:1] + [i] + before[1:],
     "alone": lambda before, i: [i],
     "absent": lambda before, i: before,

@@ -764,7 +764,8 @@ __device__ __forceinline__ void sparse_attn_body(
             if (n & 1) STEM_SCHED_FENCE();             // in the order of their use
         }
         const auto v_rq = v_request(j);
-        const int j_nxt = __builtin_amdgcn_readlane(list_reg, (it + 1) & 63);   // 0 past the end
+        // (past the count any value: what lies in the list's row there.  Only to be used clamped, and with has_next)
+        const int j_nxt = __builtin_amdgcn_readlane(list_reg, (it + 1) & 63);
         clear_sum();
         STEM_SCHED_FENCE();
 #pragma unroll

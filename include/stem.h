@@ -41,6 +41,8 @@
  *     spreads as IEEE arithmetic spreads it (a non-finite key or value makes the output rows that
  *     attend to it non-finite, a non-finite pooled score is ranked by its bit pattern), and
  *     affects nothing else; no entry point reads or writes out of bounds or hangs because of it.
+ *     In its own block a value can also reach the output rows of earlier queries: their weight
+ *     for it is 0, and 0 times inf or NaN is NaN.  (Keys cannot; lse never depends on values.)
  *   - Supported: head_dim 64, 128 or 256; block_size 64 or 128; 1 <= batch <= STEM_MAX_BATCH; Hq a
  *     multiple of Hkv; at most STEM_MAX_BLOCKS blocks per sequence.
  */

@@ -103,12 +103,14 @@ WorkspaceLayout workspace_layout(const Problem& p, int ad_stride) {
     return w;
 }
 
-// Claiming (claim_row) costs 1 us for clearing the counters and 1 to 2 us for each row claimed, and gains what the
-// XCDs differ by at the end.  Attention alone, by workgroup id / claimed: gqa 32 / 8, 128K at 8 % 9671 / 9447 us, 32K at
-// 15 % 1160 / 1148; 28 / 4, 64K dense 25.4 / 25.0 ms; d = 256, 32K 2432 / 2378; B = 64, 100K 8699 / 8448; but 16K 317 / 317, 24K
-// 694 / 692, 12 prompts to 2047 tokens 108 / 110, B = 64, 16K 376 / 380.  So: 1e12 operations and more (about
-// 0.9 ms), lists bounded by kmax, and eight rounds of what runs at a time, below which an eighth is less than a
-// round.
+// Claiming (claim_row) costs the launch that clears the counters, 2 to 5 us in kernel traces, and 1 to 2 us for each row
+// claimed, and gains what the XCDs differ by at the end.  So: 1e12 operations and more (about 0.9 ms), lists bounded by kmax,
+// and eight rounds of what runs at a time, below which an eighth is less than a round.  Attention alone with claims
+// over without, one box, medians of five (runs of one side differ by 0.3 to 3 %): 32 / 8 heads, 128K at 8 % of the
+// blocks 0.973, 32K at 8 % 0.994 and 15 % 0.986, 24K at 15 % 0.993, 16K at 40 % 0.990; 28 / 4, 64K at 3 % 0.990, dense 0.977;
+// d = 64, 64K at 5 % 0.990; d = 256, 32K at 6 % 0.992; B = 64, 32K at 10 % 0.998; 64 prompts of 1500 dense, an eighth /
+// a quarter 0.994 / 1.003.  Fewer operations: 32K at 5 % 0.991, 16K at 20 % 0.997, B = 64, 32K at 5 % 1.004.  Four rounds (8K
+// tokens after 120K): at 5 % 1.003, 20 % 0.995, dense 1.001.
 bool attention_claims_rows(const Problem& p, int32_t kmax, int (*units)()) {
     double blocks = 0.0;                               // of one head: rows first .. last - 1 list at most min(i + 1, kmax)
     for (int s = 0; s < p.batch; ++s) {
@@ -133,9 +135,14 @@ AttentionGrid attention_grid(const Problem& p, int32_t kmax, bool queue, int (*u
     ag.claim_from = 0x7fffffff;
     ag.slots = per_xcd;
     if (queue && attention_claims_rows(p, kmax, units)) {
-        // (rows go out from the last to the first: where lists grow with the row the last ones handed out are short, and a
-        // quarter of the rows is about an eighth of the blocks.  64K dense by workgroup id / an eighth / a quarter
-        // 25411 / 25013 / 24858 us; 5 % density 1388 / 1376 / 1378, packed 4675 / 4613 / 4629)
+        // Rows go out from the last to the first: where lists grow with the row the last ones handed out are short, and a
+        // quarter of the rows is about an eighth of the blocks.  An eighth / a quarter over none, by kmax as a share of
+        // NBmax: 28 / 4 heads, 64K, 3 % 0.990 / 0.993, 6 % 0.987 / 0.988, 12 % 0.983 / 0.978, 25 % 0.986 / 0.979, 48 % 0.991 /
+        // 0.978, 52 % 0.990 / 0.978, dense 0.991 / 0.977; 8K + 16K + 32K + 72K packed 6 % 0.990 / 0.991, 30 % 0.984 / 0.976, 48 %
+        // 0.986 / 0.979, 60 % 0.988 / 0.979, dense 0.988 / 0.980; four of 16K 9 % 0.989 / 0.992, 48 % 0.980 / 0.978, 59 % 0.978 /
+        // 0.973; 48K and twelve of 2K 10 % 0.983 / 0.985, dense 0.981 / 0.969; 32 of 4K dense 0.988 / 0.989; B = 64, 32K 10 % 0.998 /
+        // 1.003, dense 0.990 / 0.979; 32K tokens after 96K dense 0.971 / 0.974.  The two cross at about an eighth of NBmax;
+        // between there and a half the rule leaves up to 1 % (both sides of a half measure the same).
         const int64_t claimed = per_xcd / (kmax > p.NBmax / 2 ? 4 : 8);
         const int64_t slots = per_xcd + (claimed + 3) / 4;
         if (slots * 8 <= kMaxWorkgroups) {             // (not for the claiming's sake may a call be refused)

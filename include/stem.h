@@ -264,7 +264,7 @@ int stem_sparse_attn(const stem_shape* shape, const void* q, const void* k, cons
 
 /*
  * stem_sparse_attn with scratch for handing out the last rows of a long call as the chip's dies get to them,
- * instead of an equal share to each (they are not equally fast: 1 to 3 % of calls of a millisecond and more).
+ * instead of an equal share to each (they are not equally fast: up to 3 % of calls of a millisecond and more).
  * The same bits as without.
  *   - stem_attn_queue_bytes: STEM_ATTN_QUEUE_BYTES if a call of this shape and kmax makes use of it on the
  *     current device, else 0.

@@ -106,7 +106,7 @@ WorkspaceLayout workspace_layout(const Problem& p, int ad_stride) {
 // Claiming (claim_row) costs the launch that clears the counters, 2 to 5 us in kernel traces, and 1 to 2 us for each row
 // claimed, and gains what the XCDs differ by at the end.  So: 1e12 operations and more (about 0.9 ms), lists bounded by kmax,
 // and eight rounds of what runs at a time, below which an eighth is less than a round.  Attention alone with claims
-// over without, one box, medians of five (runs of one side differ by 0.3 to 3 %): 32 / 8 heads, 128K at 8 % of the
+// over without, one GPU, medians of five (runs of one side differ by 0.3 to 3 %): 32 / 8 heads, 128K at 8 % of the
 // blocks 0.973, 32K at 8 % 0.994 and 15 % 0.986, 24K at 15 % 0.993, 16K at 40 % 0.990; 28 / 4, 64K at 3 % 0.990, dense 0.977;
 // d = 64, 64K at 5 % 0.990; d = 256, 32K at 6 % 0.992; B = 64, 32K at 10 % 0.998; 64 prompts of 1500 dense, an eighth /
 // a quarter 0.994 / 1.003.  Fewer operations: 32K at 5 % 0.991, 16K at 20 % 0.997, B = 64, 32K at 5 % 1.004.  Four rounds (8K

@@ -18,13 +18,19 @@ LIB = os.path.join(PKG, "libstem_hip.so")
 
 SOURCES = ["stem_api.cpp", "stem_pool.hip", "stem_scores.hip", "stem_select.hip", "stem_attn.hip", "stem_static.hip"]
 
-# instantiations of sparse_attn_kernel: block sizes 64 and 128 times head sizes 64, 128 and 256
-ATTENTION_KERNELS = 6
+# instantiations of sparse_attn_kernel: block sizes 64 and 128 times head sizes 64, 128 and 256, and at head sizes 64 and 128
+# the two numbers of queries per wave
+ATTENTION_KERNELS = 10
 
 # -packed-fp32-ops: keep the compiler from forming v_pk_*_f32 out of plain float code.
 COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-I" + os.path.join(ROOT, "include"),
           "-I" + CSRC, "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-Wall", "-Wno-unused-command-line-argument"]
+
+# Flags of single sources.  The attention kernels' rare branches (the softmax's slow path) are uniform over a wave; left out of
+# control-flow structurizing they stay plain branches.  Structurized, the value of every register that such a branch may change
+# was copied on the common path too, and the B = 128, d = 128 kernel spilled 79 registers.
+FLAGS = {"stem_attn.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions"]}
 
 
 def hipcc() -> str:
@@ -36,7 +42,7 @@ def hipcc() -> str:
 
 def _compile(src: str, extra) -> str:
     obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
-    cmd = [hipcc(), *COMMON, *extra, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [hipcc(), *COMMON, *FLAGS.get(src, []), *extra, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("hipcc failed for %s:\n%s\n%s" % (src, res.stdout, res.stderr))
@@ -51,7 +57,7 @@ def check_wait_states(extra=()) -> None:
     compile it to assembly once more and verify the distances in what the compiler made of it."""
     from . import wait_states
     asm_path = os.path.join(OBJ, "stem_attn.s")
-    cmd = [hipcc(), *COMMON, *extra, "--cuda-device-only", "-S", "-x", "hip", os.path.join(CSRC, "stem_attn.hip"),
+    cmd = [hipcc(), *COMMON, *FLAGS["stem_attn.hip"], *extra, "--cuda-device-only", "-S", "-x", "hip", os.path.join(CSRC, "stem_attn.hip"),
            "-o", asm_path]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:

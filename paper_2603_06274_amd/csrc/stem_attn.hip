@@ -1,54 +1,33 @@
 // Stage 3 (Algorithm 1 step 3d): block-sparse causal flash attention over the selected key blocks.
 //
-// One workgroup owns one (query head, query block): B query rows, 32 per wavefront.  Per listed key
+// One workgroup owns one (query head, query block): B query rows, 32 (or 16) per wavefront.  Per listed key
 // block each wave runs
-//     S^T = K Q^T      v_mfma_f32_32x32x16_bf16, A = K rows from LDS, B = the wave's Q rows (regs)
-//     online softmax   exp2 domain, fp32, one query column per lane
+//     S^T = K Q^T      A = K rows from LDS, B = the wave's Q rows (registers)
+//     online softmax   exp2 domain, fp32
 //     O^T += V^T P^T   A = V^T rows read from row-major V in LDS with ds_read_b64_tr_b16,
 //                      B = P^T taken straight from the S^T accumulators
-// Computing the transposed products puts one query in one lane, so the softmax row reductions are
-// in-lane plus a single exchange with lane^32, and the S^T accumulator registers are already in
-// the B-operand layout of the second product: the key rows of each 32-row S^T tile are fed in an
-// order (bits 2 and 3 of the row index swapped) that makes each lane's eight accumulator values of
-// a 16-key step eight consecutive keys.
+// Computing the transposed products puts one query in one lane (and its partners at the same lane number modulo 16
+// or 32), so the softmax row reductions are in-lane plus an exchange between those lanes, and the S^T accumulator
+// registers are already in the B-operand layout of the second product.
 //
-// K and V blocks go from global memory straight into LDS (buffer_load ... lds, no staging
-// registers), one buffer each, refilled in split phases behind two barriers per block: the V block
-// is requested while S^T starts and must have landed when S^T ends; the next K block
-// is requested during O^T and must have landed when the next iteration starts.  Two workgroups
-// share a CU, so one workgroup's matrix work fills the other's waits (at head size 256 the two
-// 64 KiB buffers and about 490 registers leave room for one).
+// K and V blocks go from global memory straight into LDS (buffer_load ... lds, no staging registers).  Two workgroups
+// share a CU, so one workgroup's matrix work fills the other's waits (at head size 256 128 KiB of buffers and
+// about 490 registers leave room for one).
 //
-// Inside a wave the instruction stream is kept dense around the matrix instructions: LDS operands
-// are read four (B = 64: two) matrix instructions ahead into a ring of registers, the softmax of a block is
-// spread pair by pair over the wave's own matrix instructions (the eight pairs of a 32-key tile
-// under the matrix instructions that follow the tile), and the softmax runs without a running
-// maximum: a per-query reference is set
-// on the first block and moved only when a window of probabilities overflows (slow path).
-// The vector unit's issue slots are what the kernel runs short of (every vector instruction taken
-// out of the loop shows in the run time), so whatever can go elsewhere does: the row sums of the
-// probabilities are taken by the matrix pipe (a small product with a 0/1 matrix), the
-// per-request address arithmetic by the scalar unit (the scalar offset operand of the loads).
-// A row's own work beside its blocks counts the same way where lists are short: no zeros are written to
-// accumulators that the first block's products can start, only tiles on or above the wave's diagonal are masked,
-// maxima are taken three at a time, and Q and the list are asked for before the count is known.  Attention before /
-// now: 5 % density (lists of 13), 64K 1435 / 1420 us; 128K (42) 9984 / 9956; 12 prompts to 2047 tokens 110.1 / 109.1.
-// Every list of the selection ends with the diagonal block, where a wave's queries see only the key tiles up to
-// their own: that block has a body of its own that leaves the others out of both products (3/8 of its work
-// at B = 128, 1/4 at 64).  The wave with all tiles still takes the block's time, but its neighbours on the SIMD
-// gain: before / now, 5 % density, 64K 1421 / 1390 us; 32K at 15 % (lists of 20) 1208 / 1184; 128K 9956 / 9822;
-// 12 prompts to 2047 tokens 104.9 / 100.2; d = 64, 64K 1500 / 1480; dense 64K (256 blocks) within 0.3 %.  Not
-// at d = 256, one wave per SIMD: nobody is there to use the time.
+// Long calls are bound by power: with all inputs zero the same launches take 0.7 of their time, at a clock of 2.4 instead of
+// 1.5 to 1.7 GHz.  What takes instructions, operand traffic or energy per operation out therefore shows in the run time,
+// and what only fills idle cycles shows less.
 //
-// The kernel is a template over the block size B (64, 128) and the head size D (64, 128, 256).
+// Head sizes 64 and 128 (sparse_attn_body): matrix instruction 16x16x32, the three steps of half blocks pipelined.
+// Head size 256 (sparse_attn_body_256): 32x32x16, placed by hand.
 //
 // LDS layouts (rows of 2 D bytes, unpadded: the direct loads write 1 KiB contiguously): K has its
 // 16-byte chunks XORed with (row & 15), so the 16 rows a quarter-wave reads one chunk of spread
-// over all banks; V has its 64-byte groups XORed with (row & 3), which does the same for the
-// 4-row x 32-byte footprint of a transposing read.  At D = 64 two 128-byte rows share the 64
-// banks, so the terms are ((row >> 1) & 7) and ((row >> 1) & 1) there.  The swizzle is applied on
-// the global side (each lane fetches the chunk that belongs at its LDS position).
+// over all banks; V has its 32-byte groups (head size 256: 64-byte groups) XORed with row bits, which does the same for
+// the rows of a transposing read.  At D = 64 two 128-byte rows share the 64 banks, so the row's bit 0 is left out of the
+// terms.  The swizzle is applied on the global side (each lane fetches the chunk that belongs at its LDS position).
 #include <type_traits>
+#include <utility>
 
 #include "stem_common.h"
 
@@ -57,13 +36,15 @@ namespace stem {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2_t;
 typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2_t;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4_t;
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
 
-__device__ __forceinline__ bf16x8_t as_bf16x8(uint4 x) { return __builtin_bit_cast(bf16x8_t, x); }
+__device__ __forceinline__ u32x4_t as_u32x4(uint4 x) { return u32x4_t{x.x, x.y, x.z, x.w}; }
+__device__ __forceinline__ bf16x8_t as_bf16x8(u32x4_t x) { return __builtin_bit_cast(bf16x8_t, x); }
 
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     f32x2_t f = {lo, hi};
@@ -78,14 +59,24 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
     return r;
 }
 
-// Lanes (query lane % 32 of the tile, half lane / 32) whose query lies before the key of accumulator x of the
-// tile on the diagonal, key 16 (x / 8) + 8 (lane / 32) + x % 8
+// Lanes whose query (16-query tile, lane % 16) lies before key 4 (lane / 16) + x of the 16 keys on the diagonal
 constexpr uint64_t lanes_before_key(int x) {
     uint64_t lanes = 0;
     for (int l = 0; l < 64; ++l)
-        if (16 * (x / 8) + 8 * (l / 32) + x % 8 > l % 32) lanes |= 1ull << l;
+        if (4 * (l / 16) + x > l % 16) lanes |= 1ull << l;
     return lanes;
 }
+
+// f(0), f(1), .. f(N - 1) with compile-time arguments: what is inside is unrolled by the front end, whatever its size
+template <typename F, int... I>
+__device__ __forceinline__ void for_each_constant(std::integer_sequence<int, I...>, F&& f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unrolled(F&& f) {
+    for_each_constant(std::make_integer_sequence<int, N>{}, f);
+}
+#define STEM_INLINE __attribute__((always_inline))
 
 __device__ __forceinline__ int swap_bits_2_3(int x) {
     return (x & ~12) | ((x & 4) << 1) | ((x & 8) >> 1);
@@ -100,9 +91,10 @@ __device__ __forceinline__ int swap_bits_2_3(int x) {
         asm volatile("" ::: "memory");              \
     } while (0)
 // s_waitcnt with only vmcnt set (gfx9 encoding: vmcnt[3:0], expcnt[6:4]=7, lgkmcnt[11:8]=15); the
-// builtin, unlike inline asm, is seen by the compiler's own wait-count bookkeeping.
-#define STEM_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(0x0F70 | (N))
-// the same with only lgkmcnt set (vmcnt is split over bits [3:0] and [15:14])
+// builtin, unlike inline asm, is seen by the compiler's own wait-count bookkeeping.  vmcnt is split over bits [3:0] and
+// [15:14].
+#define STEM_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(0x0F70 | ((N) & 15) | (((N) >> 4) << 14))
+// the same with only lgkmcnt set
 #define STEM_WAIT_LGKMCNT_CASE(N) case N: __builtin_amdgcn_s_waitcnt(0xC07F | ((N) << 8)); break;
 __device__ __forceinline__ void wait_lgkmcnt(int n) {   // n is a constant after unrolling: the switch folds away
     switch (n) {
@@ -116,12 +108,26 @@ __device__ __forceinline__ void wait_lgkmcnt(int n) {   // n is a constant after
 
 // Nothing is scheduled across this point: keeps the next group of LDS operand reads ahead of the
 // matrix instructions that consume the current group, operand reads in the order of their use, and a matrix
-// instruction ahead of the softmax pair that goes under it (the compiler put the first pair of a tile, which waits
-// for the tile's last product, before the next tile's first product, and read a block's first operands in an order
-// of its own, with one wait for all of them).  Attention alone, without / with the last two: 128K 9410 / 9329 us,
-// 64K dense 25208 / 24964, 5 % 1351 / 1338, 32K 1141 / 1133, d = 64 64K 1443 / 1430, B = 64 100K 7979 / 7894, one head of 4096
-// 13.55 / 13.13; d = 256 as before.
+// instruction ahead of the softmax steps that go under it.
 #define STEM_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
+
+// O^T += V^T P^T, 16 x 16 tile, 32 keys.  Written out because the compiler's form for four result registers lets the
+// result land in other registers than the addend: over a branch that rescales O (the slow path of the softmax) it then
+// copied all of O, on the common path too.  What the compiler does not know for such an instruction is kept by the code
+// around it and checked in the finished assembly (wait_states.py): 8 issue slots before a vector access to the result.
+__device__ __forceinline__ void mfma_output(f32x4_t& c, u32x4_t a, u32x4_t b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+// Idle issue slots between the instructions that wrote o and vector instructions that touch it.  (Every register is named as
+// one that the wait modifies: only that dependence keeps the compiler from moving the others across it.)
+template <int N, int M, int Q>
+__device__ __forceinline__ void wait_states_output(f32x4_t (&o)[M][Q]) {
+#pragma unroll
+    for (int x = 0; x < M * Q; ++x) asm volatile("" : "+v"(o[x / Q][x % Q]));
+    asm volatile("s_nop %1" : "+v"(o[0][0]) : "n"(N - 1));
+#pragma unroll
+    for (int x = 0; x < M * Q; ++x) asm volatile("" : "+v"(o[x / Q][x % Q]));
+}
 
 // Matrix instructions with the register file chosen by hand (head size 256).  A wave that may use
 // more than 256 registers has them in two halves: vector registers, which every instruction can
@@ -132,12 +138,10 @@ __device__ __forceinline__ void wait_lgkmcnt(int n) {   // n is a constant after
 // placement is ours: S^T results in vector registers, the O^T accumulators and the Q operands in
 // accumulator registers, no copy in the loop.  The price: the compiler no longer knows these are
 // matrix instructions, so the wait states it would insert are placed by hand where the instruction
-// order does not already guarantee them (kManualHazards sites below): 12 issue slots between a
+// order does not already guarantee them (the wait_states sites below): 12 issue slots between a
 // 32x32x16 product and a vector access to its result, 5 after a 4x4x4 one, 2 between a vector
 // write and a matrix instruction that reads it.  The build checks the finished assembly for these
 // distances (wait_states.py), since register allocation may add copies the source does not show.
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ u32x4_t as_u32x4(uint4 x) { return u32x4_t{x.x, x.y, x.z, x.w}; }
 __device__ __forceinline__ void mfma_scores_first(f32x16_t& d, uint4 a, const u32x4_t& b) {
     // (early clobber: the result registers must not be the ones an operand is still read from)
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(as_u32x4(a)), "a"(b));
@@ -145,11 +149,11 @@ __device__ __forceinline__ void mfma_scores_first(f32x16_t& d, uint4 a, const u3
 __device__ __forceinline__ void mfma_scores(f32x16_t& d, uint4 a, const u32x4_t& b) {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(as_u32x4(a)), "a"(b));
 }
-__device__ __forceinline__ void mfma_output(f32x16_t& d, uint4 a, uint4 b) {
+__device__ __forceinline__ void mfma_output_acc(f32x16_t& d, uint4 a, uint4 b) {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(as_u32x4(a)), "v"(as_u32x4(b)));
 }
 // the first product into an O^T tile: nothing to add to, so no zero has to be written beforehand
-__device__ __forceinline__ void mfma_output_first(f32x16_t& d, uint4 a, uint4 b) {
+__device__ __forceinline__ void mfma_output_acc_first(f32x16_t& d, uint4 a, uint4 b) {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=a"(d) : "v"(as_u32x4(a)), "v"(as_u32x4(b)));
 }
 // Pins a Q operand to accumulator registers where it is loaded.  (Given only the "a" constraint at
@@ -213,7 +217,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t sequence_resource(const uint16
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(first_row), 0, (int)bytes, 0x00020000);
 }
 
-// When the softmax pairs of a block are issued and where its reference may be checked, for KT
+// Head size 256: when the softmax pairs of a block are issued and where its reference may be checked, for KT
 // 32-key tiles per block and KS = D / 16 matrix instructions per S^T tile.  Slot s = 0 .. 2*NS-1
 // counts the wave's matrix instructions of one block (S^T first, then O^T).  Pair q = 8*t + x/2 may
 // be issued once tile t of S^T is complete (slot KS*t + KS - 1) and must be done before O^T reaches
@@ -227,16 +231,16 @@ struct SoftmaxSchedule {
     static constexpr int DT = KS / 2;                  // matrix instructions per 16-key step of O^T
     static constexpr int NP = KT * 8;                  // accumulator pairs per block and lane
     static constexpr int kChecks = 2;
-    static constexpr int kMaxPerSlot = KS < 8 ? 2 : 1;
+    static constexpr int kMaxPerSlot = 1;
     // The reference is checked when O^T starts (tiles 0 .. KT-2 issued, nothing consumed) and when
     // O^T reaches the last tile (its pairs issued, all others consumed).
     static constexpr int check_slot(int c) { return c == 0 ? NS : NS + KS * (KT - 1); }
     // slot after whose matrix instruction pair q is issued: the eight pairs of tile t are spread over
-    // the KS slots that follow the tile's completion.  At d = 256, where the matrix instructions are
-    // placed by hand, a tile's first pair keeps kLead + 1 matrix instructions (and the operand wait of
+    // the KS slots that follow the tile's completion.  The matrix instructions are
+    // placed by hand: a tile's first pair keeps kLead + 1 matrix instructions (and the operand wait of
     // every second one) between itself and the instruction that completed the tile: the 12 issue
     // slots after which that instruction's result may be read by a vector instruction.
-    static constexpr int kLead = KS == 16 ? 7 : 0;
+    static constexpr int kLead = 7;
     static constexpr int issue_slot(int q) { return (q / 8 + 1) * KS + kLead + ((q % 8) * (KS - kLead)) / 8; }
     // slot of the O^T instruction that first consumes pair q
     static constexpr int use_slot(int q) { return NS + DT * (2 * (q / 8) + (q % 8) / 4); }
@@ -259,7 +263,7 @@ struct SoftmaxSchedule {
         for (int c = 0; c < kChecks; ++c) {
             const int slot = check_slot(c);
             if (slot < NS || slot % DT) return false;
-            if (pairs_by(slot - 1) % 8) return false;        // the row sums are taken up to four pairs at a time, once more by tiles
+            if (pairs_by(slot - 1) % 2) return false;        // the row sums are taken two pairs at a time
             if (lo > 4 * ((slot - NS) / DT)) return false;   // pairs below the window are consumed (4 per step)
             for (int q = lo; q < pairs_by(slot - 1); ++q)
                 if (use_slot(q) < slot) return false;        // pairs of the window are not consumed yet
@@ -279,9 +283,7 @@ struct SoftmaxSchedule {
     }
     static constexpr Table kTable = make_table();
 };
-static_assert(SoftmaxSchedule<4, 8>::valid() && SoftmaxSchedule<2, 8>::valid(), "softmax schedule, d = 128");
 static_assert(SoftmaxSchedule<4, 16>::valid() && SoftmaxSchedule<2, 16>::valid(), "softmax schedule, d = 256");
-static_assert(SoftmaxSchedule<4, 4>::valid() && SoftmaxSchedule<2, 4>::valid(), "softmax schedule, d = 64");
 
 // The order in which the query-block rows of a packed batch are handed out (launch_sparse_attn says when): the
 // sequences by the length of their longest list's bound (the block index of the last row), longest first, and a
@@ -334,39 +336,25 @@ __device__ __forceinline__ bool claim_row(int32_t* taken, int claim_from, Rows r
 // All queues at the start of a launch.  (A kernel and not a memset, which a captured graph would not replay reliably.)
 __global__ void clear_row_queues_kernel(int32_t* taken) { taken[threadIdx.x * kQueueStride] = 0; }
 
-// The body takes the two LDS buffers as __restrict__ parameters: once inlined, every access carries
-// alias-scope information, which lets the compiler's wait-count insertion tell a read of one buffer
-// from an in-flight global->LDS load into the other (otherwise it waits for all of them).
-template <int B, int D>
-__device__ __forceinline__ void sparse_attn_body(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-    const int32_t* __restrict__ counts, const int32_t* __restrict__ indices,
-    uint16_t* __restrict__ out, float* __restrict__ lse, const SeqTable& seq, const RowWalk& walk, int Hq, int R, int G,
-    int order, int claim_from, int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh,
-    float scale, int items_per_xcd, int xcds_per_kv_head, int32_t* __restrict__ taken, unsigned char* __restrict__ k_lds,
-    unsigned char* __restrict__ v_lds) {
-    constexpr int KT = B / 32;                         // 32-key tiles per block
-    constexpr int KS = D / 16;                         // 16-wide steps of S^T along d; also requests per wave, tensor and block
-    constexpr int DT = D / 32;                         // 32-row tiles of O^T along d
-    constexpr int NW = B / 32;                         // waves
-    constexpr int kRowBytes = D * 2;                   // one K or V row in LDS
-    constexpr int kSliceRows = 1024 / kRowBytes;       // rows one wave-wide 1 KiB request covers
-    // head size 256 needs more than 256 registers per lane: matrix instructions by hand (see above)
-    constexpr bool kManualHazards = D == 256;
-    // LDS swizzles, as XORs on the 16-byte chunk index of a row: K spreads the 16 rows a quarter-wave
-    // reads one chunk of over all banks, V the 4 rows x 32 bytes of a transposing read (at d = 64 two
-    // 128-byte rows share the 64 banks, so the row's bit 0 does the spreading by itself)
-    auto k_swz = [](int row) { return D == 64 ? (row >> 1) & 7 : row & 15; };
-    auto v_swz = [](int row) { return (D == 64 ? (row >> 1) & 1 : row & 3) << 2; };
+// The row of a workgroup
+struct RowPlace {
+    int g, h;                                          // KV head, query head
+    int r, i;                                          // row of the call, block index in its sequence
+    int seq_lo, seq_hi;                                // key token rows the call may read
+    int tok_q0, q_hi;                                  // its first query token (Q, O and lse hold the chunk's tokens only), end of the sequence's
+};
 
-    // ---- which (head, row): consecutive workgroup ids go to different XCDs (each with its own
-    // L2), so an XCD should see few KV heads, and all XCDs equal work.  With xcds_per_kv_head = m > 0
-    // (Hkv divides 8) XCD x serves KV head x / m and every m-th row of it, rows descending (long
-    // rows first), the G heads of a group side by side; otherwise every XCD takes a contiguous
-    // range of the (KV head, row descending, head in group) order ----
+// Which (head, row): consecutive workgroup ids go to different XCDs (each with its own L2), so an XCD should see few KV
+// heads, and all XCDs equal work.  With xcds_per_kv_head = m > 0 (Hkv divides 8) XCD x serves KV head x / m and every
+// m-th row of it, rows descending (long rows first), the G heads of a group side by side; otherwise every XCD takes a
+// contiguous range of the (KV head, row descending, head in group) order.  false: no row.  claimed: two words of LDS that
+// are not in use yet.
+template <int B, bool WALK>
+__device__ __forceinline__ bool find_row(const SeqTable& seq, const RowWalk& walk, int Hq, int R, int G, int order,
+                                         int claim_from, int items_per_xcd, int xcds_per_kv_head,
+                                         int32_t* __restrict__ taken, int* claimed, RowPlace& p) {
     int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     if (__builtin_expect(slot >= claim_from, 0)) {     // (travels beside `order`)
-        int* const claimed = reinterpret_cast<int*>(k_lds);   // not in use yet
         if (threadIdx.x < 64) {
             const bool found = claim_row(taken, claim_from, [&](int x) {
                 return rows_of_xcd(x, Hq, R, G, items_per_xcd, xcds_per_kv_head) - claim_from;
@@ -380,28 +368,28 @@ __device__ __forceinline__ void sparse_attn_body(
         xcd = __builtin_amdgcn_readfirstlane(claimed[0]);
         slot = __builtin_amdgcn_readfirstlane(claimed[1]);
         __syncthreads();
-        if (xcd < 0) return;
+        if (xcd < 0) return false;
     }
-    int g, h, pos;                                     // pos: place of the row in the walk
+    int pos;                                           // place of the row in the walk
     if (xcds_per_kv_head > 0) {
         pos = (slot / G) * xcds_per_kv_head + xcd % xcds_per_kv_head;
-        if (slot >= items_per_xcd || pos >= R) return;
-        g = xcd / xcds_per_kv_head;
-        h = g * G + slot % G;
+        if (slot >= items_per_xcd || pos >= R) return false;
+        p.g = xcd / xcds_per_kv_head;
+        p.h = p.g * G + slot % G;
     } else {
         const int64_t item = (int64_t)xcd * items_per_xcd + slot;
-        if (slot >= items_per_xcd || item >= (int64_t)Hq * R) return;
-        g = (int)(item / ((int64_t)R * G));
-        const int rem = (int)(item - (int64_t)g * R * G);
+        if (slot >= items_per_xcd || item >= (int64_t)Hq * R) return false;
+        p.g = (int)(item / ((int64_t)R * G));
+        const int rem = (int)(item - (int64_t)p.g * R * G);
         pos = rem / G;
-        h = g * G + rem % G;
+        p.h = p.g * G + rem % G;
     }
 
     // The row comes first: its count and list entries are what everything else waits for.  `order` travels
     // beside R, so that a call of one sequence waits for no load here.  In the walk's order the sequence and its
     // place are found as in place_in, by a load per lane of either.
     int r = R - 1 - pos, s = 0;
-    if (D != 256 && order == kWalk) {
+    if (WALK && order == kWalk) {
         const int x = threadIdx.x & 63;
         const int start_x = walk.start[x], seq_x = walk.seq[x];
         const int turn = (int)__popcll(__builtin_amdgcn_ballot_w64(start_x <= pos)) - 1;
@@ -411,10 +399,45 @@ __device__ __forceinline__ void sparse_attn_body(
         s = seq_of_row(seq, r);
     }
     const int ic = r - seq.row_start[s];               // row inside the call's chunk of the sequence
-    const int i = seq.first_block[s] + ic;             // block index in the sequence
-    const int seq_lo = seq.tok_start[s], seq_hi = seq.kv_end[s];   // key token rows the call may read
-    const int tok_q0 = seq.q_tok_start[s] + ic * B;    // Q, O and lse hold the chunk's tokens only
-    const int q_hi = seq.q_tok_start[s + 1];
+    p.r = r;
+    p.i = seq.first_block[s] + ic;
+    p.seq_lo = seq.tok_start[s];
+    p.seq_hi = seq.kv_end[s];
+    p.tok_q0 = seq.q_tok_start[s] + ic * B;
+    p.q_hi = seq.q_tok_start[s + 1];
+    return true;
+}
+
+// The body takes the two LDS buffers as __restrict__ parameters: once inlined, every access carries
+// alias-scope information, which lets the compiler's wait-count insertion tell a read of one buffer
+// from an in-flight global->LDS load into the other (otherwise it waits for all of them).
+//
+// Head size 256.  Products of 32 x 32 x 16: one query per lane.  K and V have a buffer each, refilled in split phases behind
+// two barriers per block: the V block is requested while S^T starts and must have landed when S^T ends; the next K block
+// is requested during O^T and must have landed when the next block starts.  The softmax of a block is spread pair by
+// pair over the wave's own matrix instructions (the eight pairs of a 32-key tile under the matrix instructions that follow the
+// tile).  A wave has its SIMD for itself: with products of 16 x 16 x 32 and half blocks pipelined, as at the other sizes, calls
+// that fill the chip take the same time (32K, 15 % density: 2370 / 2373 us) and small ones more (51 / 58 us: twice the
+// matrix instructions, and nobody else to issue in between).
+template <int B>
+__device__ __forceinline__ void sparse_attn_body_256(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const int32_t* __restrict__ counts, const int32_t* __restrict__ indices, uint16_t* __restrict__ out,
+    float* __restrict__ lse, const RowPlace& row, int R, int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh,
+    int64_t kv_st, int64_t kv_sh, float scale, unsigned char* __restrict__ k_lds, unsigned char* __restrict__ v_lds) {
+    constexpr int D = 256;
+    const int g = row.g, h = row.h, r = row.r, i = row.i, seq_lo = row.seq_lo, seq_hi = row.seq_hi, tok_q0 = row.tok_q0,
+              q_hi = row.q_hi;
+    constexpr int KT = B / 32;                         // 32-key tiles per block
+    constexpr int KS = D / 16;                         // 16-wide steps of S^T along d; also requests per wave, tensor and block
+    constexpr int DT = D / 32;                         // 32-row tiles of O^T along d
+    constexpr int NW = B / 32;                         // waves
+    constexpr int kRowBytes = D * 2;                   // one K or V row in LDS
+    constexpr int kSliceRows = 1024 / kRowBytes;       // rows one wave-wide 1 KiB request covers
+    // LDS swizzles, as XORs on the 16-byte chunk index of a row: K spreads the 16 rows a quarter-wave
+    // reads one chunk of over all banks, V the 4 rows x 32 bytes of a transposing read
+    auto k_swz = [](int row) { return row & 15; };
+    auto v_swz = [](int row) { return (row & 3) << 2; };
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -432,18 +455,13 @@ __device__ __forceinline__ void sparse_attn_body(
 
     // ---- Q rows of this wave as B operands: KS k-steps of 16 along d.  Queries past the end repeat the
     //      last one (no branch around a load); what they give is not stored ----
-    bf16x8_t q_reg[KS];
-    u32x4_t q_acc[kManualHazards ? KS : 1];            // the same, for the hand-placed form
+    u32x4_t q_acc[KS];
     {
         const uint16_t* src = q + (int64_t)min(tok_q, q_hi - 1) * q_st + (int64_t)h * q_sh + hi * 8;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            const uint4 x = *reinterpret_cast<const uint4*>(src + ks * 16);
-            q_reg[ks] = as_bf16x8(x);
-            if constexpr (kManualHazards) {
-                q_acc[ks] = as_u32x4(x);
-                pin_to_acc(q_acc[ks]);
-            }
+            q_acc[ks] = as_u32x4(*reinterpret_cast<const uint4*>(src + ks * 16));
+            pin_to_acc(q_acc[ks]);
         }
     }
 
@@ -458,9 +476,8 @@ __device__ __forceinline__ void sparse_attn_body(
     const int slice_row = (lane * 16) / kRowBytes, pc = ((lane * 16) % kRowBytes) >> 4;
     const int lrow = w * kSliceRows + slice_row;       // row of slice u = 0
     const uint32_t lane_row_off = (uint32_t)(lrow * row_bytes);
-    constexpr int kKVariants = D == 256 ? (B == 128 ? 2 : 4) : (D == 128 && B == 64) ? 2 : 1;
-    static_assert(D == 64 ? (NW * kSliceRows) % 16 == 0 : (kKVariants * NW * kSliceRows) % 16 == 0,
-                  "the K swizzle term of slice u repeats with period kKVariants");
+    constexpr int kKVariants = B == 128 ? 2 : 4;
+    static_assert((kKVariants * NW * kSliceRows) % 16 == 0, "the K swizzle term of slice u repeats with period kKVariants");
     static_assert((NW * kSliceRows) % 4 == 0, "the V swizzle term does not depend on the slice");
     uint32_t k_off[kKVariants];
 #pragma unroll
@@ -508,7 +525,7 @@ __device__ __forceinline__ void sparse_attn_body(
     f32x16_t o_acc[DT];                                // the first block's products start it
     const float neg_inf = -__builtin_huge_valf();
     float m_ref = neg_inf;                             // softmax reference (raw score units)
-    float l_run = 0.f;                                 // softmax sum of the query (of this lane's keys, unless kStepSums)
+    float l_run = 0.f;                                 // softmax sum of the query over this lane's keys
     const float sl2 = scale * 1.4426950408889634f;
 
     // per-lane LDS offsets that do not change between blocks.  Both swizzles are XORs of address
@@ -540,10 +557,7 @@ __device__ __forceinline__ void sparse_attn_body(
     // their use: the loaded LDS latency is several matrix instructions long.  They are consumed
     // two at a time behind one wait (every instruction, waits included, takes an issue slot of
     // the wave).  An O^T operand is two reads, and at most 15 reads can be counted in flight.
-    // Reading further ahead costs more than it hides, with two waves on a SIMD: six ahead / four (two at B = 64), attention
-    // alone: 128K 9393 / 9340 us, 64K dense 25252 / 25135, 5 % 1356 / 1345, 32K 1142 / 1137, d = 64 64K 1437 / 1430, one
-    // head of 4096 16.6 / 16.5; B = 64 100K six / four / two 8015 / 7922 / 7855; two at B = 128 up to 3 % slower in small calls.
-    constexpr int kAhead = B == 64 && D != 256 ? 2 : 4, kSlots = kAhead + 2;
+    constexpr int kAhead = 4, kSlots = kAhead + 2;
 
     // The softmax of a block is 8*KT accumulator pairs per lane.  Vector and matrix instructions
     // of the SAME wave overlap well, those of two waves sharing a SIMD do not, so the pairs are
@@ -552,11 +566,6 @@ __device__ __forceinline__ void sparse_attn_body(
     constexpr int NS = Sched::NS;
     auto pairs_by = [](int slot) { return Sched::kTable.v[slot + 1]; };
     constexpr int kCheckSlot[2] = {Sched::check_slot(0), Sched::check_slot(1)};
-
-    // 0/1 operand of the row-sum product (softmax_pair; keep_sums_apart for what is not finite): row m takes the lane groups g of 16 with g % 2 = (m / 4) % 2
-    constexpr bool kStepSums = B == 128 && D != 256;
-    const uint32_t own_pair = ((lane >> 2) ^ (lane >> 4)) & 1 ? 0u : 0x3f803f80u;
-    const uint4 own_query = make_uint4(own_pair, own_pair, own_pair, own_pair);
 
     f32x16_t s_acc[KT];
     uint32_t p_pk[KT][8];                              // bf16 pairs: [tile][16-key step * 4 + pair]
@@ -568,20 +577,12 @@ __device__ __forceinline__ void sparse_attn_body(
     // v_mfma_f32_4x4x4_16B_bf16 lane l supplies column l % 4 of block l / 4 of B (four values along the contraction, two
     // pairs) and receives that column of the 4 x 4 result, so with A = ones every lane gets the sum of its own four
     // values, in each of its four result registers.
-    // At B = 128, d = 64 and 128, a 16-key step at a time: the B operand that the step's O^T product takes (lane l: query
-    // l % 32, keys 8 (l / 32) .. + 7) is, to v_mfma_f32_16x16x32_bf16, column l % 16 and lane group l / 16 of the
-    // contraction, so groups 0 and 2 hold query c, 1 and 3 query c + 16, and a 0/1 operand that picks a group's parity by
-    // the result's row gives every lane the sum over all sixteen keys of its own query.  Eight of these take the
-    // matrix pipe the time of the sixteen others, with half the issue slots: 128K 9221 / 9176 us, 64K dense
-    // 25133 / 25025, 5 % 1326 / 1318, d = 64 64K 1425 / 1416; at B = 64 no difference, and 0.05 us more per call.
     auto softmax_pair = [&](int q) {
         const int t = q >> 3, x = (q & 7) * 2;
         // hand-placed form: a matrix result may be read 12 issue slots after its instruction; the
         // schedule keeps that many instructions in between (kLead), two more for margin
-        if constexpr (kManualHazards) {
-            static_assert(!kManualHazards || Sched::kLead + 1 + (Sched::kLead + 1) / 2 >= 12, "S^T -> softmax distance");
-            if ((q & 7) == 0) wait_states_v<2>(s_acc[t]);
-        }
+        static_assert(Sched::kLead + 1 + (Sched::kLead + 1) / 2 >= 12, "S^T -> softmax distance");
+        if ((q & 7) == 0) wait_states_v<2>(s_acc[t]);
         const float p0 = __builtin_amdgcn_exp2f(s_acc[t][x] * sl2 - off);
         const float p1 = __builtin_amdgcn_exp2f(s_acc[t][x + 1] * sl2 - off);
         uint32_t pk = pack_bf16(p0, p1);
@@ -590,62 +591,19 @@ __device__ __forceinline__ void sparse_attn_body(
         // each pair next to "its" matrix instruction.
         asm volatile("" : "+v"(pk));
         p_pk[t][q & 7] = pk;
-        if constexpr (kStepSums) {
-            if ((q & 3) == 3) {                        // windows hold whole 16-key steps
-                const int u = q & 4;
-                const uint4 step = make_uint4(p_pk[t][u], p_pk[t][u + 1], p_pk[t][u + 2], p_pk[t][u + 3]);
-                l_win = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(own_query), as_bf16x8(step), l_win, 0, 0, 0);
-            }
-        } else if (q & 1) {
-            const uint2 four = make_uint2(p_pk[t][(q & 7) - 1], pk);
-            const uint2 ones = make_uint2(0x3f803f80u, 0x3f803f80u);
-            if constexpr (kManualHazards)
-                mfma_row_sum(l_win, ones, four);
-            else
-                l_win = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(s16x4_t, ones),
-                                                               __builtin_bit_cast(s16x4_t, four), l_win, 0, 0, 0);
-        }
+        if (q & 1)
+            mfma_row_sum(l_win, make_uint2(0x3f803f80u, 0x3f803f80u), make_uint2(p_pk[t][(q & 7) - 1], pk));
     };
-    auto softmax_slot = [&](int slot) {                // one pair per slot at most (two at d = 64)
+    auto softmax_slot = [&](int slot) {                // one pair per slot at most
 #pragma unroll
         for (int q = pairs_by(slot - 1); q < pairs_by(slot); ++q) softmax_pair(q);
     };
     auto window_sum = [&]() {
-        if constexpr (kManualHazards) wait_states_v<6>(l_win);   // after the window's last row-sum product
+        wait_states_v<6>(l_win);                       // after the window's last row-sum product
         return l_win[0];
     };
     auto clear_sum = [&]() { l_win = f32x4_t{0.f, 0.f, 0.f, 0.f}; };
-    // The row sums of a window whose probabilities were formed with a reference that suits them, where a sum is
-    // not finite all the same (a score was NaN or inf): the 0/1 operand leaves the other query of a column out of the
-    // product only as long as that one's probabilities are finite (0 x inf and 0 x NaN are NaN), so here the two go into
-    // a product each, with zeros for the other's, which is what the common product makes of finite ones: the same bits
-    // for a finite query.  there(t): whether the wave has tile t (diagonal block).
     auto sums_finite = [&]() { return __builtin_amdgcn_ballot_w64(!(window_sum() < -neg_inf)) == 0; };
-    auto keep_sums_apart = [&](int q_lo, int q_hi, auto there) {
-        if constexpr (kStepSums) {
-            if (sums_finite()) return;
-            float own = 0.f;
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const bool mine = ((lane >> 4) & 1) == half;
-                clear_sum();
-#pragma unroll
-                for (int t = q_lo / 8; t < q_hi / 8; ++t) {
-                    if (!there(t)) continue;
-#pragma unroll
-                    for (int u = 0; u < 8; u += 4) {
-                        const uint4 step = make_uint4(mine ? p_pk[t][u] : 0u, mine ? p_pk[t][u + 1] : 0u,
-                                                      mine ? p_pk[t][u + 2] : 0u, mine ? p_pk[t][u + 3] : 0u);
-                        l_win = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(own_query), as_bf16x8(step), l_win,
-                                                                       0, 0, 0);
-                    }
-                }
-                if (mine) own = l_win[0];
-            }
-            l_win[0] = own;
-        }
-    };
-    auto whole_block = [](int) { return true; };
     // exp2-domain offset of the reference; a query that has seen nothing yet (m_ref = -inf) uses 0,
     // which keeps its masked scores at exp2(-inf) = 0
     auto reference_offset = [&]() { return m_ref == neg_inf ? 0.f : m_ref * sl2; };
@@ -675,12 +633,12 @@ __device__ __forceinline__ void sparse_attn_body(
             const float corr = (m_ref == neg_inf) ? 0.f : __builtin_amdgcn_exp2f((m_ref - mx) * sl2);
             m_ref = mx;
             l_run *= corr;
-            if constexpr (kManualHazards) wait_states_acc<16>(o_acc);   // the last O^T instruction has written
+            wait_states_acc<16>(o_acc);                // the last O^T instruction has written
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
                 for (int x = 0; x < 16; ++x) o_acc[dt][x] *= corr;
-            if constexpr (kManualHazards) wait_states_acc<4>(o_acc);    // before the next one reads them
+            wait_states_acc<4>(o_acc);                 // before the next one reads them
         }
         off = reference_offset();
         asm volatile("" : "+v"(off));                  // not folded into the exponentials: the bits of the common path
@@ -693,7 +651,6 @@ __device__ __forceinline__ void sparse_attn_body(
         raise_reference(window_max(q_lo, q_hi), finite);
 #pragma unroll
         for (int q = q_lo; q < q_hi; ++q) softmax_pair(q);
-        if (!finite) keep_sums_apart(q_lo, q_hi, whole_block);
     };
     // The first window of a row, pairs [0, q_hi): O and l are still zero, so there is nothing to
     // rescale; a query that sees none of the window's keys keeps m_ref = -inf (offset 0, zero
@@ -704,7 +661,6 @@ __device__ __forceinline__ void sparse_attn_body(
         clear_sum();
 #pragma unroll
         for (int q = 0; q < q_hi; ++q) softmax_pair(q);
-        keep_sums_apart(0, q_hi, whole_block);
         l_run += window_sum();
         clear_sum();
     };
@@ -722,20 +678,18 @@ __device__ __forceinline__ void sparse_attn_body(
     };
     // accumulator x of tile t is key t*32 + 16*(x/8) + 8*hi + x%8 of the block
     auto mask_tile = [&](int t, int limit) {
-        if constexpr (kManualHazards) wait_states_v<16>(s_acc[t]);   // the tile's last matrix instruction has written
+        wait_states_v<16>(s_acc[t]);                   // the tile's last matrix instruction has written
 #pragma unroll
         for (int x = 0; x < 16; ++x)
             if (t * 32 + 16 * (x >> 3) + (x & 7) > limit) s_acc[t][x] = neg_inf;
     };
 
     // The matrix instruction of S^T under which request u of V is issued, and of O^T for the next K.  At B = 64 a
-    // product lasts only 16 of them (32 at d = 256), about the latency of a block that comes from beyond the L2, so
-    // requests go out at the start, two at a time; at B = 128 they are spread, which leaves the LDS reads alone,
-    // to the middle of S^T and two thirds of O^T.  Attention alone, spread over the first half of S^T and all of O^T as
-    // at first / now: B = 64, 100K tokens at 6 % 8321 / 7876 us, d = 64, 64K at 5 % 1384 / 1348, d = 256, 64K 5198 / 4745
-    // (two V at a time 4768, and 30.7 against 29.1 us for one head of 4096), one head of 4096 13.8 / 13.5; B = 128, one third
-    // earlier for K 1.000 to 0.996, everything at the start up to 1 % slower, d = 256 7 %.
-    auto v_slot = [](int u) { return B == 128 ? 2 * u : D == 256 ? u : u / 2; };
+    // product lasts only 32 of them, about the latency of a block that comes from beyond the L2, so requests go out at the
+    // start; at B = 128 they are spread, which leaves the LDS reads alone, to the middle of S^T and two thirds of O^T.
+    // Attention alone, spread over the first half of S^T and all of O^T / this: B = 64, 64K tokens 5198 / 4745 us; B = 128,
+    // everything at the start 7 % slower.
+    auto v_slot = [](int u) { return B == 128 ? 2 * u : u; };
     auto k_slot = [](int u) { return B == 128 ? 3 * u + 1 : u / 2; };
     static_assert(2 * (KS - 1) < NS && 3 * (KS - 1) + 1 < 4 * KS, "every request has a slot");
     const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -780,13 +734,8 @@ __device__ __forceinline__ void sparse_attn_body(
 #pragma unroll
                 for (int u = 0; u < KS; ++u)
                     if (v_slot(u) == n) v_rq.issue(u, v_slice0, slice_step, slice_lds_step);
-                if constexpr (kManualHazards) {
-                    if ((n % KS) == 0) mfma_scores_first(s_acc[t], ka[n % kSlots], q_acc[n % KS]);
-                    else mfma_scores(s_acc[t], ka[n % kSlots], q_acc[n % KS]);
-                } else {
-                    s_acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ka[n % kSlots]), q_reg[n % KS],
-                                                                      (n % KS) == 0 ? zero16 : s_acc[t], 0, 0, 0);
-                }
+                if ((n % KS) == 0) mfma_scores_first(s_acc[t], ka[n % kSlots], q_acc[n % KS]);
+                else mfma_scores(s_acc[t], ka[n % kSlots], q_acc[n % KS]);
                 if constexpr (!kFirst) {
                     if (n >= KS) STEM_SCHED_FENCE();   // the matrix instruction first
                     softmax_slot(n);
@@ -823,12 +772,8 @@ __device__ __forceinline__ void sparse_attn_body(
                     if (k_slot(u) == n) k_rq.issue(u, k_slice0, slice_step, slice_lds_step);
                 const int g2 = n / DT, t = g2 >> 1, u = g2 & 1, dt = n % DT;
                 const uint4 pb = make_uint4(p_pk[t][u * 4], p_pk[t][u * 4 + 1], p_pk[t][u * 4 + 2], p_pk[t][u * 4 + 3]);
-                if constexpr (kManualHazards) {
-                    if (kFirst && n < DT) mfma_output_first(o_acc[dt], va[n % kSlots], pb);
-                    else mfma_output(o_acc[dt], va[n % kSlots], pb);
-                } else
-                    o_acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(va[n % kSlots]), as_bf16x8(pb),
-                                                                       kFirst && n < DT ? zero16 : o_acc[dt], 0, 0, 0);
+                if (kFirst && n < DT) mfma_output_acc_first(o_acc[dt], va[n % kSlots], pb);
+                else mfma_output_acc(o_acc[dt], va[n % kSlots], pb);
                 STEM_SCHED_FENCE();
                 softmax_slot(NS + n);
                 STEM_SCHED_FENCE();
@@ -841,130 +786,20 @@ __device__ __forceinline__ void sparse_attn_body(
         pv_range(kCheckSlot[1] - NS, NS);
         j_cur = j_nxt;
     };
-    // The diagonal block at the end of a list: wave w's queries see its key tiles 0 .. w, and no block follows.
-    // One window for all its pairs, formed before O^T starts (a tile's under the next tile's products, the last
-    // tile's by themselves); the operand ring starts anew with every tile, so that nothing is carried past a tile
-    // that may not be there.
-    auto diagonal_block = [&](bool alone) {
-        STEM_WAIT_VMCNT(0);
-        STEM_BARRIER();                                // K(i) is in LDS; V buffer is free
-        const auto v_rq = v_request(i);
-        clear_sum();
-        // (B = 128, d = 128 has no register left: the operands of O^T are read after the check, or it spills)
-        constexpr bool kTight = B == 128 && D == 128;
-        static_assert(kAhead <= KS, "a tile fills the ring");
-#pragma unroll
-        for (int t = 0; t < KT; ++t) {
-            if (t > 0 && t > w) {                      // wave-uniform
-                // nothing of an earlier block lives on in this tile's registers (no instruction)
-                asm volatile("" : "=v"(s_acc[t]));
-#pragma unroll
-                for (int x = 0; x < 8; ++x) asm volatile("" : "=v"(p_pk[t][x]));
-                continue;
-            }
-            uint4 ka[kSlots];
-#pragma unroll
-            for (int n = 0; n < kAhead; ++n) {
-                ka[n] = load_k(t * KS + n);
-                if (n & 1) STEM_SCHED_FENCE();
-            }
-            STEM_SCHED_FENCE();
-#pragma unroll
-            for (int n = t * KS; n < t * KS + KS; ++n) {
-                const int x = n % KS;
-                if (x + kAhead < KS) ka[(x + kAhead) % kSlots] = load_k(n + kAhead);
-                if ((x & 1) == 0) wait_lgkmcnt((x + kAhead + 1 < KS ? kAhead + 1 : KS - x) - 2);
-                if (t == 0) v_rq.issue(n, v_slice0, slice_step, slice_lds_step);   // every wave has this tile
-                s_acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ka[x % kSlots]), q_reg[x],
-                                                                  x == 0 ? zero16 : s_acc[t], 0, 0, 0);
-                if (t > 0) {                           // pairs of tile t - 1
-                    STEM_SCHED_FENCE();
-                    softmax_slot(n);
-                }
-                STEM_SCHED_FENCE();
-            }
-            if (t == w) {
-#pragma unroll
-                for (int x = 0; x < 16; ++x)
-                    s_acc[t][x] = __builtin_amdgcn_inverse_ballot_w64(lanes_before_key(x)) ? neg_inf : s_acc[t][x];
-#pragma unroll
-                for (int q = 8 * t; q < 8 * t + 8; ++q) softmax_pair(q);
-            }
-        }
-
-        STEM_WAIT_VMCNT(0);
-        STEM_BARRIER();                                // V(i) is in LDS
-        constexpr int kPre = kTight ? 0 : kAhead;
-        uint4 va[kSlots];
-#pragma unroll
-        for (int n = 0; n < kPre; ++n) {
-            va[n] = load_v(n);
-            if (n & 1) STEM_SCHED_FENCE();
-        }
-        STEM_SCHED_FENCE();
-        if (needs_fix(window_sum())) {                 // fix_window of the tiles that the wave has, as one window
-            float mx = lane_max(0, 8);
-#pragma unroll
-            for (int t = 1; t < KT - 1; ++t)
-                if (t <= w) mx = fmaxf(mx, lane_max(8 * t, 8 * t + 8));
-            mx = both_lanes_max(mx);
-            // (a row of this block alone takes its reference, like any row from its first window, from the tiles before
-            // the last, unless the last one's probabilities overflow it)
-            if (w == KT - 1) {
-                const float all = fmaxf(mx, window_max(8 * KT - 8, 8 * KT));
-                if (!alone || (all - mx) * sl2 > 16.f) mx = all;
-            }
-            const bool finite = sums_finite();
-            raise_reference(mx, finite);
-#pragma unroll
-            for (int t = 0; t < KT; ++t) {
-                if (t > 0 && t > w) continue;
-#pragma unroll
-                for (int q = 8 * t; q < 8 * t + 8; ++q) softmax_pair(q);
-            }
-            if (!finite) keep_sums_apart(0, 8 * KT, [&](int t) { return t == 0 || t <= w; });
-        }
-        l_run += window_sum();
-        STEM_SCHED_FENCE();
-#pragma unroll
-        for (int n = kPre; n < kAhead; ++n) {
-            va[n] = load_v(n);
-            if (n & 1) STEM_SCHED_FENCE();
-        }
-#pragma unroll
-        for (int t = 0; t < KT; ++t) {
-            if (t > 0 && t > w) continue;
-#pragma unroll
-            for (int n = t * KS; n < t * KS + KS; ++n) {
-                if (n + kAhead < NS) va[(n + kAhead) % kSlots] = load_v(n + kAhead);
-                if ((n & 1) == 0) wait_lgkmcnt(2 * ((n + kAhead + 1 < NS ? kAhead + 1 : NS - n) - 2));
-                const int u = (n / DT) & 1, dt = n % DT;
-                const uint4 pb = make_uint4(p_pk[t][u * 4], p_pk[t][u * 4 + 1], p_pk[t][u * 4 + 2], p_pk[t][u * 4 + 3]);
-                o_acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(va[n % kSlots]), as_bf16x8(pb),
-                                                                   o_acc[dt], 0, 0, 0);
-                STEM_SCHED_FENCE();
-            }
-        }
-    };
     int it = 0;
-    if (cnt > 1 || (cnt == 1 && (kManualHazards || j_cur != i))) {
+    if (cnt > 0) {
         one_block(it++, std::true_type{});
     } else {
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) o_acc[dt] = zero16;
     }
-    for (; it < cnt && (kManualHazards || it + 1 < cnt || j_cur != i); ++it) one_block(it, std::false_type{});
-    if constexpr (!kManualHazards)
-        if (it < cnt) diagonal_block(it == 0);
+    for (; it < cnt; ++it) one_block(it, std::false_type{});
     STEM_WAIT_VMCNT(0);                                // no request may outlive the workgroup's LDS
-    if constexpr (kManualHazards) wait_states_acc<16>(o_acc);   // the last O^T instructions have written
+    wait_states_acc<16>(o_acc);                        // the last O^T instructions have written
 
     // ---- normalise and store: accumulator x of d tile dt is column dt*32 + 8*(x/4) + 4*hi + x%4 ----
-    float l_tot = l_run;
-    if constexpr (!kStepSums) {                        // each lane has summed its own half of the keys
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
-        l_tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-    }
+    const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
+    const float l_tot = __uint_as_float(halves[0]) + __uint_as_float(halves[1]);   // each lane has summed its own half of the keys
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
     // A lane holds four columns of every group of eight (the other four sit in lane ^ 32).  Two
     // groups at a time, one half-wave swap per packed register gives each lane eight consecutive
@@ -983,32 +818,614 @@ __device__ __forceinline__ void sparse_attn_body(
             const auto s1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
             packed[dt][m] = make_uint4(s0[0], s1[0], s0[1], s1[1]);
         }
-    // (the lane's query from the lane's number once more: no register holds it through the blocks, of which B = 128, d = 128
-    // has none left)
-    const int lane_end = kManualHazards ? lane : __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-    const int tok_end = tok_q0 + w * 32 + (lane_end & 31), hi_end = lane_end >> 5;
-    if (tok_end < q_hi) {
-        uint16_t* dst = out + (int64_t)tok_end * q_st + (int64_t)h * q_sh + hi_end * 8;
+    if (tok_q < q_hi) {
+        uint16_t* dst = out + (int64_t)tok_q * q_st + (int64_t)h * q_sh + hi * 8;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
             for (int m = 0; m < 2; ++m) *reinterpret_cast<uint4*>(dst + dt * 32 + m * 16) = packed[dt][m];
-        if (lse != nullptr && hi_end == 0)
-            lse[(int64_t)h * T + tok_end] = l_tot > 0.f ? m_ref * scale + __logf(l_tot) : neg_inf;
+        if (lse != nullptr && hi == 0)
+            lse[(int64_t)h * T + tok_q] = l_tot > 0.f ? m_ref * scale + __logf(l_tot) : neg_inf;
     }
 }
 
-template <int B, int D>
-__global__ __launch_bounds__(B * 2, D == 256 ? 1 : 2) void sparse_attn_kernel(
+// Head sizes 64 and 128.  Products of 16 x 16 x 32: at the power limit this instruction gives a ninth more operations per
+// second than 32 x 32 x 16 (registers only 2020 / 1800 TFLOP/s, with the LDS reads and exponentials of this kernel beside it
+// 1710 / 1540; with all inputs zero both reach 2440), and with two tiles of 16 queries per wave an LDS operand feeds as many
+// operations.  Lane l has query l % 16 of each of the wave's QW tiles and, of 16 keys, the four from 4 (l / 16) on; two such
+// key tiles are what the second product takes from a lane.  (QW: see launch_sparse_attn.)
+//
+// A block is worked on in halves of B / 2 keys, and the three steps of consecutive halves overlap.  Phase p is
+//     S^T of half p, under it the second half of the softmax of half p - 1;
+//     the reference check of half p - 1;
+//     O^T of half p - 1, under it the first half of the softmax of half p,
+// so that every matrix instruction has the same share of the softmax beside it (all of a block's under its last tile and a half of
+// S^T and first of O^T before: two waves of a SIMD in that part at once left the matrix pipe idle).  The LDS operands of the
+// two products are one stream that is read kAhead operands ahead, across phases too; K and V have two buffers each, one per half,
+// and where the stream goes on to the next phase the wave waits for the requests that fill it and for the others to have
+// read what the next phase's requests overwrite: one barrier per half block.  These requests are issued during S^T.
+//
+// Before (32 x 32 x 16, softmax under the same block's products) / now, attention alone: 128K, 8 % of the blocks 9248 / 8807 us;
+// 32K, 15 % 1120 / 1064; 64K, 5 % 1345 / 1281; d = 64, 64K 1433 / 1386; B = 64, 100K tokens 7870 / 7696; 12 prompts to 2047
+// tokens 100.4 / 95.7.  128K in shader cycles: 1.441e7 / 1.470e7, at 1.49 / 1.60 GHz.
+//
+// Every query's arithmetic is its 16-query tile's own: a reference moves for a tile at a time, and no step depends on
+// how many tiles share a wave.
+template <int B, int D, int QW>
+__device__ __forceinline__ void sparse_attn_body(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const int32_t* __restrict__ counts, const int32_t* __restrict__ indices, uint16_t* __restrict__ out,
+    float* __restrict__ lse, const RowPlace& row, int R, int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh,
+    int64_t kv_st, int64_t kv_sh, float scale, unsigned char* __restrict__ k_lds_a, unsigned char* __restrict__ k_lds_b,
+    unsigned char* __restrict__ v_lds_a, unsigned char* __restrict__ v_lds_b) {
+    // (a parameter of its own for every buffer: alias-scope information then tells the compiler's wait-count insertion a
+    // read of one buffer from a request in flight into another; otherwise it waits for all of them)
+    constexpr int KT = B / 32;                         // 32-key tiles per block
+    constexpr int KS = D / 16;                         // LDS operands of a tile, in either product
+    constexpr int KD = D / 32;                         // 32-wide steps of S^T along d
+    constexpr int NW = B / (16 * QW);                  // waves
+    constexpr int KR = D * QW / 32;                    // requests per wave, tensor and block
+    constexpr int TP = KT / 2;                         // tiles per half block
+    constexpr int HS = TP * KS;                        // LDS operands of a half block, in either product
+    constexpr int NP = TP * 4 * QW;                    // softmax pairs per lane and half block
+    constexpr int kRowBytes = D * 2;                   // one K or V row in LDS
+    constexpr int kSliceRows = 1024 / kRowBytes;       // rows one wave-wide 1 KiB request covers
+    // LDS swizzles, as XORs on the 16-byte chunk index of a row: K spreads the 16 rows a quarter-wave reads one chunk of over
+    // all banks, V the 8 rows x 32 bytes of half a transposing read (at d = 64 two 128-byte rows share the 64 banks)
+    auto k_swz = [](int row) { return D == 64 ? (row >> 1) & 7 : row & 15; };
+    auto v_swz = [](int row) { return (D == 64 ? (row >> 1) & 3 : row & 7) << 1; };
+    using C0 = std::integral_constant<int, 0>;
+    using C1 = std::integral_constant<int, 1>;
+
+    const int i = row.i;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int w_tile = w * QW / 2;                     // the 32-key tile that holds the keys on this wave's diagonal
+    const int c16 = lane & 15, grp = lane >> 4;
+
+    const int64_t list_row = (int64_t)(shared_lists ? row.g : row.h) * R + row.r;   // whose list: the KV head's or the query head's
+    const int32_t* list = indices + list_row * kmax;
+    // the first 64 entries without waiting for the count (a row has room for kmax; what lies beyond the count is
+    // clamped where it is used as an address, and never used otherwise)
+    int list_reg = lane < kmax ? list[lane] : 0;
+    const int cnt = min(counts[list_row], kmax);
+
+    // ---- Q rows of this wave as B operands: per tile, KD steps of 32 along d.  Queries past the end repeat the last one (no
+    //      branch around a load); what they give is not stored ----
+    u32x4_t q_reg[QW][KD];
+#pragma unroll
+    for (int qt = 0; qt < QW; ++qt) {
+        const uint16_t* src = q + (int64_t)min(row.tok_q0 + (w * QW + qt) * 16 + c16, row.q_hi - 1) * q_st +
+                              (int64_t)row.h * q_sh + grp * 8;
+#pragma unroll
+        for (int ks = 0; ks < KD; ++ks) q_reg[qt][ks] = as_u32x4(*reinterpret_cast<const uint4*>(src + ks * 32));
+    }
+
+    // per-lane byte offsets of the block requests (BlockRequest): slice u of wave w is the 1 KiB at LDS offset
+    // (u NW + w) KiB of the block; lane l writes chunk pc of row (u NW + w) kSliceRows + slice_row there and fetches the chunk
+    // that belongs at that position, i.e. the swizzle is applied to the global column.  Only the low bits of the row
+    // enter the swizzle, so it repeats in u with a short period.
+    const int64_t row_bytes = kv_st * 2;
+    const int slice_row = (lane * 16) / kRowBytes, pc = ((lane * 16) % kRowBytes) >> 4;
+    const int lrow = w * kSliceRows + slice_row;       // row of slice u = 0
+    const uint32_t lane_row_off = (uint32_t)(lrow * row_bytes);
+    constexpr int kKVariants = D == 128 && NW * kSliceRows < 16 ? 16 / (NW * kSliceRows) : 1;
+    static_assert((kKVariants * NW * kSliceRows) % 16 == 0, "the K swizzle term of slice u repeats with period kKVariants");
+    static_assert((NW * kSliceRows) % 8 == 0, "the V swizzle term does not depend on the slice");
+    uint32_t k_off[kKVariants];
+#pragma unroll
+    for (int x = 0; x < kKVariants; ++x) k_off[x] = lane_row_off + ((pc ^ k_swz(lrow + x * NW * kSliceRows)) << 4);
+    const uint32_t v_off = lane_row_off + ((pc ^ v_swz(lrow)) << 4);
+    const int64_t first_row = (int64_t)row.g * kv_sh + (int64_t)row.seq_lo * kv_st;
+    const auto k_rsrc = sequence_resource(k + first_row, row.seq_hi - row.seq_lo, row_bytes, kRowBytes);
+    const auto v_rsrc = sequence_resource(v + first_row, row.seq_hi - row.seq_lo, row_bytes, kRowBytes);
+    const uint32_t block_bytes = (uint32_t)(B * row_bytes);
+    const uint32_t slice_step = (uint32_t)(NW * kSliceRows * row_bytes);   // rows of slices u and u+1 of one wave
+    constexpr int slice_lds_step = NW * 1024;
+    auto k_request = [&](int j) {
+        const uint32_t off = j * block_bytes;
+        BlockRequest<kKVariants> rq{k_rsrc, {}};
+#pragma unroll
+        for (int x = 0; x < kKVariants; ++x) rq.lane_off[x] = k_off[x] + off;
+        return rq;
+    };
+    auto v_request = [&](int j) { return BlockRequest<1>{v_rsrc, {v_off + j * block_bytes}}; };
+    // the first KR / 2 requests of a block are its first half
+    auto issue_k = [&](const BlockRequest<kKVariants>& rq, int u) {
+        rq.issue(u, (u < KR / 2 ? k_lds_a : k_lds_b - (KR / 2) * slice_lds_step) + w * 1024, slice_step, slice_lds_step);
+    };
+    auto issue_v = [&](const BlockRequest<1>& rq, int u) {
+        rq.issue(u, (u < KR / 2 ? v_lds_a : v_lds_b - (KR / 2) * slice_lds_step) + w * 1024, slice_step, slice_lds_step);
+    };
+
+    // List entries outside 0..i break the precondition; they are processed as fully masked
+    // blocks (clamped for addressing), which costs time but keeps the control flow flat.
+    auto usable = [&](int j) { return j >= 0 && j <= i; };
+    auto clamped = [&](int j) { return min(max(j, 0), i); };
+    // The list lives in a vector register, 64 entries at a time (lane e holds entry e of the
+    // chunk), and entries are taken out with v_readlane: no scalar load sits in the loop, so the
+    // in-order LDS operand reads are the only users of their counter there.
+    auto list_chunk = [&](int first) {                 // (lane from its number: no register holds an address through the blocks)
+        const int e = first + __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        return e < cnt ? list[e] : 0;
+    };
+    int j_cur = __builtin_amdgcn_readlane(list_reg, 0);
+    {                                                  // (an empty list: a block that nothing uses)
+        const auto rk = k_request(clamped(j_cur));
+        const auto rv = v_request(clamped(j_cur));
+#pragma unroll
+        for (int u = 0; u < KR; ++u) issue_k(rk, u);
+#pragma unroll
+        for (int u = 0; u < KR / 2; ++u) issue_v(rv, u);
+    }
+
+    // The output pointers are taken now: a scalar load still in flight would make every wait for LDS operands in the
+    // blocks one for all of them (the two kinds return in any order on one counter).
+    asm volatile("" : : "s"(out), "s"(lse));
+
+    const f32x4_t zero4 = {0.f, 0.f, 0.f, 0.f};
+    f32x4_t o_acc[KS][QW];                             // [16-column tile][query tile]
+#pragma unroll
+    for (int x = 0; x < KS * QW; ++x) o_acc[x / QW][x % QW] = zero4;
+    const float neg_inf = -__builtin_huge_valf();
+    const float sl2 = scale * 1.4426950408889634f;
+    float m_ref[QW], off[QW], l_run[QW];               // softmax reference (raw score units) and, negated, in exp2 units; sum
+#pragma unroll
+    for (int qt = 0; qt < QW; ++qt) {
+        m_ref[qt] = neg_inf;
+        off[qt] = l_run[qt] = 0.f;
+    }
+    bool unseen = false;                               // a query has no reference yet: all it has met is masked
+
+    // per-lane LDS offsets that do not change between blocks.  Both swizzles are XORs of address
+    // bits that are zero in the unswizzled per-lane offset, so the offset of an operand is one
+    // v_xor of a per-lane base with a constant, plus an immediate.
+    const uint32_t k_base = c16 * kRowBytes + ((k_swz(c16) ^ grp) << 4);
+    // transposing V read: lane l fetches row 4 (l / 16) + (l % 16) / 4 of 16 rows, 8 bytes at column 16 dt + 4 (l % 4)
+    const int v_row = grp * 4 + (c16 >> 2);
+    const uint32_t v_base = v_row * kRowBytes + (v_swz(v_row) << 4) + ((lane & 3) << 3);
+    // Operand n of S^T of half P: tile n / KS, 16 keys n % 2 of it, 32-wide step (n % KS) / 2 along d; and of O^T: tile n / KS,
+    // 16 columns n % KS (the tile's 32 keys in two reads).
+    auto load_k = [&](int P, int n) {
+        const int t = n / KS, kt = n & 1, ks = (n % KS) >> 1;
+        return *reinterpret_cast<const u32x4_t*>((P ? k_lds_b : k_lds_a) + (k_base ^ (ks << 6)) + (t * 32 + kt * 16) * kRowBytes);
+    };
+    auto load_v = [&](int P, int n) {
+        const int t = n / KS, dt = n % KS;
+        const unsigned char* p0 = (P ? v_lds_b : v_lds_a) + (v_base ^ (dt << 5)) + t * 32 * kRowBytes;
+        const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p0);
+        const s16x4_t up = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(p0 + 16 * kRowBytes));
+        const uint2 lo2 = __builtin_bit_cast(uint2, lo), up2 = __builtin_bit_cast(uint2, up);
+        return u32x4_t{lo2.x, lo2.y, up2.x, up2.y};
+    };
+    // Operands are read this many ahead of their use, and used two at a time behind one wait.  Attention alone, 4 / 2 ahead:
+    // B = 64, 100K 8480 / 8185 us (requests early in both: 8047 / 7931), d = 64, 64K 1435 / 1431, 128K 8994 / 8998, 5 % 1317 / 1316.
+    // With one tile per wave an operand is used up in half the time: 4 / 6 / 8 ahead one head of 4096 (B = 64) 12.3 / 11.7 / 11.8,
+    // 25 rows of 12 blocks (B = 128) 35.8 / 35.7 / 34.9.
+    constexpr int kWanted = QW == 1 ? (B == 64 ? 6 : 8) : B == 64 || D == 64 ? 2 : 4;
+    constexpr int kAhead = kWanted < HS ? kWanted : HS;
+    // The operand of S^T under which request u of a phase is issued, K's first.  B = 64 and d = 64, over all of S^T / its first
+    // half: 100K 8185 / 7931 us, d = 64 1436 / 1431; 128K the other way round, 8994 / 9041.
+    auto request_slot = [](int u) { return B == 64 || D == 64 ? u * HS / (2 * KR) : u * HS / KR; };
+
+    f32x4_t s_acc[2][TP][2][QW];                       // [half][tile][16 keys][query tile]
+    u32x4_t p_pk[2][TP][QW];                           // bf16 pairs: [half][tile][query tile], [2 * 16 keys + pair]
+    f32x4_t l_win[QW];                                 // row sums of the current half (four equal copies)
+    float f0 = 0.f, f1 = 0.f;                          // the pair in flight
+    const uint32_t one2 = 0x3f803f80u;
+    const u32x4_t ones = {one2, one2, one2, one2};
+
+    // Step u % 4 of softmax pair u / 4 of half P: exponents, two exponentials, packing to bf16.  The row sums are taken from the
+    // rounded values by the matrix pipe, a tile's 32 keys at a time: a product of the tile's P^T operand with ones, which
+    // gives every lane the sum of its own query.
+    auto softmax_step = [&](auto P_tag, auto u_tag) STEM_INLINE {
+        constexpr int P = decltype(P_tag)::value, u = decltype(u_tag)::value, pair = u >> 2;
+        constexpr int t = pair / (4 * QW), qt = (pair >> 2) % QW, kt = (pair >> 1) & 1, x = (pair & 1) * 2;
+        // (an opaque use of each result: without it the compiler gathers the softmax next to the consumer of the
+        // probabilities instead of leaving each step under its matrix instruction)
+        if constexpr ((u & 3) == 0) {
+            f0 = __builtin_fmaf(s_acc[P][t][kt][qt][x], sl2, off[qt]);
+            f1 = __builtin_fmaf(s_acc[P][t][kt][qt][x + 1], sl2, off[qt]);
+            asm volatile("" : "+v"(f0), "+v"(f1));
+        } else if constexpr ((u & 3) == 1) {
+            f0 = __builtin_amdgcn_exp2f(f0);
+            asm volatile("" : "+v"(f0));
+        } else if constexpr ((u & 3) == 2) {
+            f1 = __builtin_amdgcn_exp2f(f1);
+            asm volatile("" : "+v"(f1));
+        } else {
+            uint32_t pk = pack_bf16(f0, f1);
+            asm volatile("" : "+v"(pk));
+            p_pk[P][t][qt][pair & 3] = pk;
+            if constexpr ((pair & 3) == 3)
+                l_win[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ones), as_bf16x8(p_pk[P][t][qt]),
+                                                                   t == 0 ? zero4 : l_win[qt], 0, 0, 0);
+        }
+    };
+    // pairs first .. first + N - 1, one after the other
+    auto softmax_pairs = [&](auto P_tag, auto first, auto N) STEM_INLINE {
+        unrolled<4 * decltype(N)::value>([&](auto u) STEM_INLINE {
+            softmax_step(P_tag, std::integral_constant<int, 4 * decltype(first)::value + decltype(u)::value>{});
+        });
+    };
+    // the steps of these pairs that go under matrix instruction `at` of the `span` that share them: step u to
+    // (u + 1) span / n, so that no step waits for the one before it, the last one to the last
+    auto softmax_under = [&](auto P_tag, auto first, auto N, auto at_tag, auto span_tag) STEM_INLINE {
+        constexpr int n = 4 * decltype(N)::value, span = decltype(span_tag)::value, at = decltype(at_tag)::value;
+        constexpr int from = (at * n + span - 1) / span - 1, next = at == span - 1 ? n : ((at + 1) * n + span - 1) / span - 1;
+        constexpr int lo = from < 0 ? 0 : from, hi = next < n ? next : n;
+        if constexpr (at < span && lo < hi)
+            unrolled<hi - lo>([&](auto u) STEM_INLINE {
+                softmax_step(P_tag, std::integral_constant<int, 4 * decltype(first)::value + lo + decltype(u)::value>{});
+            });
+    };
+    using kAll = std::integral_constant<int, NP>;
+    using kHalf = std::integral_constant<int, NP / 2>;
+
+    auto negated_offset = [&](int qt) { return m_ref[qt] == neg_inf ? 0.f : -m_ref[qt] * sl2; };   // 0: masked scores stay at exp2(-inf) = 0
+    // largest score of the query in half P (all of its lanes get it), ignoring NaN
+    auto half_max = [&](int P, int qt) {
+        float mx2[2] = {neg_inf, neg_inf};
+#pragma unroll
+        for (int t = 0; t < TP; ++t)
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt) {
+                mx2[0] = max3(mx2[0], s_acc[P][t][kt][qt][0], s_acc[P][t][kt][qt][1]);
+                mx2[1] = max3(mx2[1], s_acc[P][t][kt][qt][2], s_acc[P][t][kt][qt][3]);
+            }
+        const float mx = max3(mx2[0], mx2[1], mx2[1]);
+        const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+        const float y = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+        const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+        return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+    };
+    auto note_unseen = [&]() {
+        bool none = m_ref[0] == neg_inf;
+        if constexpr (QW == 2) none |= m_ref[1] == neg_inf;
+        unseen = __builtin_amdgcn_ballot_w64(none) != 0;
+    };
+    // The slow path of a half: for a query tile that needs it, moves the references of the tile's queries up to their true
+    // maximum where that is higher (rescaling O and l) and forms the half's probabilities anew.  Where sums are not finite
+    // only if a query gains by it: one that has no reference, or probabilities far beyond its own (a sum over 2^16 of 128 keys
+    // at most holds one over 2^9), and a finite score to go to.  A query that is NaN or inf for good comes here with
+    // every half and leaves the others as they are.
+    auto fix_half = [&](auto P_tag) STEM_INLINE {
+        constexpr int P = decltype(P_tag)::value;
+        wait_states_output<16>(o_acc);                 // the last O^T instruction has written
+#pragma unroll
+        for (int qt = 0; qt < QW; ++qt) {
+            const bool needs = __builtin_amdgcn_ballot_w64((m_ref[qt] == neg_inf) | !(l_win[qt][0] <= 65536.0f)) != 0;
+            const float mx = half_max(P, qt);
+            const bool gains = (mx < -neg_inf) & (mx > m_ref[qt]) & ((m_ref[qt] == neg_inf) | (mx * sl2 + off[qt] > 8.9f));
+            const bool moves = (__builtin_amdgcn_ballot_w64(!(l_win[qt][0] < -neg_inf)) == 0) | (__builtin_amdgcn_ballot_w64(gains) != 0);
+            const bool up = needs & moves & (mx > m_ref[qt]);
+            const float corr = !up ? 1.f : m_ref[qt] == neg_inf ? 0.f : __builtin_amdgcn_exp2f((m_ref[qt] - mx) * sl2);
+            m_ref[qt] = up ? mx : m_ref[qt];
+            l_run[qt] *= corr;
+#pragma unroll
+            for (int dt = 0; dt < KS; ++dt)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) o_acc[dt][qt][x] *= corr;
+            off[qt] = negated_offset(qt);
+            asm volatile("" : "+v"(off[qt]));          // not folded into the exponents: the bits of the common path
+        }
+        softmax_pairs(P_tag, C0{}, kAll{});            // (those of a tile that stays come out as they were)
+        wait_states_output<4>(o_acc);                  // before the next one reads them
+        note_unseen();
+    };
+    // A half needs the slow path if a query has no reference yet or if its sum is not a modest finite number (a
+    // probability above 2^16, inf, NaN: the reference is too low for this half).
+    auto check_half = [&](auto P_tag) STEM_INLINE {
+        bool high = !(l_win[0][0] <= 65536.0f);
+        if constexpr (QW == 2) high |= !(l_win[1][0] <= 65536.0f);
+        if (unseen || __builtin_amdgcn_ballot_w64(high) != 0) fix_half(P_tag);
+#pragma unroll
+        for (int qt = 0; qt < QW; ++qt) l_run[qt] += l_win[qt][0];
+    };
+    // Masks the tiles of half P from `from` on: keys above the query on the diagonal block (w_tile and later), all keys of an
+    // entry that cannot be used
+    auto mask_half = [&](int P, int from, bool all) {
+        const f32x4_t none = {neg_inf, neg_inf, neg_inf, neg_inf};
+#pragma unroll
+        for (int tt = 0; tt < TP; ++tt) {
+            const int t = P * TP + tt;
+            if (t < from) continue;
+            auto diagonal = [&](f32x4_t& s) {          // 16 queries against the same 16 keys
+#pragma unroll
+                for (int x = 0; x < 4; ++x) s[x] = __builtin_amdgcn_inverse_ballot_w64(lanes_before_key(x)) ? neg_inf : s[x];
+            };
+            if (all || t > w_tile) {
+#pragma unroll
+                for (int x = 0; x < 2 * QW; ++x) s_acc[P][tt][x / QW][x % QW] = none;
+            } else if constexpr (QW == 2) {
+                s_acc[P][tt][1][0] = none;
+                diagonal(s_acc[P][tt][0][0]);
+                diagonal(s_acc[P][tt][1][1]);
+            } else if (w & 1) {
+                diagonal(s_acc[P][tt][1][0]);
+            } else {
+                s_acc[P][tt][1][0] = none;
+                diagonal(s_acc[P][tt][0][0]);
+            }
+        }
+    };
+    auto block_mask = [&](int j, int& from, bool& all) {
+        all = !usable(j);
+        from = all ? 0 : j == i ? w_tile : KT;
+    };
+
+    // The matrix instructions of LDS operand m, `even` and `odd` being it and its partner of the pair m & ~1, m | 1.  With two query
+    // tiles a pair's four instructions change one operand at a time.  under(h): what goes under the operand's h-th.
+    auto scores = [&](auto P_tag, auto m_tag, u32x4_t even, u32x4_t odd, auto under) STEM_INLINE {
+        constexpr int P = decltype(P_tag)::value, m = decltype(m_tag)::value, h = m & 1, t = m / KS, ks = (m % KS) >> 1;
+        auto product = [&](f32x4_t& c, u32x4_t a, u32x4_t b) STEM_INLINE {
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a), as_bf16x8(b), ks == 0 ? zero4 : c, 0, 0, 0);
+            STEM_SCHED_FENCE();
+        };
+        if constexpr (QW == 2) {
+            product(s_acc[P][t][h][h], h ? odd : even, q_reg[h][ks]);
+            under(C0{});
+            STEM_SCHED_FENCE();
+            product(s_acc[P][t][1 - h][h], h ? even : odd, q_reg[h][ks]);
+            under(C1{});
+        } else {
+            product(s_acc[P][t][h][0], h ? odd : even, q_reg[0][ks]);
+            under(C0{});
+        }
+        STEM_SCHED_FENCE();
+    };
+    auto outputs = [&](auto P_tag, auto m_tag, u32x4_t even, u32x4_t odd, auto under) STEM_INLINE {
+        constexpr int P = decltype(P_tag)::value, m = decltype(m_tag)::value, h = m & 1, t = m / KS, dt = (m % KS) & ~1;
+        auto product = [&](f32x4_t& c, u32x4_t a, u32x4_t b) STEM_INLINE {
+            mfma_output(c, a, b);
+            STEM_SCHED_FENCE();
+        };
+        if constexpr (QW == 2) {
+            product(o_acc[dt + h][h], h ? odd : even, p_pk[P][t][h]);
+            under(C0{});
+            STEM_SCHED_FENCE();
+            product(o_acc[dt + 1 - h][h], h ? even : odd, p_pk[P][t][h]);
+            under(C1{});
+        } else {
+            product(o_acc[dt + h][0], h ? odd : even, p_pk[P][t][0]);
+            under(C0{});
+        }
+        STEM_SCHED_FENCE();
+    };
+    auto nothing = [](auto) {};
+    // Where the reading side goes on to the next phase.  A wave's own reads have to be back before the others may ask for what
+    // overwrites the buffer they read from.
+    auto cross = [&]() {
+        wait_lgkmcnt(0);
+        STEM_WAIT_VMCNT(0);
+        STEM_BARRIER();
+    };
+    auto waited = [&](int reads_behind) {
+        wait_lgkmcnt(reads_behind);
+        STEM_SCHED_FENCE();
+    };
+    u32x4_t ring[kAhead];                              // the first operands of the next phase
+    // Matrix instructions left free of softmax before the check, which reads the sums
+    constexpr int kReserve = QW * HS >= 8 ? 4 : 2;
+    using kUnderScores = std::integral_constant<int, QW * HS - kReserve>;
+    using kUnderOutputs = std::integral_constant<int, QW * HS>;
+
+    // One phase: half P of a block, and O^T of the half before it.  request(m): the requests under operand m.
+    auto phase = [&](auto P_tag, int mask_from, bool mask_all, auto request) STEM_INLINE {
+        constexpr int P = decltype(P_tag)::value, Q = 1 - P;
+        using Before = std::integral_constant<int, Q>;
+        u32x4_t op[2 * HS + kAhead];
+        unrolled<kAhead>([&](auto m) STEM_INLINE { op[m] = ring[m]; });
+        unrolled<2 * HS>([&](auto m_tag) STEM_INLINE {
+            constexpr int m = decltype(m_tag)::value;
+            if constexpr ((m & 1) == 0) {
+                constexpr int a = m + kAhead;
+                if constexpr (a == 2 * HS) cross();
+                op[a] = a < HS ? load_k(P, a) : a < 2 * HS ? load_v(Q, a - HS) : load_k(Q, a - 2 * HS);
+                op[a + 1] = a < HS ? load_k(P, a + 1) : a < 2 * HS ? load_v(Q, a + 1 - HS) : load_k(Q, a + 1 - 2 * HS);
+                // operands m + 2 .. a + 1 may be under way, those of O^T in two reads
+                constexpr int v_lo = m + 2 > HS ? m + 2 : HS, v_hi = a + 2 < 2 * HS ? a + 2 : 2 * HS;
+                if constexpr (a != 2 * HS) waited(kAhead + (v_hi > v_lo ? v_hi - v_lo : 0));
+            }
+            if constexpr (m < HS) {
+                request(m);
+                scores(P_tag, m_tag, op[m & ~1], op[m | 1], [&](auto h) STEM_INLINE {
+                    softmax_under(Before{}, kHalf{}, kHalf{}, std::integral_constant<int, QW * m + decltype(h)::value>{}, kUnderScores{});
+                });
+                if constexpr (m == HS - 1) {
+                    if (mask_from < KT) mask_half(P, mask_from, mask_all);
+                    check_half(Before{});
+                    STEM_SCHED_FENCE();
+                }
+            } else {
+                outputs(Before{}, std::integral_constant<int, m - HS>{}, op[m & ~1], op[m | 1], [&](auto h) STEM_INLINE {
+                    softmax_under(P_tag, C0{}, kHalf{}, std::integral_constant<int, QW * (m - HS) + decltype(h)::value>{}, kUnderOutputs{});
+                });
+            }
+        });
+        unrolled<kAhead>([&](auto m) STEM_INLINE { ring[m] = op[2 * HS + m]; });
+    };
+
+    if (cnt > 0) {
+        int mask_from;
+        bool mask_all;
+        block_mask(j_cur, mask_from, mask_all);
+        STEM_WAIT_VMCNT(KR);                           // the first half of K is there (its second and V's first may not be)
+        STEM_BARRIER();
+        // ---- the first half: S^T alone; the references are its largest scores; the first half of its softmax ----
+        {
+            u32x4_t op[HS + kAhead];
+            unrolled<kAhead>([&](auto m) STEM_INLINE {
+                op[m] = load_k(0, m);
+                if (m & 1) STEM_SCHED_FENCE();
+            });
+            unrolled<HS>([&](auto m_tag) STEM_INLINE {
+                constexpr int m = decltype(m_tag)::value, a = m + kAhead;
+                if constexpr ((m & 1) == 0) {
+                    if constexpr (a == HS) cross();
+                    op[a] = a < HS ? load_k(0, a) : load_k(1, a - HS);
+                    op[a + 1] = a < HS ? load_k(0, a + 1) : load_k(1, a + 1 - HS);
+                    waited(kAhead);
+                }
+                scores(C0{}, m_tag, op[m & ~1], op[m | 1], nothing);
+            });
+            unrolled<kAhead>([&](auto m) STEM_INLINE { ring[m] = op[HS + m]; });
+            if (mask_from < KT) mask_half(0, mask_from, mask_all);
+#pragma unroll
+            for (int qt = 0; qt < QW; ++qt) {
+                m_ref[qt] = half_max(0, qt);
+                off[qt] = negated_offset(qt);
+            }
+            note_unseen();
+            softmax_pairs(C0{}, C0{}, kHalf{});
+        }
+        // ---- second half of block `it`, first half of the next ----
+#pragma unroll 1
+        for (int it = 0; it + 1 < cnt; ++it) {
+            if (((it + 1) & 63) == 0) list_reg = list_chunk(it + 1);
+            const int j_nxt = __builtin_amdgcn_readlane(list_reg, (it + 1) & 63);
+            {
+                const auto rk = k_request(clamped(j_nxt));
+                const auto rv = v_request(clamped(j_cur));
+                phase(C1{}, mask_from, mask_all, [&](int m) STEM_INLINE {
+#pragma unroll
+                    for (int u = 0; u < KR / 2; ++u) {
+                        if (m == request_slot(u)) issue_k(rk, u);
+                        if (m == request_slot(u + KR / 2)) issue_v(rv, u + KR / 2);
+                    }
+                });
+            }
+            j_cur = j_nxt;
+            block_mask(j_cur, mask_from, mask_all);
+            {
+                const auto rk = k_request(clamped(j_cur));
+                const auto rv = v_request(clamped(j_cur));
+                phase(C0{}, mask_from, mask_all, [&](int m) STEM_INLINE {
+#pragma unroll
+                    for (int u = 0; u < KR / 2; ++u) {
+                        if (m == request_slot(u)) issue_k(rk, u + KR / 2);
+                        if (m == request_slot(u + KR / 2)) issue_v(rv, u);
+                    }
+                });
+            }
+        }
+        // ---- second half of the last block.  On the diagonal block the waves whose queries come before it leave it out of
+        //      both products: their neighbours on the SIMD gain.  (Its softmax they make of what lies in the registers and do
+        //      not use: a branch around it would have the code of O^T twice.) ----
+        const bool second = mask_from == KT || mask_all || w_tile >= TP;
+        {
+            const auto rv = v_request(clamped(j_cur));
+#pragma unroll
+            for (int u = KR / 2; u < KR; ++u) issue_v(rv, u);
+        }
+        auto output_half = [&](auto P_tag, auto under) STEM_INLINE {
+            constexpr int P = decltype(P_tag)::value;
+            u32x4_t op[HS + kAhead];
+            unrolled<kAhead>([&](auto m) STEM_INLINE {
+                op[m] = load_v(P, m);
+                if (m & 1) STEM_SCHED_FENCE();
+            });
+            unrolled<HS>([&](auto m_tag) STEM_INLINE {
+                constexpr int m = decltype(m_tag)::value, a = m + kAhead;
+                if constexpr ((m & 1) == 0) {
+                    if constexpr (a < HS) {
+                        op[a] = load_v(P, a);
+                        op[a + 1] = load_v(P, a + 1);
+                    }
+                    waited(a < HS ? 2 * kAhead : 2 * (HS - m - 2));
+                }
+                outputs(P_tag, m_tag, op[m & ~1], op[m | 1], [&](auto h) STEM_INLINE {
+                    under(std::integral_constant<int, QW * m + decltype(h)::value>{});
+                });
+            });
+        };
+        if (second) {
+            u32x4_t op[HS + kAhead];
+            unrolled<kAhead>([&](auto m) STEM_INLINE { op[m] = ring[m]; });
+            unrolled<HS>([&](auto m_tag) STEM_INLINE {
+                constexpr int m = decltype(m_tag)::value, a = m + kAhead;
+                if constexpr ((m & 1) == 0) {
+                    if constexpr (a < HS) {
+                        op[a] = load_k(1, a);
+                        op[a + 1] = load_k(1, a + 1);
+                    }
+                    waited(a < HS ? kAhead : HS - m - 2);
+                }
+                scores(C1{}, m_tag, op[m & ~1], op[m | 1], [&](auto h) STEM_INLINE {
+                    softmax_under(C0{}, kHalf{}, kHalf{}, std::integral_constant<int, QW * m + decltype(h)::value>{}, kUnderScores{});
+                });
+            });
+            if (mask_from < KT) mask_half(1, mask_from, mask_all);
+        } else {
+            softmax_pairs(C0{}, kHalf{}, kHalf{});
+#pragma unroll
+            for (int x = 0; x < 2 * QW * TP; ++x) asm volatile("" : "=v"(s_acc[1][x / (2 * QW)][(x / QW) & 1][x % QW]));
+        }
+        check_half(C0{});
+        output_half(C0{}, [&](auto at) STEM_INLINE { softmax_under(C1{}, C0{}, kAll{}, at, kUnderOutputs{}); });
+        STEM_WAIT_VMCNT(0);
+        STEM_BARRIER();                                // the second half of V is there
+        if (second) {
+            check_half(C1{});
+            output_half(C1{}, nothing);
+        }
+    }
+    STEM_WAIT_VMCNT(0);                                // no request may outlive the workgroup's LDS
+    wait_states_output<16>(o_acc);                     // the last O^T instructions have written
+
+    // ---- normalise and store: accumulator x of column tile dt is column dt*16 + 4*(lane/16) + x.  Two column tiles at a time,
+    //      one exchange between neighbouring groups of 16 lanes per packed register gives each lane eight consecutive columns,
+    //      i.e. 16-byte stores.  (The exchange runs in every lane, valid query or not.) ----
+    const int lane_end = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));   // not held through the blocks
+    const int c_end = lane_end & 15, g_end = lane_end >> 4;
+#pragma unroll
+    for (int qt = 0; qt < QW; ++qt) {
+        const float inv = l_run[qt] > 0.f ? 1.0f / l_run[qt] : 0.f;
+        uint4 packed[KD];
+#pragma unroll
+        for (int x = 0; x < KD; ++x) {
+            const f32x4_t a = o_acc[2 * x][qt], b = o_acc[2 * x + 1][qt];
+            const uint32_t a0 = pack_bf16(a[0] * inv, a[1] * inv), a1 = pack_bf16(a[2] * inv, a[3] * inv);
+            const uint32_t b0 = pack_bf16(b[0] * inv, b[1] * inv), b1 = pack_bf16(b[2] * inv, b[3] * inv);
+            const auto s0 = __builtin_amdgcn_permlane16_swap(a0, b0, false, false);
+            const auto s1 = __builtin_amdgcn_permlane16_swap(a1, b1, false, false);
+            packed[x] = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+        }
+        const int tok = row.tok_q0 + (w * QW + qt) * 16 + c_end;
+        if (tok < row.q_hi) {
+            uint16_t* dst = out + (int64_t)tok * q_st + (int64_t)row.h * q_sh + (g_end & 1) * 16 + (g_end >> 1) * 8;
+#pragma unroll
+            for (int x = 0; x < KD; ++x) *reinterpret_cast<uint4*>(dst + x * 32) = packed[x];
+            if (lse != nullptr && g_end == qt)
+                lse[(int64_t)row.h * T + tok] = l_run[qt] > 0.f ? m_ref[qt] * scale + __logf(l_run[qt]) : neg_inf;
+        }
+    }
+}
+
+// QW: 16-query tiles per wave (launch_sparse_attn says when one)
+template <int B, int D, int QW>
+__global__ __launch_bounds__(B * 4 / QW, D == 256 ? 1 : 2) void sparse_attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ counts, const int32_t* __restrict__ indices,
     uint16_t* __restrict__ out, float* __restrict__ lse, SeqTable seq, RowWalk walk, int Hq, int R, int G,
     int order, int claim_from, int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh,
     float scale, int items_per_xcd, int xcds_per_kv_head, int32_t* __restrict__ taken) {
-    __shared__ __attribute__((aligned(1024))) unsigned char k_lds[B * D * 2];
-    __shared__ __attribute__((aligned(1024))) unsigned char v_lds[B * D * 2];
-    sparse_attn_body<B, D>(q, k, v, counts, indices, out, lse, seq, walk, Hq, R, G, order, claim_from, T, kmax, shared_lists,
-                           q_st, q_sh, kv_st, kv_sh, scale, items_per_xcd, xcds_per_kv_head, taken, k_lds, v_lds);
+    if constexpr (D == 256) {
+        static_assert(QW == 2, "a wave of 32 queries");
+        __shared__ __attribute__((aligned(1024))) unsigned char k_lds[B * D * 2], v_lds[B * D * 2];
+        RowPlace row;
+        if (!find_row<B, false>(seq, walk, Hq, R, G, order, claim_from, items_per_xcd, xcds_per_kv_head, taken,
+                                reinterpret_cast<int*>(k_lds), row)) return;
+        sparse_attn_body_256<B>(q, k, v, counts, indices, out, lse, row, R, T, kmax, shared_lists, q_st, q_sh, kv_st, kv_sh,
+                                scale, k_lds, v_lds);
+    } else {
+        __shared__ __attribute__((aligned(1024))) unsigned char k_lds[B * D], k_lds2[B * D], v_lds[B * D], v_lds2[B * D];
+        RowPlace row;
+        if (!find_row<B, true>(seq, walk, Hq, R, G, order, claim_from, items_per_xcd, xcds_per_kv_head, taken,
+                               reinterpret_cast<int*>(k_lds), row)) return;
+        sparse_attn_body<B, D, QW>(q, k, v, counts, indices, out, lse, row, R, T, kmax, shared_lists, q_st, q_sh, kv_st,
+                                   kv_sh, scale, k_lds, k_lds2, v_lds, v_lds2);
+    }
 }
 
 int launch_sparse_attn(const Problem& p, const void* q, const void* k, const void* v,
@@ -1020,7 +1437,7 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     const int64_t items = (int64_t)p.Hq * p.R;
     const AttentionGrid ag = attention_grid(p, kmax, queue != nullptr);
     if (ag.slots * 8 > kMaxWorkgroups) return STEM_ERR_UNSUPPORTED;
-    dim3 grid((unsigned)(ag.slots * 8)), block(p.B * 2);
+    dim3 grid((unsigned)(ag.slots * 8));
     // The walk's order is for batches of ten sequences and more, at d = 64 and 128, where rows wait for a place (1.5
     // to 8 times what runs at a time: two workgroups per CU at B = 128, four at B = 64), lists grow with the row
     // (kmax is more than half of the longest sequence's blocks, and these are three or more) and the sequences
@@ -1061,16 +1478,27 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     const uint16_t* vv = static_cast<const uint16_t*>(v);
     uint16_t* oo = static_cast<uint16_t*>(out);
     if (ag.slots > ag.items_per_xcd) hipLaunchKernelGGL(clear_row_queues_kernel, dim3(1), dim3(8), 0, stream, queue);
-#define STEM_ATTN_LAUNCH(BB, DD)                                                                          \
-    hipLaunchKernelGGL((sparse_attn_kernel<BB, DD>), grid, block, 0, stream, qq, kk, vv, counts, indices, \
+#define STEM_ATTN_LAUNCH(BB, DD, QW)                                                                        \
+    hipLaunchKernelGGL((sparse_attn_kernel<BB, DD, QW>), grid, dim3(BB * 4 / QW), 0, stream, qq, kk, vv, counts, indices, \
                        oo, lse, p.seq, walk, p.Hq, p.R, p.G, order, ag.claim_from, p.T, kmax, lists_per_kv_head, p.q_st, p.q_sh, \
                        p.kv_st, p.kv_sh, softmax_scale, ag.items_per_xcd, ag.xcds_per_kv_head, queue)
-    if (p.B == 128 && p.d == 128) STEM_ATTN_LAUNCH(128, 128);
-    else if (p.B == 64 && p.d == 128) STEM_ATTN_LAUNCH(64, 128);
-    else if (p.B == 128 && p.d == 64) STEM_ATTN_LAUNCH(128, 64);
-    else if (p.B == 64 && p.d == 64) STEM_ATTN_LAUNCH(64, 64);
-    else if (p.B == 128 && p.d == 256) STEM_ATTN_LAUNCH(128, 256);
-    else if (p.B == 64 && p.d == 256) STEM_ATTN_LAUNCH(64, 256);
+    // One 16-query tile per wave, and twice the waves, where the chip has room for them: up to two rows per CU at B = 64, up to
+    // three per four CUs at B = 128, d = 128, one per CU at d = 64 (a CU's waves then read each LDS operand twice as often).
+    // Attention alone, lists of 8 % of the longest row's blocks and all of the short ones, one tile / two: B = 64, d = 128, 250 rows
+    // 21.2 / 22.9 us, 380 35.6 / 42.1, 500 51.3 / 55.3, 640 80.7 / 76.3; d = 64, 500 35.5 / 42.2, 640 53.4 / 52.5; B = 128, d = 128,
+    // 100 15.3 / 16.8, 250 41.4 / 40.7, 270 59.7 / 45.9; d = 64, 250 27.8 / 29.1, 270 42.0 / 31.9.  The bits are the same.
+    const int64_t cus = compute_units();
+    const bool narrow = p.B == 64 ? items <= 2 * cus : p.d == 128 ? 4 * items <= 3 * cus : items <= cus;
+    if (p.B == 128 && p.d == 128 && narrow) STEM_ATTN_LAUNCH(128, 128, 1);
+    else if (p.B == 128 && p.d == 128) STEM_ATTN_LAUNCH(128, 128, 2);
+    else if (p.B == 64 && p.d == 128 && narrow) STEM_ATTN_LAUNCH(64, 128, 1);
+    else if (p.B == 64 && p.d == 128) STEM_ATTN_LAUNCH(64, 128, 2);
+    else if (p.B == 128 && p.d == 64 && narrow) STEM_ATTN_LAUNCH(128, 64, 1);
+    else if (p.B == 128 && p.d == 64) STEM_ATTN_LAUNCH(128, 64, 2);
+    else if (p.B == 64 && p.d == 64 && narrow) STEM_ATTN_LAUNCH(64, 64, 1);
+    else if (p.B == 64 && p.d == 64) STEM_ATTN_LAUNCH(64, 64, 2);
+    else if (p.B == 128 && p.d == 256) STEM_ATTN_LAUNCH(128, 256, 2);
+    else if (p.B == 64 && p.d == 256) STEM_ATTN_LAUNCH(64, 256, 2);
     else return STEM_ERR_UNSUPPORTED;
 #undef STEM_ATTN_LAUNCH
     return check_launch();

@@ -123,3 +123,14 @@ def test_rows_of_a_batch_in_another_order(B, d, heads, lens):
     c.check_part(whole, [2])
     c.check_part(whole, sorted(range(len(lens)), key=lambda s: lens[s]))
     c.check_part(whole, [8, 1, 0], [(9, 12), (0, 1), (2, 5)])
+
+
+@pytest.mark.parametrize("B,d,heads,line", [(64, 128, 8, 2.0), (64, 64, 8, 2.0), (128, 128, 4, 0.75), (128, 64, 4, 1.0)])
+def test_rows_on_both_sides_of_the_line_between_wave_shapes(B, d, heads, line):
+    """Calls of at most `line` rows per CU run with half as many queries per wave: a call just above the line, the same rows
+    in one on it, and one row of it."""
+    blocks = int(line * torch.cuda.get_device_properties(0).multi_processor_count) // heads
+    c = Call(B, d, heads, 2, ((blocks + 1) * B - 3,), 40)
+    whole = c.attend([0])
+    c.check_part(whole, [0], [(1, blocks + 1)])
+    c.check_part(whole, [0], [(blocks, blocks + 1)])

@@ -845,9 +845,9 @@ __device__ __forceinline__ void sparse_attn_body_256(
 // and where the stream goes on to the next phase the wave waits for the requests that fill it and for the others to have
 // read what the next phase's requests overwrite: one barrier per half block.  These requests are issued during S^T.
 //
-// Before (32 x 32 x 16, softmax under the same block's products) / now, attention alone: 128K, 8 % of the blocks 9248 / 8807 us;
-// 32K, 15 % 1120 / 1064; 64K, 5 % 1345 / 1281; d = 64, 64K 1433 / 1386; B = 64, 100K tokens 7870 / 7696; 12 prompts to 2047
-// tokens 100.4 / 95.7.  128K in shader cycles: 1.441e7 / 1.470e7, at 1.49 / 1.60 GHz.
+// Before (32 x 32 x 16, softmax under the same block's products) / now, attention alone: 128K, 8 % of the blocks 9317 / 8605 us;
+// 64K, all 24842 / 22633; 32K, 15 % 1131 / 1050; 64K, 5 % 1346 / 1264; d = 64, 64K 1434 / 1364; B = 64, 100K tokens 7821 / 7716; 12 prompts to
+// 2047 tokens 100.9 / 93.2.  128K in shader cycles: 1.441e7 / 1.433e7, at 1.49 / 1.60 GHz.
 //
 // Every query's arithmetic is its 16-query tile's own: a reference moves for a tile at a time, and no step depends on
 // how many tiles share a wave.
@@ -999,10 +999,10 @@ __device__ __forceinline__ void sparse_attn_body(
         return u32x4_t{lo2.x, lo2.y, up2.x, up2.y};
     };
     // Operands are read this many ahead of their use, and used two at a time behind one wait.  Attention alone, 4 / 2 ahead:
-    // B = 64, 100K 8480 / 8185 us (requests early in both: 8047 / 7931), d = 64, 64K 1435 / 1431, 128K 8994 / 8998, 5 % 1317 / 1316.
-    // With one tile per wave an operand is used up in half the time: 4 / 6 / 8 ahead one head of 4096 (B = 64) 12.3 / 11.7 / 11.8,
-    // 25 rows of 12 blocks (B = 128) 35.8 / 35.7 / 34.9.
-    constexpr int kWanted = QW == 1 ? (B == 64 ? 6 : 8) : B == 64 || D == 64 ? 2 : 4;
+    // 128K 8716 / 8698 us, 5 % 1285 / 1279, 32K 1066 / 1064, B = 64 100K 7725 / 7687 (and six 3 to 4 % slower than four).  With one
+    // tile per wave an operand is used up in half the time: 4 / 6 / 8 ahead one head of 4096 (B = 64) 12.3 / 11.7 / 11.8, 25 rows of
+    // 12 blocks (B = 128) 35.8 / 35.7 / 34.9.
+    constexpr int kWanted = QW == 1 ? (B == 64 ? 6 : 8) : 2;
     constexpr int kAhead = kWanted < HS ? kWanted : HS;
     // The operand of S^T under which request u of a phase is issued, K's first.  B = 64 and d = 64, over all of S^T / its first
     // half: 100K 8185 / 7931 us, d = 64 1436 / 1431; 128K the other way round, 8994 / 9041.
@@ -1013,11 +1013,19 @@ __device__ __forceinline__ void sparse_attn_body(
     f32x4_t l_win[QW];                                 // row sums of the current half (four equal copies)
     float f0 = 0.f, f1 = 0.f;                          // the pair in flight
     const uint32_t one2 = 0x3f803f80u;
-    const u32x4_t ones = {one2, one2, one2, one2};
+    u32x4_t ones = {one2, one2, one2, one2};
+    // (kept in vector registers instead of moved there for every use: 128K 8698 / 8684 us, d = 64 1383 / 1377; B = 64 100K 7687 / 7740)
+    if constexpr (B == 128) asm volatile("" : "+v"(ones));
 
     // Step u % 4 of softmax pair u / 4 of half P: exponents, two exponentials, packing to bf16.  The row sums are taken from the
     // rounded values by the matrix pipe, a tile's 32 keys at a time: a product of the tile's P^T operand with ones, which
-    // gives every lane the sum of its own query.
+    // gives every lane the sum of its own query.  It is issued a step into the next pair (at the end of a run of pairs at once),
+    // so that it does not wait for the packing (128K 8684 / 8659 us).
+    auto row_sum = [&](auto P_tag, auto pair_tag) STEM_INLINE {     // of the four pairs that end with this one
+        constexpr int P = decltype(P_tag)::value, pair = decltype(pair_tag)::value, t = pair / (4 * QW), qt = (pair >> 2) % QW;
+        l_win[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ones), as_bf16x8(p_pk[P][t][qt]), t == 0 ? zero4 : l_win[qt],
+                                                           0, 0, 0);
+    };
     auto softmax_step = [&](auto P_tag, auto u_tag) STEM_INLINE {
         constexpr int P = decltype(P_tag)::value, u = decltype(u_tag)::value, pair = u >> 2;
         constexpr int t = pair / (4 * QW), qt = (pair >> 2) % QW, kt = (pair >> 1) & 1, x = (pair & 1) * 2;
@@ -1028,6 +1036,7 @@ __device__ __forceinline__ void sparse_attn_body(
             f1 = __builtin_fmaf(s_acc[P][t][kt][qt][x + 1], sl2, off[qt]);
             asm volatile("" : "+v"(f0), "+v"(f1));
         } else if constexpr ((u & 3) == 1) {
+            if constexpr ((pair & 3) == 0 && pair > 0 && pair != NP / 2) row_sum(P_tag, std::integral_constant<int, pair - 1>{});
             f0 = __builtin_amdgcn_exp2f(f0);
             asm volatile("" : "+v"(f0));
         } else if constexpr ((u & 3) == 2) {
@@ -1037,9 +1046,7 @@ __device__ __forceinline__ void sparse_attn_body(
             uint32_t pk = pack_bf16(f0, f1);
             asm volatile("" : "+v"(pk));
             p_pk[P][t][qt][pair & 3] = pk;
-            if constexpr ((pair & 3) == 3)
-                l_win[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ones), as_bf16x8(p_pk[P][t][qt]),
-                                                                   t == 0 ? zero4 : l_win[qt], 0, 0, 0);
+            if constexpr ((pair & 3) == 3 && (pair == NP - 1 || pair == NP / 2 - 1)) row_sum(P_tag, std::integral_constant<int, pair>{});
         }
     };
     // pairs first .. first + N - 1, one after the other
@@ -1116,6 +1123,9 @@ __device__ __forceinline__ void sparse_attn_body(
     // A half needs the slow path if a query has no reference yet or if its sum is not a modest finite number (a
     // probability above 2^16, inf, NaN: the reference is too low for this half).
     auto check_half = [&](auto P_tag) STEM_INLINE {
+        // (the last sum's product has been issued just before; across the branches of the masks, which may lie in between, the
+        // compiler kept four of the seven idle slots that its result needs)
+        if constexpr (QW == 1) asm volatile("s_nop 3" : "+v"(l_win[0]));
         bool high = !(l_win[0][0] <= 65536.0f);
         if constexpr (QW == 2) high |= !(l_win[1][0] <= 65536.0f);
         if (unseen || __builtin_amdgcn_ballot_w64(high) != 0) fix_half(P_tag);
@@ -1205,10 +1215,7 @@ __device__ __forceinline__ void sparse_attn_body(
         STEM_SCHED_FENCE();
     };
     u32x4_t ring[kAhead];                              // the first operands of the next phase
-    // Matrix instructions left free of softmax before the check, which reads the sums
-    constexpr int kReserve = QW * HS >= 8 ? 4 : 2;
-    using kUnderScores = std::integral_constant<int, QW * HS - kReserve>;
-    using kUnderOutputs = std::integral_constant<int, QW * HS>;
+    using kSpan = std::integral_constant<int, QW * HS>;    // matrix instructions of either product in a phase
 
     // One phase: half P of a block, and O^T of the half before it.  request(m): the requests under operand m.
     auto phase = [&](auto P_tag, int mask_from, bool mask_all, auto request) STEM_INLINE {
@@ -1230,7 +1237,7 @@ __device__ __forceinline__ void sparse_attn_body(
             if constexpr (m < HS) {
                 request(m);
                 scores(P_tag, m_tag, op[m & ~1], op[m | 1], [&](auto h) STEM_INLINE {
-                    softmax_under(Before{}, kHalf{}, kHalf{}, std::integral_constant<int, QW * m + decltype(h)::value>{}, kUnderScores{});
+                    softmax_under(Before{}, kHalf{}, kHalf{}, std::integral_constant<int, QW * m + decltype(h)::value>{}, kSpan{});
                 });
                 if constexpr (m == HS - 1) {
                     if (mask_from < KT) mask_half(P, mask_from, mask_all);
@@ -1239,7 +1246,7 @@ __device__ __forceinline__ void sparse_attn_body(
                 }
             } else {
                 outputs(Before{}, std::integral_constant<int, m - HS>{}, op[m & ~1], op[m | 1], [&](auto h) STEM_INLINE {
-                    softmax_under(P_tag, C0{}, kHalf{}, std::integral_constant<int, QW * (m - HS) + decltype(h)::value>{}, kUnderOutputs{});
+                    softmax_under(P_tag, C0{}, kHalf{}, std::integral_constant<int, QW * (m - HS) + decltype(h)::value>{}, kSpan{});
                 });
             }
         });
@@ -1352,7 +1359,7 @@ __device__ __forceinline__ void sparse_attn_body(
                     waited(a < HS ? kAhead : HS - m - 2);
                 }
                 scores(C1{}, m_tag, op[m & ~1], op[m | 1], [&](auto h) STEM_INLINE {
-                    softmax_under(C0{}, kHalf{}, kHalf{}, std::integral_constant<int, QW * m + decltype(h)::value>{}, kUnderScores{});
+                    softmax_under(C0{}, kHalf{}, kHalf{}, std::integral_constant<int, QW * m + decltype(h)::value>{}, kSpan{});
                 });
             });
             if (mask_from < KT) mask_half(1, mask_from, mask_all);
@@ -1362,7 +1369,7 @@ __device__ __forceinline__ void sparse_attn_body(
             for (int x = 0; x < 2 * QW * TP; ++x) asm volatile("" : "=v"(s_acc[1][x / (2 * QW)][(x / QW) & 1][x % QW]));
         }
         check_half(C0{});
-        output_half(C0{}, [&](auto at) STEM_INLINE { softmax_under(C1{}, C0{}, kAll{}, at, kUnderOutputs{}); });
+        output_half(C0{}, [&](auto at) STEM_INLINE { softmax_under(C1{}, C0{}, kAll{}, at, kSpan{}); });
         STEM_WAIT_VMCNT(0);
         STEM_BARRIER();                                // the second half of V is there
         if (second) {

@@ -18,9 +18,9 @@ LIB = os.path.join(PKG, "libstem_hip.so")
 
 SOURCES = ["stem_api.cpp", "stem_pool.hip", "stem_scores.hip", "stem_select.hip", "stem_attn.hip", "stem_static.hip"]
 
-# instantiations of sparse_attn_kernel: block sizes 64 and 128 times head sizes 64, 128 and 256, and at head sizes 64 and 128
-# the two numbers of queries per wave
-ATTENTION_KERNELS = 10
+# instantiations of sparse_attn_kernel: block sizes 64 and 128 times head sizes 64, 128 and 256 times the two numbers of
+# queries per wave
+ATTENTION_KERNELS = 12
 
 # -packed-fp32-ops: keep the compiler from forming v_pk_*_f32 out of plain float code.
 COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-I" + os.path.join(ROOT, "include"),
@@ -29,8 +29,9 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-I" + os.path.
 
 # Flags of single sources.  The attention kernels' rare branches (the softmax's slow path) are uniform over a wave; left out of
 # control-flow structurizing they stay plain branches.  Structurized, the value of every register that such a branch may change
-# was copied on the common path too, and the B = 128, d = 128 kernel spilled 79 registers.
-FLAGS = {"stem_attn.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions"]}
+# was copied on the common path too, and the B = 128, d = 128 kernel spilled 79 registers.  Results of the matrix instructions
+# that the compiler places stay in vector registers also in a kernel that uses accumulator registers by hand (head size 256).
+FLAGS = {"stem_attn.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions", "-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def hipcc() -> str:

@@ -6,25 +6,21 @@
 //     online softmax   exp2 domain, fp32
 //     O^T += V^T P^T   A = V^T rows read from row-major V in LDS with ds_read_b64_tr_b16,
 //                      B = P^T taken straight from the S^T accumulators
-// Computing the transposed products puts one query in one lane (and its partners at the same lane number modulo 16
-// or 32), so the softmax row reductions are in-lane plus an exchange between those lanes, and the S^T accumulator
+// Computing the transposed products puts one query in one lane (and its partners at the same lane number modulo 16),
+// so the softmax row reductions are in-lane plus an exchange between those lanes, and the S^T accumulator
 // registers are already in the B-operand layout of the second product.
 //
 // K and V blocks go from global memory straight into LDS (buffer_load ... lds, no staging registers).  Two workgroups
-// share a CU, so one workgroup's matrix work fills the other's waits (at head size 256 128 KiB of buffers and
-// about 490 registers leave room for one).
+// share a CU, so one workgroup's matrix work fills the other's waits (at head size 256 and B = 128 its 128 KiB of
+// buffers leave room for one).
 //
 // Long calls are bound by power: with all inputs zero the same launches take 0.7 of their time, at a clock of 2.4 instead of
 // 1.5 to 1.7 GHz.  What takes instructions, operand traffic or energy per operation out therefore shows in the run time,
 // and what only fills idle cycles shows less.
 //
-// Head sizes 64 and 128 (sparse_attn_body): matrix instruction 16x16x32, the three steps of half blocks pipelined.
-// Head size 256 (sparse_attn_body_256): 32x32x16, placed by hand.
-//
 // LDS layouts (rows of 2 D bytes, unpadded: the direct loads write 1 KiB contiguously): K has its
 // 16-byte chunks XORed with (row & 15), so the 16 rows a quarter-wave reads one chunk of spread
-// over all banks; V has its 32-byte groups (head size 256: 64-byte groups) XORed with row bits, which does the same for
-// the rows of a transposing read.  At D = 64 two 128-byte rows share the 64 banks, so the row's bit 0 is left out of the
+// over all banks; V has its 32-byte groups XORed with row bits, which does the same for the rows of a transposing read.  At D = 64 two 128-byte rows share the 64 banks, so the row's bit 0 is left out of the
 // terms.  The swizzle is applied on the global side (each lane fetches the chunk that belongs at its LDS position).
 #include <type_traits>
 #include <utility>
@@ -34,7 +30,6 @@
 namespace stem {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2_t;
@@ -78,10 +73,6 @@ __device__ __forceinline__ void unrolled(F&& f) {
 }
 #define STEM_INLINE __attribute__((always_inline))
 
-__device__ __forceinline__ int swap_bits_2_3(int x) {
-    return (x & ~12) | ((x & 4) << 1) | ((x & 8) >> 1);
-}
-
 // Workgroup barrier without the memory fence of __syncthreads (which would wait for every
 // outstanding global->LDS load); the waits are placed by hand.
 #define STEM_BARRIER()                              \
@@ -115,72 +106,30 @@ __device__ __forceinline__ void wait_lgkmcnt(int n) {   // n is a constant after
 // result land in other registers than the addend: over a branch that rescales O (the slow path of the softmax) it then
 // copied all of O, on the common path too.  What the compiler does not know for such an instruction is kept by the code
 // around it and checked in the finished assembly (wait_states.py): 8 issue slots before a vector access to the result.
+template <bool ACC>
 __device__ __forceinline__ void mfma_output(f32x4_t& c, u32x4_t a, u32x4_t b) {
-    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+    if constexpr (ACC) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+    else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
 }
 // Idle issue slots between the instructions that wrote o and vector instructions that touch it.  (Every register is named as
 // one that the wait modifies: only that dependence keeps the compiler from moving the others across it.)
-template <int N, int M, int Q>
+// (ACC: o lies in accumulator registers.)
+template <int N, bool ACC, int M, int Q>
 __device__ __forceinline__ void wait_states_output(f32x4_t (&o)[M][Q]) {
+    auto here = [&]() STEM_INLINE {
 #pragma unroll
-    for (int x = 0; x < M * Q; ++x) asm volatile("" : "+v"(o[x / Q][x % Q]));
-    asm volatile("s_nop %1" : "+v"(o[0][0]) : "n"(N - 1));
-#pragma unroll
-    for (int x = 0; x < M * Q; ++x) asm volatile("" : "+v"(o[x / Q][x % Q]));
+        for (int x = 0; x < M * Q; ++x) {
+            if constexpr (ACC) asm volatile("" : "+a"(o[x / Q][x % Q]));
+            else asm volatile("" : "+v"(o[x / Q][x % Q]));
+        }
+    };
+    here();
+    asm volatile("s_nop %0" : : "n"(N - 1));
+    here();
 }
 
-// Matrix instructions with the register file chosen by hand (head size 256).  A wave that may use
-// more than 256 registers has them in two halves: vector registers, which every instruction can
-// use, and accumulator registers, which only matrix instructions (and copies) can.  Left to itself
-// the compiler then puts the results of ALL matrix instructions of a function into accumulator
-// registers, also the S^T scores that the softmax has to read with vector instructions, and copies
-// them back and forth (about 400 copies per block at d = 256).  Written as inline assembly the
-// placement is ours: S^T results in vector registers, the O^T accumulators and the Q operands in
-// accumulator registers, no copy in the loop.  The price: the compiler no longer knows these are
-// matrix instructions, so the wait states it would insert are placed by hand where the instruction
-// order does not already guarantee them (the wait_states sites below): 12 issue slots between a
-// 32x32x16 product and a vector access to its result, 5 after a 4x4x4 one, 2 between a vector
-// write and a matrix instruction that reads it.  The build checks the finished assembly for these
-// distances (wait_states.py), since register allocation may add copies the source does not show.
-__device__ __forceinline__ void mfma_scores_first(f32x16_t& d, uint4 a, const u32x4_t& b) {
-    // (early clobber: the result registers must not be the ones an operand is still read from)
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(as_u32x4(a)), "a"(b));
-}
-__device__ __forceinline__ void mfma_scores(f32x16_t& d, uint4 a, const u32x4_t& b) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(as_u32x4(a)), "a"(b));
-}
-__device__ __forceinline__ void mfma_output_acc(f32x16_t& d, uint4 a, uint4 b) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(as_u32x4(a)), "v"(as_u32x4(b)));
-}
-// the first product into an O^T tile: nothing to add to, so no zero has to be written beforehand
-__device__ __forceinline__ void mfma_output_acc_first(f32x16_t& d, uint4 a, uint4 b) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=a"(d) : "v"(as_u32x4(a)), "v"(as_u32x4(b)));
-}
-// Pins a Q operand to accumulator registers where it is loaded.  (Given only the "a" constraint at
-// its uses, the compiler copies it there right before each use, and a matrix instruction may read
-// a register a vector instruction has written only two issue slots later.)
+// Pins a Q operand to accumulator registers where it is loaded (kAcc, sparse_attn_body).
 __device__ __forceinline__ void pin_to_acc(u32x4_t& x) { asm volatile("" : "+a"(x)); }
-// the row-sum product; its B operand has just been written by a vector instruction (2 wait states)
-__device__ __forceinline__ void mfma_row_sum(f32x4_t& d, uint2 ones, uint2 four) {
-    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-    asm volatile("s_nop 1\n\tv_mfma_f32_4x4x4_16b_bf16 %0, %1, %2, %0"
-                 : "+v"(d)
-                 : "v"(u32x2_t{ones.x, ones.y}), "v"(u32x2_t{four.x, four.y}));
-}
-// Idle issue slots (4 cycles each): what separates a matrix instruction's write from a dependent
-// vector access when nothing else does.  Each form names the registers it protects as operands it
-// "modifies": only that data dependence keeps the compiler from moving the dependent instructions
-// to the other side of the wait.
-template <int N, typename R>
-__device__ __forceinline__ void wait_states_v(R& r) {  // r: a result in vector registers
-    asm volatile("s_nop %1" : "+v"(r) : "n"(N - 1));
-}
-template <int N>
-__device__ __forceinline__ void wait_states_acc(f32x16_t (&o)[8]) {   // o: the O^T accumulators
-    asm volatile("s_nop %8"
-                 : "+a"(o[0]), "+a"(o[1]), "+a"(o[2]), "+a"(o[3]), "+a"(o[4]), "+a"(o[5]), "+a"(o[6]), "+a"(o[7])
-                 : "n"(N - 1));
-}
 
 // One 1 KiB slice (1024 / 2D rows) of a B x D bf16 block, global -> LDS.  A block is D / 16 slices
 // per wave: wave w issues slices u*NW + w, so that the row's swizzle term depends on u with a short
@@ -216,74 +165,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t sequence_resource(const uint16
     const int64_t bytes = rows > 0 ? (int64_t)(rows - 1) * row_bytes + head_bytes : 0;   // < 2^31 (host check)
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(first_row), 0, (int)bytes, 0x00020000);
 }
-
-// Head size 256: when the softmax pairs of a block are issued and where its reference may be checked, for KT
-// 32-key tiles per block and KS = D / 16 matrix instructions per S^T tile.  Slot s = 0 .. 2*NS-1
-// counts the wave's matrix instructions of one block (S^T first, then O^T).  Pair q = 8*t + x/2 may
-// be issued once tile t of S^T is complete (slot KS*t + KS - 1) and must be done before O^T reaches
-// its 16 keys (slot NS + DT*(2t + (q%8)/4), DT = KS / 2 instructions per 16-key step).  At a check
-// slot every pair issued so far must be either consumed by O^T already or part of the window being
-// checked (the pairs issued since the previous check), so that moving the reference there leaves
-// no stale probability behind.  valid() states exactly that and is asserted at compile time.
-template <int KT, int KS>
-struct SoftmaxSchedule {
-    static constexpr int NS = KT * KS;                 // matrix instructions per product and block
-    static constexpr int DT = KS / 2;                  // matrix instructions per 16-key step of O^T
-    static constexpr int NP = KT * 8;                  // accumulator pairs per block and lane
-    static constexpr int kChecks = 2;
-    static constexpr int kMaxPerSlot = 1;
-    // The reference is checked when O^T starts (tiles 0 .. KT-2 issued, nothing consumed) and when
-    // O^T reaches the last tile (its pairs issued, all others consumed).
-    static constexpr int check_slot(int c) { return c == 0 ? NS : NS + KS * (KT - 1); }
-    // slot after whose matrix instruction pair q is issued: the eight pairs of tile t are spread over
-    // the KS slots that follow the tile's completion.  The matrix instructions are
-    // placed by hand: a tile's first pair keeps kLead + 1 matrix instructions (and the operand wait of
-    // every second one) between itself and the instruction that completed the tile: the 12 issue
-    // slots after which that instruction's result may be read by a vector instruction.
-    static constexpr int kLead = 7;
-    static constexpr int issue_slot(int q) { return (q / 8 + 1) * KS + kLead + ((q % 8) * (KS - kLead)) / 8; }
-    // slot of the O^T instruction that first consumes pair q
-    static constexpr int use_slot(int q) { return NS + DT * (2 * (q / 8) + (q % 8) / 4); }
-    // pairs issued once slot `slot` is issued
-    static constexpr int pairs_by(int slot) {
-        int n = 0;
-        for (int q = 0; q < NP; ++q) n += issue_slot(q) <= slot ? 1 : 0;
-        return n;
-    }
-    static constexpr bool valid() {
-        for (int s = 0; s < 2 * NS; ++s) {
-            const int before = s == 0 ? 0 : pairs_by(s - 1), now = pairs_by(s);
-            if (now < before || now > before + kMaxPerSlot) return false;
-            for (int q = before; q < now; ++q) {
-                if (s <= KS * (q / 8) + KS - 1) return false;                // its S^T tile is complete
-                if (s >= use_slot(q)) return false;                          // O^T has not reached it
-            }
-        }
-        int lo = 0;
-        for (int c = 0; c < kChecks; ++c) {
-            const int slot = check_slot(c);
-            if (slot < NS || slot % DT) return false;
-            if (pairs_by(slot - 1) % 2) return false;        // the row sums are taken two pairs at a time
-            if (lo > 4 * ((slot - NS) / DT)) return false;   // pairs below the window are consumed (4 per step)
-            for (int q = lo; q < pairs_by(slot - 1); ++q)
-                if (use_slot(q) < slot) return false;        // pairs of the window are not consumed yet
-            lo = pairs_by(slot - 1);
-        }
-        return lo == NP && pairs_by(2 * NS - 1) == NP;
-    }
-    // pairs_by as a table (entry slot + 1; entry 0 stands for "before slot 0"), so that the unrolled
-    // kernel indexes registers with literal constants
-    struct Table {
-        int v[2 * NS + 1];
-    };
-    static constexpr Table make_table() {
-        Table t{};
-        for (int s = 0; s < 2 * NS; ++s) t.v[s + 1] = pairs_by(s);
-        return t;
-    }
-    static constexpr Table kTable = make_table();
-};
-static_assert(SoftmaxSchedule<4, 16>::valid() && SoftmaxSchedule<2, 16>::valid(), "softmax schedule, d = 256");
 
 // The order in which the query-block rows of a packed batch are handed out (launch_sparse_attn says when): the
 // sequences by the length of their longest list's bound (the block index of the last row), longest first, and a
@@ -408,428 +289,7 @@ __device__ __forceinline__ bool find_row(const SeqTable& seq, const RowWalk& wal
     return true;
 }
 
-// The body takes the two LDS buffers as __restrict__ parameters: once inlined, every access carries
-// alias-scope information, which lets the compiler's wait-count insertion tell a read of one buffer
-// from an in-flight global->LDS load into the other (otherwise it waits for all of them).
-//
-// Head size 256.  Products of 32 x 32 x 16: one query per lane.  K and V have a buffer each, refilled in split phases behind
-// two barriers per block: the V block is requested while S^T starts and must have landed when S^T ends; the next K block
-// is requested during O^T and must have landed when the next block starts.  The softmax of a block is spread pair by
-// pair over the wave's own matrix instructions (the eight pairs of a 32-key tile under the matrix instructions that follow the
-// tile).  A wave has its SIMD for itself: with products of 16 x 16 x 32 and half blocks pipelined, as at the other sizes, calls
-// that fill the chip take the same time (32K, 15 % density: 2370 / 2373 us) and small ones more (51 / 58 us: twice the
-// matrix instructions, and nobody else to issue in between).
-template <int B>
-__device__ __forceinline__ void sparse_attn_body_256(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-    const int32_t* __restrict__ counts, const int32_t* __restrict__ indices, uint16_t* __restrict__ out,
-    float* __restrict__ lse, const RowPlace& row, int R, int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh,
-    int64_t kv_st, int64_t kv_sh, float scale, unsigned char* __restrict__ k_lds, unsigned char* __restrict__ v_lds) {
-    constexpr int D = 256;
-    const int g = row.g, h = row.h, r = row.r, i = row.i, seq_lo = row.seq_lo, seq_hi = row.seq_hi, tok_q0 = row.tok_q0,
-              q_hi = row.q_hi;
-    constexpr int KT = B / 32;                         // 32-key tiles per block
-    constexpr int KS = D / 16;                         // 16-wide steps of S^T along d; also requests per wave, tensor and block
-    constexpr int DT = D / 32;                         // 32-row tiles of O^T along d
-    constexpr int NW = B / 32;                         // waves
-    constexpr int kRowBytes = D * 2;                   // one K or V row in LDS
-    constexpr int kSliceRows = 1024 / kRowBytes;       // rows one wave-wide 1 KiB request covers
-    // LDS swizzles, as XORs on the 16-byte chunk index of a row: K spreads the 16 rows a quarter-wave
-    // reads one chunk of over all banks, V the 4 rows x 32 bytes of a transposing read
-    auto k_swz = [](int row) { return row & 15; };
-    auto v_swz = [](int row) { return (row & 3) << 2; };
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int col = lane & 31, hi = lane >> 5;
-    const int qrow = w * 32 + col;                     // query row inside the block
-    const int tok_q = tok_q0 + qrow;
-
-    const int lh = shared_lists ? g : h;               // whose list: the KV head's or the query head's
-    const int64_t list_row = (int64_t)lh * R + r;
-    const int32_t* list = indices + list_row * kmax;
-    // the first 64 entries without waiting for the count (a row has room for kmax; what lies beyond the count is
-    // clamped where it is used as an address, and never used otherwise)
-    int list_reg = lane < kmax ? list[lane] : 0;
-    const int cnt = min(counts[list_row], kmax);
-
-    // ---- Q rows of this wave as B operands: KS k-steps of 16 along d.  Queries past the end repeat the
-    //      last one (no branch around a load); what they give is not stored ----
-    u32x4_t q_acc[KS];
-    {
-        const uint16_t* src = q + (int64_t)min(tok_q, q_hi - 1) * q_st + (int64_t)h * q_sh + hi * 8;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            q_acc[ks] = as_u32x4(*reinterpret_cast<const uint4*>(src + ks * 16));
-            pin_to_acc(q_acc[ks]);
-        }
-    }
-
-    const uint16_t* k_head = k + (int64_t)g * kv_sh;
-    const uint16_t* v_head = v + (int64_t)g * kv_sh;
-
-    // per-lane byte offsets of the block requests (BlockRequest): slice u of wave w is the 1 KiB at
-    // LDS offset (u NW + w) KiB; lane l writes chunk pc of row (u NW + w) kSliceRows + slice_row there
-    // and fetches the chunk that belongs at that position, i.e. the swizzle is applied to the global
-    // column.  Only the low bits of the row enter the swizzle, so it repeats in u with a short period.
-    const int64_t row_bytes = kv_st * 2;
-    const int slice_row = (lane * 16) / kRowBytes, pc = ((lane * 16) % kRowBytes) >> 4;
-    const int lrow = w * kSliceRows + slice_row;       // row of slice u = 0
-    const uint32_t lane_row_off = (uint32_t)(lrow * row_bytes);
-    constexpr int kKVariants = B == 128 ? 2 : 4;
-    static_assert((kKVariants * NW * kSliceRows) % 16 == 0, "the K swizzle term of slice u repeats with period kKVariants");
-    static_assert((NW * kSliceRows) % 4 == 0, "the V swizzle term does not depend on the slice");
-    uint32_t k_off[kKVariants];
-#pragma unroll
-    for (int x = 0; x < kKVariants; ++x) k_off[x] = lane_row_off + ((pc ^ k_swz(lrow + x * NW * kSliceRows)) << 4);
-    const uint32_t v_off = lane_row_off + ((pc ^ v_swz(lrow)) << 4);   // NW kSliceRows is a multiple of 4
-    const auto k_rsrc = sequence_resource(k_head + (int64_t)seq_lo * kv_st, seq_hi - seq_lo, row_bytes, kRowBytes);
-    const auto v_rsrc = sequence_resource(v_head + (int64_t)seq_lo * kv_st, seq_hi - seq_lo, row_bytes, kRowBytes);
-    const uint32_t block_bytes = (uint32_t)(B * row_bytes);
-    const uint32_t slice_step = (uint32_t)(NW * kSliceRows * row_bytes);   // rows of slices u and u+1 of one wave
-    constexpr int slice_lds_step = NW * 1024;
-    // !real: an offset beyond any sequence, so that nothing is fetched (zeros land in LDS)
-    auto k_request = [&](int j, bool real) {
-        const uint32_t off = real ? j * block_bytes : 0x80000000u;
-        BlockRequest<kKVariants> rq{k_rsrc, {}};
-#pragma unroll
-        for (int x = 0; x < kKVariants; ++x) rq.lane_off[x] = k_off[x] + off;
-        return rq;
-    };
-    auto v_request = [&](int j) {
-        const uint32_t off = j * block_bytes;
-        return BlockRequest<1>{v_rsrc, {v_off + off}};
-    };
-    unsigned char* k_slice0 = k_lds + w * 1024;        // this wave's first request slice
-    unsigned char* v_slice0 = v_lds + w * 1024;
-
-    // List entries outside 0..i break the precondition; they are processed as fully masked
-    // blocks (clamped for addressing), which costs time but keeps the control flow flat.
-    auto usable = [&](int j) { return j >= 0 && j <= i; };
-    auto clamped = [&](int j) { return min(max(j, 0), i); };
-    // The list lives in a vector register, 64 entries at a time (lane e holds entry e of the
-    // chunk), and entries are taken out with v_readlane: no scalar load sits in the loop, so the
-    // in-order LDS operand reads are the only users of their counter there.
-    auto list_chunk = [&](int first) { return first + lane < cnt ? list[first + lane] : 0; };
-    int j_cur = __builtin_amdgcn_readlane(list_reg, 0);
-    {                                                  // (an empty list: a block that nothing uses)
-        const auto rq = k_request(clamped(j_cur), true);
-#pragma unroll
-        for (int u = 0; u < KS; ++u) rq.issue(u, k_slice0, slice_step, slice_lds_step);
-    }
-
-    // The output pointers are taken now: a scalar load still in flight would make every wait for LDS operands in the
-    // blocks one for all of them (the two kinds return in any order on one counter).
-    asm volatile("" : : "s"(out), "s"(lse));
-
-    f32x16_t o_acc[DT];                                // the first block's products start it
-    const float neg_inf = -__builtin_huge_valf();
-    float m_ref = neg_inf;                             // softmax reference (raw score units)
-    float l_run = 0.f;                                 // softmax sum of the query over this lane's keys
-    const float sl2 = scale * 1.4426950408889634f;
-
-    // per-lane LDS offsets that do not change between blocks.  Both swizzles are XORs of address
-    // bits that are zero in the unswizzled per-lane offset, so the offset of operand n is one
-    // v_xor of a per-lane base with a constant, plus an immediate.
-    const int k_row = swap_bits_2_3(col);              // + t*32, which leaves the swizzle term alone
-    const uint32_t k_base0 = k_row * kRowBytes + ((k_swz(k_row) ^ hi) << 4);
-    // transposing V read: lane l fetches row key0 + 8*hi + (l%16)/4 (+4), 8 bytes at column
-    // dt*32 + 16*((l>>4)&1) + 4*(l&3); the 64-byte group index dt is XORed with (row & 3)
-    const int v_row = hi * 8 + ((lane & 15) >> 2);     // key0 and the +4 leave the swizzle term alone
-    const uint32_t v_base0 = v_row * kRowBytes + (v_swz(v_row) << 4) + (((lane >> 4) & 1) << 5) + ((lane & 3) << 3);
-    const uint32_t k_base = k_base0, v_base = v_base0;
-
-    // Operand n of S^T (matrix instruction n: key tile n/KS, 16-wide step n%KS along d; the lane's
-    // 16-byte chunk is 2*(n%KS) + hi) and of O^T (matrix instruction n: 16-key step n/DT, d tile n%DT).
-    auto load_k = [&](int n) {
-        const int t = n / KS, ks = n % KS;
-        return *reinterpret_cast<const uint4*>(k_lds + (k_base ^ (ks << 5)) + t * 32 * kRowBytes);
-    };
-    auto load_v = [&](int n) {
-        const int step = n / DT, dt = n % DT;
-        const unsigned char* p0 = v_lds + (v_base ^ (dt << 6)) + step * 16 * kRowBytes;
-        const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p0);
-        const s16x4_t up = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(p0 + 4 * kRowBytes));
-        const uint2 lo2 = __builtin_bit_cast(uint2, lo), up2 = __builtin_bit_cast(uint2, up);
-        return make_uint4(lo2.x, lo2.y, up2.x, up2.y);
-    };
-    // Operands travel through a ring of kSlots registers, read kAhead matrix instructions before
-    // their use: the loaded LDS latency is several matrix instructions long.  They are consumed
-    // two at a time behind one wait (every instruction, waits included, takes an issue slot of
-    // the wave).  An O^T operand is two reads, and at most 15 reads can be counted in flight.
-    constexpr int kAhead = 4, kSlots = kAhead + 2;
-
-    // The softmax of a block is 8*KT accumulator pairs per lane.  Vector and matrix instructions
-    // of the SAME wave overlap well, those of two waves sharing a SIMD do not, so the pairs are
-    // spread over the wave's own matrix instructions (SoftmaxSchedule).
-    using Sched = SoftmaxSchedule<KT, KS>;
-    constexpr int NS = Sched::NS;
-    auto pairs_by = [](int slot) { return Sched::kTable.v[slot + 1]; };
-    constexpr int kCheckSlot[2] = {Sched::check_slot(0), Sched::check_slot(1)};
-
-    f32x16_t s_acc[KT];
-    uint32_t p_pk[KT][8];                              // bf16 pairs: [tile][16-key step * 4 + pair]
-    f32x4_t l_win = {0.f, 0.f, 0.f, 0.f};              // row sum of the current window (four equal copies)
-    float off = 0.f;                                   // reference in exp2 units; changes on the slow path only
-
-    // softmax of pair q (tile q/8, accumulators 2*(q%8) and +1): exp2 domain, reference m_ref,
-    // packed to bf16.  The row sum is taken from the rounded values by the matrix pipe: in
-    // v_mfma_f32_4x4x4_16B_bf16 lane l supplies column l % 4 of block l / 4 of B (four values along the contraction, two
-    // pairs) and receives that column of the 4 x 4 result, so with A = ones every lane gets the sum of its own four
-    // values, in each of its four result registers.
-    auto softmax_pair = [&](int q) {
-        const int t = q >> 3, x = (q & 7) * 2;
-        // hand-placed form: a matrix result may be read 12 issue slots after its instruction; the
-        // schedule keeps that many instructions in between (kLead), two more for margin
-        static_assert(Sched::kLead + 1 + (Sched::kLead + 1) / 2 >= 12, "S^T -> softmax distance");
-        if ((q & 7) == 0) wait_states_v<2>(s_acc[t]);
-        const float p0 = __builtin_amdgcn_exp2f(s_acc[t][x] * sl2 - off);
-        const float p1 = __builtin_amdgcn_exp2f(s_acc[t][x + 1] * sl2 - off);
-        uint32_t pk = pack_bf16(p0, p1);
-        // An opaque use of the result at this point of the instruction stream: without it the
-        // compiler gathers the softmax next to the consumer of the results instead of leaving
-        // each pair next to "its" matrix instruction.
-        asm volatile("" : "+v"(pk));
-        p_pk[t][q & 7] = pk;
-        if (q & 1)
-            mfma_row_sum(l_win, make_uint2(0x3f803f80u, 0x3f803f80u), make_uint2(p_pk[t][(q & 7) - 1], pk));
-    };
-    auto softmax_slot = [&](int slot) {                // one pair per slot at most
-#pragma unroll
-        for (int q = pairs_by(slot - 1); q < pairs_by(slot); ++q) softmax_pair(q);
-    };
-    auto window_sum = [&]() {
-        wait_states_v<6>(l_win);                       // after the window's last row-sum product
-        return l_win[0];
-    };
-    auto clear_sum = [&]() { l_win = f32x4_t{0.f, 0.f, 0.f, 0.f}; };
-    auto sums_finite = [&]() { return __builtin_amdgcn_ballot_w64(!(window_sum() < -neg_inf)) == 0; };
-    // exp2-domain offset of the reference; a query that has seen nothing yet (m_ref = -inf) uses 0,
-    // which keeps its masked scores at exp2(-inf) = 0
-    auto reference_offset = [&]() { return m_ref == neg_inf ? 0.f : m_ref * sl2; };
-    // Largest score of the query in pairs [q_lo, q_hi) (both of its lanes get it)
-    auto lane_max = [&](int q_lo, int q_hi) {          // of this lane's keys
-        float mx4[4] = {neg_inf, neg_inf, neg_inf, neg_inf};
-#pragma unroll
-        for (int q = q_lo; q < q_hi; ++q)
-            mx4[q & 3] = max3(mx4[q & 3], s_acc[q >> 3][(q & 7) * 2], s_acc[q >> 3][(q & 7) * 2 + 1]);
-        return max3(max3(mx4[0], mx4[1], mx4[2]), mx4[3], mx4[3]);
-    };
-    auto both_lanes_max = [&](float mx) {
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-        return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-    };
-    auto window_max = [&](int q_lo, int q_hi) { return both_lanes_max(lane_max(q_lo, q_hi)); };
-    // Moves the references of the wave's queries up to mx (rescaling O and l) where that is higher, and starts the
-    // window's sum anew.  Where sums are not finite only if a query gains by it: one that has no reference, or
-    // probabilities far beyond its own (a sum over 2^16 of 128 keys at most holds one over 2^9), and a finite score to go
-    // to.  A query that is NaN or inf for good comes here with every window and leaves the others as they are.
-    auto raise_reference = [&](float mx, bool finite) {
-        if (!finite) {
-            const bool gains = mx < -neg_inf && mx > m_ref && (m_ref == neg_inf || mx * sl2 - off > 8.9f);
-            finite = __builtin_amdgcn_ballot_w64(gains) != 0;
-        }
-        if (finite && mx > m_ref) {
-            const float corr = (m_ref == neg_inf) ? 0.f : __builtin_amdgcn_exp2f((m_ref - mx) * sl2);
-            m_ref = mx;
-            l_run *= corr;
-            wait_states_acc<16>(o_acc);                // the last O^T instruction has written
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int x = 0; x < 16; ++x) o_acc[dt][x] *= corr;
-            wait_states_acc<4>(o_acc);                 // before the next one reads them
-        }
-        off = reference_offset();
-        asm volatile("" : "+v"(off));                  // not folded into the exponentials: the bits of the common path
-        clear_sum();
-    };
-    // Slow path for the window of pairs [q_lo, q_hi): take their true maximum, move the reference
-    // up to it, and recompute the window's probabilities.
-    auto fix_window = [&](int q_lo, int q_hi) {
-        const bool finite = sums_finite();
-        raise_reference(window_max(q_lo, q_hi), finite);
-#pragma unroll
-        for (int q = q_lo; q < q_hi; ++q) softmax_pair(q);
-    };
-    // The first window of a row, pairs [0, q_hi): O and l are still zero, so there is nothing to
-    // rescale; a query that sees none of the window's keys keeps m_ref = -inf (offset 0, zero
-    // probabilities) and gets its reference from a later window's slow path.
-    auto first_window = [&](int q_hi) {
-        m_ref = window_max(0, q_hi);
-        off = reference_offset();
-        clear_sum();
-#pragma unroll
-        for (int q = 0; q < q_hi; ++q) softmax_pair(q);
-        l_run += window_sum();
-        clear_sum();
-    };
-    // A window needs the slow path if a query has no reference yet (nothing visible to it so far:
-    // every query on the first block) or if its sum is not a modest finite number (a probability
-    // above 2^16, inf, NaN: the reference is too low for this window).
-    auto needs_fix = [&](float sum) {
-        return __builtin_amdgcn_ballot_w64(m_ref == neg_inf || !(sum <= 65536.0f)) != 0;
-    };
-    auto check_window = [&](int c) {                   // at slot boundary kCheckSlot[c]
-        const int q_lo = c == 0 ? 0 : pairs_by(kCheckSlot[c - 1] - 1), q_hi = pairs_by(kCheckSlot[c] - 1);
-        if (needs_fix(window_sum())) fix_window(q_lo, q_hi);
-        l_run += window_sum();
-        clear_sum();
-    };
-    // accumulator x of tile t is key t*32 + 16*(x/8) + 8*hi + x%8 of the block
-    auto mask_tile = [&](int t, int limit) {
-        wait_states_v<16>(s_acc[t]);                   // the tile's last matrix instruction has written
-#pragma unroll
-        for (int x = 0; x < 16; ++x)
-            if (t * 32 + 16 * (x >> 3) + (x & 7) > limit) s_acc[t][x] = neg_inf;
-    };
-
-    // The matrix instruction of S^T under which request u of V is issued, and of O^T for the next K.  At B = 64 a
-    // product lasts only 32 of them, about the latency of a block that comes from beyond the L2, so requests go out at the
-    // start; at B = 128 they are spread, which leaves the LDS reads alone, to the middle of S^T and two thirds of O^T.
-    // Attention alone, spread over the first half of S^T and all of O^T / this: B = 64, 64K tokens 5198 / 4745 us; B = 128,
-    // everything at the start 7 % slower.
-    auto v_slot = [](int u) { return B == 128 ? 2 * u : u; };
-    auto k_slot = [](int u) { return B == 128 ? 3 * u + 1 : u / 2; };
-    static_assert(2 * (KS - 1) < NS && 3 * (KS - 1) + 1 < 4 * KS, "every request has a slot");
-    const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-
-    // One listed block.  The first block of a row is a version of its own (first_tag = true): no
-    // query has a reference yet, so the probabilities of the first window cannot be formed under
-    // the S^T products; they are formed once, at the first check point, from the window's maximum.
-    auto one_block = [&](int it, auto first_tag) {
-        constexpr bool kFirst = decltype(first_tag)::value;
-        const int j = clamped(j_cur);
-        const bool has_next = it + 1 < cnt;
-        if (((it + 1) & 63) == 0) list_reg = list_chunk(it + 1);
-        // on the diagonal block keys above the query are masked, which spares the tiles before the wave's own;
-        // an unusable entry is masked entirely
-        const int mask_from = !usable(j_cur) ? 0 : j == i ? w : KT;
-        const int mask_limit = usable(j_cur) ? qrow - 8 * hi : -1;
-
-        STEM_WAIT_VMCNT(0);
-        STEM_BARRIER();                                // K(j) is in LDS; V buffer is free
-
-        // ---- S^T = K Q^T, with the V requests in between ----
-        uint4 ka[kSlots];
-#pragma unroll
-        for (int n = 0; n < kAhead; ++n) {
-            ka[n] = load_k(n);
-            if (n & 1) STEM_SCHED_FENCE();             // in the order of their use
-        }
-        const auto v_rq = v_request(j);
-        // (past the count any value: what lies in the list's row there.  Only to be used clamped, and with has_next)
-        const int j_nxt = __builtin_amdgcn_readlane(list_reg, (it + 1) & 63);
-        clear_sum();
-        STEM_SCHED_FENCE();
-#pragma unroll
-        for (int t = 0; t < KT; ++t) {
-#pragma unroll
-            for (int n = t * KS; n < t * KS + KS; ++n) {
-                if ((n & 1) == 0) {
-                    if (n + kAhead < NS) ka[(n + kAhead) % kSlots] = load_k(n + kAhead);
-                    if (n + kAhead + 1 < NS) ka[(n + kAhead + 1) % kSlots] = load_k(n + kAhead + 1);
-                    wait_lgkmcnt((n + kAhead + 2 < NS ? kAhead + 2 : NS - n) - 2);
-                }
-#pragma unroll
-                for (int u = 0; u < KS; ++u)
-                    if (v_slot(u) == n) v_rq.issue(u, v_slice0, slice_step, slice_lds_step);
-                if ((n % KS) == 0) mfma_scores_first(s_acc[t], ka[n % kSlots], q_acc[n % KS]);
-                else mfma_scores(s_acc[t], ka[n % kSlots], q_acc[n % KS]);
-                if constexpr (!kFirst) {
-                    if (n >= KS) STEM_SCHED_FENCE();   // the matrix instruction first
-                    softmax_slot(n);
-                }
-                STEM_SCHED_FENCE();
-            }
-            if (t >= mask_from) mask_tile(t, mask_limit);
-        }
-
-        STEM_WAIT_VMCNT(0);
-        STEM_BARRIER();                                // every wave is done with K(j); V(j) is in LDS
-
-        // ---- O^T += V^T P^T, with the next block's K requests in between; after the last block they
-        //      are empty (an offset beyond the resource: nothing is fetched) ----
-        uint4 va[kSlots];
-#pragma unroll
-        for (int n = 0; n < kAhead; ++n) {
-            va[n] = load_v(n);
-            if (n & 1) STEM_SCHED_FENCE();
-        }
-        const auto k_rq = k_request(clamped(j_nxt), has_next);
-        STEM_SCHED_FENCE();
-        auto pv_range = [&](int n_lo, int n_hi) {      // even bounds
-#pragma unroll
-            for (int n = n_lo; n < n_hi; ++n) {
-                if ((n & 1) == 0) {
-                    if (n + kAhead < NS) va[(n + kAhead) % kSlots] = load_v(n + kAhead);
-                    wait_lgkmcnt(2 * ((n + kAhead + 1 < NS ? kAhead + 1 : NS - n) - 2));
-                } else {
-                    if (n + kAhead < NS) va[(n + kAhead) % kSlots] = load_v(n + kAhead);
-                }
-#pragma unroll
-                for (int u = 0; u < KS; ++u)
-                    if (k_slot(u) == n) k_rq.issue(u, k_slice0, slice_step, slice_lds_step);
-                const int g2 = n / DT, t = g2 >> 1, u = g2 & 1, dt = n % DT;
-                const uint4 pb = make_uint4(p_pk[t][u * 4], p_pk[t][u * 4 + 1], p_pk[t][u * 4 + 2], p_pk[t][u * 4 + 3]);
-                if (kFirst && n < DT) mfma_output_acc_first(o_acc[dt], va[n % kSlots], pb);
-                else mfma_output_acc(o_acc[dt], va[n % kSlots], pb);
-                STEM_SCHED_FENCE();
-                softmax_slot(NS + n);
-                STEM_SCHED_FENCE();
-            }
-        };
-        if constexpr (kFirst) first_window(pairs_by(kCheckSlot[0] - 1));
-        else check_window(0);
-        pv_range(0, kCheckSlot[1] - NS);
-        check_window(1);
-        pv_range(kCheckSlot[1] - NS, NS);
-        j_cur = j_nxt;
-    };
-    int it = 0;
-    if (cnt > 0) {
-        one_block(it++, std::true_type{});
-    } else {
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) o_acc[dt] = zero16;
-    }
-    for (; it < cnt; ++it) one_block(it, std::false_type{});
-    STEM_WAIT_VMCNT(0);                                // no request may outlive the workgroup's LDS
-    wait_states_acc<16>(o_acc);                        // the last O^T instructions have written
-
-    // ---- normalise and store: accumulator x of d tile dt is column dt*32 + 8*(x/4) + 4*hi + x%4 ----
-    const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
-    const float l_tot = __uint_as_float(halves[0]) + __uint_as_float(halves[1]);   // each lane has summed its own half of the keys
-    const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-    // A lane holds four columns of every group of eight (the other four sit in lane ^ 32).  Two
-    // groups at a time, one half-wave swap per packed register gives each lane eight consecutive
-    // columns, i.e. 16-byte stores.  (The swap runs in every lane, valid query or not.)
-    uint4 packed[DT][2];
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int m = 0; m < 2; ++m) {
-            const int xa = m * 8, xb = m * 8 + 4;      // accumulators of groups 2m and 2m+1
-            const uint32_t a0 = pack_bf16(o_acc[dt][xa + 0] * inv, o_acc[dt][xa + 1] * inv);
-            const uint32_t a1 = pack_bf16(o_acc[dt][xa + 2] * inv, o_acc[dt][xa + 3] * inv);
-            const uint32_t b0 = pack_bf16(o_acc[dt][xb + 0] * inv, o_acc[dt][xb + 1] * inv);
-            const uint32_t b1 = pack_bf16(o_acc[dt][xb + 2] * inv, o_acc[dt][xb + 3] * inv);
-            const auto s0 = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
-            const auto s1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
-            packed[dt][m] = make_uint4(s0[0], s1[0], s0[1], s1[1]);
-        }
-    if (tok_q < q_hi) {
-        uint16_t* dst = out + (int64_t)tok_q * q_st + (int64_t)h * q_sh + hi * 8;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int m = 0; m < 2; ++m) *reinterpret_cast<uint4*>(dst + dt * 32 + m * 16) = packed[dt][m];
-        if (lse != nullptr && hi == 0)
-            lse[(int64_t)h * T + tok_q] = l_tot > 0.f ? m_ref * scale + __logf(l_tot) : neg_inf;
-    }
-}
-
-// Head sizes 64 and 128.  Products of 16 x 16 x 32: at the power limit this instruction gives a ninth more operations per
+// Products of 16 x 16 x 32: at the power limit this instruction gives a ninth more operations per
 // second than 32 x 32 x 16 (registers only 2020 / 1800 TFLOP/s, with the LDS reads and exponentials of this kernel beside it
 // 1710 / 1540; with all inputs zero both reach 2440), and with two tiles of 16 queries per wave an LDS operand feeds as many
 // operations.  Lane l has query l % 16 of each of the wave's QW tiles and, of 16 keys, the four from 4 (l / 16) on; two such
@@ -848,6 +308,15 @@ __device__ __forceinline__ void sparse_attn_body_256(
 // Before (32 x 32 x 16, softmax under the same block's products) / now, attention alone: 128K, 8 % of the blocks 9317 / 8605 us;
 // 64K, all 24842 / 22633; 32K, 15 % 1131 / 1050; 64K, 5 % 1346 / 1264; d = 64, 64K 1434 / 1364; B = 64, 100K tokens 7821 / 7716; 12 prompts to
 // 2047 tokens 100.9 / 93.2.  128K in shader cycles: 1.441e7 / 1.433e7, at 1.49 / 1.60 GHz.
+//
+// Head size 256.  A wave of 32 queries needs 462 (B = 64: 408) registers, so it has its SIMD for itself, and half of them are
+// accumulator registers, which only matrix instructions and copies can reach (kAcc): O and Q lie there, everything that the
+// softmax touches in vector registers.  Left to itself the compiler placed the scores there as well, or O in vector registers and
+// copied other values back and forth, 116 copies per block (32K, 15 %: 2587 us; by a flag for this file the results of the
+// other matrix instructions stay in vector registers, which alone gave 2491).  With 16 queries a wave needs 226, and two share a SIMD;
+// each LDS operand then feeds one matrix instruction.  Before (32 x 32 x 16, one wave per SIMD, the softmax under the same
+// block's products, two barriers per block) / now, attention alone, B = 128: 32K, 15 % 2377 / 2241 us; 115 blocks, 54 of them kept
+// 2109 / 1986; 20K + 45K, 4 % 642 / 599; 8 short prompts 124 / 109; B = 64: 203 blocks, 54 kept 1125 / 1100; 24K packed 745 / 655.
 //
 // Every query's arithmetic is its 16-query tile's own: a reference moves for a tile at a time, and no step depends on
 // how many tiles share a wave.
@@ -868,6 +337,7 @@ __device__ __forceinline__ void sparse_attn_body(
     constexpr int TP = KT / 2;                         // tiles per half block
     constexpr int HS = TP * KS;                        // LDS operands of a half block, in either product
     constexpr int NP = TP * 4 * QW;                    // softmax pairs per lane and half block
+    constexpr bool kAcc = D == 256 && QW == 2;         // O and Q in accumulator registers
     constexpr int kRowBytes = D * 2;                   // one K or V row in LDS
     constexpr int kSliceRows = 1024 / kRowBytes;       // rows one wave-wide 1 KiB request covers
     // LDS swizzles, as XORs on the 16-byte chunk index of a row: K spreads the 16 rows a quarter-wave reads one chunk of over
@@ -909,13 +379,16 @@ __device__ __forceinline__ void sparse_attn_body(
     const int slice_row = (lane * 16) / kRowBytes, pc = ((lane * 16) % kRowBytes) >> 4;
     const int lrow = w * kSliceRows + slice_row;       // row of slice u = 0
     const uint32_t lane_row_off = (uint32_t)(lrow * row_bytes);
-    constexpr int kKVariants = D == 128 && NW * kSliceRows < 16 ? 16 / (NW * kSliceRows) : 1;
+    constexpr int kKVariants = D >= 128 && NW * kSliceRows < 16 ? 16 / (NW * kSliceRows) : 1;
     static_assert((kKVariants * NW * kSliceRows) % 16 == 0, "the K swizzle term of slice u repeats with period kKVariants");
-    static_assert((NW * kSliceRows) % 8 == 0, "the V swizzle term does not depend on the slice");
+    constexpr int kVVariants = NW * kSliceRows < 8 ? 8 / (NW * kSliceRows) : 1;
+    static_assert((kVVariants * NW * kSliceRows) % 8 == 0, "the V swizzle term of slice u repeats with period kVVariants");
     uint32_t k_off[kKVariants];
 #pragma unroll
     for (int x = 0; x < kKVariants; ++x) k_off[x] = lane_row_off + ((pc ^ k_swz(lrow + x * NW * kSliceRows)) << 4);
-    const uint32_t v_off = lane_row_off + ((pc ^ v_swz(lrow)) << 4);
+    uint32_t v_off[kVVariants];
+#pragma unroll
+    for (int x = 0; x < kVVariants; ++x) v_off[x] = lane_row_off + ((pc ^ v_swz(lrow + x * NW * kSliceRows)) << 4);
     const int64_t first_row = (int64_t)row.g * kv_sh + (int64_t)row.seq_lo * kv_st;
     const auto k_rsrc = sequence_resource(k + first_row, row.seq_hi - row.seq_lo, row_bytes, kRowBytes);
     const auto v_rsrc = sequence_resource(v + first_row, row.seq_hi - row.seq_lo, row_bytes, kRowBytes);
@@ -929,12 +402,17 @@ __device__ __forceinline__ void sparse_attn_body(
         for (int x = 0; x < kKVariants; ++x) rq.lane_off[x] = k_off[x] + off;
         return rq;
     };
-    auto v_request = [&](int j) { return BlockRequest<1>{v_rsrc, {v_off + j * block_bytes}}; };
+    auto v_request = [&](int j) {
+        BlockRequest<kVVariants> rq{v_rsrc, {}};
+#pragma unroll
+        for (int x = 0; x < kVVariants; ++x) rq.lane_off[x] = v_off[x] + j * block_bytes;
+        return rq;
+    };
     // the first KR / 2 requests of a block are its first half
     auto issue_k = [&](const BlockRequest<kKVariants>& rq, int u) {
         rq.issue(u, (u < KR / 2 ? k_lds_a : k_lds_b - (KR / 2) * slice_lds_step) + w * 1024, slice_step, slice_lds_step);
     };
-    auto issue_v = [&](const BlockRequest<1>& rq, int u) {
+    auto issue_v = [&](const BlockRequest<kVVariants>& rq, int u) {
         rq.issue(u, (u < KR / 2 ? v_lds_a : v_lds_b - (KR / 2) * slice_lds_step) + w * 1024, slice_step, slice_lds_step);
     };
 
@@ -963,6 +441,10 @@ __device__ __forceinline__ void sparse_attn_body(
     // blocks one for all of them (the two kinds return in any order on one counter).
     asm volatile("" : : "s"(out), "s"(lse));
 
+    if constexpr (kAcc) {
+#pragma unroll
+        for (int x = 0; x < QW * KD; ++x) pin_to_acc(q_reg[x / KD][x % KD]);
+    }
     const f32x4_t zero4 = {0.f, 0.f, 0.f, 0.f};
     f32x4_t o_acc[KS][QW];                             // [16-column tile][query tile]
 #pragma unroll
@@ -1001,12 +483,14 @@ __device__ __forceinline__ void sparse_attn_body(
     // Operands are read this many ahead of their use, and used two at a time behind one wait.  Attention alone, 4 / 2 ahead:
     // 128K 8716 / 8698 us, 5 % 1285 / 1279, 32K 1066 / 1064, B = 64 100K 7725 / 7687 (and six 3 to 4 % slower than four).  With one
     // tile per wave an operand is used up in half the time: 4 / 6 / 8 ahead one head of 4096 (B = 64) 12.3 / 11.7 / 11.8, 25 rows of
-    // 12 blocks (B = 128) 35.8 / 35.7 / 34.9.
-    constexpr int kWanted = QW == 1 ? (B == 64 ? 6 : 8) : 2;
+    // 12 blocks (B = 128) 35.8 / 35.7 / 34.9; at d = 256, 2 / 4 / 6 / 8 ahead, 32K 2435 / 2451 / 2456 / 2457.
+    constexpr int kWanted = QW == 1 && D != 256 ? (B == 64 ? 6 : 8) : 2;
     constexpr int kAhead = kWanted < HS ? kWanted : HS;
     // The operand of S^T under which request u of a phase is issued, K's first.  B = 64 and d = 64, over all of S^T / its first
     // half: 100K 8185 / 7931 us, d = 64 1436 / 1431; 128K the other way round, 8994 / 9041.
-    auto request_slot = [](int u) { return B == 64 || D == 64 ? u * HS / (2 * KR) : u * HS / KR; };
+    // d = 256, B = 64: two tiles per wave, 256 blocks of which 50 kept 1403 / 1365; one tile, 100 rows of 8 blocks 13.4 / 14.1.
+    constexpr bool kEarly = (B == 64 || D == 64) && !(D == 256 && QW == 1);
+    auto request_slot = [](int u) { return kEarly ? u * HS / (2 * KR) : u * HS / KR; };
 
     f32x4_t s_acc[2][TP][2][QW];                       // [half][tile][16 keys][query tile]
     u32x4_t p_pk[2][TP][QW];                           // bf16 pairs: [half][tile][query tile], [2 * 16 keys + pair]
@@ -1098,7 +582,8 @@ __device__ __forceinline__ void sparse_attn_body(
     // every half and leaves the others as they are.
     auto fix_half = [&](auto P_tag) STEM_INLINE {
         constexpr int P = decltype(P_tag)::value;
-        wait_states_output<16>(o_acc);                 // the last O^T instruction has written
+        wait_states_output<16, kAcc>(o_acc);           // the last O^T instruction has written
+        if constexpr (kAcc) asm volatile("" : "+v"(l_win[0]), "+v"(l_win[QW - 1]));   // and the last row sum's
 #pragma unroll
         for (int qt = 0; qt < QW; ++qt) {
             const bool needs = __builtin_amdgcn_ballot_w64((m_ref[qt] == neg_inf) | !(l_win[qt][0] <= 65536.0f)) != 0;
@@ -1117,7 +602,7 @@ __device__ __forceinline__ void sparse_attn_body(
             asm volatile("" : "+v"(off[qt]));          // not folded into the exponents: the bits of the common path
         }
         softmax_pairs(P_tag, C0{}, kAll{});            // (those of a tile that stays come out as they were)
-        wait_states_output<4>(o_acc);                  // before the next one reads them
+        wait_states_output<4, kAcc>(o_acc);            // before the next one reads them
         note_unseen();
     };
     // A half needs the slow path if a query has no reference yet or if its sum is not a modest finite number (a
@@ -1187,7 +672,7 @@ __device__ __forceinline__ void sparse_attn_body(
     auto outputs = [&](auto P_tag, auto m_tag, u32x4_t even, u32x4_t odd, auto under) STEM_INLINE {
         constexpr int P = decltype(P_tag)::value, m = decltype(m_tag)::value, h = m & 1, t = m / KS, dt = (m % KS) & ~1;
         auto product = [&](f32x4_t& c, u32x4_t a, u32x4_t b) STEM_INLINE {
-            mfma_output(c, a, b);
+            mfma_output<kAcc>(c, a, b);
             STEM_SCHED_FENCE();
         };
         if constexpr (QW == 2) {
@@ -1245,6 +730,7 @@ __device__ __forceinline__ void sparse_attn_body(
                     STEM_SCHED_FENCE();
                 }
             } else {
+                request(m);
                 outputs(Before{}, std::integral_constant<int, m - HS>{}, op[m & ~1], op[m | 1], [&](auto h) STEM_INLINE {
                     softmax_under(P_tag, C0{}, kHalf{}, std::integral_constant<int, QW * (m - HS) + decltype(h)::value>{}, kSpan{});
                 });
@@ -1345,6 +831,8 @@ __device__ __forceinline__ void sparse_attn_body(
                     under(std::integral_constant<int, QW * m + decltype(h)::value>{});
                 });
             });
+            // (where paths meet the compiler may move O to other registers)
+            if constexpr (kAcc) wait_states_output<8, kAcc>(o_acc);
         };
         if (second) {
             u32x4_t op[HS + kAhead];
@@ -1378,7 +866,7 @@ __device__ __forceinline__ void sparse_attn_body(
         }
     }
     STEM_WAIT_VMCNT(0);                                // no request may outlive the workgroup's LDS
-    wait_states_output<16>(o_acc);                     // the last O^T instructions have written
+    wait_states_output<16, kAcc>(o_acc);               // the last O^T instructions have written
 
     // ---- normalise and store: accumulator x of column tile dt is column dt*16 + 4*(lane/16) + x.  Two column tiles at a time,
     //      one exchange between neighbouring groups of 16 lanes per packed register gives each lane eight consecutive columns,
@@ -1411,28 +899,18 @@ __device__ __forceinline__ void sparse_attn_body(
 
 // QW: 16-query tiles per wave (launch_sparse_attn says when one)
 template <int B, int D, int QW>
-__global__ __launch_bounds__(B * 4 / QW, D == 256 ? 1 : 2) void sparse_attn_kernel(
+__global__ __launch_bounds__(B * 4 / QW, D == 256 && QW == 2 ? 1 : 2) void sparse_attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ counts, const int32_t* __restrict__ indices,
     uint16_t* __restrict__ out, float* __restrict__ lse, SeqTable seq, RowWalk walk, int Hq, int R, int G,
     int order, int claim_from, int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh,
     float scale, int items_per_xcd, int xcds_per_kv_head, int32_t* __restrict__ taken) {
-    if constexpr (D == 256) {
-        static_assert(QW == 2, "a wave of 32 queries");
-        __shared__ __attribute__((aligned(1024))) unsigned char k_lds[B * D * 2], v_lds[B * D * 2];
-        RowPlace row;
-        if (!find_row<B, false>(seq, walk, Hq, R, G, order, claim_from, items_per_xcd, xcds_per_kv_head, taken,
-                                reinterpret_cast<int*>(k_lds), row)) return;
-        sparse_attn_body_256<B>(q, k, v, counts, indices, out, lse, row, R, T, kmax, shared_lists, q_st, q_sh, kv_st, kv_sh,
-                                scale, k_lds, v_lds);
-    } else {
-        __shared__ __attribute__((aligned(1024))) unsigned char k_lds[B * D], k_lds2[B * D], v_lds[B * D], v_lds2[B * D];
-        RowPlace row;
-        if (!find_row<B, true>(seq, walk, Hq, R, G, order, claim_from, items_per_xcd, xcds_per_kv_head, taken,
-                               reinterpret_cast<int*>(k_lds), row)) return;
-        sparse_attn_body<B, D, QW>(q, k, v, counts, indices, out, lse, row, R, T, kmax, shared_lists, q_st, q_sh, kv_st,
-                                   kv_sh, scale, k_lds, k_lds2, v_lds, v_lds2);
-    }
+    __shared__ __attribute__((aligned(1024))) unsigned char k_lds[B * D], k_lds2[B * D], v_lds[B * D], v_lds2[B * D];
+    RowPlace row;
+    if (!find_row<B, D != 256>(seq, walk, Hq, R, G, order, claim_from, items_per_xcd, xcds_per_kv_head, taken,
+                           reinterpret_cast<int*>(k_lds), row)) return;
+    sparse_attn_body<B, D, QW>(q, k, v, counts, indices, out, lse, row, R, T, kmax, shared_lists, q_st, q_sh, kv_st,
+                               kv_sh, scale, k_lds, k_lds2, v_lds, v_lds2);
 }
 
 int launch_sparse_attn(const Problem& p, const void* q, const void* k, const void* v,
@@ -1495,7 +973,12 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     // 21.2 / 22.9 us, 380 35.6 / 42.1, 500 51.3 / 55.3, 640 80.7 / 76.3; d = 64, 500 35.5 / 42.2, 640 53.4 / 52.5; B = 128, d = 128,
     // 100 15.3 / 16.8, 250 41.4 / 40.7, 270 59.7 / 45.9; d = 64, 250 27.8 / 29.1, 270 42.0 / 31.9.  The bits are the same.
     const int64_t cus = compute_units();
-    const bool narrow = p.B == 64 ? items <= 2 * cus : p.d == 128 ? 4 * items <= 3 * cus : items <= cus;
+    // d = 256: up to what runs at a time (one row per CU at B = 128, two at B = 64), and beyond where lists are short, which the
+    // second wave of a SIMD helps most: one tile / two, B = 128, 100 rows of 20 blocks 58.9 / 61.4, 224 63.4 / 63.5, 264 69.1 / 67.1;
+    // 264 rows of 8 blocks 40.5 / 41.5, 3200 403 / 409, 8192 1066 / 1049; 3200 of 20 843 / 808.  B = 64, 496 rows of 20 blocks
+    // 37.1 / 39.4, 1008 70.0 / 73.9, 1536 109 / 110, 3200 246 / 236; 3200 of 8 blocks 120 / 124, 8192 340 / 326.
+    const bool few = p.B == 64 ? items <= 2 * cus : p.d == 128 ? 4 * items <= 3 * cus : items <= cus;
+    const bool narrow = few || (p.d == 256 && ((items <= 16 * cus && kmax <= 10) || (p.B == 64 && items <= 6 * cus && kmax <= 20)));
     if (p.B == 128 && p.d == 128 && narrow) STEM_ATTN_LAUNCH(128, 128, 1);
     else if (p.B == 128 && p.d == 128) STEM_ATTN_LAUNCH(128, 128, 2);
     else if (p.B == 64 && p.d == 128 && narrow) STEM_ATTN_LAUNCH(64, 128, 1);
@@ -1504,7 +987,9 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     else if (p.B == 128 && p.d == 64) STEM_ATTN_LAUNCH(128, 64, 2);
     else if (p.B == 64 && p.d == 64 && narrow) STEM_ATTN_LAUNCH(64, 64, 1);
     else if (p.B == 64 && p.d == 64) STEM_ATTN_LAUNCH(64, 64, 2);
+    else if (p.B == 128 && p.d == 256 && narrow) STEM_ATTN_LAUNCH(128, 256, 1);
     else if (p.B == 128 && p.d == 256) STEM_ATTN_LAUNCH(128, 256, 2);
+    else if (p.B == 64 && p.d == 256 && narrow) STEM_ATTN_LAUNCH(64, 256, 1);
     else if (p.B == 64 && p.d == 256) STEM_ATTN_LAUNCH(64, 256, 2);
     else return STEM_ERR_UNSUPPORTED;
 #undef STEM_ATTN_LAUNCH

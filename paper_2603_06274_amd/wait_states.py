@@ -1,7 +1,7 @@
 """Checks the wait states around hand-placed matrix instructions in a kernel's gfx950 assembly.
 
-The attention kernel for head size 256 issues its matrix instructions from inline assembly (so that
-it, not the compiler, decides which results live in vector and which in accumulator registers).
+The attention kernel issues the matrix instructions of its second product from inline assembly (so that
+it, not the compiler, decides in which registers their results live).
 The compiler does not look inside inline assembly, so it inserts none of the idle issue slots
 ("wait states") the hardware needs between a matrix instruction and a dependent access; the kernel
 places them itself.  Register allocation can still put a copy next to a matrix instruction that the

@@ -125,7 +125,8 @@ def test_rows_of_a_batch_in_another_order(B, d, heads, lens):
     c.check_part(whole, [8, 1, 0], [(9, 12), (0, 1), (2, 5)])
 
 
-@pytest.mark.parametrize("B,d,heads,line", [(64, 128, 8, 2.0), (64, 64, 8, 2.0), (128, 128, 4, 0.75), (128, 64, 4, 1.0)])
+@pytest.mark.parametrize("B,d,heads,line", [(64, 128, 8, 2.0), (64, 64, 8, 2.0), (128, 128, 4, 0.75), (128, 64, 4, 1.0),
+                                            (64, 256, 8, 2.0), (128, 256, 4, 1.0)])
 def test_rows_on_both_sides_of_the_line_between_wave_shapes(B, d, heads, line):
     """Calls of at most `line` rows per CU run with half as many queries per wave: a call just above the line, the same rows
     in one on it, and one row of it."""
@@ -134,3 +135,15 @@ def test_rows_on_both_sides_of_the_line_between_wave_shapes(B, d, heads, line):
     whole = c.attend([0])
     c.check_part(whole, [0], [(1, blocks + 1)])
     c.check_part(whole, [0], [(blocks, blocks + 1)])
+
+
+@pytest.mark.parametrize("B,rows_per_cu,kmax", [(128, 16, 10), (64, 16, 10), (64, 6, 20)])
+def test_rows_on_both_sides_of_the_lines_between_wave_shapes_at_d_256(B, rows_per_cu, kmax):
+    """Head size 256, lists with room for `kmax` blocks: a call just above `rows_per_cu` rows per CU, the same rows in one
+    on it; and with room for one block more, where the wider shape starts."""
+    blocks = rows_per_cu * torch.cuda.get_device_properties(0).multi_processor_count // 32
+    c = Call(B, 256, 32, 4, ((blocks + 1) * B - 3,), kmax)
+    whole = c.attend([0])
+    c.check_part(whole, [0], [(1, blocks + 1)])
+    c.indices = torch.cat([c.indices, torch.full_like(c.indices[:, :, :1], -1)], dim=2)
+    c.check_part(whole, [0], [(1, blocks + 1)])

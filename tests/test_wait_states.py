@@ -92,11 +92,11 @@ def test_attention_kernel_assembly_passes():
     build.check_wait_states()                      # raises with the offending lines
     with open(os.path.join(build.OBJ, "stem_attn.s")) as f:
         asm = f.read()
-    hand_placed = [k for k in wait_states.kernels(asm, "sparse_attn_kernel") if "ELi256E" in k]
+    hand_placed = [k for k in wait_states.kernels(asm, "sparse_attn_kernel") if "ELi256ELi2E" in k]
     assert len(hand_placed) == 2
     for k in hand_placed:                          # the check did look at hand-placed instructions
         body = asm[asm.index(k + ":"):]
-        assert "v_mfma_f32_32x32x16_bf16 v[" in body[:body.index(".Lfunc_end")]
+        assert "v_mfma_f32_16x16x32_bf16 a[" in body[:body.index(".Lfunc_end")]
 
 
 @pytest.mark.parametrize("found", [build.ATTENTION_KERNELS - 1, build.ATTENTION_KERNELS + 1])

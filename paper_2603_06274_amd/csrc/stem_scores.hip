@@ -52,6 +52,35 @@ struct ScoreTile {                                     // what one tile's work n
     int i0, j0, n_rows, n, first;
 };
 
+// tile f of the list: head-major, then sequence, row tile, column tile
+__device__ __forceinline__ ScoreTile score_tile(int f, const SeqTable& seq, const TileTable& tiles, int tiles_per_head,
+                                                const float* q_bar, const float* k_bar, const float* m_v, float* scores,
+                                                int R, int Rk, int NBmax, int G, int depth) {
+    const int h = f / tiles_per_head;
+    int x = f - h * tiles_per_head;
+    const int s = place_in(tiles.causal_start, seq.batch, x);
+    x -= tiles.causal_start[s];
+    const int row0 = seq.row_start[s];
+    const int first = seq.first_block[s];              // block index of the sequence's first row in the call
+    int it = 0;
+    for (int c = causal_tiles_of_row_tile(0, first, NBmax); x >= c; c = causal_tiles_of_row_tile(it, first, NBmax)) {
+        x -= c;
+        ++it;
+    }
+    const int g = h / G;
+    ScoreTile t;
+    t.n_rows = seq.row_start[s + 1] - row0;            // query-block rows of this sequence in the call
+    t.first = first;
+    t.n = first + t.n_rows;                            // key blocks the call can see
+    t.i0 = it * kTile;
+    t.j0 = x * kTile;
+    t.a_src = q_bar + ((int64_t)h * R + row0) * depth;
+    t.b_src = k_bar + ((int64_t)g * Rk + seq.key_row_start[s]) * depth;
+    t.m_v = m_v + (int64_t)g * Rk + seq.key_row_start[s];
+    t.out = scores + ((int64_t)h * R + row0) * NBmax;
+    return t;
+}
+
 __global__ __launch_bounds__(kScoreThreads) void block_scores_kernel(
     const float* __restrict__ q_bar, const float* __restrict__ k_bar, const float* __restrict__ m_v,
     float* __restrict__ scores, SeqTable seq, TileTable tiles, int tiles_per_head, int total_tiles, int R,
@@ -61,31 +90,8 @@ __global__ __launch_bounds__(kScoreThreads) void block_scores_kernel(
     const int depth = S * d;                           // floats per pooled block
     const float neg_inf = -__builtin_huge_valf();
 
-    // tile f of the list: head-major, then sequence, row tile, column tile
     auto decode = [&](int f) {
-        const int h = f / tiles_per_head;
-        int x = f - h * tiles_per_head;
-        const int s = place_in(tiles.causal_start, seq.batch, x);
-        x -= tiles.causal_start[s];
-        const int row0 = seq.row_start[s];
-        const int first = seq.first_block[s];          // block index of the sequence's first row in the call
-        int it = 0;
-        for (int c = causal_tiles_of_row_tile(0, first, NBmax); x >= c; c = causal_tiles_of_row_tile(it, first, NBmax)) {
-            x -= c;
-            ++it;
-        }
-        const int g = h / G;
-        ScoreTile t;
-        t.n_rows = seq.row_start[s + 1] - row0;        // query-block rows of this sequence in the call
-        t.first = first;
-        t.n = first + t.n_rows;                        // key blocks the call can see
-        t.i0 = it * kTile;
-        t.j0 = x * kTile;
-        t.a_src = q_bar + ((int64_t)h * R + row0) * depth;
-        t.b_src = k_bar + ((int64_t)g * Rk + seq.key_row_start[s]) * depth;
-        t.m_v = m_v + (int64_t)g * Rk + seq.key_row_start[s];
-        t.out = scores + ((int64_t)h * R + row0) * NBmax;
-        return t;
+        return score_tile(f, seq, tiles, tiles_per_head, q_bar, k_bar, m_v, scores, R, Rk, NBmax, G, depth);
     };
 
     // [row][k] with rows 144 bytes apart: the 16-byte reads of 16 consecutive rows fall on 16
@@ -204,6 +210,95 @@ __global__ __launch_bounds__(kScoreThreads) void block_scores_kernel(
     }
 }
 
+// Few tiles leave the chip idle and are a chain of latencies each.  Four workgroups per tile, a 32 x 32 quarter each, a 16 x 16
+// part per wave on v_mfma_f32_16x16x4_f32 (the products of a tile then run on four CUs), and the operands in slices of CH
+// floats, the most that divides the depth: one fetch, one barrier.  The sums run in the order of block_scores_kernel, so the
+// scores are the same bits: of every 8 positions a step there adds x and 4 + x; of every 16, step 0 here takes
+// (0, 4, 1, 5) from the four groups of 16 lanes, step 1 (2, 6, 3, 7), and steps 2 and 3 the same of the second eight.
+// One tile, d = 128: 6.6 / 4.9 us by itself; depth 2048, 15 tiles 51.0 / 23.3.
+template <int CH>
+__global__ __launch_bounds__(256) void block_scores_few_kernel(
+    const float* __restrict__ q_bar, const float* __restrict__ k_bar, const float* __restrict__ m_v,
+    float* __restrict__ scores, SeqTable seq, TileTable tiles, int tiles_per_head, int R, int Rk, int NBmax, int G, int S,
+    int d_log2, float beta, float route_scale) {
+    constexpr int kRows = kTile / 2;
+    constexpr int kParts = kRows * CH / 4 / 256;       // 16-byte parts per thread, operand and slice
+    const int tid = threadIdx.x;
+    const int d = 1 << d_log2;
+    const int depth = S * d;                           // a multiple of CH
+    ScoreTile t = score_tile(blockIdx.x >> 2, seq, tiles, tiles_per_head, q_bar, k_bar, m_v, scores, R, Rk, NBmax, G, depth);
+    t.i0 += (blockIdx.x >> 1 & 1) * kRows;             // this workgroup's quarter
+    t.j0 += (blockIdx.x & 1) * kRows;
+    if (t.i0 >= t.n_rows || t.j0 >= NBmax) return;
+    const bool visible = t.j0 <= t.first + t.i0 + kRows - 1;   // not entirely above the diagonal
+    // rows of CH + 4 floats: the 16-byte reads of 16 consecutive rows fall on 16 different groups of four banks
+    __shared__ __attribute__((aligned(16))) float a_s[kRows][CH + 4];
+    __shared__ __attribute__((aligned(16))) float b_s[kRows][CH + 4];
+
+    const int lane = tid & 63, wv = tid >> 6;
+    const int r = lane & 15, c = lane >> 4;
+    const int wi = (wv >> 1) * 16, wj = (wv & 1) * 16; // this wave's part of the quarter
+    const int j = t.j0 + wj + r;
+    const float mag = (j < t.n) ? t.m_v[j] : 0.f;
+
+    float4 av[kParts], bv[kParts];
+    auto fetch = [&](int kc) {
+#pragma unroll
+        for (int u = 0; u < kParts; ++u) {
+            const int idx = tid + 256 * u;
+            const int row = idx / (CH / 4), col = kc + idx % (CH / 4) * 4;
+            // the residue class of the query block's column; its partner is class S-1-a
+            const int kb = (S - 1 - (col >> d_log2)) * d + (col & (d - 1));
+            av[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            bv[u] = av[u];
+            if (t.i0 + row < t.n_rows) av[u] = *reinterpret_cast<const float4*>(t.a_src + (int64_t)(t.i0 + row) * depth + col);
+            if (t.j0 + row < t.n) bv[u] = *reinterpret_cast<const float4*>(t.b_src + (int64_t)(t.j0 + row) * depth + kb);
+        }
+    };
+    auto swap_halves = [](float& a, float& b) {        // upper half of a <-> lower half of b
+        const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        a = __uint_as_float(y[0]);
+        b = __uint_as_float(y[1]);
+    };
+    typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    if (visible) fetch(0);
+    for (int kc = 0; kc < depth && visible; kc += CH) {
+        if (kc > 0) __syncthreads();                   // the last slice's reads
+#pragma unroll
+        for (int u = 0; u < kParts; ++u) {
+            const int idx = tid + 256 * u;
+            const int row = idx / (CH / 4), col = idx % (CH / 4) * 4;
+            *reinterpret_cast<float4*>(&a_s[row][col]) = av[u];
+            *reinterpret_cast<float4*>(&b_s[row][col]) = bv[u];
+        }
+        __syncthreads();
+        if (kc + CH < depth) fetch(kc + CH);
+#pragma unroll
+        for (int u = 0; u < CH / 16; ++u) {
+            float4 a = *reinterpret_cast<const float4*>(&a_s[wi + r][16 * u + 4 * c]);
+            float4 b = *reinterpret_cast<const float4*>(&b_s[wj + r][16 * u + 4 * c]);
+            swap_halves(a.x, a.y);
+            swap_halves(a.z, a.w);
+            swap_halves(b.x, b.y);
+            swap_halves(b.z, b.w);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b.z, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.y, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b.w, acc, 0, 0, 0);
+        }
+    }
+    // accumulator x of a lane: row wi + 4 c + x, column wj + r
+    const float m = beta * fmaxf(0.f, mag);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        const int i = t.i0 + wi + 4 * c + x;
+        if (i >= t.n_rows || j >= NBmax) continue;
+        t.out[(int64_t)i * NBmax + j] =
+            (j <= t.first + i) ? fmaf(route_scale / (float)S, acc[x], m) : -__builtin_huge_valf();
+    }
+}
+
 // The tiles entirely above the diagonal, for callers that want the whole rectangle defined.
 __global__ __launch_bounds__(kScoreThreads) void fill_non_causal_kernel(float* __restrict__ scores, SeqTable seq,
                                                                         TileTable tiles, int R, int NBmax) {
@@ -256,9 +351,21 @@ int launch_block_scores(const Problem& p, int ad_stride, const float* q_bar, con
     if (cus <= 0) return STEM_ERR_HIP;
     const int total = causal * p.Hq;
     const int workgroups = total < cus * kScoreWorkgroupsPerCU ? total : cus * kScoreWorkgroupsPerCU;
-    hipLaunchKernelGGL(block_scores_kernel, dim3(workgroups), dim3(kScoreThreads), 0, stream, q_bar, k_bar, m_v,
-                       scores, p.seq, tiles, causal, total, p.R, p.Rk, p.NBmax, p.G, ad_stride,
-                       __builtin_ctz(p.d), beta, route_scale);
+    // Up to half a tile per CU in quarters.  A pass, 64 x 64 tiles / quarters: 1 tile 26.7 / 24.4 us, 32 170.0 / 166.9, 84 499.1 /
+    // 497.4, 120 413.4 / 412.1, 192 827.0 / 826.2 and 1201.8 / 1202.8, 384 131.8 / 132.5, 768 82.7 / 87.1; the deeper the more:
+    // depth 256, 32 tiles 341.6 / 334.7; 512, 8 72.1 / 65.3; 1024, 96 594 / 588; 2048, 32 111.3 / 87.0, 192 1213.7 / 1217.5.
+#define STEM_SCORES_FEW(CH)                                                                                             \
+    hipLaunchKernelGGL(block_scores_few_kernel<CH>, dim3(4 * total), dim3(256), 0, stream, q_bar, k_bar, m_v, scores, p.seq, \
+                       tiles, causal, p.R, p.Rk, p.NBmax, p.G, ad_stride, __builtin_ctz(p.d), beta, route_scale)
+    const int depth = p.d * ad_stride;
+    if (2 * total > cus)
+        hipLaunchKernelGGL(block_scores_kernel, dim3(workgroups), dim3(kScoreThreads), 0, stream, q_bar, k_bar, m_v,
+                           scores, p.seq, tiles, causal, total, p.R, p.Rk, p.NBmax, p.G, ad_stride,
+                           __builtin_ctz(p.d), beta, route_scale);
+    else if (depth % 256 == 0) STEM_SCORES_FEW(256);
+    else if (depth % 128 == 0) STEM_SCORES_FEW(128);
+    else STEM_SCORES_FEW(64);
+#undef STEM_SCORES_FEW
     if (fill_non_causal) {
         dim3 grid(row_tiles, (p.NBmax + kTile - 1) / kTile, p.Hq);
         hipLaunchKernelGGL(fill_non_causal_kernel, grid, dim3(kScoreThreads), 0, stream, scores, p.seq, tiles,

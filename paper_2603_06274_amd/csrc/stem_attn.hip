@@ -609,8 +609,9 @@ __device__ __forceinline__ void sparse_attn_body(
     // probability above 2^16, inf, NaN: the reference is too low for this half).
     auto check_half = [&](auto P_tag) STEM_INLINE {
         // (the last sum's product has been issued just before; across the branches of the masks, which may lie in between, the
-        // compiler kept four of the seven idle slots that its result needs)
+        // compiler kept four of the eight idle slots that its result needs at QW = 1, B = 128, and seven at QW = 2, B = 64)
         if constexpr (QW == 1) asm volatile("s_nop 3" : "+v"(l_win[0]));
+        else if constexpr (B == 64) asm volatile("s_nop 0" : "+v"(l_win[1]));
         bool high = !(l_win[0][0] <= 65536.0f);
         if constexpr (QW == 2) high |= !(l_win[1][0] <= 65536.0f);
         if (unseen || __builtin_amdgcn_ballot_w64(high) != 0) fix_half(P_tag);

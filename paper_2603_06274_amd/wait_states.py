@@ -14,8 +14,9 @@ Rules checked (wait states = instructions issued in between, `s_nop N` counting 
     different-but-overlapping C operand 10 later; the identical C operand (accumulation) may
     follow at once (two matrix results that overlap need nothing: the matrix pipe completes in
     order, and the compiler's own code for the builtin form places them back to back);
-  * for a 16x16x32 one (4 passes) the distances are 8 and 6; for one that the compiler placed, i.e. outside the inline
-    assembly of a function that has some, what its own code keeps, 7 and 5;
+  * for a 16x16x32 one (4 passes) the distances are 8 and 6, whether it stands in inline assembly or the compiler placed
+    it: in straight code the compiler keeps them, over branches it has left 7, and 4, and an access in inline assembly
+    it does not see;
   * for a 4x4x4 matrix instruction (2 passes) the distances are 5 and 4, and the next
     accumulation into the identical registers needs 2;
   * a matrix instruction may read a register 2 wait states after a vector instruction wrote it.
@@ -57,13 +58,6 @@ def check_kernel(asm: str, symbol: str) -> List[str]:
     end = next(i for i in range(start, len(src)) if src[i].startswith(".Lfunc_end"))
     labels = {m.group(1): i for i in range(start, end) for m in [_LABEL.match(src[i])] if m}
     found = set()
-    # lines of inline assembly; all of them where nothing is marked as such
-    by_hand, inside = [], False
-    for l in src[:end]:
-        inside = (inside or "#ASMSTART" in l) and "#ASMEND" not in l
-        by_hand.append(inside)
-    if not any(by_hand[start:]):
-        by_hand = [True] * end
 
     def scan(i: int, pending: List[Tuple], written: Dict, state: int, depth: int, first: int) -> None:
         nested = depth > 0
@@ -113,8 +107,7 @@ def check_kernel(asm: str, symbol: str) -> List[str]:
                         found.add("matrix read after vector write, line %d `%s` after line %d `%s`: %d wait states, 2 needed"
                                   % (i, line, written[r][1], written[r][2], state - written[r][0] - 1))
                         break
-                need, need_c = (5, 4) if "4x4x4" in op else ((8, 6) if by_hand[i - 1] else (7, 5)) if "16x16x32" in op \
-                    else (12, 10)
+                need, need_c = (5, 4) if "4x4x4" in op else (8, 6) if "16x16x32" in op else (12, 10)
                 pending[:] = [p for p in pending if state - p[3] - 1 < p[1] and p[0] != dst]
                 pending.append((dst, need, need_c, state, i, line))
                 state += 1

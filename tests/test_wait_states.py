@@ -65,6 +65,25 @@ def test_four_pass_instruction():
     assert not broken(row_sum + FILLER * 6 + shifted)
 
 
+def test_products_of_the_compiler_keep_the_same_distances():
+    """A function with a product in inline assembly beside one that the compiler placed: both are held to 8 and 6."""
+    by_hand = "\t;;#ASMSTART\n\tv_mfma_f32_16x16x32_bf16 v[0:3], v[36:39], v[44:47], v[0:3]\n\t;;#ASMEND\n"
+    placed = "\tv_mfma_f32_16x16x32_bf16 v[40:43], v[36:39], v[44:47], 0\n"
+    for product, at in ((by_hand, 0), (placed, 40)):
+        other = by_hand if product is placed else ""
+        read = "\tv_cmp_nge_f32_e64 s[8:9], s7, v%d\n" % at
+        assert broken(other + product + FILLER * 7 + read)
+        assert not broken(other + product + FILLER * 8 + read)
+        shifted = "\tv_mfma_f32_16x16x32_bf16 v[%d:%d], v[36:39], v[48:51], v[%d:%d]\n" % (at + 2, at + 5, at + 2, at + 5)
+        assert broken(other + product + FILLER * 5 + shifted)
+        assert not broken(other + product + FILLER * 6 + shifted)
+    # over the branches around a block that is rarely taken, as in the check of a half block
+    jump = "\ts_cmp_lg_u32 s1, 0\n\ts_cbranch_scc1 .LBB0_2\n" + FILLER * 9 + ".LBB0_2:\n"
+    read = "\tv_cmp_nge_f32_e64 s[8:9], s7, v40\n"
+    assert broken(by_hand + placed + jump + FILLER * 5 + read)
+    assert not broken(by_hand + placed + jump + FILLER * 6 + read)
+
+
 def test_matrix_read_after_vector_write():
     write = "\tv_accvgpr_write_b32 a2, v9\n"
     assert broken(write + FILLER + S_TILE)

@@ -812,6 +812,9 @@ __device__ __forceinline__ void sparse_attn_body(
 #pragma unroll
             for (int u = KR / 2; u < KR; ++u) issue_v(rv, u);
         }
+        // (A tile of values whose keys all come after the wave's queries is left out of O^T: a NaN or inf there would not stay
+        // out by its weight of zero.)
+        const int last_tile = mask_from == KT || mask_all ? KT - 1 : w_tile;
         auto output_half = [&](auto P_tag, auto under) STEM_INLINE {
             constexpr int P = decltype(P_tag)::value;
             u32x4_t op[HS + kAhead];
@@ -819,7 +822,7 @@ __device__ __forceinline__ void sparse_attn_body(
                 op[m] = load_v(P, m);
                 if (m & 1) STEM_SCHED_FENCE();
             });
-            unrolled<HS>([&](auto m_tag) STEM_INLINE {
+            auto operand = [&](auto m_tag) STEM_INLINE {
                 constexpr int m = decltype(m_tag)::value, a = m + kAhead;
                 if constexpr ((m & 1) == 0) {
                     if constexpr (a < HS) {
@@ -831,7 +834,12 @@ __device__ __forceinline__ void sparse_attn_body(
                 outputs(P_tag, m_tag, op[m & ~1], op[m | 1], [&](auto h) STEM_INLINE {
                     under(std::integral_constant<int, QW * m + decltype(h)::value>{});
                 });
-            });
+            };
+            unrolled<KS>(operand);
+            if constexpr (TP == 2) {
+                if (last_tile > P * TP)
+                    unrolled<KS>([&](auto m) STEM_INLINE { operand(std::integral_constant<int, KS + decltype(m)::value>{}); });
+            }
             // (where paths meet the compiler may move O to other registers)
             if constexpr (kAcc) wait_states_output<8, kAcc>(o_acc);
         };

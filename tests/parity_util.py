@@ -271,3 +271,40 @@ def oracle_attention_pairs(w: wl.Workload, qkv, counts, indices, pairs):
         t0 = lo + i * w.block_size
         res.append((h, r, t0, t0 + o.shape[0], o, l))
     return res
+
+
+def two_tiles_per_wave(B: int, d: int, rows: int, kmax: int, cus: int) -> bool:
+    """Whether a launch of `rows` (head, query block) pairs gives a wave 32 queries (the rule of launch_sparse_attn)."""
+    few = rows <= 2 * cus if B == 64 else 4 * rows <= 3 * cus if d == 128 else rows <= cus
+    return not few and not (d == 256 and ((rows <= 16 * cus and kmax <= 10) or (B == 64 and rows <= 6 * cus and kmax <= 20)))
+
+
+def widen_attention(monkeypatch) -> None:
+    """Every stem_sparse_attn of a test becomes a launch of 32 queries per wave: the call's heads several times over, with room
+    for 24 blocks in a list.  The test gets the first copy; the others, and the call as it is, have to give the same bits."""
+    from paper_2603_06274_amd import binding as sb
+    attend = sb.stem_sparse_attn
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+
+    def widened(shape, q, k, v, counts, indices, kmax, scale, out, lse, lists_per_kv_head=False):
+        assert not lists_per_kv_head and shape.chunk is None
+        B, d, Hq, rows = shape.c.block_size, q.shape[2], q.shape[1], counts.shape[0] * counts.shape[1]
+        n = next(n for n in range(1, 1000) if two_tiles_per_wave(B, d, n * rows, max(24, kmax), cus))
+        assert not two_tiles_per_wave(B, d, rows, kmax, cus)
+        room = torch.full((*indices.shape[:2], max(24, kmax)), -1, dtype=torch.int32, device=q.device)
+        room[:, :, :kmax] = indices
+        qn, kn, vn = (x.repeat(1, n, 1) for x in (q, k, v))
+        out_n = torch.full_like(qn, float("nan"))
+        lse_n = torch.full((n * Hq, q.shape[0]), float("nan"), device=q.device)
+        attend(sb.Shape.from_tensors(qn, kn, B, shape.cu_seqlens), qn, kn, vn, counts.repeat(n, 1),
+               room.repeat(n, 1, 1), room.shape[2], scale, out_n, None if lse is None else lse_n)
+        attend(shape, q, k, v, counts, indices, kmax, scale, out, lse)
+        torch.cuda.synchronize()
+        bits = lambda x: x.view(torch.int16 if x.dtype == torch.bfloat16 else torch.int32)
+        assert torch.equal(bits(out_n).view(-1, n, Hq, d), bits(out)[:, None].expand(-1, n, -1, -1).contiguous())
+        out.copy_(out_n[:, :Hq])
+        if lse is not None:
+            assert torch.equal(bits(lse_n).view(n, Hq, -1), bits(lse)[None].expand(n, -1, -1).contiguous())
+            lse.copy_(lse_n[:Hq])
+
+    monkeypatch.setattr(sb, "stem_sparse_attn", widened)

@@ -318,8 +318,15 @@ __device__ __forceinline__ bool find_row(const SeqTable& seq, const RowWalk& wal
 // block's products, two barriers per block) / now, attention alone, B = 128: 32K, 15 % 2377 / 2241 us; 115 blocks, 54 of them kept
 // 2109 / 1986; 20K + 45K, 4 % 642 / 599; 8 short prompts 124 / 109; B = 64: 203 blocks, 54 kept 1125 / 1100; 24K packed 745 / 655.
 //
+// LDS there: 128 KiB at B = 128, where the immediate offset of a read reaches 64 KiB.  With K below and V from 64 KiB on the second
+// half of V took two more vector instructions for every read, 62 per block, with nobody on the SIMD to fill them in.  So V lies
+// below, and the distance to K is in a lane's base, which the bases of a half's reads are formed from anyway.  Attention alone
+// before / now: 228 rows of 100 blocks 302 / 273 us (32 x 32 x 16 products 294), 64 of 50 137 / 131 (134), 3072 of 20 768 / 740.
+//
 // Every query's arithmetic is its 16-query tile's own: a reference moves for a tile at a time, and no step depends on
 // how many tiles share a wave.
+template <int B, int D>
+constexpr bool kKeysBeyondOffset = 4 * B * D > 65536;
 template <int B, int D, int QW>
 __device__ __forceinline__ void sparse_attn_body(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -327,6 +334,7 @@ __device__ __forceinline__ void sparse_attn_body(
     float* __restrict__ lse, const RowPlace& row, int R, int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh,
     int64_t kv_st, int64_t kv_sh, float scale, unsigned char* __restrict__ k_lds_a, unsigned char* __restrict__ k_lds_b,
     unsigned char* __restrict__ v_lds_a, unsigned char* __restrict__ v_lds_b) {
+    // (where K lies beyond the immediate offset its parameters are kKeysAt short of it)
     // (a parameter of its own for every buffer: alias-scope information then tells the compiler's wait-count insertion a
     // read of one buffer from a request in flight into another; otherwise it waits for all of them)
     constexpr int KT = B / 32;                         // 32-key tiles per block
@@ -337,6 +345,7 @@ __device__ __forceinline__ void sparse_attn_body(
     constexpr int TP = KT / 2;                         // tiles per half block
     constexpr int HS = TP * KS;                        // LDS operands of a half block, in either product
     constexpr int NP = TP * 4 * QW;                    // softmax pairs per lane and half block
+    constexpr int kKeysAt = kKeysBeyondOffset<B, D> ? 2 * B * D : 0;   // (sparse_attn_kernel)
     constexpr bool kAcc = D == 256 && QW == 2;         // O and Q in accumulator registers
     constexpr int kRowBytes = D * 2;                   // one K or V row in LDS
     constexpr int kSliceRows = 1024 / kRowBytes;       // rows one wave-wide 1 KiB request covers
@@ -410,7 +419,7 @@ __device__ __forceinline__ void sparse_attn_body(
     };
     // the first KR / 2 requests of a block are its first half
     auto issue_k = [&](const BlockRequest<kKVariants>& rq, int u) {
-        rq.issue(u, (u < KR / 2 ? k_lds_a : k_lds_b - (KR / 2) * slice_lds_step) + w * 1024, slice_step, slice_lds_step);
+        rq.issue(u, (u < KR / 2 ? k_lds_a : k_lds_b - (KR / 2) * slice_lds_step) + kKeysAt + w * 1024, slice_step, slice_lds_step);
     };
     auto issue_v = [&](const BlockRequest<kVVariants>& rq, int u) {
         rq.issue(u, (u < KR / 2 ? v_lds_a : v_lds_b - (KR / 2) * slice_lds_step) + w * 1024, slice_step, slice_lds_step);
@@ -462,7 +471,11 @@ __device__ __forceinline__ void sparse_attn_body(
     // per-lane LDS offsets that do not change between blocks.  Both swizzles are XORs of address
     // bits that are zero in the unswizzled per-lane offset, so the offset of an operand is one
     // v_xor of a per-lane base with a constant, plus an immediate.
-    const uint32_t k_base = c16 * kRowBytes + ((k_swz(c16) ^ grp) << 4);
+    uint32_t k_base = c16 * kRowBytes + ((k_swz(c16) ^ grp) << 4);
+    if constexpr (kKeysAt > 0) {
+        k_base += kKeysAt;
+        asm("" : "+v"(k_base));                        // stays in the base: the rest is a constant within the immediate offset
+    }
     // transposing V read: lane l fetches row 4 (l / 16) + (l % 16) / 4 of 16 rows, 8 bytes at column 16 dt + 4 (l % 4)
     const int v_row = grp * 4 + (c16 >> 2);
     const uint32_t v_base = v_row * kRowBytes + (v_swz(v_row) << 4) + ((lane & 3) << 3);
@@ -914,12 +927,13 @@ __global__ __launch_bounds__(B * 4 / QW, D == 256 && QW == 2 ? 1 : 2) void spars
     uint16_t* __restrict__ out, float* __restrict__ lse, SeqTable seq, RowWalk walk, int Hq, int R, int G,
     int order, int claim_from, int T, int kmax, bool shared_lists, int64_t q_st, int64_t q_sh, int64_t kv_st, int64_t kv_sh,
     float scale, int items_per_xcd, int xcds_per_kv_head, int32_t* __restrict__ taken) {
-    __shared__ __attribute__((aligned(1024))) unsigned char k_lds[B * D], k_lds2[B * D], v_lds[B * D], v_lds2[B * D];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * B * D];   // the halves of V, then those of K
+    unsigned char* k_lds = lds + (kKeysBeyondOffset<B, D> ? 0 : 2 * B * D);
     RowPlace row;
     if (!find_row<B, D != 256>(seq, walk, Hq, R, G, order, claim_from, items_per_xcd, xcds_per_kv_head, taken,
-                           reinterpret_cast<int*>(k_lds), row)) return;
+                           reinterpret_cast<int*>(lds), row)) return;
     sparse_attn_body<B, D, QW>(q, k, v, counts, indices, out, lse, row, R, T, kmax, shared_lists, q_st, q_sh, kv_st,
-                               kv_sh, scale, k_lds, k_lds2, v_lds, v_lds2);
+                               kv_sh, scale, k_lds, k_lds + B * D, lds, lds + B * D);
 }
 
 int launch_sparse_attn(const Problem& p, const void* q, const void* k, const void* v,
@@ -982,12 +996,13 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     // 21.2 / 22.9 us, 380 35.6 / 42.1, 500 51.3 / 55.3, 640 80.7 / 76.3; d = 64, 500 35.5 / 42.2, 640 53.4 / 52.5; B = 128, d = 128,
     // 100 15.3 / 16.8, 250 41.4 / 40.7, 270 59.7 / 45.9; d = 64, 250 27.8 / 29.1, 270 42.0 / 31.9.  The bits are the same.
     const int64_t cus = compute_units();
-    // d = 256: up to what runs at a time (one row per CU at B = 128, two at B = 64), and beyond where lists are short, which the
-    // second wave of a SIMD helps most: one tile / two, B = 128, 100 rows of 20 blocks 58.9 / 61.4, 224 63.4 / 63.5, 264 69.1 / 67.1;
-    // 264 rows of 8 blocks 40.5 / 41.5, 3200 403 / 409, 8192 1066 / 1049; 3200 of 20 843 / 808.  B = 64, 496 rows of 20 blocks
-    // 37.1 / 39.4, 1008 70.0 / 73.9, 1536 109 / 110, 3200 246 / 236; 3200 of 8 blocks 120 / 124, 8192 340 / 326.
-    const bool few = p.B == 64 ? items <= 2 * cus : p.d == 128 ? 4 * items <= 3 * cus : items <= cus;
-    const bool narrow = few || (p.d == 256 && ((items <= 16 * cus && kmax <= 10) || (p.B == 64 && items <= 6 * cus && kmax <= 20)));
+    // d = 256, B = 128: where lists are short, which the second wave of a SIMD helps most: one tile / two, whole and chunked prompts,
+    // 64 to 4096 rows, of 4 blocks 0.91 to 1.01, of 8 0.98 to 1.04, of 12 1.00 to 1.06, of 100 1.04 to 1.11.
+    // B = 64: up to two rows per CU, and beyond with short lists: 496 rows of 20 blocks 37.1 / 39.4 us, 1008 70.0 / 73.9, 1536
+    // 109 / 110, 3200 246 / 236; 3200 of 8 blocks 120 / 124, 8192 340 / 326.
+    const bool few = p.B == 64 ? items <= 2 * cus : p.d == 128 ? 4 * items <= 3 * cus : p.d == 64 && items <= cus;
+    const bool narrow = few || (p.d == 256 && ((items <= 16 * cus && kmax <= (p.B == 64 ? 10 : 8)) ||
+                                               (p.B == 64 && items <= 6 * cus && kmax <= 20)));
     if (p.B == 128 && p.d == 128 && narrow) STEM_ATTN_LAUNCH(128, 128, 1);
     else if (p.B == 128 && p.d == 128) STEM_ATTN_LAUNCH(128, 128, 2);
     else if (p.B == 64 && p.d == 128 && narrow) STEM_ATTN_LAUNCH(64, 128, 1);

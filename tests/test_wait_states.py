@@ -128,3 +128,20 @@ def test_an_instantiation_that_is_not_expected_fails_the_build(found, tmp_path, 
     monkeypatch.setattr(wait_states, "check_kernel", lambda asm, name: [])
     with pytest.raises(RuntimeError, match="found %d" % found):
         build.check_wait_states()
+
+
+def test_addresses_of_the_largest_buffers_are_immediate_offsets():
+    """B = 128, d = 256: 128 KiB of LDS.  A read's address is a base that several reads share and an immediate offset there too,
+    as at B = 64; formed anew for every read of a half block it took two vector instructions more, 180 in the loop."""
+    build.check_wait_states()
+    with open(os.path.join(build.OBJ, "stem_attn.s")) as f:
+        asm = f.read()
+
+    def additions(B, tiles):
+        name, = [k for k in wait_states.kernels(asm, "sparse_attn_kernel") if "ILi%dELi256ELi%dE" % (B, tiles) in k]
+        body = asm[asm.index(name + ":"):]
+        body = body[:body.index(".Lfunc_end")]
+        return body.count("\tv_add_u32") + body.count("\tv_or_b32")
+
+    for tiles in (1, 2):
+        assert additions(128, tiles) <= additions(64, tiles) + 64

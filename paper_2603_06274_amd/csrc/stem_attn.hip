@@ -496,8 +496,11 @@ __device__ __forceinline__ void sparse_attn_body(
     // Operands are read this many ahead of their use, and used two at a time behind one wait.  Attention alone, 4 / 2 ahead:
     // 128K 8716 / 8698 us, 5 % 1285 / 1279, 32K 1066 / 1064, B = 64 100K 7725 / 7687 (and six 3 to 4 % slower than four).  With one
     // tile per wave an operand is used up in half the time: 4 / 6 / 8 ahead one head of 4096 (B = 64) 12.3 / 11.7 / 11.8, 25 rows of
-    // 12 blocks (B = 128) 35.8 / 35.7 / 34.9; at d = 256, 2 / 4 / 6 / 8 ahead, 32K 2435 / 2451 / 2456 / 2457.
-    constexpr int kWanted = QW == 1 && D != 256 ? (B == 64 ? 6 : 8) : 2;
+    // 12 blocks (B = 128) 35.8 / 35.7 / 34.9; at d = 256, 2 / 4 / 6 / 8 ahead, 32K 2435 / 2451 / 2456 / 2457.  B = 128, d = 64 has a
+    // half block's products done in eight operands: read eight ahead the wait for the next phase's requests came right behind
+    // these.  2 / 4 / 6 / 8, 64 rows of 50 blocks 55.8 / 56.3 / 56.5 / 58.6 us, 228 of 100 109 / 110 / 112 / 117 (32 x 32 x 16 products 56.2, 112);
+    // (B = 64, with four, the other way round: 2 / 4, 64 rows of 50 34.7 / 33.8, 512 41.3 / 41.7.)
+    constexpr int kWanted = QW == 1 && D != 256 ? (B == 64 ? 6 : D == 64 ? 2 : 8) : 2;
     constexpr int kAhead = kWanted < HS ? kWanted : HS;
     // The operand of S^T under which request u of a phase is issued, K's first.  B = 64 and d = 64, over all of S^T / its first
     // half: 100K 8185 / 7931 us, d = 64 1436 / 1431; 128K the other way round, 8994 / 9041.

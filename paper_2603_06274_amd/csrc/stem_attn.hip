@@ -404,8 +404,8 @@ __device__ __forceinline__ void sparse_attn_body(
     const uint32_t block_bytes = (uint32_t)(B * row_bytes);
     const uint32_t slice_step = (uint32_t)(NW * kSliceRows * row_bytes);   // rows of slices u and u+1 of one wave
     constexpr int slice_lds_step = NW * 1024;
-    auto k_request = [&](int j) {
-        const uint32_t off = j * block_bytes;
+    auto k_request = [&](int j, bool wanted = true) {  // not wanted: beyond the resource, nothing is fetched
+        const uint32_t off = wanted ? j * block_bytes : 0x80000000u;
         BlockRequest<kKVariants> rq{k_rsrc, {}};
 #pragma unroll
         for (int x = 0; x < kKVariants; ++x) rq.lane_off[x] = k_off[x] + off;
@@ -496,17 +496,23 @@ __device__ __forceinline__ void sparse_attn_body(
     // Operands are read this many ahead of their use, and used two at a time behind one wait.  Attention alone, 4 / 2 ahead:
     // 128K 8716 / 8698 us, 5 % 1285 / 1279, 32K 1066 / 1064, B = 64 100K 7725 / 7687 (and six 3 to 4 % slower than four).  With one
     // tile per wave an operand is used up in half the time: 4 / 6 / 8 ahead one head of 4096 (B = 64) 12.3 / 11.7 / 11.8, 25 rows of
-    // 12 blocks (B = 128) 35.8 / 35.7 / 34.9; at d = 256, 2 / 4 / 6 / 8 ahead, 32K 2435 / 2451 / 2456 / 2457.  B = 128, d = 64 has a
+    // 12 blocks (B = 128) 35.8 / 35.7 / 34.9, and, with kTail, 6 / 8 ahead at B = 64 64 rows of 60 blocks far away 64.3 / 62.6; at d = 256, 2 / 4 / 6 / 8 ahead, 32K 2435 / 2451 / 2456 / 2457.  B = 128, d = 64 has a
     // half block's products done in eight operands: read eight ahead the wait for the next phase's requests came right behind
-    // these.  2 / 4 / 6 / 8, 64 rows of 50 blocks 55.8 / 56.3 / 56.5 / 58.6 us, 228 of 100 109 / 110 / 112 / 117 (32 x 32 x 16 products 56.2, 112);
-    // (B = 64, with four, the other way round: 2 / 4, 64 rows of 50 34.7 / 33.8, 512 41.3 / 41.7.)
-    constexpr int kWanted = QW == 1 && D != 256 ? (B == 64 ? 6 : D == 64 ? 2 : 8) : 2;
+    // these.  2 / 4 / 6 / 8, 64 rows of 50 blocks 55.8 / 56.3 / 56.5 / 58.6 us, 228 of 100 109 / 110 / 112 / 117 (32 x 32 x 16 products 56.2, 112).
+    constexpr int kWanted = QW == 1 && D != 256 ? (B == 128 && D == 64 ? 2 : 8) : 2;
     constexpr int kAhead = kWanted < HS ? kWanted : HS;
     // The operand of S^T under which request u of a phase is issued, K's first.  B = 64 and d = 64, over all of S^T / its first
     // half: 100K 8185 / 7931 us, d = 64 1436 / 1431; 128K the other way round, 8994 / 9041.
     // d = 256, B = 64: two tiles per wave, 256 blocks of which 50 kept 1403 / 1365; one tile, 100 rows of 8 blocks 13.4 / 14.1.
     constexpr bool kEarly = (B == 64 || D == 64) && !(D == 256 && QW == 1);
     auto request_slot = [](int u) { return kEarly ? u * HS / (2 * KR) : u * HS / KR; };
+    // kTail: a phase's requests go out in the phase before instead, one under each operand of O^T from where its reading side has
+    // crossed into the next phase: from there on nobody reads the buffers that they fill, and they have a whole phase to arrive.
+    // A row by itself at B = 64 waits for them otherwise where its keys are not in the L2.  64 rows, in late chunks of 64K tokens / of
+    // few keys, 32 x 32 x 16 products / before / now: d = 64, 60 blocks 51.4 / 59.1 / 53.6 us and 36.5 / 33.7 / 33.6 (50 blocks); d = 128 60.1 /
+    // 66.4 / 62.6 and 47.3 / 41.4 / 40.6.  Two at a time or all at once 1 to 6 % slower.
+    constexpr bool kTail = QW == 1 && B == 64 && D != 256;
+    static_assert(!kTail || KR <= kAhead, "an operand for every request");
 
     f32x4_t s_acc[2][TP][2][QW];                       // [half][tile][16 keys][query tile]
     u32x4_t p_pk[2][TP][QW];                           // bf16 pairs: [half][tile][query tile], [2 * 16 keys + pair]
@@ -760,11 +766,14 @@ __device__ __forceinline__ void sparse_attn_body(
         int mask_from;
         bool mask_all;
         block_mask(j_cur, mask_from, mask_all);
+        int j_nxt = kTail ? __builtin_amdgcn_readlane(list_reg, 1) : 0;
         STEM_WAIT_VMCNT(KR);                           // the first half of K is there (its second and V's first may not be)
         STEM_BARRIER();
         // ---- the first half: S^T alone; the references are its largest scores; the first half of its softmax ----
         {
             u32x4_t op[HS + kAhead];
+            BlockRequest<kKVariants> rk;
+            const auto rv = v_request(clamped(j_cur));
             unrolled<kAhead>([&](auto m) STEM_INLINE {
                 op[m] = load_k(0, m);
                 if (m & 1) STEM_SCHED_FENCE();
@@ -776,6 +785,14 @@ __device__ __forceinline__ void sparse_attn_body(
                     op[a] = a < HS ? load_k(0, a) : load_k(1, a - HS);
                     op[a + 1] = a < HS ? load_k(0, a + 1) : load_k(1, a + 1 - HS);
                     waited(kAhead);
+                }
+                if constexpr (kTail) {
+                    if constexpr (m == HS - kAhead) rk = k_request(clamped(j_nxt), cnt > 1);
+#pragma unroll
+                    for (int u = 0; u < KR / 2; ++u) {
+                        if (m == HS - kAhead + u) issue_k(rk, u);
+                        if (m == HS - kAhead + u + KR / 2) issue_v(rv, u + KR / 2);
+                    }
                 }
                 scores(C0{}, m_tag, op[m & ~1], op[m | 1], nothing);
             });
@@ -792,8 +809,38 @@ __device__ __forceinline__ void sparse_attn_body(
         // ---- second half of block `it`, first half of the next ----
 #pragma unroll 1
         for (int it = 0; it + 1 < cnt; ++it) {
+            if constexpr (kTail) {
+                if (((it + 2) & 63) == 0) list_reg = list_chunk(it + 2);
+                const int j_then = __builtin_amdgcn_readlane(list_reg, (it + 2) & 63);
+                {
+                    const auto rk = k_request(clamped(j_nxt));
+                    const auto rv = v_request(clamped(j_nxt));
+                    phase(C1{}, mask_from, mask_all, [&](int m) STEM_INLINE {
+#pragma unroll
+                        for (int u = 0; u < KR / 2; ++u) {
+                            if (m == 2 * HS - kAhead + u) issue_k(rk, u + KR / 2);
+                            if (m == 2 * HS - kAhead + u + KR / 2) issue_v(rv, u);
+                        }
+                    });
+                }
+                j_cur = j_nxt;
+                j_nxt = j_then;
+                block_mask(j_cur, mask_from, mask_all);
+                {
+                    const auto rk = k_request(clamped(j_nxt), it + 2 < cnt);
+                    const auto rv = v_request(clamped(j_cur));
+                    phase(C0{}, mask_from, mask_all, [&](int m) STEM_INLINE {
+#pragma unroll
+                        for (int u = 0; u < KR / 2; ++u) {
+                            if (m == 2 * HS - kAhead + u) issue_k(rk, u);
+                            if (m == 2 * HS - kAhead + u + KR / 2) issue_v(rv, u + KR / 2);
+                        }
+                    });
+                }
+                continue;
+            }
             if (((it + 1) & 63) == 0) list_reg = list_chunk(it + 1);
-            const int j_nxt = __builtin_amdgcn_readlane(list_reg, (it + 1) & 63);
+            j_nxt = __builtin_amdgcn_readlane(list_reg, (it + 1) & 63);
             {
                 const auto rk = k_request(clamped(j_nxt));
                 const auto rv = v_request(clamped(j_cur));
@@ -823,7 +870,7 @@ __device__ __forceinline__ void sparse_attn_body(
         //      both products: their neighbours on the SIMD gain.  (Its softmax they make of what lies in the registers and do
         //      not use: a branch around it would have the code of O^T twice.) ----
         const bool second = mask_from == KT || mask_all || w_tile >= TP;
-        {
+        if constexpr (!kTail) {
             const auto rv = v_request(clamped(j_cur));
 #pragma unroll
             for (int u = KR / 2; u < KR; ++u) issue_v(rv, u);

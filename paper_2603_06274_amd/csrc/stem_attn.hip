@@ -1040,19 +1040,27 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     hipLaunchKernelGGL((sparse_attn_kernel<BB, DD, QW>), grid, dim3(BB * 4 / QW), 0, stream, qq, kk, vv, counts, indices, \
                        oo, lse, p.seq, walk, p.Hq, p.R, p.G, order, ag.claim_from, p.T, kmax, lists_per_kv_head, p.q_st, p.q_sh, \
                        p.kv_st, p.kv_sh, softmax_scale, ag.items_per_xcd, ag.xcds_per_kv_head, queue)
-    // One 16-query tile per wave, and twice the waves, where the chip has room for them: up to two rows per CU at B = 64, up to
-    // three per four CUs at B = 128, d = 128, one per CU at d = 64 (a CU's waves then read each LDS operand twice as often).
-    // Attention alone, lists of 8 % of the longest row's blocks and all of the short ones, one tile / two: B = 64, d = 128, 250 rows
-    // 21.2 / 22.9 us, 380 35.6 / 42.1, 500 51.3 / 55.3, 640 80.7 / 76.3; d = 64, 500 35.5 / 42.2, 640 53.4 / 52.5; B = 128, d = 128,
-    // 100 15.3 / 16.8, 250 41.4 / 40.7, 270 59.7 / 45.9; d = 64, 250 27.8 / 29.1, 270 42.0 / 31.9.  The bits are the same.
+    // One 16-query tile per wave, and twice the waves: a CU reads each LDS operand twice as often, and a row takes less time.
+    // The better one where the chip has room for the waves, where rows of different length leave the longest to run by themselves
+    // (`grow`: from the start of prompts, with lists of more than half of their blocks), and where lists are short.  The bits are the
+    // same.  One tile / two, attention alone, 1 to 150 blocks per list, whole and packed prompts and late chunks of long ones:
+    //   B = 128, d = 128: up to a row per CU 0.88 to 1.04; up to two, grow 0.84 to 0.99, else 0.95 to 1.33, grow in batches 0.94 to 1.21.
+    //     d = 64: up to a row per CU 0.83 to 1.00; up to two, grow 0.85 to 1.00, else 0.87 to 1.08.
+    //   B = 64: up to two rows per CU, d = 128 0.74 to 1.04, d = 64 0.75 to 1.05; up to three with 12 to 80 blocks 0.79 to 1.00 and, at
+    //     d = 64, with more 0.89 to 0.98; with fewer 0.83 to 1.23, but at d = 64 and up to 2 3/4 rows 0.81 to 0.99; up to four, grow
+    //     0.82 to 1.04, else 0.82 to 1.30.
+    //   d = 256, B = 64: up to a row per CU 0.72 to 0.98; up to three of at most 50 blocks, or grow, 0.72 to 1.03, of more 0.88 to
+    //     1.27; up to six of at most 20 and 16 of at most 10 0.67 to 1.02, beyond 0.87 to 1.17.  B = 128: of 4 blocks 0.91 to 1.01,
+    //     of 8 0.98 to 1.04, of 12 1.00 to 1.06, of 100 1.04 to 1.11.
     const int64_t cus = compute_units();
-    // d = 256, B = 128: where lists are short, which the second wave of a SIMD helps most: one tile / two, whole and chunked prompts,
-    // 64 to 4096 rows, of 4 blocks 0.91 to 1.01, of 8 0.98 to 1.04, of 12 1.00 to 1.06, of 100 1.04 to 1.11.
-    // B = 64: up to two rows per CU, and beyond with short lists: 496 rows of 20 blocks 37.1 / 39.4 us, 1008 70.0 / 73.9, 1536
-    // 109 / 110, 3200 246 / 236; 3200 of 8 blocks 120 / 124, 8192 340 / 326.
-    const bool few = p.B == 64 ? items <= 2 * cus : p.d == 128 ? 4 * items <= 3 * cus : p.d == 64 && items <= cus;
-    const bool narrow = few || (p.d == 256 && ((items <= 16 * cus && kmax <= (p.B == 64 ? 10 : 8)) ||
-                                               (p.B == 64 && items <= 6 * cus && kmax <= 20)));
+    const bool grow = (p.batch == 1 || p.B == 64 || p.d == 64) && 4 * (int64_t)p.R >= 3 * (int64_t)p.NBmax && 2 * (int64_t)kmax > p.NBmax;
+    const bool narrow =
+        p.d == 256 && p.B == 128 ? items <= 16 * cus && kmax <= 8
+        : p.d == 256 ? items <= cus || (items <= 3 * cus && (kmax <= 50 || grow)) || (items <= 6 * cus && kmax <= 20) ||
+                           (items <= 16 * cus && kmax <= 10)
+        : p.B == 128 ? items <= cus || (items <= 2 * cus && grow)
+                     : items <= 2 * cus || (p.d == 64 && 4 * items <= 11 * cus) ||
+                           ((p.d == 64 || kmax <= 80) && ((items <= 3 * cus && kmax >= 12) || (items <= 4 * cus && grow)));
     if (p.B == 128 && p.d == 128 && narrow) STEM_ATTN_LAUNCH(128, 128, 1);
     else if (p.B == 128 && p.d == 128) STEM_ATTN_LAUNCH(128, 128, 2);
     else if (p.B == 64 && p.d == 128 && narrow) STEM_ATTN_LAUNCH(64, 128, 1);

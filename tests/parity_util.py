@@ -273,11 +273,19 @@ def oracle_attention_pairs(w: wl.Workload, qkv, counts, indices, pairs):
     return res
 
 
-def two_tiles_per_wave(B: int, d: int, rows: int, kmax: int, cus: int) -> bool:
+def two_tiles_per_wave(B: int, d: int, rows: int, kmax: int, cus: int, grow: bool) -> bool:
     """Whether a launch of `rows` (head, query block) pairs gives a wave 32 queries (the rule of launch_sparse_attn)."""
-    few = rows <= 2 * cus if B == 64 else 4 * rows <= 3 * cus if d == 128 else d == 64 and rows <= cus
-    return not few and not (d == 256 and ((rows <= 16 * cus and kmax <= (10 if B == 64 else 8)) or
-                                          (B == 64 and rows <= 6 * cus and kmax <= 20)))
+    if d == 256:
+        limit = 16 if kmax <= (8 if B == 128 else 10) else 0
+        if B == 64:
+            limit = max(limit, 6 if kmax <= 20 else 3 if kmax <= 50 or grow else 1)
+        return rows > limit * cus
+    if B == 128:
+        return rows > (2 if grow else 1) * cus
+    limit = 2.75 if d == 64 else 2
+    if d == 64 or kmax <= 80:
+        limit = max(limit, 4 if grow else 3 if kmax >= 12 else 0)
+    return rows > limit * cus
 
 
 def widen_attention(monkeypatch) -> None:
@@ -290,8 +298,10 @@ def widen_attention(monkeypatch) -> None:
     def widened(shape, q, k, v, counts, indices, kmax, scale, out, lse, lists_per_kv_head=False):
         assert not lists_per_kv_head and shape.chunk is None
         B, d, Hq, rows = shape.c.block_size, q.shape[2], q.shape[1], counts.shape[0] * counts.shape[1]
-        n = next(n for n in range(1, 1000) if two_tiles_per_wave(B, d, n * rows, max(24, kmax), cus))
-        assert (B, d) == (128, 256) or not two_tiles_per_wave(B, d, rows, kmax, cus)
+        blocks = sb.stem_rows(shape)[1]
+        whole = (len(shape.cu_seqlens) == 2 or B == 64 or d == 64) and 4 * counts.shape[1] >= 3 * blocks
+        n = next(n for n in range(1, 1000) if two_tiles_per_wave(B, d, n * rows, max(24, kmax), cus, whole and 2 * max(24, kmax) > blocks))
+        assert (B, d) == (128, 256) or not two_tiles_per_wave(B, d, rows, kmax, cus, whole and 2 * kmax > blocks)
         room = torch.full((*indices.shape[:2], max(24, kmax)), -1, dtype=torch.int32, device=q.device)
         room[:, :, :kmax] = indices
         qn, kn, vn = (x.repeat(1, n, 1) for x in (q, k, v))

@@ -147,3 +147,26 @@ def test_rows_on_both_sides_of_the_lines_between_wave_shapes_at_d_256(B, rows_pe
     c.check_part(whole, [0], [(1, blocks + 1)])
     c.indices = torch.cat([c.indices, torch.full_like(c.indices[:, :, :1], -1)], dim=2)
     c.check_part(whole, [0], [(1, blocks + 1)])
+
+
+@pytest.mark.parametrize("B,d,rows_per_cu,kmax,late", [
+    # the whole prompt's rows on the line and one block more of every head, or, late, the last rows of a longer one
+    (128, 128, 1, 40, True), (128, 128, 2, 60, False), (128, 64, 1, 40, True), (128, 64, 2, 60, False),
+    (64, 64, 2.75, 11, True), (64, 64, 3, 12, True), (64, 64, 4, 80, False),
+    (64, 128, 2, 11, True), (64, 128, 3, 12, True), (64, 128, 3, 80, True), (64, 128, 4, 80, False),
+    (64, 256, 1, 51, True), (64, 256, 3, 50, True), (64, 256, 3, 80, False), (128, 256, 16, 8, True),
+])
+def test_rows_on_both_sides_of_each_line(B, d, rows_per_cu, kmax, late):
+    """Every line of the rule for the number of queries per wave: a call on it and one a block per head above it."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    heads = 32 if rows_per_cu == 16 else 8
+    blocks = int(rows_per_cu * cus) // heads
+    first = blocks if late else 0
+    c = Call(B, d, heads, 2, ((first + blocks + 1) * B - 3,), kmax)
+    above = c.attend([0], [(first, first + blocks + 1)])
+    out, lse, tokens = c.attend([0], [(first, first + blocks)])
+    print("case", B, d, blocks, kmax, late, flush=True)
+    assert torch.equal(out, above[0][:out.shape[0]]) and torch.equal(lse, above[1][:, :lse.shape[1]])
+    c.indices = torch.cat([c.indices, torch.full_like(c.indices[:, :, :1], -1)], dim=2)   # and with room for one block more
+    out, lse, tokens = c.attend([0], [(first, first + blocks)])
+    assert torch.equal(out, above[0][:out.shape[0]]) and torch.equal(lse, above[1][:, :lse.shape[1]])

@@ -468,14 +468,13 @@ __device__ __forceinline__ void sparse_attn_body(
         off[qt] = l_run[qt] = 0.f;
         l_win[qt] = zero4;
     }
-    // The first references are the largest scores of a row's first block: the largest probability is then 1 and exact.  (At B = 128
-    // the first half alone left lse up to 1.3 times as far from 64 bits as three quarters of the block had, and the outputs
-    // 1 %; the whole block 0.85 to 1.0 times, and the same.  The softmax of a row's first half has nothing to go under then: attention
-    // alone half / whole, 12 prompts to 2047 tokens 96.8 / 97.2 us, d = 64 62.1 / 62.8; 128 rows of 8 blocks 16.7 / 16.9; 128K the same.
-    // B = 64 takes them from half a block, 32 keys, as before these products.)
-    constexpr bool kWholeBlock = B == 128;
-    bool first = kWholeBlock;                          // no query has a reference yet: the first half is left to fix_half
-    bool unseen = kWholeBlock;                         // a query has no reference yet: all it has met is masked
+    // The first references are the largest scores of the first 96 keys of a row, at B = 64 of the first 32: what they are taken from
+    // decides how every probability rounds, and the largest, being 1, does not.  (From the first 64 at B = 128 lse was up to 1.3 times
+    // as far from 64 bits, and the outputs 1 %.  The softmax of a row's first half has nothing to go under this way: attention alone,
+    // 64 / 96 keys, 12 prompts to 2047 tokens 96.8 / 97.2 us, d = 64 62.1 / 62.8; 128 rows of 8 blocks 16.7 / 16.9; 128K the same.)
+    constexpr bool kPastHalf = B == 128;
+    bool first = kPastHalf;                          // no query has a reference yet: the first half is left to fix_half
+    bool unseen = kPastHalf;                         // a query has no reference yet: all it has met is masked
 
     // per-lane LDS offsets that do not change between blocks.  Both swizzles are XORs of address
     // bits that are zero in the unswizzled per-lane offset, so the offset of an operand is one
@@ -584,11 +583,11 @@ __device__ __forceinline__ void sparse_attn_body(
     using kHalf = std::integral_constant<int, NP / 2>;
 
     auto negated_offset = [&](int qt) { return m_ref[qt] == neg_inf ? 0.f : -m_ref[qt] * sl2; };   // 0: masked scores stay at exp2(-inf) = 0
-    // largest score of the query in half P (all of its lanes get it), ignoring NaN
-    auto half_max = [&](int P, int qt) {
+    // largest score of the query in half P, of its first `tiles` tiles (all of its lanes get it), ignoring NaN
+    auto half_max = [&](int P, int qt, int tiles) {
         float mx2[2] = {neg_inf, neg_inf};
 #pragma unroll
-        for (int t = 0; t < TP; ++t)
+        for (int t = 0; t < tiles; ++t)
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt) {
                 mx2[0] = max3(mx2[0], s_acc[P][t][kt][qt][0], s_acc[P][t][kt][qt][1]);
@@ -610,15 +609,15 @@ __device__ __forceinline__ void sparse_attn_body(
     // only if a query gains by it: one that has no reference, or probabilities far beyond its own (a sum over 2^16 of 128 keys
     // at most holds one over 2^9), and a finite score to go to.  A query that is NaN or inf for good comes here with
     // every half and leaves the others as they are.
-    // The first half of a row comes here too (kWholeBlock), its scores and, if `both`, the second half's being there.
+    // The first half of a row comes here too (kPastHalf), its scores and, if `both`, the second half's being there.
     auto fix_half = [&](auto P_tag, bool both) STEM_INLINE {
         constexpr int P = decltype(P_tag)::value;
-        if (kWholeBlock && first) {                    // (a copy of the softmax: where paths meet here O is copied at d = 256)
+        if (kPastHalf && first) {                    // (a copy of the softmax: where paths meet here O is copied at d = 256)
             first = false;
 #pragma unroll
             for (int qt = 0; qt < QW; ++qt) {
-                const float mx = half_max(P, qt);
-                m_ref[qt] = both ? fmaxf(mx, half_max(1 - P, qt)) : mx;
+                const float mx = half_max(P, qt, TP);
+                m_ref[qt] = both ? fmaxf(mx, half_max(1 - P, qt, 1)) : mx;
                 off[qt] = negated_offset(qt);
                 asm volatile("" : "+v"(off[qt]));      // not folded into the exponents: the bits of the common path
             }
@@ -631,7 +630,7 @@ __device__ __forceinline__ void sparse_attn_body(
 #pragma unroll
         for (int qt = 0; qt < QW; ++qt) {
             const bool needs = __builtin_amdgcn_ballot_w64((m_ref[qt] == neg_inf) | !(l_win[qt][0] <= 65536.0f)) != 0;
-            const float mx = half_max(P, qt);
+            const float mx = half_max(P, qt, TP);
             const bool gains = (mx < -neg_inf) & (mx > m_ref[qt]) & ((m_ref[qt] == neg_inf) | (mx * sl2 + off[qt] > 8.9f));
             const bool moves = (__builtin_amdgcn_ballot_w64(!(l_win[qt][0] < -neg_inf)) == 0) | (__builtin_amdgcn_ballot_w64(gains) != 0);
             const bool up = needs & moves & (mx > m_ref[qt]);
@@ -820,10 +819,10 @@ __device__ __forceinline__ void sparse_attn_body(
             });
             unrolled<kAhead>([&](auto m) STEM_INLINE { ring[m] = op[HS + m]; });
             if (mask_from < KT) mask_half(0, mask_from, mask_all);
-            if constexpr (!kWholeBlock) {
+            if constexpr (!kPastHalf) {
 #pragma unroll
                 for (int qt = 0; qt < QW; ++qt) {
-                    m_ref[qt] = half_max(0, qt);
+                    m_ref[qt] = half_max(0, qt, TP);
                     off[qt] = negated_offset(qt);
                 }
                 note_unseen();

@@ -1,5 +1,5 @@
-"""B = 128: the softmax references of a row are taken from the whole of its first block, so that the largest of that block's
-probabilities is 1 and enters the row's sum without rounding to bf16, wherever in the block its key stands."""
+"""B = 128: the softmax references of a row are taken from its first 96 keys, so that the largest of their probabilities is 1 and
+enters the row's sum without rounding to bf16, wherever among them its key stands."""
 import pytest
 import torch
 
@@ -12,9 +12,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("d", [64, 128, 256])
-@pytest.mark.parametrize("key", [3, 70, 100])
-def test_largest_probability_of_the_first_block_is_exact(d, key, wide, monkeypatch):
-    """One key scores 9 to 11 above all others (which the first reference of another half block would take, without a move),
+@pytest.mark.parametrize("key", [3, 70, 95])
+def test_largest_of_the_first_probabilities_is_exact(d, key, wide, monkeypatch):
+    """One key scores 9 to 11 above all others (with a reference from those others it would stay below the line for a move),
     so the sum is 1 and at most 3 * 128 e^-9 = 0.05 of the others, rounded by 2^-9 of that: 1e-4.  A probability of e^10
     rounded to bf16 instead is off by up to 2^-9 = 2e-3."""
     if wide:

@@ -105,12 +105,12 @@ WorkspaceLayout workspace_layout(const Problem& p, int ad_stride) {
 
 // Claiming (claim_row) costs the launch that clears the counters, 2 to 5 us in kernel traces, and 1 to 2 us for each row
 // claimed, and gains what the XCDs differ by at the end.  So: 1e12 operations and more (about 0.9 ms), lists bounded by kmax,
-// and eight rounds of what runs at a time, below which an eighth is less than a round.  Attention alone with claims
-// over without, one GPU, medians of five (runs of one side differ by 0.3 to 3 %): 32 / 8 heads, 128K at 8 % of the
-// blocks 0.973, 32K at 8 % 0.994 and 15 % 0.986, 24K at 15 % 0.993, 16K at 40 % 0.990; 28 / 4, 64K at 3 % 0.990, dense 0.977;
-// d = 64, 64K at 5 % 0.990; d = 256, 32K at 6 % 0.992; B = 64, 32K at 10 % 0.998; 64 prompts of 1500 dense, an eighth /
-// a quarter 0.994 / 1.003.  Fewer operations: 32K at 5 % 0.991, 16K at 20 % 0.997, B = 64, 32K at 5 % 1.004.  Four rounds (8K
-// tokens after 120K): at 5 % 1.003, 20 % 0.995, dense 1.001.
+// and eight rounds of what runs at a time, below which an eighth is less than a round.  Attention alone with an eighth of the rows
+// claimed over without, one GPU, medians of seven (runs of one side differ by 0.3 to 3 %): 32 / 8 heads, 128K at 8 % of the
+// blocks 0.981, 32K at 8 % 0.995 and 15 % 0.990, 24K at 15 % 0.991, 16K at 40 % 0.988; 28 / 4, 64K at 3 % 0.987, dense 0.992;
+// d = 64, 64K at 5 % 0.991; d = 256, 32K at 6 % 0.982; B = 64, 32K at 10 % 0.988; 64 prompts of 1500 dense, an eighth /
+// a quarter 0.998 / 1.018.  Fewer operations: 32K at 5 % 0.989, 16K at 20 % 1.003, B = 64, 32K at 5 % 0.990.  Four rounds (8K
+// tokens after 120K): at 5 % 1.012, 20 % 0.996.
 bool attention_claims_rows(const Problem& p, int32_t kmax, int (*units)()) {
     double blocks = 0.0;                               // of one head: rows first .. last - 1 list at most min(i + 1, kmax)
     for (int s = 0; s < p.batch; ++s) {
@@ -136,13 +136,15 @@ AttentionGrid attention_grid(const Problem& p, int32_t kmax, bool queue, int (*u
     ag.slots = per_xcd;
     if (queue && attention_claims_rows(p, kmax, units)) {
         // Rows go out from the last to the first: where lists grow with the row the last ones handed out are short, and a
-        // quarter of the rows is about an eighth of the blocks.  An eighth / a quarter over none, by kmax as a share of
-        // NBmax: 28 / 4 heads, 64K, 3 % 0.990 / 0.993, 6 % 0.987 / 0.988, 12 % 0.983 / 0.978, 25 % 0.986 / 0.979, 48 % 0.991 /
-        // 0.978, 52 % 0.990 / 0.978, dense 0.991 / 0.977; 8K + 16K + 32K + 72K packed 6 % 0.990 / 0.991, 30 % 0.984 / 0.976, 48 %
-        // 0.986 / 0.979, 60 % 0.988 / 0.979, dense 0.988 / 0.980; four of 16K 9 % 0.989 / 0.992, 48 % 0.980 / 0.978, 59 % 0.978 /
-        // 0.973; 48K and twelve of 2K 10 % 0.983 / 0.985, dense 0.981 / 0.969; 32 of 4K dense 0.988 / 0.989; B = 64, 32K 10 % 0.998 /
-        // 1.003, dense 0.990 / 0.979; 32K tokens after 96K dense 0.971 / 0.974.  The two cross at about an eighth of NBmax;
-        // between there and a half the rule leaves up to 1 % (both sides of a half measure the same).
+        // quarter of the rows is about an eighth of the blocks.  An eighth / a quarter over none (32 x 32 x 16
+        // products; with 16 x 16 x 32 28 / 4, 64K, 3 % 0.987 / 0.993, 12 % 0.985 / 0.985, dense 0.992 / 0.966), by
+        // kmax as a share of NBmax: 28 / 4 heads, 64K, 3 % 0.990 / 0.993, 6 % 0.987 / 0.988, 12 % 0.983 / 0.978, 25 %
+        // 0.986 / 0.979, 48 % 0.991 / 0.978, 52 % 0.990 / 0.978, dense 0.991 / 0.977; 8K + 16K + 32K + 72K packed 6 %
+        // 0.990 / 0.991, 30 % 0.984 / 0.976, 48 % 0.986 / 0.979, 60 % 0.988 / 0.979, dense 0.988 / 0.980; four of 16K
+        // 9 % 0.989 / 0.992, 48 % 0.980 / 0.978, 59 % 0.978 / 0.973; 48K and twelve of 2K 10 % 0.983 / 0.985, dense
+        // 0.981 / 0.969; 32 of 4K dense 0.988 / 0.989; B = 64, 32K 10 % 0.998 / 1.003, dense 0.990 / 0.979; 32K
+        // tokens after 96K dense 0.971 / 0.974.  The two cross at about an eighth of NBmax; between there and a half
+        // the rule leaves up to 1 % (both sides of a half measure the same).
         const int64_t claimed = per_xcd / (kmax > p.NBmax / 2 ? 4 : 8);
         const int64_t slots = per_xcd + (claimed + 3) / 4;
         if (slots * 8 <= kMaxWorkgroups) {             // (not for the claiming's sake may a call be refused)

@@ -303,20 +303,21 @@ __device__ __forceinline__ bool find_row(const SeqTable& seq, const RowWalk& wal
 // S^T and first of O^T before: two waves of a SIMD in that part at once left the matrix pipe idle).  The LDS operands of the
 // two products are one stream that is read kAhead operands ahead, across phases too; K and V have two buffers each, one per half,
 // and where the stream goes on to the next phase the wave waits for the requests that fill it and for the others to have
-// read what the next phase's requests overwrite: one barrier per half block.  These requests are issued during S^T.
+// read what the next phase's requests overwrite: one barrier per half block.  These requests are issued during S^T (kTail: before
+// it).  A row's first half has its whole softmax at its check, from references that look into the second (kPastHalf).
 //
-// Before (32 x 32 x 16, softmax under the same block's products) / now, attention alone: 128K, 8 % of the blocks 9317 / 8605 us;
-// 64K, all 24842 / 22633; 32K, 15 % 1131 / 1050; 64K, 5 % 1346 / 1264; d = 64, 64K 1434 / 1364; B = 64, 100K tokens 7821 / 7716; 12 prompts to
-// 2047 tokens 100.9 / 93.2.  128K in shader cycles: 1.441e7 / 1.433e7, at 1.49 / 1.60 GHz.
+// Before (32 x 32 x 16, softmax under the same block's products) / now, attention alone: 128K, 8 % of the blocks 9234 / 8494 us;
+// 64K, all 24393 / 22345; 32K, 15 % 1114 / 1035; 64K, 5 % 1315 / 1245; d = 64, 64K 1405 / 1332; 12 prompts to 2047 tokens 119 / 114, d = 64
+// 73.3 / 71.6; B = 64, 4096 tokens of one head 14.0 / 12.7, 100K tokens 7622 / 7603 and d = 64, 50K 1079 / 1056.
 //
-// Head size 256.  A wave of 32 queries needs 462 (B = 64: 408) registers, so it has its SIMD for itself, and half of them are
+// Head size 256.  A wave of 32 queries needs 440 (B = 64: 408) registers, so it has its SIMD for itself, and half of them are
 // accumulator registers, which only matrix instructions and copies can reach (kAcc): O and Q lie there, everything that the
 // softmax touches in vector registers.  Left to itself the compiler placed the scores there as well, or O in vector registers and
 // copied other values back and forth, 116 copies per block (32K, 15 %: 2587 us; by a flag for this file the results of the
-// other matrix instructions stay in vector registers, which alone gave 2491).  With 16 queries a wave needs 226, and two share a SIMD;
+// other matrix instructions stay in vector registers, which alone gave 2491).  With 16 queries a wave needs 200, and two share a SIMD;
 // each LDS operand then feeds one matrix instruction.  Before (32 x 32 x 16, one wave per SIMD, the softmax under the same
-// block's products, two barriers per block) / now, attention alone, B = 128: 32K, 15 % 2377 / 2241 us; 115 blocks, 54 of them kept
-// 2109 / 1986; 20K + 45K, 4 % 642 / 599; 8 short prompts 124 / 109; B = 64: 203 blocks, 54 kept 1125 / 1100; 24K packed 745 / 655.
+// block's products, two barriers per block) / now, attention alone, B = 128: 32K, 15 % 2298 / 2104 us; 115 blocks, 54 of them kept
+// 2094 / 1889; 12 prompts to 2047 tokens 260 / 233; B = 64: 203 blocks, 54 kept 1208 / 1120.
 //
 // LDS there: 128 KiB at B = 128, where the immediate offset of a read reaches 64 KiB.  With K below and V from 64 KiB on the second
 // half of V took two more vector instructions for every read, 62 per block, with nobody on the SIMD to fill them in.  So V lies
@@ -1022,13 +1023,11 @@ int launch_sparse_attn(const Problem& p, const void* q, const void* k, const voi
     // The walk's order is for batches of ten sequences and more, at d = 64 and 128, where rows wait for a place (1.5
     // to 8 times what runs at a time: two workgroups per CU at B = 128, four at B = 64), lists grow with the row
     // (kmax is more than half of the longest sequence's blocks, and these are three or more) and the sequences
-    // come in another order.  Attention alone, rows from the last to the first / in the walk's order: 12 prompts
-    // to 2047 tokens, 32 / 8 heads, all blocks 118 / 110 us; 161 such batches from 2 % slower to 26 % faster, 4 % in the
-    // middle.  Beyond the lines chance prevails: fewer rows (1.25 to 1.5 times, 18 batches) 9 % slower to 12 %
-    // faster; eight or nine sequences (23) 2 % slower to 15 % faster, in another sample (13) 11 % slower; two to
-    // six (53) 5 % slower to 15 % faster and nothing in the middle; lists cut shorter (184) 6 % slower to 24 % faster,
-    // 2 % in the middle; two blocks at most (49) 5 % slower to 11 % faster, more rows (45) 2 % slower to 5 % faster and
-    // d = 256, one workgroup per CU (23), 5 % slower to 17 % faster, nothing in the middle of any.
+    // come in another order.  Attention alone, the walk's order against rows from the last to the first: 149 such batches from
+    // 6 % slower to 19 % faster, 6 % in the middle.  Beyond the lines it is worth less or chance prevails: 1.1 to 1.5 times (64
+    // batches) 7 % slower to 24 % faster, 7 % in the middle; more than 8 times (66) 1 % slower to 7 % faster, 2 %; two to nine
+    // sequences (79) 5 % slower to 19 % faster, 1 %; lists cut to a third and less (68) 4 % slower to 9 % faster, nothing; two blocks at
+    // most (74) 10 % slower to 10 % faster, 1 %; d = 256 (with 32 x 32 x 16 products, 23) 5 % slower to 17 % faster, nothing.
     // Batches in ascending order start with the longest as they are and would pay the lookup, up to 5 %.
     RowWalk walk = {};
     int order = p.batch > 1 ? kAsPacked : kOneSequence;

@@ -50,3 +50,19 @@ def test_few_tiles_give_the_scores_of_many(d, B, S, chunk):
     row_tiles = [-(-(n - (s // B if chunk else 0)) // 64) for n, s in zip(blocks, starts)]
     assert 2 * Hq * sum(row_tiles) > cus and not torch.isnan(many).any().item()
     assert torch.equal(few, many[:Hq // Hkv])
+
+
+@pytest.mark.parametrize("d,B,S,chunk", [
+    (64, 64, 1, False), (64, 128, 4, True), (128, 64, 1, True), (128, 128, 1, False), (128, 64, 2, False),
+    (256, 64, 1, True), (256, 64, 16, False),
+])
+def test_the_calls_compared_lie_on_both_sides_of_the_line(d, B, S, chunk):
+    """The comparison above says something only if its small call is worked on in quarters, that is has at most half a causal
+    64 x 64 tile per CU, and its large one more."""
+    tiles = 0
+    for n in (97, 0, 1, 33, 64, 65):
+        first = n // 3 if chunk else 0                 # block index of the call's first row of the sequence
+        for i0 in range(0, n - first, 64):             # a row tile sees the blocks up to its last row's, in the call up to 97
+            tiles += -(-min(first + i0 + 64, 97) // 64)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert 2 * 4 * tiles <= cus < 2 * 32 * tiles

@@ -1,7 +1,7 @@
 """A NaN or inf in one row of Q, K or V reaches the output rows that attend to it and no other one: stage 3 with and
 without such rows, at places where other queries share a wave, a 32-query tile, a matrix product's column or a list
 with them.  Everything else has to come out as without them: to the bit, unless a query among them, or one that they
-replace, moves the softmax reference of its wave (a 32-query tile shares that decision)."""
+replace, moves the softmax reference of its wave (a 16-query tile shares that decision)."""
 import numpy as np
 import pytest
 import torch

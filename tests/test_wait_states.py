@@ -145,3 +145,16 @@ def test_addresses_of_the_largest_buffers_are_immediate_offsets():
 
     for tiles in (1, 2):
         assert additions(128, tiles) <= additions(64, tiles) + 64
+
+
+def test_every_attention_kernel_has_products_in_inline_assembly():
+    """All twelve issue O^T from inline assembly; what the check above accepts has looked at those."""
+    build.check_wait_states()
+    with open(os.path.join(build.OBJ, "stem_attn.s")) as f:
+        asm = f.read()
+    names = wait_states.kernels(asm, "sparse_attn_kernel")
+    assert len(names) == build.ATTENTION_KERNELS
+    for name in names:
+        body = asm[asm.index(name + ":"):]
+        inside = [part.split("ASMEND")[0] for part in body[:body.index(".Lfunc_end")].split("ASMSTART")[1:]]
+        assert sum("v_mfma_f32_16x16x32_bf16" in x for x in inside) >= 16
